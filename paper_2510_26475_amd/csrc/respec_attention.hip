@@ -1176,96 +1176,131 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
 // ------------------------------------------------------------------------------------------
 // combine: merge the partials of every (sequence, KV head) that a work-group boundary cut
 // ------------------------------------------------------------------------------------------
-template <int D, typename OutT>
-__global__ __launch_bounds__(256) void attn_combine_kernel(AttnParams p) {
-    // (eight values of d per thread: half as many work-groups as with four, so that the launch
-    // fits the device in one round; the kernel is a chain of two memory latencies, not bandwidth)
-    constexpr int kTpc = D / 8;             // threads per column
-    constexpr int kCols = 256 / kTpc;       // columns per block
+// A column's row of D values is covered by D/8 lanes, eight values each.  What bounds the kernel
+// is memory latency, not bandwidth: the cut table, then the partials, a few in flight at a time.
+// PW = 1: a wave folds all parts of its columns, four waves per work-group.  PW > 1: the PW waves
+// of a work-group share the columns of one wave and fold a contiguous slice of the parts each;
+// the slices are merged through LDS in part order.  A short batch cuts every sequence into many
+// parts (one sequence: all of the split), which one wave per column walks four at a time, a round
+// trip each.  Measured (3B shape, k = 4; PW = 1 / 4 / 8): 8 sequences of 2304 tokens, 16 parts
+// each, 7.3 / 4.2 / 5.1 us; one sequence of 4096 tokens, 128 parts, 41 / 9.8 / 7.4 us (7B shape,
+// 64 parts: 22 / 6.0 / 5.6 us); 14B shape, 32 sequences of 5 parts each, 4.8 / 9.8 / 13.8 us.
+// (With the loads of a batch behind conditions and one fold per part the first two took 13-20 and
+// 85 us.)
+template <int D, typename OutT, int PW>
+__global__ __launch_bounds__(PW == 1 ? 256 : 64 * PW) void attn_combine_kernel(AttnParams p) {
+    constexpr int kTpc = D / 8;                   // lanes per column
+    constexpr int kColsPerWave = 64 / kTpc;
+    constexpr int kColWaves = PW == 1 ? 4 : 1;    // waves of the work-group with columns of their own
+    constexpr int kBatch = PW == 1 ? 4 : 8;       // parts in flight per wave
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kvh = blockIdx.x % p.Hkv;  // blockIdx.x = sequence * Hkv + KV head
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && *p.error_flag != 0) {
-        // a wave of the main kernel gave up waiting for its partner: the results cannot be
-        // trusted, so make that impossible to miss
-        static_cast<OutT *>(p.out)[0] = sizeof(OutT) == 2 ? (OutT)0x7fc0 : (OutT)0;
-        if (p.lse) p.lse[0] = NAN;
-    }
     const int4 cut = *reinterpret_cast<const int4 *>(p.cuts + 4 * (int64_t)blockIdx.x);
     const bool dense = p.error_flag[1] != 0;  // every part owns tiles
+    const bool poison = blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && p.error_flag[0] != 0;
     const int r_first = cut.x, r_last = cut.y;
-    if (r_first == r_last) return;          // one wave saw the whole sequence and wrote it (or no tiles)
-    SeqInfo si{};
-    si.q0 = cut.z;
-    si.R = cut.w;
-    Split sp{};
-    if (!dense) sp = make_split(p, p.tile_prefix[p.B]);
-    const int sub = kvh % p.HI;
-    const int n = blockIdx.y * kCols + threadIdx.x / kTpc;
-    const int d8 = (threadIdx.x % kTpc) * 8;
-    const int M = p.G * si.R;
-    if (n >= M) return;
-    const int i = n / p.G, gh = n % p.G;
-    // partials in key order: slot 2*u+1 of the first part's wave u, then slot 2*u of the later
-    // ones; when there are fewer tiles than parts some own no tile and wrote nothing.  They are
-    // folded in that order, four at a time so that their loads are in flight together.
-    float mt = -INFINITY, lt = 0.f;
-    floatx4 o = {0.f, 0.f, 0.f, 0.f}, o2 = {0.f, 0.f, 0.f, 0.f};
-    for (int r = r_first; r <= r_last;) {
-        int64_t prow[4];
-        int cnt = 0;
-        for (; r <= r_last && cnt < 4; ++r) {
-            if (!dense && !part_owns_tiles(sp, r)) continue;
-            const int w = r * p.HI + sub;
-            const int64_t row = (int64_t)(r == r_first ? 2 * w + 1 : 2 * w) * p.Mpad + n;
-            if (cnt == 0) prow[0] = row;
-            if (cnt == 1) prow[1] = row;
-            if (cnt == 2) prow[2] = row;
-            if (cnt == 3) prow[3] = row;
-            ++cnt;
-        }
-        floatx4 stats[4];
-        u32x4 q[4];
+    const int R = cut.w, M = p.G * R;
+    if (r_first != r_last) {  // block-uniform (equal: one wave saw the whole sequence and wrote it, or no tiles)
+        Split sp{};
+        if (!dense) sp = make_split(p, p.tile_prefix[p.B]);
+        const int sub = kvh % p.HI;
+        const int n = (blockIdx.y * kColWaves + (PW == 1 ? wave : 0)) * kColsPerWave + lane / kTpc;
+        const int d8 = (lane % kTpc) * 8;
+        const int nc = max(0, min(n, M - 1));  // lanes past the last column read it again and write nothing
+        // partials in key order: slot 2*u+1 of the first part's wave u, then slot 2*u of the later
+        // ones; when there are fewer tiles than parts some own no tile and wrote nothing.  The
+        // loads of a batch carry no condition, so that they are in flight together; what a batch
+        // reads past the slice, or of a part without tiles, gets weight zero.
+        const int per = (r_last - r_first + PW) / PW;  // parts of a slice
+        const int r0 = r_first + (PW == 1 ? 0 : wave * per), r1 = min(r0 + per, r_last + 1);
+        float mt = -INFINITY, lt = 0.f;
+        floatx4 o = {0.f, 0.f, 0.f, 0.f}, o2 = {0.f, 0.f, 0.f, 0.f};
+        for (int rb = r0; rb < r1; rb += kBatch) {
+            floatx4 stats[kBatch];
+            u32x4 q[kBatch];
+            bool have[kBatch];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j < cnt) {
-                stats[j] = *reinterpret_cast<const floatx4 *>(p.ws_ml + prow[j] * 4);
-                q[j] = *reinterpret_cast<const u32x4 *>(p.ws_o + prow[j] * D + d8);
+            for (int j = 0; j < kBatch; ++j) {
+                const int r = min(rb + j, r1 - 1);
+                const int w = r * p.HI + sub;
+                const int64_t row = (int64_t)(r == r_first ? 2 * w + 1 : 2 * w) * p.Mpad + nc;
+                stats[j] = *reinterpret_cast<const floatx4 *>(p.ws_ml + row * 4);
+                q[j] = *reinterpret_cast<const u32x4 *>(p.ws_o + row * D + d8);
+                have[j] = rb + j < r1 && (dense || part_owns_tiles(sp, r));
             }
-        }
+            float mnew = mt;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j < cnt) {
-                const float mnew = fmaxf(mt, stats[j][0]);
-                const float msafe = mnew == -INFINITY ? 0.f : mnew;
-                const float keep = exp2f(mt - msafe), wgt = exp2f(stats[j][0] - msafe);
-                const float unit = stats[j][2] * (1.f / 32767.f) * wgt;
+            for (int j = 0; j < kBatch; ++j) mnew = fmaxf(mnew, have[j] ? stats[j][0] : -INFINITY);
+            const float msafe = mnew == -INFINITY ? 0.f : mnew;
+            const float keep = exp2f(mt - msafe);
+            lt *= keep;
+            o *= keep;
+            o2 *= keep;
+            mt = mnew;
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const float wgt = have[j] ? exp2f(stats[j][0] - msafe) : 0.f;
+                const float unit = have[j] ? stats[j][2] * (1.f / 32767.f) * wgt : 0.f;
                 const floatx4 x = {(float)(int16_t)(q[j][0] & 0xffffu), (float)(int16_t)(q[j][0] >> 16),
                                    (float)(int16_t)(q[j][1] & 0xffffu), (float)(int16_t)(q[j][1] >> 16)};
                 const floatx4 x2 = {(float)(int16_t)(q[j][2] & 0xffffu), (float)(int16_t)(q[j][2] >> 16),
                                     (float)(int16_t)(q[j][3] & 0xffffu), (float)(int16_t)(q[j][3] >> 16)};
-                lt = lt * keep + stats[j][1] * wgt;
-                o = o * keep + x * unit;
-                o2 = o2 * keep + x2 * unit;
-                mt = mnew;
+                lt += have[j] ? stats[j][1] * wgt : 0.f;
+                o = o + x * unit;
+                o2 = o2 + x2 * unit;
             }
         }
+        if constexpr (PW > 1) {
+            __shared__ floatx4 sh_o[PW][2][64];
+            __shared__ floatx2 sh_ml[PW][64];
+            sh_o[wave][0][lane] = o;
+            sh_o[wave][1][lane] = o2;
+            sh_ml[wave][lane] = floatx2{mt, lt};
+            __syncthreads();
+            if (wave == 0) {
+                floatx2 ml[PW];
+                float mall = -INFINITY;
+#pragma unroll
+                for (int w = 0; w < PW; ++w) {
+                    ml[w] = sh_ml[w][lane];
+                    mall = fmaxf(mall, ml[w][0]);
+                }
+                const float msafe = mall == -INFINITY ? 0.f : mall;
+                lt = 0.f;
+                o = o2 = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < PW; ++w) {
+                    const float wgt = exp2f(ml[w][0] - msafe);
+                    lt += ml[w][1] * wgt;
+                    o = o + sh_o[w][0][lane] * wgt;
+                    o2 = o2 + sh_o[w][1][lane] * wgt;
+                }
+                mt = mall;
+            }
+        }
+        if (n < M && (PW == 1 || wave == 0)) {
+            const int i = n / p.G, gh = n % p.G;
+            const float inv = lt > 0.f ? 1.f / lt : 0.f;
+            const int64_t orow = (int64_t)(cut.z + i) * p.Hq + kvh * p.G + gh;
+            OutT *dst = static_cast<OutT *>(p.out) + orow * D + d8;
+            const bf16x2 a = __builtin_convertvector(floatx2{o[0] * inv, o[1] * inv}, bf16x2);
+            const bf16x2 c2 = __builtin_convertvector(floatx2{o[2] * inv, o[3] * inv}, bf16x2);
+            const bf16x2 a2 = __builtin_convertvector(floatx2{o2[0] * inv, o2[1] * inv}, bf16x2);
+            const bf16x2 c4 = __builtin_convertvector(floatx2{o2[2] * inv, o2[3] * inv}, bf16x2);
+            *reinterpret_cast<u32x4 *>(dst) =
+                u32x4{__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, c2),
+                      __builtin_bit_cast(uint32_t, a2), __builtin_bit_cast(uint32_t, c4)};
+            if (p.lse && d8 == 0)
+                p.lse[orow] = lt > 0.f ? (mt + log2f(lt)) * 0.6931471805599453f : -INFINITY;
+        }
     }
-    const float inv = lt > 0.f ? 1.f / lt : 0.f;
-    const int64_t orow = (int64_t)(si.q0 + i) * p.Hq + kvh * p.G + gh;
-    OutT *dst = static_cast<OutT *>(p.out) + orow * D + d8;
-    if constexpr (sizeof(OutT) == 2) {
-        const bf16x2 a = __builtin_convertvector(floatx2{o[0] * inv, o[1] * inv}, bf16x2);
-        const bf16x2 c2 = __builtin_convertvector(floatx2{o[2] * inv, o[3] * inv}, bf16x2);
-        const bf16x2 a2 = __builtin_convertvector(floatx2{o2[0] * inv, o2[1] * inv}, bf16x2);
-        const bf16x2 c4 = __builtin_convertvector(floatx2{o2[2] * inv, o2[3] * inv}, bf16x2);
-        *reinterpret_cast<u32x4 *>(dst) =
-            u32x4{__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, c2),
-                  __builtin_bit_cast(uint32_t, a2), __builtin_bit_cast(uint32_t, c4)};
-    } else {
-        *reinterpret_cast<floatx4 *>(dst) = o * inv;
-        *reinterpret_cast<floatx4 *>(dst + 4) = o2 * inv;
+    if (poison) {
+        // a wave of the main kernel gave up waiting for its partner: the results cannot be
+        // trusted, so make that impossible to miss (this thread's own row was written above)
+        static_cast<OutT *>(p.out)[0] = (OutT)0x7fc0;
+        if (p.lse) p.lse[0] = NAN;
     }
-    if (p.lse && d8 == 0)
-        p.lse[orow] = lt > 0.f ? (mt + log2f(lt)) * 0.6931471805599453f : -INFINITY;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1389,6 +1424,25 @@ hipError_t launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream) {
         if (dev >= 0) configured[dev] = true;
     }
     hipLaunchKernelGGL((attn_bf16_kernel<D, NT, uint16_t, CW>), grid, dim3(2 * kConsumers * 64), smem, stream, p);
+    return hipGetLastError();
+}
+
+// The combine kernel's form (see there), by the parts a (sequence, KV head) has on average: sharing
+// them between waves wins from 16 parts on (7.3 -> 4.2 us) and loses at 8 (5.5 -> 6.8 us); eight
+// waves win over four from 64 on (6.0 -> 5.6 us).
+// forced: 1, 4 or 8 (RESPEC_ATTN_COMBINE), 0 = by this rule.
+template <int D>
+hipError_t launch_combine(const AttnParams &p, int M, long forced, hipStream_t stream) {
+    const int cols_per_wave = 64 / (D / 8);
+    const int64_t pairs = (int64_t)p.B * p.Hkv;
+    const int groups = (M + cols_per_wave - 1) / cols_per_wave;
+    const long pw = forced == 1 || forced == 4 || forced == 8 ? forced : p.W >= 64 * pairs ? 8 : p.W >= 12 * pairs ? 4 : 1;
+    if (pw == 8)
+        hipLaunchKernelGGL((attn_combine_kernel<D, uint16_t, 8>), dim3((unsigned)pairs, (unsigned)groups), dim3(512), 0, stream, p);
+    else if (pw == 4)
+        hipLaunchKernelGGL((attn_combine_kernel<D, uint16_t, 4>), dim3((unsigned)pairs, (unsigned)groups), dim3(256), 0, stream, p);
+    else
+        hipLaunchKernelGGL((attn_combine_kernel<D, uint16_t, 1>), dim3((unsigned)pairs, (unsigned)((groups + 3) / 4)), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 
@@ -1624,13 +1678,8 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
         g_mark_after_main = nullptr;
     }
     {
-        const int cols_per_block = 256 / (D / 8);
-        const dim3 cgrid((unsigned)(B * Hkv), (unsigned)((M + cols_per_block - 1) / cols_per_block));
-        if (D == 128)
-            hipLaunchKernelGGL((attn_combine_kernel<128, uint16_t>), cgrid, dim3(256), 0, stream, p);
-        else
-            hipLaunchKernelGGL((attn_combine_kernel<64, uint16_t>), cgrid, dim3(256), 0, stream, p);
-        err = hipGetLastError();
+        err = D == 128 ? launch_combine<128>(p, M, kn.get(&Knobs::attn_combine, 0), stream)
+                       : launch_combine<64>(p, M, kn.get(&Knobs::attn_combine, 0), stream);
         if (err != hipSuccess)
             return fail(RESPEC_ERR_HIP, "verify_attention: combine launch failed: %s", hipGetErrorString(err));
     }

@@ -33,6 +33,7 @@ struct Knobs {
     long attn_wide;         // RESPEC_ATTN_WIDE: 0/1 one or two consumer waves per range (2-4 column tiles)
     long attn_quad;         // RESPEC_ATTN_QUAD: 0/1/2 four consumers per range never / by rule / also narrow blocks
     long attn_inline;       // RESPEC_ATTN_INLINE: 0 = the set-up kernel also for small batches
+    long attn_combine;      // RESPEC_ATTN_COMBINE: waves that share a column's parts in the combine kernel (1, 4, 8)
     long sampler_split;     // RESPEC_SAMPLER_SPLIT: work-groups per sequence (1, 2, 4, 8)
     long sampler_two_term;  // RESPEC_SAMPLER_TWO_TERM: never the one-fma exponent
     long sampler_guarded;   // RESPEC_SAMPLER_GUARDED: the guarded normaliser pass everywhere
