@@ -5,16 +5,16 @@
 // bf16 path.  The G*(k_b+1) query rows that share one KV head are the columns of 16-wide
 // MFMA tiles.  Work is cut into 32-key tiles of one (KV head, sequence); the tiles form flat
 // lists ordered (head, sequence, tile) that are split evenly over a fixed number of ranges
-// (four per compute unit), so every range streams the same number of bytes whatever the mix of
-// sequence lengths.  One work-group per compute unit holds four pairs of waves: the consumer
-// of a pair computes its range, the producer walks the same range ahead of it and only moves
-// tiles (global memory -> registers -> a two-slot ring in LDS).  Scores are computed
+// (two to four per compute unit), so every range streams the same number of bytes whatever the mix
+// of sequence lengths.  One work-group per compute unit holds four producer waves, which walk a
+// range ahead of its consumers and only move tiles (global memory -> registers -> a ring in LDS),
+// and four or eight consumer waves, which compute.  Scores are computed
 // transposed (S^T = K Q^T, v_mfma_f32_16x16x32_bf16) so that a lane's four accumulator rows
 // are keys and its column is one query row: the probabilities then feed the second product
 // (O^T = V^T P^T) straight from registers, and the softmax statistics of a row live in one
 // lane column.  The contraction indices of both products are permuted freely (any order is
 // valid as long as both operands agree), which is what lets K be read from LDS in 16-byte
-// pieces and V in 8-byte pieces along d with a register-level 2-byte regroup.
+// pieces and V with the transposing LDS reads of gfx950.
 // A range is walked as segments (one sequence each).  A segment that covers a whole sequence
 // writes the output; a sequence cut by a range border leaves partials (max, sum, unnormalised
 // O as 16-bit fixed point), at most two per range, which a second kernel folds in a fixed
@@ -42,14 +42,16 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTileKeys = 32;         // keys per wave tile
 constexpr int kColTile = 16;          // query rows per MFMA column tile
 constexpr int kMaxColsPerBlock = 64;  // 4 column tiles
 constexpr float kRescaleSlack = 8.f;  // log2 units
-constexpr int kConsumers = 4;         // computing waves per work-group (one per SIMD), each with a
-                                      // producer wave; one work-group per compute unit
-constexpr int kSlots = 2;             // tiles in a pair's LDS ring = tiles a producer keeps in flight
+constexpr float kNoMax = -3.402823466e38f;  // reference of a row that has seen no key (finite: -inf minus it is -inf)
+constexpr int kProducers = 4;         // waves per work-group that move tiles (one per SIMD), beside four
+                                      // or eight computing ones; one work-group per compute unit
+constexpr int kSlots = 2;             // tiles in a producer's LDS ring = tiles it keeps in flight
 constexpr int kMaxWaves = 2048;       // upper bound of the split width (sizes the workspace)
 
 // Where a wave's range of the flat tile list starts and how many tiles it holds, with the
@@ -96,7 +98,9 @@ struct AttnParams {
     int32_t *cuts;         // [B][Hkv][4] first and last part that hold tiles of the (sequence,
                            // head), first query row, query rows; error_flag[1]: every part owns tiles
     int32_t Mpad;          // G*max_q rounded up to kColTile
-    float scale2;          // sm_scale * log2(e)
+    float scale2;          // sm_scale * log2(e) (fp32 kernel)
+    float scale_abs;       // its magnitude, at least 1e-37, and ...
+    uint32_t q_sign;       // ... the sign bits that make up for it, two bf16 (bf16 kernel)
     int32_t inline_setup;  // the main kernel builds the split itself (no set-up kernel in front of it)
 };
 
@@ -331,14 +335,17 @@ template <int D>
 struct Bf16Cfg {
     static constexpr int kRowElems = D + 8;                 // padded LDS row (bf16 elements)
     static constexpr int kRowBytes = kRowElems * 2;
-    static constexpr int kTileBytes = kTileKeys * kRowBytes;  // one K or V tile
-    static constexpr int kWaveBytes = 2 * kTileBytes;         // K + V
+    // (V rows are padded by 32 bytes: the four rows that sixteen lanes of a transposing read touch
+    // then fall into different banks; K rows by 16: sixteen rows read at one column do)
+    static constexpr int kVRowBytes = (D + 16) * 2;
+    static constexpr int kTileBytes = kTileKeys * kRowBytes;    // one K tile
+    static constexpr int kVTileBytes = kTileKeys * kVRowBytes;  // one V tile
+    static constexpr int kWaveBytes = kTileBytes + kVTileBytes; // K + V
     static constexpr int kLanesPerRow = D / 8;                // 16-byte pieces per key row
     static constexpr int kRowsPerLoad = 64 / kLanesPerRow;
     static constexpr int kLoads = kTileKeys / kRowsPerLoad;   // global loads per tile per lane
     static constexpr int kKSteps = D / 32;                    // MFMA k-steps of S^T
     static constexpr int kDTiles = D / 16;                    // 16-row d tiles of O^T
-    static constexpr int kEpl = D / 16;                       // V elements per lane per key
     static constexpr int kMergeStride = D + 4;                // fp32 row of the write-out staging (floats)
 };
 
@@ -411,13 +418,13 @@ __device__ inline TileOffsets paged_tile_offsets(const AttnParams &p, const SeqI
     return o;
 }
 
-template <int D>
+template <int D, int RowBytes>
 __device__ inline void store_tile(const u32x4 (&r)[Bf16Cfg<D>::kLoads], char *lds, int lane) {
     using C = Bf16Cfg<D>;
     const int rl = lane / C::kLanesPerRow, cl = lane % C::kLanesPerRow;
 #pragma unroll
     for (int j = 0; j < C::kLoads; ++j)
-        *reinterpret_cast<u32x4 *>(lds + (j * C::kRowsPerLoad + rl) * C::kRowBytes + cl * 16) = r[j];
+        *reinterpret_cast<u32x4 *>(lds + (j * C::kRowsPerLoad + rl) * RowBytes + cl * 16) = r[j];
 }
 
 // Position of a wave in the flat tile list.  The bounds of the next sequence that has tiles
@@ -480,8 +487,23 @@ __device__ inline void wait_at_least(LdsCounter flag, uint32_t need, bool &alive
     *error_flag = 1;
 }
 
-// One work-group per compute unit: four consumer waves (one per SIMD) and four producer
-// waves.  Consumer i owns an equal range of the flat tile list; producer i walks the same
+// LDS of one form of the kernel.  Eight consumers beside the four producers leave a wave 168
+// registers; two column tiles at D = 128 do not fit with their query rows (32 registers), which
+// then live in LDS, in the room of every producer's second slot: the range's tiles still
+// alternate between its producers' slots.
+template <int D, int NT, int NC>
+struct Bf16Form {
+    using C = Bf16Cfg<D>;
+    static constexpr bool kQueryInLds = D == 128 && NT == 2 && NC == 8;
+    static constexpr int kLdsSlots = kQueryInLds ? 1 : kSlots;
+    static constexpr int kQueryBytes = kQueryInLds ? NT * kColTile * C::kRowBytes : 0;  // per consumer
+    static constexpr int kQueryOffset = kProducers * kLdsSlots * C::kWaveBytes;
+    static constexpr int kCounterOffset = kQueryOffset + NC * kQueryBytes;
+    static constexpr int kBytes = kCounterOffset + (kProducers + 2 * NC) * (int)sizeof(uint32_t);
+};
+
+// One work-group per compute unit: NC consumer waves (one or two per SIMD) and four producer
+// waves.  CW = 1: consumer i owns an equal range of the flat tile list; producer i walks the same
 // range ahead of it and does nothing but move tiles: global memory -> registers (two tiles in
 // flight) -> the pair's two-slot ring in LDS.  A wave that computes cannot keep the memory
 // pipeline of its compute unit full (a request can only be issued between two tiles' worth of
@@ -491,48 +513,50 @@ __device__ inline void wait_at_least(LdsCounter flag, uint32_t need, bool &alive
 // execute in order, so a counter written after the data (or after the last read) needs no
 // further fence.
 //
-// CW ("column ways") = 2 is the form for wide column blocks (more than 32 query columns): the
-// accumulators of 64 columns do not fit a wave's registers, so two consumers share one range,
-// each with half of the columns, and the two producers of the range move its tiles in turn
-// (producer w the tiles j = w mod 2, each into its own ring).  A work-group then walks two
-// ranges instead of four.  Each consumer keeps its own `consumed`; a producer reuses a slot once
-// both have passed it.  CW = 4 is the same with all four consumers on one range (up to 128
-// columns: the trees of a drafter that proposes ten to eighteen nodes per sequence at a group of
-// seven heads): the four producers take the range's tiles in turn and the work-group walks one
-// range.  With 16 columns per consumer the same form serves narrow blocks on small batches, where
-// a quarter of the ranges means a quarter of the partials.
-template <int D, int NT, typename OutT, int CW>
-__global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnParams p) {
+// CW ("column ways") = 2 and 4: that many consumers share one range, each with NT column tiles of
+// its own (the accumulators and query rows of 64 columns do not fit a wave's registers), and the
+// producers that the work-group has per range (PW) move its tiles in turn, producer w the tiles
+// j = w mod PW.  Each consumer keeps its own `consumed`; a producer reuses a slot once all of them
+// have passed it.  Every consumer of a range sees every tile, so these forms are bound by the
+// consumers: with one per SIMD (NC = 4) the dependent phases of a tile (scores, softmax, second
+// product) leave the SIMD idle between them.  NC = 8 puts two on each SIMD, on different ranges
+// (B = 256 at the 7B shape, trees of 91 columns: 409 -> 340 us per call by HIP events, 311 us with
+// the shorter loop below as well).
+template <int D, int NT, typename OutT, int CW, int NC>
+__global__ __launch_bounds__((NC + kProducers) * 64, 1) void attn_bf16_kernel(AttnParams p) {
     using C = Bf16Cfg<D>;
     static_assert(CW == 1 || CW == 2 || CW == 4, "one, two or four consumers per range");
-    constexpr int kStreams = kConsumers / CW;     // ranges per work-group
-    extern __shared__ __align__(16) char smem[];  // [kConsumers][kSlots][kWaveBytes] | counters
-    const LdsCounter counters = (LdsCounter)(smem + kConsumers * kSlots * C::kWaveBytes);
+    constexpr int kStreams = NC / CW;             // ranges per work-group
+    constexpr int PW = kProducers / kStreams;     // producers per range
+    static_assert(PW >= 1 && kStreams * PW == kProducers, "the producers are shared out evenly");
+    using F = Bf16Form<D, NT, NC>;
+    extern __shared__ __align__(16) char smem[];  // [kProducers][F::kLdsSlots][kWaveBytes] | query rows | counters
+    const LdsCounter counters = (LdsCounter)(smem + F::kCounterOffset);
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform by construction
-    const bool producer = wave >= kConsumers;
-    const int role = producer ? wave - kConsumers : wave;  // index among the producers / consumers
-    const int stream = role / CW, way = role % CW;
+    const bool producer = wave >= NC;
+    const int role = producer ? wave - NC : wave;  // index among the producers / consumers
+    const int stream = producer ? role / PW : role / CW, way = producer ? role % PW : role % CW;
     const int c16 = lane & 15, g4 = lane >> 4;
     const int u = blockIdx.x * kStreams + stream;  // index of this range in the split
     // columns of a column block: 64 with one consumer per range, else what the consumers hold
     constexpr int kBlockCols = CW == 1 ? kMaxColsPerBlock : CW * NT * kColTile;
     const int col0 = blockIdx.y * kBlockCols + (producer ? 0 : way * NT * kColTile);
 
-    if (threadIdx.x < 3 * kConsumers) counters[threadIdx.x] = 0;
+    if (threadIdx.x < kProducers + 2 * NC) counters[threadIdx.x] = 0;
     // The split, built by every work-group for itself when the batch is small enough (one kernel
     // launch and its gap less in front of every call).  The bounds of all sequences and their
     // tile prefix are staged in the LDS that the rings will use afterwards, so the searches below
     // read no global memory.  Each work-group also leaves its own starting points and its share
     // of the cut table in the workspace: the combine kernel reads the table, and a later layer
     // of the same forward reads the starting points.
-    __shared__ int32_t sh_wave_sum[2 * kConsumers];
-    __shared__ WaveStart sh_start[kConsumers];
+    __shared__ int32_t sh_wave_sum[NC + kProducers];
+    __shared__ WaveStart sh_start[kStreams];
     if (p.inline_setup) {  // uniform over the launch
-        constexpr int kBlock = 2 * kConsumers * 64;
+        constexpr int kBlock = (NC + kProducers) * 64;
         static_assert((size_t)kInlineSeqs * sizeof(SeqInfo) + (kInlineSeqs + 1) * sizeof(int32_t) <=
-                          (size_t)kConsumers * kSlots * C::kWaveBytes, "the staging fits where the rings will be");
+                          (size_t)F::kCounterOffset, "the staging fits where the rings will be");
         SeqInfo *sh_seq = reinterpret_cast<SeqInfo *>(smem);
         int32_t *sh_prefix = reinterpret_cast<int32_t *>(smem + (size_t)kInlineSeqs * sizeof(SeqInfo));
         int base = 0;
@@ -553,7 +577,7 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
             __syncthreads();
             int before = 0, all = 0;
 #pragma unroll
-            for (int w = 0; w < 2 * kConsumers; ++w) {
+            for (int w = 0; w < NC + kProducers; ++w) {
                 const int x = sh_wave_sum[w];
                 if (w < (int)(threadIdx.x >> 6)) before += x;
                 all += x;
@@ -595,8 +619,8 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
     // filled[r]: tiles producer r has written to its ring; consumed[r]: tiles of the range that
     // consumer r has finished with; read_done[r]: tiles whose K and V consumer r has read (CW > 1)
     const LdsCounter filled = counters;
-    const LdsCounter consumed = counters + kConsumers;
-    const LdsCounter read_done = counters + 2 * kConsumers;
+    const LdsCounter consumed = counters + kProducers;
+    const LdsCounter read_done = consumed + NC;
 
     if (u >= p.W) return;  // wave-uniform, and the same for all waves of a range
     int32_t start[10];  // the fields of this range's WaveStart, wave-uniform
@@ -640,17 +664,17 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
             row_off[j] = (uint32_t)(lane / C::kLanesPerRow + j * C::kRowsPerLoad) * (uint32_t)row_bytes +
                          (uint32_t)(lane % C::kLanesPerRow) * 16u;
         u32x4 kr[kSlots][C::kLoads], vr[kSlots][C::kLoads];
-        char *ring = smem + role * (kSlots * C::kWaveBytes);
-        // this producer moves the range's tiles way, way + CW, ...: `pos` is the tile the cursor
+        char *ring = smem + role * (F::kLdsSlots * C::kWaveBytes);
+        // this producer moves the range's tiles way, way + PW, ...: `pos` is the tile the cursor
         // points at, n_local the number of tiles that are this producer's
         int pos = way;
-        const int n_local = (n_tiles - way + CW - 1) / CW;
+        const int n_local = (n_tiles - way + PW - 1) / PW;
         // Every step issues its tile requests, also when the range has no tile left: the count
         // of requests behind a buffer's own is then the same on every path, and the wait for a
         // buffer leaves exactly the younger ones in flight.  An idle request re-reads one
         // 256-byte piece of the last tile, which the caches hold.
         bool next_known = false;  // cp.nb / cp.nh / cp.nsi have been looked up
-        if (CW > 1 && way > 0 && way < n_tiles) {  // producer `way` starts `way` tiles in
+        if (PW > 1 && way > 0 && way < n_tiles) {  // producer `way` starts `way` tiles in
             cursor_find_next(p, cp);
             next_known = true;
             for (int c = 0; c < way; ++c) cursor_advance(p, cp);
@@ -678,32 +702,32 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
                 next_known = true;
             }
             if (live) {
-                if (pos + CW < n_tiles) {
+                if (pos + PW < n_tiles) {
 #pragma unroll
-                    for (int c = 0; c < CW; ++c) cursor_advance(p, cp);
+                    for (int c = 0; c < PW; ++c) cursor_advance(p, cp);
                     // the page ids of the tile after this one: a scalar look-up that has a whole
                     // step to arrive
                     if (paged) next_off = paged_tile_offsets(p, cp.si, cp.t, cp.h, D * 2, row_bytes);
                 }
-                pos += CW;
+                pos += PW;
             }
         };
-        // j: index among this producer's own tiles (tile CW * j + way of the range)
+        // j: index among this producer's own tiles (tile PW * j + way of the range)
         auto move = [&](auto S, const int j) __attribute__((always_inline)) {
             constexpr int s = decltype(S)::value;
             if (j < n_local) {
                 // slot s is free once every consumer of the range has finished with the tile
-                // that was in it, this producer's tile j - 2
-                if (j >= kSlots) {
-                    const uint32_t need = (uint32_t)(CW * (j - kSlots) + way + 1);
+                // that was in it, this producer's tile j - kLdsSlots
+                if (j >= F::kLdsSlots) {
+                    const uint32_t need = (uint32_t)(PW * (j - F::kLdsSlots) + way + 1);
 #pragma unroll
                     for (int c = 0; c < CW; ++c)
                         wait_at_least(consumed + stream * CW + c, need, alive, p.error_flag);
                 }
                 asm volatile("" ::: "memory");
-                char *slot = ring + s * C::kWaveBytes;
-                store_tile<D>(kr[s], slot, lane);
-                store_tile<D>(vr[s], slot + C::kTileBytes, lane);
+                char *slot = ring + (s % F::kLdsSlots) * C::kWaveBytes;
+                store_tile<D, C::kRowBytes>(kr[s], slot, lane);
+                store_tile<D, C::kVRowBytes>(vr[s], slot + C::kTileBytes, lane);
                 asm volatile("" ::: "memory");
                 filled[role] = (uint32_t)(j + 1);
             }
@@ -721,6 +745,13 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
     // ----------------------------------------------------------------------------------------
     // consumer
     // ----------------------------------------------------------------------------------------
+    if (CW > 1 && col0 >= p.G * p.max_q) {
+        // no query row of any sequence has a column here (a block of 91 columns leaves the fourth
+        // consumer of 32 without any): never waited for
+        read_done[role] = 0x7fffffffu;
+        consumed[role] = 0x7fffffffu;
+        return;
+    }
     // this lane's columns: query row i and head gh within the group, fixed for the kernel
     int col_i[NT], col_gh[NT];
 #pragma unroll
@@ -729,6 +760,27 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
         col_i[nt] = n / p.G;
         col_gh[nt] = n % p.G;
     }
+    // (where registers are short the pair is packed into one of them)
+    constexpr bool kPackColumns = F::kQueryInLds || (D == 128 && NT >= 3);
+    int col_packed[NT];
+    if constexpr (kPackColumns) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            col_packed[nt] = col_i[nt] << 16 | col_gh[nt];
+            asm volatile("" : "+v"(col_packed[nt]));
+        }
+    }
+    auto unpack_columns = [&]() __attribute__((always_inline)) {
+        if constexpr (kPackColumns) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                int v = col_packed[nt];
+                asm volatile("" : "+v"(v));
+                col_i[nt] = v >> 16;
+                col_gh[nt] = v & 0xffff;
+            }
+        }
+    };
 
     auto load_q = [&](bf16x8(&dst)[NT][C::kKSteps], const SeqInfo &s, int kvh) __attribute__((always_inline)) {
 #pragma unroll
@@ -740,18 +792,20 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
             for (int t = 0; t < C::kKSteps; ++t) {
                 u32x4 raw = {0u, 0u, 0u, 0u};
                 if (valid) raw = *reinterpret_cast<const u32x4 *>(qrow + (t * 32 + g4 * 8) * 2);
+                raw ^= p.q_sign;  // (a negative scale: the rows are negated, which is exact)
                 dst[nt][t] = __builtin_bit_cast(bf16x8, raw);
             }
         }
     };
 
-    bf16x8 qreg[NT][C::kKSteps];  // query rows of the segment at hand
-    load_q(qreg, cp.si, cp.h);    // of the first segment, requested before anything else
+    bf16x8 qreg[NT][C::kKSteps];  // query rows of the segment at hand (F::kQueryInLds: in LDS instead)
+    if constexpr (!F::kQueryInLds) load_q(qreg, cp.si, cp.h);  // of the first segment, requested before anything else
+    char *q_lds = smem + F::kQueryOffset + role * F::kQueryBytes;  // F::kQueryInLds: this wave's rows
     cursor_find_next(p, cp);
     // query rows of the next segment, requested when the current one begins (not kept for the
     // widest column blocks at D = 128, where the registers do not allow it: a segment then
     // starts by waiting for its query rows)
-    constexpr bool kPrefetchQ = !(D == 128 && NT >= 3);
+    constexpr bool kPrefetchQ = !(D == 128 && NT >= 3) && !F::kQueryInLds;
     bf16x8 qnext[kPrefetchQ ? NT : 1][C::kKSteps];
     bool qnext_valid = false;
     bool q_in_place = false;  // qreg already holds the rows of the segment that begins
@@ -768,23 +822,33 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
     for (int idx = 0; idx < n_tiles; ++idx) {
         const int key0 = cp.t * kTileKeys;
         const int kvh = cp.h;
-        // tile idx of the range is tile idx / CW of producer idx % CW of this range
-        const int src = stream * CW + idx % CW;
-        char *k_lds = smem + src * (kSlots * C::kWaveBytes) + ((idx / CW) % kSlots) * C::kWaveBytes;
+        // tile idx of the range is tile idx / PW of producer idx % PW of this range
+        const int src = stream * PW + idx % PW;
+        char *k_lds = smem + src * (F::kLdsSlots * C::kWaveBytes) + ((idx / PW) % F::kLdsSlots) * C::kWaveBytes;
         char *v_lds = k_lds + C::kTileBytes;
         if (idx == 0 || cp.t == 0) {  // a segment begins
+            unpack_columns();
             seg_t_first = cp.t;
             first_masked_key = cp.si.L - cp.si.R + 1;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 col_limit[nt] = col_i[nt] < cp.si.R ? (tree ? cp.si.L - 1 : cp.si.L - cp.si.R + col_i[nt]) : -1;
                 col_mask[nt] = tree && col_i[nt] < cp.si.R ? p.tree_mask[cp.si.q0 + col_i[nt]] : 0;
-                m_run[nt] = -INFINITY;
+                m_run[nt] = kNoMax;
                 l_run[nt] = 0.f;
 #pragma unroll
                 for (int t = 0; t < C::kDTiles; ++t) acc_o[nt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
-            if (q_in_place) {
+            if constexpr (F::kQueryInLds) {
+                bf16x8 qrow[NT][C::kKSteps];
+                load_q(qrow, cp.si, cp.h);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int t = 0; t < C::kKSteps; ++t)
+                        *reinterpret_cast<u32x4 *>(q_lds + (nt * kColTile + c16) * C::kRowBytes + (t * 32 + g4 * 8) * 2) =
+                            __builtin_bit_cast(u32x4, qrow[nt][t]);
+            } else if (q_in_place) {
                 // (moved over at the end of the previous segment)
             } else if (kPrefetchQ && qnext_valid) {
 #pragma unroll
@@ -801,14 +865,39 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
             }
         }
 
-        wait_at_least(filled + src, (uint32_t)(idx / CW + 1), alive, p.error_flag);
+        wait_at_least(filled + src, (uint32_t)(idx / PW + 1), alive, p.error_flag);
         asm volatile("" ::: "memory");
 
         // S^T[key, col] = sum_d K[key, d] Q[col, d]; two 16-key sub-tiles
         floatx4 s_acc[NT][2];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) s_acc[nt][0] = s_acc[nt][1] = floatx4{0.f, 0.f, 0.f, 0.f};
-        {
+        if constexpr (F::kQueryInLds) {
+            // one step = the four (NT = 2) fragments of a 32-wide slice of d: both key sub-tiles and
+            // every column tile, read one step ahead of the products that use them
+            u32x4 kf[2][2], qf[2][NT];
+            auto read_step = [&](const int t) __attribute__((always_inline)) {
+#pragma unroll
+                for (int js = 0; js < 2; ++js)
+                    kf[t & 1][js] = *reinterpret_cast<const u32x4 *>(k_lds + (js * 16 + c16) * C::kRowBytes + (t * 32 + g4 * 8) * 2);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    qf[t & 1][nt] = *reinterpret_cast<const u32x4 *>(q_lds + (nt * kColTile + c16) * C::kRowBytes + (t * 32 + g4 * 8) * 2);
+            };
+            read_step(0);
+#pragma unroll
+            for (int t = 0; t < C::kKSteps; ++t) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (t + 1 < C::kKSteps) read_step(t + 1);
+#pragma unroll
+                for (int js = 0; js < 2; ++js)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        s_acc[nt][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, kf[t & 1][js]), __builtin_bit_cast(bf16x8, qf[t & 1][nt]), s_acc[nt][js], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
             // The K fragments are read a few steps ahead of the products that use them: with one
             // consumer wave per SIMD nothing else hides the latency of a read, and left to
             // itself the compiler waits for each read right behind its issue.  The scheduling
@@ -835,51 +924,65 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
             __builtin_amdgcn_sched_barrier(0);
         }
 
-        // online softmax per column; accumulator element (js, i) is key key0 + 16 js + 4 g4 + i
+        // Online softmax per column; accumulator element (js, i) is key key0 + 16 js + 4 g4 + i.  The
+        // scores stay unscaled: the scale is positive, so it commutes with the maximum, and it is
+        // applied in the multiply-add that forms the exponent.
         const bool tail = key0 + kTileKeys > first_masked_key;  // wave-uniform
-        bf16x8 pfrag[NT];
-        float alpha[NT];
-        bool rescale = false;
+        if (tail) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            float sv[8];
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int js = 0; js < 2; ++js)
+                for (int js = 0; js < 2; ++js)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float x = s_acc[nt][js][i] * p.scale2;
-                    if (tail) {
+                    for (int i = 0; i < 4; ++i) {
                         const int key = key0 + js * 16 + g4 * 4 + i;
                         bool seen = key <= col_limit[nt];
                         if (tree) {
                             const int j = key - (first_masked_key - 1);  // index among the new tokens
                             seen = seen && (j < 0 || ((col_mask[nt] >> (j & 63)) & 1u));
                         }
-                        x = seen ? x : -INFINITY;
+                        s_acc[nt][js][i] = seen ? s_acc[nt][js][i] : -INFINITY;
                     }
-                    sv[js * 4 + i] = x;
-                }
-            float mloc = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])),
-                               fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-            mloc = max_across_rows(mloc);
-            // The exponent reference m_run follows the running maximum lazily: it moves only
-            // when the maximum has grown by more than kRescaleSlack (probabilities then stay
-            // below 2^kRescaleSlack, harmless in bf16 and fp32), so that rescaling the
-            // accumulators is a rare event instead of one per tile.
-            const bool grow = mloc > m_run[nt] + kRescaleSlack;
-            const float mnew = grow ? mloc : m_run[nt];
-            const float msafe = mnew == -INFINITY ? 0.f : mnew;
-            alpha[nt] = hw_exp2(m_run[nt] - msafe);
-            rescale |= grow;
+        }
+        // The exponent reference m_run follows the running maximum lazily: it moves only when some
+        // key's score exceeds it by more than kRescaleSlack (probabilities then stay below
+        // 2^kRescaleSlack, harmless in bf16 and fp32).  Nearly every tile therefore takes one
+        // comparison per lane and column; the maximum across lanes, the factor for what has been
+        // accumulated and its application belong to the rare tile that moves a reference.  (With
+        // the maximum across lanes formed for every tile and the scale applied to every score the
+        // loop had about 270 vector instructions per tile and consumer at two column tiles, the byte
+        // permutes that the transposing reads of V replace included; it has about 190.)
+        float lane_max[NT];
+        bool rescale = false;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const floatx4 x = s_acc[nt][0], y = s_acc[nt][1];
+            lane_max[nt] = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])));
+            rescale |= fmaf(lane_max[nt], p.scale_abs, -m_run[nt]) > kRescaleSlack;
+        }
+        if (__any(rescale)) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const float mloc = max_across_rows(lane_max[nt]) * p.scale_abs;
+                const float mnew = mloc > m_run[nt] + kRescaleSlack ? mloc : m_run[nt];
+                const float alpha = hw_exp2(m_run[nt] - mnew);
+                m_run[nt] = mnew;
+                l_run[nt] *= alpha;
+#pragma unroll
+                for (int t = 0; t < C::kDTiles; ++t) acc_o[nt][t] *= alpha;
+            }
+        }
+        bf16x8 pfrag[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
             float psum = 0.f;
             float pv[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                pv[e] = hw_exp2(sv[e] - msafe);
+                pv[e] = hw_exp2(fmaf(s_acc[nt][e / 4][e % 4], p.scale_abs, -m_run[nt]));
                 psum += pv[e];
             }
-            l_run[nt] = l_run[nt] * alpha[nt] + psum;
-            m_run[nt] = mnew;
+            l_run[nt] += psum;
             bf16x8 pf;
 #pragma unroll
             for (int e = 0; e < 8; e += 2) {
@@ -889,56 +992,48 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
             }
             pfrag[nt] = pf;
         }
-        if (__any(rescale)) {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int t = 0; t < C::kDTiles; ++t) acc_o[nt][t] *= alpha[nt];
-        }
 
         // O^T[d, col] += sum_key V[key, d] P[key, col]; contraction slot e of lane group g4 is
-        // key 16 (e/4) + 4 g4 + e%4, matching the score accumulators; d tile t holds
-        // d = kEpl * r + t for MFMA row r.  V is read in 8-byte pieces (4 values of d per key):
-        // for D = 128 in two rounds, which halves the registers the regroup needs
-        constexpr int kRounds = C::kEpl / 4;
+        // key 16 (e/4) + 4 g4 + e%4, matching the score accumulators.  V is read with the
+        // transposing LDS read: the sixteen lanes of a group address four keys x sixteen d (lane i:
+        // key i/4, the four d from 4 (i%4)) and lane i receives d = i of the four keys, which is
+        // the A operand of the product as it stands (8-byte reads along d needed 32 byte permutes
+        // per tile to regroup them).
+        {
+            typedef s16x4 __attribute__((address_space(3))) *LdsV;
+            constexpr int kAhead = 3;
+            s16x4 vf[C::kDTiles][2];
+            const char *v_lane = v_lds + (4 * g4 + c16 / 4) * C::kVRowBytes + (c16 % 4) * 8;
+            auto read_v = [&](const int t) __attribute__((always_inline)) {
 #pragma unroll
-        for (int hf = 0; hf < kRounds; ++hf) {
-            uint32_t vw[8][2];
+                for (int h = 0; h < 2; ++h)
+                    vf[t][h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsV)(v_lane + h * 16 * C::kVRowBytes + t * 32));
+            };
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int key = 16 * (e / 4) + 4 * g4 + (e % 4);
-                const u32x2 raw =
-                    *reinterpret_cast<const u32x2 *>(v_lds + key * C::kRowBytes + c16 * (C::kEpl * 2) + hf * 8);
-                vw[e][0] = raw[0];
-                vw[e][1] = raw[1];
-            }
+            for (int t = 0; t < kAhead; ++t) read_v(t);
 #pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-                const int t = hf * 4 + tt;
-                uint32_t aw[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t lo = vw[2 * c][tt / 2], hi = vw[2 * c + 1][tt / 2];
-                    aw[c] = (tt & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u)
-                                     : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-                }
-                const bf16x8 a = __builtin_bit_cast(bf16x8, u32x4{aw[0], aw[1], aw[2], aw[3]});
+            for (int t = 0; t < C::kDTiles; ++t) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (t + kAhead < C::kDTiles) read_v(t + kAhead);
+                const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vf[t][0], vf[t][1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
                     acc_o[nt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pfrag[nt], acc_o[nt][t], 0, 0, 0);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
 
         if (idx == n_tiles - 1 || cp.t == cp.si.tiles - 1) {  // the segment ends
             // A segment that covers its whole sequence writes the output; otherwise it leaves a
             // partial in one of this pair's two slots (0: the sequence began in an earlier
             // range, 1: it starts here and continues in the next one).  Lane (c16, g4) holds,
-            // for column c16 of each column tile, d = kEpl * (4 g4 + r) + t in acc_o[nt][t][r]:
+            // for column c16 of each column tile, d = 16 t + 4 g4 + r in acc_o[nt][t][r]:
             // written out like that, every store would scatter 16-byte pieces over 64 rows.
             // The columns go through the ring slot of the tile just finished (still owned by
             // the consumers of the range) instead, 32 at a time, and leave it as whole rows.
             // Two consumers that share the range take half of the slot each, 16 columns at a
             // time, once both have read the tile.
+            unpack_columns();
             const bool whole = seg_t_first == 0 && cp.t == cp.si.tiles - 1;
             const int64_t slot = 2 * (int64_t)u + (seg_t_first > 0 ? 0 : 1);
             // The next segment's query rows (requested when this segment began) move into place
@@ -996,11 +1091,8 @@ __global__ __launch_bounds__(2 * kConsumers * 64, 1) void attn_bf16_kernel(AttnP
                         if (mine) {
                             float *row = stage + local * C::kMergeStride;
 #pragma unroll
-                            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                                for (int t = 0; t < C::kEpl; t += 4)
-                                    *reinterpret_cast<floatx4 *>(row + C::kEpl * (4 * g4 + r) + t) =
-                                        floatx4{acc_o[nt][t][r], acc_o[nt][t + 1][r], acc_o[nt][t + 2][r], acc_o[nt][t + 3][r]};
+                            for (int t = 0; t < C::kDTiles; ++t)
+                                *reinterpret_cast<floatx4 *>(row + 16 * t + 4 * g4) = acc_o[nt][t];
                             if (g4 == 0) {
                                 const int ci = col_i[nt];
                                 const int orow = ci < cp.si.R ? (cp.si.q0 + ci) * p.Hq + kvh * p.G + col_gh[nt] : -1;
@@ -1410,33 +1502,35 @@ int compute_units() {
     return cached[dev];
 }
 
-template <int D, int NT, int CW>
+template <int D, int NT, int CW, int NC>
 hipError_t launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream) {
-    using C = Bf16Cfg<D>;
-    const size_t smem = (size_t)kConsumers * kSlots * C::kWaveBytes + 3 * kConsumers * sizeof(uint32_t);
+    const size_t smem = Bf16Form<D, NT, NC>::kBytes;
     static bool configured[64] = {false};  // per device; benign race: the attribute is idempotent
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
     if (dev < 0 || !configured[dev]) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_kernel<D, NT, uint16_t, CW>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_kernel<D, NT, uint16_t, CW, NC>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         if (dev >= 0) configured[dev] = true;
     }
-    hipLaunchKernelGGL((attn_bf16_kernel<D, NT, uint16_t, CW>), grid, dim3(2 * kConsumers * 64), smem, stream, p);
+    hipLaunchKernelGGL((attn_bf16_kernel<D, NT, uint16_t, CW, NC>), grid, dim3((NC + kProducers) * 64), smem, stream, p);
     return hipGetLastError();
 }
 
-// The combine kernel's form (see there), by the parts a (sequence, KV head) has on average: sharing
-// them between waves wins from 16 parts on (7.3 -> 4.2 us) and loses at 8 (5.5 -> 6.8 us); eight
-// waves win over four from 64 on (6.0 -> 5.6 us).
-// forced: 1, 4 or 8 (RESPEC_ATTN_COMBINE), 0 = by this rule.
+// The combine kernel's form (see there), by the parts that the longest sequence's heads have: the
+// average, times how much longer than the average the longest can be (at most twice that is
+// counted: the bound is the caller's and may be the model's).  Sharing them between waves wins from
+// 16 parts on (7.3 -> 4.2 us) and loses at 8 (5.5 -> 6.8 us); eight waves win over four from 64 on
+// (6.0 -> 5.6 us).  forced: 1, 4 or 8 (RESPEC_ATTN_COMBINE), 0 = by this rule.
 template <int D>
-hipError_t launch_combine(const AttnParams &p, int M, long forced, hipStream_t stream) {
+hipError_t launch_combine(const AttnParams &p, int M, int64_t kv_tokens, long forced, hipStream_t stream) {
     const int cols_per_wave = 64 / (D / 8);
     const int64_t pairs = (int64_t)p.B * p.Hkv;
     const int groups = (M + cols_per_wave - 1) / cols_per_wave;
-    const long pw = forced == 1 || forced == 4 || forced == 8 ? forced : p.W >= 64 * pairs ? 8 : p.W >= 12 * pairs ? 4 : 1;
+    const double longest = std::fmin(2.0, std::fmax(1.0, (double)p.max_kv_len * p.B / (double)kv_tokens));
+    const double parts = (double)p.W / (double)pairs * longest;
+    const long pw = forced == 1 || forced == 4 || forced == 8 ? forced : parts >= 64.0 ? 8 : parts >= 12.0 ? 4 : 1;
     if (pw == 8)
         hipLaunchKernelGGL((attn_combine_kernel<D, uint16_t, 8>), dim3((unsigned)pairs, (unsigned)groups), dim3(512), 0, stream, p);
     else if (pw == 4)
@@ -1446,16 +1540,17 @@ hipError_t launch_combine(const AttnParams &p, int M, long forced, hipStream_t s
     return hipGetLastError();
 }
 
-// nt: column tiles of a column block; cw: consumers that share a range
+// nt: column tiles of a column block; cw: consumers that share a range; nc: consumers of a work-group
 template <int D>
-hipError_t launch_bf16_nt(int nt, int cw, const AttnParams &p, dim3 grid, hipStream_t stream) {
-    if (cw == 4) return nt <= 4 ? launch_bf16<D, 1, 4>(p, grid, stream) : launch_bf16<D, 2, 4>(p, grid, stream);
-    if (cw == 2) return nt <= 2 ? launch_bf16<D, 1, 2>(p, grid, stream) : launch_bf16<D, 2, 2>(p, grid, stream);
+hipError_t launch_bf16_nt(int nt, int cw, int nc, const AttnParams &p, dim3 grid, hipStream_t stream) {
+    if (cw == 4 && nc == 8) return nt <= 4 ? launch_bf16<D, 1, 4, 8>(p, grid, stream) : launch_bf16<D, 2, 4, 8>(p, grid, stream);
+    if (cw == 2) return nt <= 2 ? launch_bf16<D, 1, 2, 8>(p, grid, stream) : launch_bf16<D, 2, 2, 8>(p, grid, stream);
+    if (cw == 4) return launch_bf16<D, 1, 4, 4>(p, grid, stream);
     switch (nt) {
-        case 1: return launch_bf16<D, 1, 1>(p, grid, stream);
-        case 2: return launch_bf16<D, 2, 1>(p, grid, stream);
-        case 3: return launch_bf16<D, 3, 1>(p, grid, stream);
-        default: return launch_bf16<D, 4, 1>(p, grid, stream);
+        case 1: return launch_bf16<D, 1, 1, 4>(p, grid, stream);
+        case 2: return launch_bf16<D, 2, 1, 4>(p, grid, stream);
+        case 3: return launch_bf16<D, 3, 1, 4>(p, grid, stream);
+        default: return launch_bf16<D, 4, 1, 4>(p, grid, stream);
     }
 }
 
@@ -1588,6 +1683,10 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     p.G = Hq / Hkv;
     p.Mpad = pl.Mpad;
     p.scale2 = (float)((double)sm_scale * 1.4426950408889634074);
+    // (a scale of zero becomes 1e-37: every exponent rounds to the one it has at zero, and a hidden
+    // key's -inf stays -inf when it is scaled)
+    p.scale_abs = std::fmax(std::fabs(p.scale2), 1e-37f);
+    p.q_sign = p.scale2 < 0.f ? 0x80008000u : 0u;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     hipError_t err;
@@ -1613,36 +1712,51 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
         return RESPEC_OK;
     }
 
-    // more than 64 columns (draft trees): blocks of 128 columns, four consumers per range, so
-    // that K and V are read once per 128 columns (RESPEC_ATTN_QUAD = 0: blocks of 64 as below)
-    const Knobs kn = knobs();
-    const long quad_env = kn.get(&Knobs::attn_quad, 1);
-    const bool quad = M > kMaxColsPerBlock && quad_env != 0;
-    // Four consumers per range also serve 17 to 64 columns, 16 each, when the batch is so small
-    // that a consumer's own range would hold only a few tiles: a quarter of the ranges means a
-    // quarter of the partials and of the combine kernel's work (B = 64 at the 3B shape: combine
-    // 18 -> 10 us, main kernel unchanged; on large batches this form is bound by the consumers
-    // and 40 % slower).  RESPEC_ATTN_QUAD = 2 forces it, 0 switches it off.
+    // The form of the main kernel: consumers that share a range (cw, each with its own column
+    // tiles), consumers of a work-group (nc) and, from them, the split.  Times are per call, main
+    // and combine kernel, by rocprofv3.
+    // One column tile: a range per consumer; bound by HBM.
+    // Two tiles: two consumers per range, eight per work-group (two per SIMD hide each other's
+    // dependent phases): 66.5 us against 69.1 us with two tiles in one consumer at B = 64, k = 3 and
+    // the 7B shape, 241.8 / 242.7 us at B = 256; with 96 or more tiles per consumer of the device
+    // HBM is all that counts and the eight pollers cost more than they give (k = 4, B = 512 at the
+    // 14B shape 922 / 918 us).
+    // Three and four tiles: four consumers per range, eight per work-group (k = 4 at the 3B shape, 40
+    // columns, B = 256: 118.7 us, 128.3 with two, 138.5 with one; k = 5 and 8 at the 7B shape 261 and
+    // 270 us, 265 and 275 with two).  But that form's two ranges read two neighbouring heads of a
+    // cache row at a time where the others read four, which shows when a row is 2 KiB or more and
+    // HBM is the bound: k = 7, B = 512 at the 14B shape 980 us, 963 with one consumer per range.
+    // More than 64 columns: blocks of 128, four consumers of 32 columns per range, K and V read once
+    // per block (91 columns, B = 256 at the 7B shape: 306 us against 410 us with four consumers per
+    // work-group and the longer loop).
+    // Small batches: with fewer than four tiles per consumer of the device two tiles are spread
+    // over four consumers as well (a quarter of the ranges: a quarter of the partials to fold), and
+    // with fewer than two four consumers per work-group do (half of the ranges again: B = 8, k = 4
+    // at the 3B shape 20.5 us per call against 24.0 us; from two tiles on the eight are ahead,
+    // 22.7 us against 24.1 us at B = 8 and the 7B shape).
     // (cached tokens: the host-side total, for a paged cache what its page-table entries can hold)
+    const Knobs kn = knobs();
     const int64_t kv_tokens = paged ? (int64_t)pg.table_len * pg.page_size : total_kv;
-    const int64_t tiles_per_narrow_range =
-        (kv_tokens / kTileKeys + B) * (int64_t)Hkv / ((int64_t)kConsumers * compute_units());
-    const bool quad_narrow = M > kColTile && M <= kMaxColsPerBlock &&
-                             (quad_env == 2 || (quad_env == 1 && tiles_per_narrow_range < 16));
+    const int64_t tiles = (kv_tokens / kTileKeys + B) * (int64_t)Hkv;  // of all (head, sequence) pairs, about
+    const int64_t tiles_per_consumer = tiles / ((int64_t)kProducers * compute_units());
+    const long quad_env = kn.get(&Knobs::attn_quad, 1);  // 0: never, 2: always four consumers per range
+    const long wide = kn.get(&Knobs::attn_wide, -1);     // 0 / 1: one / two consumers per range up to 64 columns
+    const bool quad = M > kMaxColsPerBlock && quad_env != 0;
     const int block_cols = quad ? 2 * kMaxColsPerBlock : kMaxColsPerBlock;
     const int col_blocks = (M + block_cols - 1) / block_cols;
     const int cols = col_blocks == 1 ? M : kMaxColsPerBlock;
     const int nt = quad ? 8 : (cols + kColTile - 1) / kColTile;  // column tiles of a block
-    // a column block of four column tiles at D = 128 is more than one wave's registers hold
-    // (400 bytes of spills per lane, measured 1.5x slower): two consumers share each range then.
-    // Three tiles still run faster with one consumer per range and a few spills.
-    // RESPEC_ATTN_WIDE = 0 / 1 overrides the choice for any block of two or more tiles (tests,
-    // comparisons; at two tiles the shared form halves the partials and the combine's work but
-    // measured 4 us slower in the main kernel, 211 vs 206 us at B = 256 and the 7B shape).
-    const long wide = kn.get(&Knobs::attn_wide, -1);
-    const int cw = quad || quad_narrow ? 4 : (nt >= 2 && (wide < 0 ? (D == 128 && nt == 4) : wide != 0) ? 2 : 1);
-    const int streams = kConsumers / cw;  // ranges per work-group
-    // the split width: one range per consumer (or pair of consumers) of the device
+    const bool wide_rows = (int64_t)Hkv * D * 2 >= 2048 && tiles_per_consumer >= 48;
+    int cw;
+    if (quad || (quad_env == 2 && nt >= 2 && M <= kMaxColsPerBlock)) cw = 4;
+    else if (nt == 1 || wide == 0) cw = 1;
+    else if (wide > 0 || quad_env == 0 || M > kMaxColsPerBlock) cw = 2;
+    else if (nt == 2) cw = tiles_per_consumer < 4 ? 4 : tiles_per_consumer < 96 ? 2 : 1;
+    else cw = !wide_rows ? 4 : nt == 3 ? 1 : 2;
+    const long nc_env = kn.get(&Knobs::attn_consumers, 0);  // 4 / 8: the narrow four-way form's consumers
+    const int nc = cw == 1 ? 4 : cw == 4 && nt <= 4 && (nc_env ? nc_env == 4 : tiles_per_consumer < 2) ? 4 : 8;
+    const int streams = nc / cw;  // ranges per work-group
+    // the split width: one range per consumer (or group of consumers) of the device
     // (RESPEC_ATTN_WGS overrides it, for tests and sweeps)
     long W = kn.get(&Knobs::attn_wgs, 0);
     if (W <= 0) W = (long)streams * compute_units() / col_blocks;
@@ -1670,7 +1784,7 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
         g_mark_before_main = nullptr;
     }
     const dim3 grid((unsigned)((W + streams - 1) / streams), (unsigned)col_blocks);
-    err = D == 128 ? launch_bf16_nt<128>(nt, cw, p, grid, stream) : launch_bf16_nt<64>(nt, cw, p, grid, stream);
+    err = D == 128 ? launch_bf16_nt<128>(nt, cw, nc, p, grid, stream) : launch_bf16_nt<64>(nt, cw, nc, p, grid, stream);
     if (err != hipSuccess)
         return fail(RESPEC_ERR_HIP, "verify_attention: main launch failed: %s", hipGetErrorString(err));
     if (g_mark_after_main) {
@@ -1678,8 +1792,8 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
         g_mark_after_main = nullptr;
     }
     {
-        err = D == 128 ? launch_combine<128>(p, M, kn.get(&Knobs::attn_combine, 0), stream)
-                       : launch_combine<64>(p, M, kn.get(&Knobs::attn_combine, 0), stream);
+        err = D == 128 ? launch_combine<128>(p, M, kv_tokens, kn.get(&Knobs::attn_combine, 0), stream)
+                       : launch_combine<64>(p, M, kv_tokens, kn.get(&Knobs::attn_combine, 0), stream);
         if (err != hipSuccess)
             return fail(RESPEC_ERR_HIP, "verify_attention: combine launch failed: %s", hipGetErrorString(err));
     }
