@@ -60,48 +60,66 @@ __device__ inline double running_weight(double pe, double qe, const Depth &d) {
     return a;
 }
 
+// The passes are instantiated by depth: KIND = 0, 1 and 2 rejections (nearly all of them), kAnyDepth
+// = the loop over d.depth.  The passes are bound by instruction issue; with the depth tested per
+// element they had nine branches and 220 vector instructions per eight logits of both rows, now 88
+// (KIND 1) and 112 (KIND 2): B = 128, trees of 3 x 2 candidates, V = 151,936 bf16, T = 0.6 took 139.8
+// and takes 98.7 us.
+constexpr int kAnyDepth = 3;
+
 // fp64 weights a_depth(x) of the elements of one slot.
-template <bool BF16>
+template <bool BF16, int KIND>
 __device__ inline void tree_slot_weights(const u32x4 &vp, const u32x4 &vq, float Mp, double Cp, float Mq,
                                          double Cq, const Depth &d, const RowMath &p,
                                          double (&w)[Elem<BF16>::EPV]) {
     constexpr int EPV = Elem<BF16>::EPV;
     float zp[EPV], zq[EPV];
     unpack<BF16>(vp, zp);
-    unpack<BF16>(vq, zq);
-    if (d.depth == 0) {  // block-uniform
+    if constexpr (KIND > 0) unpack<BF16>(vq, zq);
 #pragma unroll
-        for (int j = 0; j < EPV; ++j) w[j] = (double)hw_exp2(exp2_arg(zp[j], Mp, p.c_hi, p.c_lo)) * Cp;
-    } else {
-#pragma unroll
-        for (int j = 0; j < EPV; ++j) {
-            const double pe = (double)hw_exp2(exp2_arg(zp[j], Mp, p.c_hi, p.c_lo)) * Cp;
+    for (int j = 0; j < EPV; ++j) {
+        const double pe = (double)hw_exp2(exp2_arg(zp[j], Mp, p.c_hi, p.c_lo)) * Cp;
+        if constexpr (KIND == 0) {
+            w[j] = pe;
+        } else {
             const double qe = (double)hw_exp2(exp2_arg(zq[j], Mq, p.c_hi, p.c_lo)) * Cq;
-            w[j] = running_weight(pe, qe, d);
+            if constexpr (KIND == kAnyDepth) {
+                w[j] = running_weight(pe, qe, d);
+            } else {
+                w[j] = fmax(pe - qe, 0.0);
+                if constexpr (KIND == 2) w[j] = fmax(w[j] * d.z1 - qe, 0.0);
+            }
         }
     }
 }
 
-// The same weights in fp32 (calls whose exponent constant rounds well): probabilities as in
-// FastNorm, every factor 1/Z_j as a two-term binary32 constant so that no systematic error
-// enters, the weights of a slot summed in fp32 in a fixed pairwise order (returned); everything
-// above a slot is carried in fp64.  About half of the instructions of the fp64 form, which is
-// what bounds these passes.
+// The same weights in fp32 (calls whose exponent constant rounds well), times a factor common to
+// the row: probabilities as in FastNorm, the weights of a slot summed in fp32 in a fixed pairwise
+// order (returned); everything above a slot is carried in fp64.  KIND 1 forms the chain sampler's
+// weights, a_1 / (1 + ep).  KIND 2 forms Z_1 a_2 / (1 + ep) = max(0, a_1 / (1 + ep) - q Z_1 / (1 + ep)),
+// which scales q instead of dividing the first difference: g = Z_1 (1 + eq) / (1 + ep), a two-term
+// binary32 constant so that no systematic error enters.  kAnyDepth forms a_depth itself, with
+// every 1/Z_j as such a constant.
 struct FastDepth {
     int depth;
-    float z1h, z1l, z2h, z2l;   // 1/Z_1 and 1/Z_2 as hi + lo
+    float g_hi, g_lo;           // KIND 2
+    float z1h, z1l, z2h, z2l;   // kAnyDepth: 1/Z_1 and 1/Z_2 as hi + lo
     const double *inv_z;
 };
 
-__device__ inline FastDepth make_fast_depth(const Depth &d) {
-    FastDepth f;
-    f.depth = d.depth;
-    f.z1h = (float)d.z1;
-    f.z1l = (float)(d.z1 - (double)f.z1h);
-    f.z2h = (float)d.z2;
-    f.z2l = (float)(d.z2 - (double)f.z2h);
-    f.inv_z = d.inv_z;
-    return f;
+// raw_1: the sum of KIND 1's weights over the row.
+__device__ inline FastDepth make_fast_depth(const Depth &d, double raw_1, const FastNorm &f) {
+    FastDepth r;
+    r.depth = d.depth;
+    const double g = raw_1 + raw_1 * (double)f.eq;
+    r.g_hi = (float)g;
+    r.g_lo = (float)(g - (double)r.g_hi);
+    r.z1h = (float)d.z1;
+    r.z1l = (float)(d.z1 - (double)r.z1h);
+    r.z2h = (float)d.z2;
+    r.z2l = (float)(d.z2 - (double)r.z2h);
+    r.inv_z = d.inv_z;
+    return r;
 }
 
 __device__ inline float running_weight_f32(float pe, float qe, const FastDepth &d) {
@@ -116,25 +134,27 @@ __device__ inline float running_weight_f32(float pe, float qe, const FastDepth &
     return a;
 }
 
-template <bool BF16>
+template <bool BF16, int KIND>
 __device__ inline float tree_slot_weights_f32(const u32x4 &vp, const u32x4 &vq, const FastNorm &f,
                                               const FastDepth &d, const RowMath &p,
                                               float (&w)[Elem<BF16>::EPV]) {
     constexpr int EPV = Elem<BF16>::EPV;
     float zp[EPV], zq[EPV];
     unpack<BF16>(vp, zp);
-    unpack<BF16>(vq, zq);
-    if (d.depth == 0) {  // block-uniform
+    if constexpr (KIND > 0) unpack<BF16>(vq, zq);
 #pragma unroll
-        for (int j = 0; j < EPV; ++j) {
-            const float pe = hw_exp2(fmaf(zp[j], p.c_f, f.Kp));
-            w[j] = fmaf(pe, f.ep, pe);
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < EPV; ++j) {
-            const float pe = hw_exp2(fmaf(zp[j], p.c_f, f.Kp)), qe = hw_exp2(fmaf(zq[j], p.c_f, f.Kq));
-            w[j] = running_weight_f32(fmaf(pe, f.ep, pe), fmaf(qe, f.eq, qe), d);
+    for (int j = 0; j < EPV; ++j) {
+        const float pe = hw_exp2(fmaf(zp[j], p.c_f, f.Kp));
+        if constexpr (KIND == 0) {
+            w[j] = pe;
+        } else {
+            const float qe = hw_exp2(fmaf(zq[j], p.c_f, f.Kq));
+            if constexpr (KIND == kAnyDepth) {
+                w[j] = running_weight_f32(fmaf(pe, f.ep, pe), fmaf(qe, f.eq, qe), d);
+            } else {
+                w[j] = fmaxf(fmaf(-qe, f.e_rel, pe - qe), 0.f);
+                if constexpr (KIND == 2) w[j] = fmaxf(fmaf(-qe, d.g_lo, fmaf(-qe, d.g_hi, w[j])), 0.f);
+            }
         }
     }
     if constexpr (EPV == 8)
@@ -147,17 +167,17 @@ __device__ inline float tree_slot_weights_f32(const u32x4 &vp, const u32x4 &vq, 
 // and streams it with coalesced loads; lanes keep their own fp64 sums, one reduction per wave
 // gives the region total (left in sh.wave_total).  Returns Z = the ordered sum of the region
 // totals, the same bits in every thread.  At depth 0 only the target row is read.
-template <bool BF16, bool FULL, bool FAST>
+template <bool BF16, bool FULL, bool FAST, int KIND>
 __device__ inline double tree_region_totals(const void *rowp, const void *rowq, int nslots, int V, float Mp,
-                                            double Sp, float Mq, double Sq, const Depth &d, SharedState &sh,
+                                            double Sp, float Mq, double Sq, const Depth &d, double raw_1, SharedState &sh,
                                             const RowMath &p) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     const bool aligned = p.aligned != 0;
-    const bool two = d.depth > 0;
+    constexpr bool two = KIND > 0;
     const double Cp = 1.0 / Sp, Cq = two ? 1.0 / Sq : 0.0;
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, two ? Sq : Sp, p);
-    const FastDepth fd = make_fast_depth(d);
+    const FastDepth fd = make_fast_depth(d, raw_1, fn);
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
     const int beg = min(wave * span, nslots), end = min(beg + span, nslots);
     __syncthreads();  // the totals of an earlier pass have been read by everyone
@@ -167,7 +187,8 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
         for (int c = 0; c < kUnroll; ++c) {  // no select behind a load: the loads of a batch go out together
             const int slot = s0 + c * 64 + lane;
             vp[c] = load_slot<BF16, FULL>(rowp, slot < end ? slot : beg, V, aligned);
-            vq[c] = two ? load_slot<BF16, FULL>(rowq, slot < end ? slot : beg, V, aligned) : vp[c];
+            if constexpr (two) vq[c] = load_slot<BF16, FULL>(rowq, slot < end ? slot : beg, V, aligned);
+            else vq[c] = vp[c];
         }
     };
     if (beg < end) {  // wave-uniform
@@ -181,10 +202,10 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
                 const u32x4 a = in ? xp[c] : neg_inf_slot<BF16>(), b = in ? xq[c] : neg_inf_slot<BF16>();
                 if constexpr (FAST) {
                     float w[EPV];
-                    lane_sum += (double)tree_slot_weights_f32<BF16>(a, b, fn, fd, p, w);
+                    lane_sum += (double)tree_slot_weights_f32<BF16, KIND>(a, b, fn, fd, p, w);
                 } else {
                     double w[EPV];
-                    tree_slot_weights<BF16>(a, b, Mp, Cp, Mq, Cq, d, p, w);
+                    tree_slot_weights<BF16, KIND>(a, b, Mp, Cp, Mq, Cq, d, p, w);
 #pragma unroll
                     for (int j = 0; j < EPV; ++j) lane_sum += w[j];
                 }
@@ -224,17 +245,17 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
 // thread whose running sum passes u*Z walks its run element by element.  The re-read adds
 // the same numbers in another order than the region pass, so at the last bit a crossing can
 // fall off the end of the region; that draw takes the last token with mass and is flagged.
-template <bool BF16, bool FULL, bool FAST>
+template <bool BF16, bool FULL, bool FAST, int KIND>
 __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, int V, float Mp, double Sp,
-                                float Mq, double Sq, const Depth &d, double u, SharedState &sh,
+                                float Mq, double Sq, const Depth &d, double raw_1, double u, SharedState &sh,
                                 const RowMath &p, int &near_edge) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     const bool aligned = p.aligned != 0;
-    const bool two = d.depth > 0;
+    constexpr bool two = KIND > 0;
     const double Cp = 1.0 / Sp, Cq = two ? 1.0 / Sq : 0.0;
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, two ? Sq : Sp, p);
-    const FastDepth fd = make_fast_depth(d);
+    const FastDepth fd = make_fast_depth(d, raw_1, fn);
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
     if (threadIdx.x == 0) {
         sh.token = -1;
@@ -271,14 +292,15 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
         for (int j = 0; j < kChunk; ++j) {  // no select behind a load: the loads go out together
             const int slot = c0 + j < my1 ? c0 + j : rb;
             vp[j] = load_slot<BF16, FULL>(rowp, slot, V, aligned);
-            if (two) vq[j] = load_slot<BF16, FULL>(rowq, slot, V, aligned);
+            if constexpr (two) vq[j] = load_slot<BF16, FULL>(rowq, slot, V, aligned);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < kChunk; ++j) {  // slots past the run count as -inf
             const bool in = c0 + j < my1;
             vp[j] = in ? vp[j] : neg_inf_slot<BF16>();
-            vq[j] = two ? (in ? vq[j] : neg_inf_slot<BF16>()) : vp[j];
+            if constexpr (two) vq[j] = in ? vq[j] : neg_inf_slot<BF16>();
+            else vq[j] = vp[j];
         }
     };
     double slot_total[kChunk];
@@ -292,13 +314,13 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
             double st = 0.0;
             if constexpr (FAST) {
                 float w[EPV];
-                st = (double)tree_slot_weights_f32<BF16>(vp[j], vq[j], fn, fd, p, w);
+                st = (double)tree_slot_weights_f32<BF16, KIND>(vp[j], vq[j], fn, fd, p, w);
 #pragma unroll
                 for (int e = 0; e < EPV; ++e)
                     if (w[e] > 0.f) my_last = (c0 + j) * EPV + e;
             } else {
                 double w[EPV];
-                tree_slot_weights<BF16>(vp[j], vq[j], Mp, Cp, Mq, Cq, d, p, w);
+                tree_slot_weights<BF16, KIND>(vp[j], vq[j], Mp, Cp, Mq, Cq, d, p, w);
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) {
                     st += w[e];
@@ -328,11 +350,11 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
             double w[EPV];
             if constexpr (FAST) {
                 float wf[EPV];
-                (void)tree_slot_weights_f32<BF16>(vp, vq, fn, fd, p, wf);
+                (void)tree_slot_weights_f32<BF16, KIND>(vp, vq, fn, fd, p, wf);
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) w[e] = (double)wf[e];
             } else {
-                tree_slot_weights<BF16>(vp, vq, Mp, Cp, Mq, Cq, d, p, w);
+                tree_slot_weights<BF16, KIND>(vp, vq, Mp, Cp, Mq, Cq, d, p, w);
             }
 #pragma unroll
             for (int e = 0; e < EPV; ++e) {
@@ -355,7 +377,7 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
                 if (cn > t) {
                     const u32x4 vp = load_slot<BF16, FULL>(rowp, my0 + j, V, aligned);
                     u32x4 vq = vp;
-                    if (two) vq = load_slot<BF16, FULL>(rowq, my0 + j, V, aligned);
+                    if constexpr (two) vq = load_slot<BF16, FULL>(rowq, my0 + j, V, aligned);
                     walk_slot(my0 + j, vp, vq);
                     // (a crossing lost to rounding inside the slot carries on with the next one)
                 } else {
@@ -424,51 +446,23 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
     __syncthreads();
 
     int cur = 0, n = 0, flag_accept = 0, flag_cdf = 0, final_token = -1, parity = 0;
+    // the walk ends at a node whose running distribution (depth, its normalisers) the final token
+    // is drawn from; the passes that the draw needs stand once, behind the walk
+    const char *rowp = tbase, *rowq = dbase;
+    float Mp = 0.f, Mq = 0.f;
+    double Sp = 1.0, Sq = 1.0;
+    double raw_1 = 1.0;        // what the pass behind the node's first rejection summed (see FastDepth)
+    int depth = 0;
+    bool have_totals = false;  // sh.wave_total holds the running distribution's region totals
+    bool have_norm = false;    // Mp, Sp belong to the node
     for (int guard = 0; guard < kMaxTreeRows; ++guard) {  // `cur` grows with every turn
-        const char *rowp = tbase + (size_t)(row0 + cur) * p.ld_t * esz;
-        const char *rowq = dbase + (size_t)(row0 + cur) * p.ld_d * esz;
+        rowp = tbase + (size_t)(row0 + cur) * p.ld_t * esz;
+        rowq = dbase + (size_t)(row0 + cur) * p.ld_d * esz;
+        depth = 0;
+        have_totals = have_norm = false;
         int c = cur + 1;
         while (c < R && sh_parent[c] != cur) ++c;
-        if (c >= R || n >= p.max_depth) {  // a leaf (or the output row is full): draw from the target
-            const Depth d0{0, 1.0, 1.0, sh_inv_z};
-            if constexpr (FULL && ONE_TERM) {
-                // One pass instead of two: the draw compares running sums with u times their
-                // total, so any reference that keeps the weights in range will do; a total that
-                // is not a positive finite number sends the draw the ordinary way below.
-                const float M0 = block_max_of_row_start<BF16>(rowp, nslots, sh);
-                if (M0 > -INFINITY && M0 < INFINITY) {  // block-uniform
-                    const double Z = tree_region_totals<BF16, FULL, ONE_TERM>(rowp, rowp, nslots, p.V, M0, 1.0, M0, 1.0, d0, sh, p);
-                    if (Z > 0.0 && Z < 1.0e300) {
-                        int edge = 0;
-                        final_token = tree_draw<BF16, FULL, ONE_TERM>(rowp, rowp, nslots, p.V, M0, 1.0, M0, 1.0, d0, (double)p.u_final[b], sh, p, edge);
-                        flag_cdf |= edge;
-                        break;
-                    }
-                }
-            }
-            float M, Mq;
-            double S, Sq;
-            if constexpr (FULL) {
-                if (!row_stats_fast<BF16, false, ONE_TERM>(rowp, rowp, nslots, p.V, sh, parity, p, M, S, Mq, Sq)) {
-                    __syncthreads();
-                    row_stats<BF16, false>(rowp, rowp, nslots, p.V, sh, parity, p, M, S, Mq, Sq);
-                }
-            } else {
-                row_stats<BF16, false>(rowp, rowp, nslots, p.V, sh, parity, p, M, S, Mq, Sq);
-            }
-            const double Z = tree_region_totals<BF16, FULL, ONE_TERM>(rowp, rowp, nslots, p.V, M, S, M, S, d0, sh, p);
-            if (Z > 0.0) {
-                int edge = 0;
-                final_token = tree_draw<BF16, FULL, ONE_TERM>(rowp, rowp, nslots, p.V, M, S, M, S, d0, (double)p.u_final[b], sh, p, edge);
-                flag_cdf |= edge;
-            } else {  // row without any finite logit: report the last token
-                final_token = p.V - 1;
-                flag_cdf = 1;
-            }
-            break;
-        }
-        float Mp, Mq;
-        double Sp, Sq;
+        if (c >= R || n >= p.max_depth) break;  // a leaf (or the output row is full): draw from the target
         if constexpr (FULL) {
             if (!row_stats_fast<BF16, true, ONE_TERM>(rowp, rowq, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq)) {
                 __syncthreads();
@@ -478,8 +472,8 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
             row_stats<BF16, true>(rowp, rowq, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
         }
         parity ^= 1;
-        int depth = 0;
-        bool have_totals = false, moved = false;
+        have_norm = true;
+        bool moved = false;
         double Zd = 1.0;  // normaliser of the running distribution (Z_depth)
         while (c < R) {
             int x = p.node_tokens[row0 + c];
@@ -519,7 +513,16 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
             depth += 1;
             {
                 const Depth d{depth, sh_inv_z[1], sh_inv_z[2], sh_inv_z};
-                Zd = tree_region_totals<BF16, FULL, ONE_TERM>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, sh, p);
+                if (depth == 1) {
+                    raw_1 = tree_region_totals<BF16, FULL, ONE_TERM, 1>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                    Zd = raw_1;
+                    if constexpr (ONE_TERM) Zd += raw_1 * (double)make_fast_norm(Mp, Sp, Mq, Sq, p).ep;
+                } else if (depth == 2) {
+                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, 2>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                    if constexpr (ONE_TERM) Zd /= raw_1;
+                } else {
+                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, kAnyDepth>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                }
             }
             if (Zd > 0.0) {
                 have_totals = true;
@@ -534,20 +537,50 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
             ++c;
             while (c < R && sh_parent[c] != cur) ++c;
         }
-        if (moved) continue;
-        // every child was rejected: one draw from the running distribution
-        const Depth d{depth, sh_inv_z[1], sh_inv_z[2], sh_inv_z};
-        if (!have_totals)
-            Zd = tree_region_totals<BF16, FULL, ONE_TERM>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, sh, p);
-        if (Zd > 0.0) {
-            int edge = 0;
-            final_token = tree_draw<BF16, FULL, ONE_TERM>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, (double)p.u_final[b], sh, p, edge);
-            flag_cdf |= edge;
-        } else {
-            final_token = p.V - 1;
-            flag_cdf = 1;
+        if (!moved) break;  // every child was rejected: one draw from the running distribution
+    }
+    const Depth d{depth, sh_inv_z[1], sh_inv_z[2], sh_inv_z};
+    double Z = 1.0;
+    if (!have_totals) {  // a leaf, or an exact tie: the target row itself
+        // At a leaf one pass serves instead of two: the draw compares running sums with u times
+        // their total, so any reference that keeps the weights in range will do; a total that is
+        // not a positive finite number sends the draw the ordinary way (normalisers first).
+        bool trial = FULL && ONE_TERM && !have_norm;
+        if (trial) {
+            Mp = block_max_of_row_start<BF16>(rowp, nslots, sh);
+            Sp = 1.0;
+            trial = Mp > -INFINITY && Mp < INFINITY;  // block-uniform
         }
-        break;
+        for (;;) {
+            if (!trial && !have_norm) {
+                bool ok = false;
+                if constexpr (FULL) {
+                    ok = row_stats_fast<BF16, false, ONE_TERM>(rowp, rowp, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
+                    if (!ok) __syncthreads();
+                }
+                if (!ok) row_stats<BF16, false>(rowp, rowp, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
+                have_norm = true;
+            }
+            Z = tree_region_totals<BF16, FULL, ONE_TERM, 0>(rowp, rowp, nslots, p.V, Mp, Sp, Mp, Sp, d, raw_1, sh, p);
+            if (!trial || (Z > 0.0 && Z < 1.0e300)) break;
+            trial = false;
+        }
+    }
+    if (Z > 0.0) {
+        const double u = (double)p.u_final[b];
+        int edge = 0;
+        if (depth == 0)
+            final_token = tree_draw<BF16, FULL, ONE_TERM, 0>(rowp, rowp, nslots, p.V, Mp, Sp, Mp, Sp, d, raw_1, u, sh, p, edge);
+        else if (depth == 1)
+            final_token = tree_draw<BF16, FULL, ONE_TERM, 1>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+        else if (depth == 2)
+            final_token = tree_draw<BF16, FULL, ONE_TERM, 2>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+        else
+            final_token = tree_draw<BF16, FULL, ONE_TERM, kAnyDepth>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+        flag_cdf |= edge;
+    } else {  // row without any finite logit: report the last token
+        final_token = p.V - 1;
+        flag_cdf = 1;
     }
     if (threadIdx.x == 0) {
         int32_t *out = out_row(), *path = path_row();

@@ -185,3 +185,17 @@ def test_bad_arguments_are_rejected_before_any_launch():
     assert e.value.status == 2
     call()
     torch.cuda.synchronize()
+
+
+# One pass per rejection, each depth a form of its own: stars whose children are all rejected now and
+# then, at temperatures with the one-term (1, 0.6) and the two-term (1.3) exponent
+@pytest.mark.parametrize("dtype,V", [("bf16", 4096), ("bf16", 1001), ("f32", 1024)])
+@pytest.mark.parametrize("T", [1.0, 0.6, 1.3])
+@pytest.mark.parametrize("children", [1, 2, 3, 6])
+def test_every_rejection_depth(oracle, dtype, V, T, children):
+    # (a first child is accepted with probability sum_x min(p, q), 0.39 (T = 0.6) to 0.59 (T = 1.3) for
+    # this recipe: of 96 sequences 37 or more take one and, a later sibling being accepted less often
+    # than the first, at T = 1.3 and six children still several reject all)
+    wl = _wl("tree_depths", V, dtype, sigma=1.5, T=T)
+    gpu, ref, _ = _parity(oracle, _batch(wl, [[-1] + [0] * children] * 96, seed=children))
+    assert 0 < (ref[2] == 0).sum() < 96
