@@ -313,8 +313,8 @@ size_t respec_rejection_sample_workspace_bytes(int32_t B, int32_t total_q, int32
  *
  *   target_logits [total_q, V], row stride ld_t elements (>= V)    logits_dt
  *   draft_logits  [total_q-B, V], row stride ld_d elements (>= V)  logits_dt; may be NULL
- *                 when total_q == B.  Rows start 16-byte aligned for the vector path
- *                 (base and stride); other alignments take a slower scalar path.
+ *                 when total_q == B.  Rows that start 16-byte aligned (base and stride)
+ *                 and hold whole 16-byte pieces are fastest; any others may be passed.
  *   draft_tokens  [total_q-B] int32 in [0,V)
  *   q_indptr      [B+1] int32 (the same array verify attention takes)
  *   u_accept      [total_q-B] f32 in [0,1);  u_final [B] f32 in [0,1)

@@ -253,7 +253,6 @@ respec_status_t respec_kd_rows(const void *target_logits, const void *draft_logi
 
     KdParams p{};
     set_row_math(p, 1.0f);
-    p.aligned = 1;
     p.target = target_logits;
     p.draft = draft_logits;
     p.weight = row_weight;

@@ -348,7 +348,6 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
                                           const RowMath &p) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
-    const bool aligned = p.aligned != 0;
     const void *rowp = part.rowp, *rowq = part.rowq;
     const int nslots = part.nslots, Vrow = part.Vrow;
     float *tab = part.tab;
@@ -360,7 +359,8 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
     const double Cp = 1.0 / Sp, Cq = RESID ? 1.0 / Sq : 0.0;
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, RESID ? Sq : Sp, p);
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
-    const int beg = min(wave * span, nslots), end = min(beg + span, nslots);
+    const int whole = FULL && !FAST ? whole_slots<BF16>(nslots, Vrow) : nslots;
+    const int beg = min(wave * span, nslots), end_all = min(beg + span, nslots), end = min(end_all, whole);
 
     // phase A: region totals (the next batch of slots is in flight while one is summed; batches
     // twice as long measured the same)
@@ -371,8 +371,8 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
 #pragma unroll
         for (int c = 0; c < kUnroll; ++c) {
             const int slot = s0 + c * 64 + lane;
-            vp[c] = load_slot<BF16, FULL, true>(rowp, slot < end ? slot : beg, Vrow, aligned);
-            if constexpr (RESID) vq[c] = load_slot<BF16, FULL, true>(rowq, slot < end ? slot : beg, Vrow, aligned);
+            vp[c] = load_slot<BF16, FULL, true, FAST>(rowp, slot < end ? slot : beg, Vrow);
+            if constexpr (RESID) vq[c] = load_slot<BF16, FULL, true, FAST>(rowq, slot < end ? slot : beg, Vrow);
         }
     };
     if (beg < end) {  // wave-uniform
@@ -422,6 +422,15 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
         for (int s = 0; s < NSETS; ++s)
             if (s < rem) sum_batch(beg + (ib + s) * kStep, rp[s], rq[s], std::false_type{});
     }
+    if constexpr (FULL && !FAST) {  // (the fp32 form serves rows of whole slots only)
+        if (beg <= whole && whole < end_all && lane == 0) {  // the row's partial slot
+            const u32x4 a = load_slot<BF16>(rowp, whole, Vrow), b = RESID ? load_slot<BF16>(rowq, whole, Vrow) : a;
+            double w[EPV];
+            slot_weights<BF16, RESID>(a, b, Mp, Cp, Mq, Cq, p, w);
+#pragma unroll
+            for (int j = 0; j < EPV; ++j) lane_sum += w[j];
+        }
+    }
     const double region_total = wave_sum(lane_sum);
     if (lane == 0) sh.wave_total[wave] = region_total;
 }
@@ -436,7 +445,6 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
                                   double &Z_out, bool &mine) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
-    const bool aligned = p.aligned != 0;
     const float Mp = nm.Mp, Mq = nm.Mq;
     const double Sp = nm.Sp, Sq = nm.Sq;
     const double Cp = 1.0 / Sp, Cq = RESID ? 1.0 / Sq : 0.0;
@@ -483,6 +491,12 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
     float *tab = part.tab;
     const bool use_tab = FAST && tab != nullptr;  // block-uniform
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
+    const int whole = FULL && !FAST ? whole_slots<BF16>(nslots, Vrow) : nslots;
+    // one slot, the partial one included (a single thread's read)
+    auto any_slot = [&](const void *row, int sidx) {
+        if constexpr (FAST) return load_slot<BF16, FULL, false, true>(row, sidx, Vrow);
+        else return load_slot<BF16>(row, sidx, Vrow);
+    };
     const int wstar = rstar % kWaves;
 
     // phase B: the block walks region wstar; thread i owns slots [rb + i*per, rb + (i+1)*per)
@@ -513,9 +527,9 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
             // one slot's elements, formed again from memory: the last of them with mass, and (if
             // walk) the first whose running sum passes t
             auto open_slot = [&](int sidx, bool walk, double &c, int &tok, double &before, double &after) -> int {
-                const u32x4 vp = load_slot<BF16, FULL>(rowp, sidx, Vrow, aligned);
+                const u32x4 vp = any_slot(rowp, sidx);
                 u32x4 vq = vp;
-                if constexpr (RESID) vq = load_slot<BF16, FULL>(rowq, sidx, Vrow, aligned);
+                if constexpr (RESID) vq = any_slot(rowq, sidx);
                 float wf[EPV];
                 (void)slot_weights_f32<BF16, RESID>(vp, vq, fn, p, wf);
                 int last = -1;
@@ -573,9 +587,9 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
     auto load_chunk = [&](int c0, u32x4 (&vp)[kChunk], u32x4 (&vq)[kChunk]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < kChunk; ++j) {
-            const int slot = c0 + j < my1 ? c0 + j : rb;
-            vp[j] = load_slot<BF16, FULL>(rowp, slot, Vrow, aligned);
-            if constexpr (RESID) vq[j] = load_slot<BF16, FULL>(rowq, slot, Vrow, aligned);
+            const int slot = FULL && !FAST ? max(0, min(c0 + j < my1 ? c0 + j : rb, whole - 1)) : c0 + j < my1 ? c0 + j : rb;
+            vp[j] = load_slot<BF16, FULL, false, FAST>(rowp, slot, Vrow);
+            if constexpr (RESID) vq[j] = load_slot<BF16, FULL, false, FAST>(rowq, slot, Vrow);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -583,7 +597,11 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
             const bool in = c0 + j < my1;
             vp[j] = in ? vp[j] : neg_inf_slot<BF16>();
             if constexpr (RESID) vq[j] = in ? vq[j] : neg_inf_slot<BF16>();
-            else vq[j] = vp[j];
+            if (FULL && !FAST && in && c0 + j >= whole) {  // the row's partial slot
+                vp[j] = load_slot<BF16>(rowp, c0 + j, Vrow);
+                if constexpr (RESID) vq[j] = load_slot<BF16>(rowq, c0 + j, Vrow);
+            }
+            if constexpr (!RESID) vq[j] = vp[j];
         }
     };
     // the totals of the slots of the first chunk are kept for the walk, and (when the registers
@@ -671,9 +689,9 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
                     if constexpr (kKeepSlots) {
                         walk_slot(my0 + j, keep_p[j], keep_q[j]);
                     } else {
-                        const u32x4 vp = load_slot<BF16, FULL>(rowp, my0 + j, Vrow, aligned);
+                        const u32x4 vp = any_slot(rowp, my0 + j);
                         u32x4 vq = vp;
-                        if constexpr (RESID) vq = load_slot<BF16, FULL>(rowq, my0 + j, Vrow, aligned);
+                        if constexpr (RESID) vq = any_slot(rowq, my0 + j);
                         walk_slot(my0 + j, vp, vq);
                     }
                     // (a crossing lost to rounding inside the slot carries on with the next one)
@@ -757,8 +775,9 @@ __device__ inline void device_row_math(RowMath &m, float temperature) {
 // The first argmax of a row: its largest logit, the lowest token id among equal ones (an
 // all -inf row gives token 0).  Every thread returns the same value.  Ends with a barrier.
 template <bool BF16, bool FULL>
-__device__ inline int row_argmax(const void *row, int nslots, int V, bool aligned, SharedState &sh) {
+__device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedState &sh) {
     constexpr int EPV = Elem<BF16>::EPV;
+    const int nslots = FULL ? whole_slots<BF16>(nslots_all, V) : nslots_all;
     constexpr int kBatch = kThreads * kUnroll;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     const int n_iter = (nslots + kBatch - 1) / kBatch;
@@ -768,7 +787,7 @@ __device__ inline int row_argmax(const void *row, int nslots, int V, bool aligne
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int slot = it * kBatch + u * kThreads + (int)threadIdx.x;
-            v[u] = load_slot<BF16, FULL>(row, it + 1 < n_iter ? slot : max(0, min(slot, nslots - 1)), V, aligned);
+            v[u] = load_slot<BF16, FULL>(row, it + 1 < n_iter ? slot : max(0, min(slot, nslots - 1)), V);
         }
     };
     float best = -INFINITY;
@@ -805,6 +824,16 @@ __device__ inline int row_argmax(const void *row, int nslots, int V, bool aligne
         compare_batch(it + 1, nv);
     } else {
         compare_batch(it, v);
+    }
+    if (nslots < nslots_all && threadIdx.x == 0) {  // the row's partial slot (the highest ids)
+        float z[EPV];
+        unpack<BF16>(load_slot<BF16>(row, nslots, V), z);
+#pragma unroll
+        for (int j = 0; j < EPV; ++j)
+            if (z[j] > best) {
+                best = z[j];
+                best_i = nslots * EPV + j;
+            }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
@@ -848,7 +877,7 @@ __device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, 
     int n = 0, a;
     for (;;) {
         const char *rowp = static_cast<const char *>(p.target) + (size_t)(row0 + n) * p.ld_t * esz;
-        a = row_argmax<BF16, FULL>(rowp, nslots, p.V, p.aligned != 0, sh);
+        a = row_argmax<BF16, FULL>(rowp, nslots, p.V, sh);
         if (n >= k) break;
         const int x = p.draft_tokens[drow0 + n];
         if (x != a) break;
@@ -1029,7 +1058,7 @@ __global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParam
             scan_row = tbase + (size_t)(row0 + k) * p.ld_t * esz;
             float M0;
             if constexpr (SHARED) M0 = last_Mp;
-            else M0 = block_max_of_row_start<BF16>(scan_row, nslots, sh);
+            else M0 = block_max_of_row_start<BF16>(scan_row, p.V / EPV, sh);
             if (M0 > -INFINITY && M0 < INFINITY) {  // block-uniform
                 double Z;
                 int edge = 0;
@@ -1149,8 +1178,6 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
     const Knobs kn = knobs();
     set_row_math(p, temps ? 1.0f : temperature, kn.get(&Knobs::sampler_two_term, 0) != 0);
     if (temps) p.one_term = 0;  // the per-sequence constants are formed on the device, two-term
-    p.aligned = aligned_to(target_logits, 16) && (ld_t * esz) % 16 == 0 &&
-                (!has_drafts || !draft_logits || (aligned_to(draft_logits, 16) && (ld_d * esz) % 16 == 0));
 
     // work-groups per sequence: as many as there are otherwise idle compute units, as long as a
     // part keeps a useful share of the row; one (and no mailbox) without a workspace
@@ -1170,6 +1197,9 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         // once: never more work-groups than compute units, whatever the knob asks for.  And a
         // pass's mark has ten bits for the stage: very long draft chains take one work-group.
         while (split > 1 && (long)B * split > cus) split /= 2;
+        // the part that holds a row's partial slot also holds whole ones
+        if (V % epv0 != 0)
+            while (split > 1 && (long)(split - 1) * (((slots_row + split - 1) / split + 63) / 64 * 64) >= V / epv0) split /= 2;
         if (2 * ((long)max_k + 1) + 4 >= 1024) split = 1;
     }
     if ((int64_t)B * split > 0x7fffffffLL)
@@ -1183,7 +1213,12 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int epv = logits_dt == RESPEC_BF16 ? 8 : 4;
-    const bool full = p.aligned && V % epv == 0 && kn.get(&Knobs::sampler_guarded, 0) == 0;
+    const bool full = V >= epv && kn.get(&Knobs::sampler_guarded, 0) == 0;
+    const bool whole_rows = V % epv == 0 && aligned_to(target_logits, 16) && (ld_t * esz) % 16 == 0 &&
+                            (!has_drafts || !draft_logits || (aligned_to(draft_logits, 16) && (ld_d * esz) % 16 == 0));
+    // rows of whole, aligned slots take fp32 weights when the exponent constant rounds well; the
+    // others keep the fp64 weights they always had
+    p.one_term = p.one_term && whole_rows;
     const bool bf = logits_dt == RESPEC_BF16, one = p.one_term != 0;
     // the final draw's table of slot totals (fp32 form, one work-group per sequence): one float
     // per 16-byte slot of a row in dynamic LDS, when that fits beside the static part

@@ -7,6 +7,7 @@
 #include "respec_common.hpp"
 
 #include <cmath>
+#include <type_traits>
 
 namespace respec {
 namespace {
@@ -41,7 +42,6 @@ struct RowMath {
     double c_d;        // log2(e)/T
     double inv_T;
     float gap;         // logit distance above the reference that forces a re-reference
-    int aligned;       // every row starts 16-byte aligned
 };
 
 inline void set_row_math(RowMath &m, float temperature, bool force_two_term = false) {
@@ -94,21 +94,27 @@ __device__ inline u32x4 neg_inf_slot() {
 }
 
 // 16 bytes of row `row` starting at element slot*EPV; elements at or beyond V read as -inf.
-// FULL: every row is 16-byte aligned and V is a whole number of slots (known on the host).
+// FULL: the slot lies inside the row (the caller takes a row's last, partial slot separately).
+// Rows start wherever their element type may (an odd vocabulary leaves them 2 or 4 bytes aligned):
+// the 16-byte loads of this device take any address, a wave's 1 KiB then touches one cache line more.
+// (Element loads for such rows took 2 to 8 times the instructions: B = 32, k = 2, fp32, V = 50,257
+// 43.6 -> 29.1 us per call.)
 // LAST_USE: the pass that reads the row for the last time marks its loads non-temporal, which
 // leaves the caches to rows that are still to be read again (3 % of the sampler's time, 6 % of
 // the distillation kernel's; the same hint on a row's first read costs 5 %: the second read
-// then misses).
-template <bool BF16, bool FULL = false, bool LAST_USE = false>
-__device__ inline u32x4 load_slot(const void *row, int slot, int V, bool aligned) {
+// then misses).  ALIGNED: the row is known to start on 16 bytes.
+template <bool BF16, bool FULL = false, bool LAST_USE = false, bool ALIGNED = false>
+__device__ inline u32x4 load_slot(const void *row, int slot, int V) {
     constexpr int EPV = Elem<BF16>::EPV;
+    typedef u32x4 u32x4_elem __attribute__((aligned(2)));
+    typedef std::conditional_t<ALIGNED, u32x4, u32x4_elem> Slot;
     // (a 32-bit unsigned byte offset from the row's uniform base: the load then takes a scalar
     // base and one offset register instead of a 64-bit address pair formed per load; rows are
     // shorter than 4 GiB, checked on the host)
-    const u32x4 *whole = reinterpret_cast<const u32x4 *>(static_cast<const char *>(row) + ((uint32_t)slot * 16u));
+    const Slot *whole = reinterpret_cast<const Slot *>(static_cast<const char *>(row) + ((uint32_t)slot * 16u));
     if constexpr (FULL) return LAST_USE ? __builtin_nontemporal_load(whole) : *whole;
     const int e0 = slot * EPV;
-    if (aligned && e0 + EPV <= V) return LAST_USE ? __builtin_nontemporal_load(whole) : *whole;
+    if (e0 + EPV <= V) return LAST_USE ? __builtin_nontemporal_load(whole) : *whole;
     uint32_t w[4];
     if constexpr (BF16) {
         const uint16_t *r = static_cast<const uint16_t *>(row);
@@ -124,6 +130,13 @@ __device__ inline u32x4 load_slot(const void *row, int slot, int V, bool aligned
         for (int j = 0; j < 4; ++j) w[j] = (e0 + j < V) ? r[e0 + j] : 0xff800000u;
     }
     return u32x4{w[0], w[1], w[2], w[3]};
+}
+
+// Of nslots slots from the start of a row (or of a part of one) with Vrow elements to the row's end,
+// those that lie inside the row; one more, the partial one, follows when this is nslots - 1.
+template <bool BF16>
+__device__ inline int whole_slots(int nslots, int Vrow) {
+    return min(nslots, Vrow / Elem<BF16>::EPV);
 }
 
 __device__ inline float hw_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -333,13 +346,13 @@ __device__ inline float slot_max(const u32x4 &v) {
     return m;
 }
 
-// The largest logit among the first kThreads slots of a (16-byte aligned, whole-slot) row; every
+// The largest logit among the first kThreads of a row's nslots whole slots; every
 // thread returns the same value (-inf when none of them is finite).  Ends with a barrier.
 template <bool BF16>
 __device__ inline float block_max_of_row_start(const void *row, int nslots, SharedState &sh) {
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     float m = -INFINITY;
-    if ((int)threadIdx.x < nslots) m = slot_max<BF16>(load_slot<BF16, true>(row, threadIdx.x, 0, true));
+    if ((int)threadIdx.x < nslots) m = slot_max<BF16>(load_slot<BF16, true, false, true>(row, threadIdx.x, 0));
     m = wave_max(m);
     __syncthreads();  // (earlier readers of arg_val are done)
     if (lane == 0) sh.arg_val[wave] = m;
@@ -356,11 +369,14 @@ __device__ inline float block_max_of_row_start(const void *row, int nslots, Shar
 // exp2 keeps full relative precision for any offset, only a logit more than ~88/c above the
 // reference would overflow.  Returns false (every thread alike) when a sum came out
 // non-finite or empty, and the caller then repeats the row with the guarded pass below.
+// The row has at least one whole slot.
 template <bool BF16, bool TWO, bool ONE_TERM>
-__device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int nslots, int Vrow,
+__device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int nslots_all, int Vrow,
                                       SharedState &sh, int parity, const RowMath &p, float &Mp,
                                       double &Sp, float &Mq, double &Sq) {
     constexpr int EPV = Elem<BF16>::EPV;
+    // (the one-term form serves rows of whole slots only)
+    const int nslots = ONE_TERM ? nslots_all : whole_slots<BF16>(nslots_all, Vrow);
     constexpr int kBatch = kThreads * kUnroll;  // slots per block iteration
     const int tid = opaque_thread_index();
     float accp[EPV], accq[EPV];
@@ -377,15 +393,15 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
         if (it + 1 < n_iter) {
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
-                vp[u] = load_slot<BF16, true>(rowp, s0 + u * kThreads, Vrow, true);
-                if constexpr (TWO) vq[u] = load_slot<BF16, true>(rowq, s0 + u * kThreads, Vrow, true);
+                vp[u] = load_slot<BF16, true, false, ONE_TERM>(rowp, s0 + u * kThreads, Vrow);
+                if constexpr (TWO) vq[u] = load_slot<BF16, true, false, ONE_TERM>(rowq, s0 + u * kThreads, Vrow);
             }
         } else {
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const int safe = max(0, min(s0 + u * kThreads, nslots - 1));
-                vp[u] = load_slot<BF16, true>(rowp, safe, Vrow, true);
-                if constexpr (TWO) vq[u] = load_slot<BF16, true>(rowq, safe, Vrow, true);
+                vp[u] = load_slot<BF16, true, false, ONE_TERM>(rowp, safe, Vrow);
+                if constexpr (TWO) vq[u] = load_slot<BF16, true, false, ONE_TERM>(rowq, safe, Vrow);
             }
         }
     };
@@ -449,6 +465,10 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
             absorb_batch(rp[s], rq[s]);
         }
     }
+    if (!ONE_TERM && nslots < nslots_all && tid == 0) {  // the row's partial slot
+        fast_absorb<BF16, ONE_TERM>(load_slot<BF16>(rowp, nslots, Vrow), accp, refp, Kp, p);
+        if constexpr (TWO) fast_absorb<BF16, ONE_TERM>(load_slot<BF16>(rowq, nslots, Vrow), accq, refq, Kq, p);
+    }
     double sp = 0.0, sq = 0.0;
 #pragma unroll
     for (int j = 0; j < EPV; ++j) {
@@ -471,15 +491,14 @@ __device__ inline void row_stats(const void *rowp, const void *rowq, int nslots,
     ThreadSum<BF16> tp, tq;
     tp.init();
     tq.init();
-    const bool aligned = p.aligned != 0;
     for (int s0 = opaque_thread_index(); s0 < nslots; s0 += kThreads * kUnroll) {
         u32x4 vp[kUnroll], vq[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int slot = s0 + u * kThreads;
-            vp[u] = slot < nslots ? load_slot<BF16>(rowp, slot, Vrow, aligned) : neg_inf_slot<BF16>();
+            vp[u] = slot < nslots ? load_slot<BF16>(rowp, slot, Vrow) : neg_inf_slot<BF16>();
             if constexpr (TWO)
-                vq[u] = slot < nslots ? load_slot<BF16>(rowq, slot, Vrow, aligned)
+                vq[u] = slot < nslots ? load_slot<BF16>(rowq, slot, Vrow)
                                       : neg_inf_slot<BF16>();
         }
 #pragma unroll

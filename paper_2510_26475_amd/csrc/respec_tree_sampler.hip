@@ -173,21 +173,21 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
                                             const RowMath &p) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
-    const bool aligned = p.aligned != 0;
     constexpr bool two = KIND > 0;
     const double Cp = 1.0 / Sp, Cq = two ? 1.0 / Sq : 0.0;
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, two ? Sq : Sp, p);
     const FastDepth fd = make_fast_depth(d, raw_1, fn);
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
-    const int beg = min(wave * span, nslots), end = min(beg + span, nslots);
+    const int whole = FULL && !FAST ? whole_slots<BF16>(nslots, V) : nslots;
+    const int beg = min(wave * span, nslots), end_all = min(beg + span, nslots), end = min(end_all, whole);
     __syncthreads();  // the totals of an earlier pass have been read by everyone
     double lane_sum = 0.0;
     auto load_batch = [&](int s0, u32x4 (&vp)[kUnroll], u32x4 (&vq)[kUnroll]) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < kUnroll; ++c) {  // no select behind a load: the loads of a batch go out together
             const int slot = s0 + c * 64 + lane;
-            vp[c] = load_slot<BF16, FULL>(rowp, slot < end ? slot : beg, V, aligned);
-            if constexpr (two) vq[c] = load_slot<BF16, FULL>(rowq, slot < end ? slot : beg, V, aligned);
+            vp[c] = load_slot<BF16, FULL, false, FAST>(rowp, slot < end ? slot : beg, V);
+            if constexpr (two) vq[c] = load_slot<BF16, FULL, false, FAST>(rowq, slot < end ? slot : beg, V);
             else vq[c] = vp[c];
         }
     };
@@ -230,6 +230,15 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
             sum_batch(s0, vp, vq, std::false_type{});
         }
     }
+    if constexpr (FULL && !FAST) {  // (the fp32 form serves rows of whole slots only)
+        if (beg <= whole && whole < end_all && lane == 0) {  // the row's partial slot
+            const u32x4 a = load_slot<BF16>(rowp, whole, V), b = two ? load_slot<BF16>(rowq, whole, V) : a;
+            double w[EPV];
+            tree_slot_weights<BF16, KIND>(a, b, Mp, Cp, Mq, Cq, d, p, w);
+#pragma unroll
+            for (int j = 0; j < EPV; ++j) lane_sum += w[j];
+        }
+    }
     const double region_total = wave_sum(lane_sum);
     if (lane == 0) sh.wave_total[wave] = region_total;
     __syncthreads();
@@ -251,7 +260,6 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
                                 const RowMath &p, int &near_edge) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
-    const bool aligned = p.aligned != 0;
     constexpr bool two = KIND > 0;
     const double Cp = 1.0 / Sp, Cq = two ? 1.0 / Sq : 0.0;
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, two ? Sq : Sp, p);
@@ -282,6 +290,11 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     if (forced) rstar = rlast;
     __syncthreads();
 
+    const int whole = FULL && !FAST ? whole_slots<BF16>(nslots, V) : nslots;
+    auto any_slot = [&](const void *row, int sidx) {
+        if constexpr (FAST) return load_slot<BF16, FULL, false, true>(row, sidx, V);
+        else return load_slot<BF16>(row, sidx, V);
+    };
     const int rb = min(rstar * span, nslots), re = min(rb + span, nslots);
     const int per = (re - rb + kThreads - 1) / kThreads;
     const int my0 = rb + threadIdx.x * per, my1 = min(my0 + per, re);
@@ -290,9 +303,9 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     auto load_chunk = [&](int c0, u32x4 (&vp)[kChunk], u32x4 (&vq)[kChunk]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < kChunk; ++j) {  // no select behind a load: the loads go out together
-            const int slot = c0 + j < my1 ? c0 + j : rb;
-            vp[j] = load_slot<BF16, FULL>(rowp, slot, V, aligned);
-            if constexpr (two) vq[j] = load_slot<BF16, FULL>(rowq, slot, V, aligned);
+            const int slot = FULL && !FAST ? max(0, min(c0 + j < my1 ? c0 + j : rb, whole - 1)) : c0 + j < my1 ? c0 + j : rb;
+            vp[j] = load_slot<BF16, FULL, false, FAST>(rowp, slot, V);
+            if constexpr (two) vq[j] = load_slot<BF16, FULL, false, FAST>(rowq, slot, V);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -300,7 +313,11 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
             const bool in = c0 + j < my1;
             vp[j] = in ? vp[j] : neg_inf_slot<BF16>();
             if constexpr (two) vq[j] = in ? vq[j] : neg_inf_slot<BF16>();
-            else vq[j] = vp[j];
+            if (FULL && !FAST && in && c0 + j >= whole) {  // the row's partial slot
+                vp[j] = load_slot<BF16>(rowp, c0 + j, V);
+                if constexpr (two) vq[j] = load_slot<BF16>(rowq, c0 + j, V);
+            }
+            if constexpr (!two) vq[j] = vp[j];
         }
     };
     double slot_total[kChunk];
@@ -375,9 +392,9 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
             if (tok < 0 && my0 + j < my1) {
                 const double cn = c + slot_total[j];
                 if (cn > t) {
-                    const u32x4 vp = load_slot<BF16, FULL>(rowp, my0 + j, V, aligned);
+                    const u32x4 vp = any_slot(rowp, my0 + j);
                     u32x4 vq = vp;
-                    if constexpr (two) vq = load_slot<BF16, FULL>(rowq, my0 + j, V, aligned);
+                    if constexpr (two) vq = any_slot(rowq, my0 + j);
                     walk_slot(my0 + j, vp, vq);
                     // (a crossing lost to rounding inside the slot carries on with the next one)
                 } else {
@@ -547,7 +564,7 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
         // not a positive finite number sends the draw the ordinary way (normalisers first).
         bool trial = FULL && ONE_TERM && !have_norm;
         if (trial) {
-            Mp = block_max_of_row_start<BF16>(rowp, nslots, sh);
+            Mp = block_max_of_row_start<BF16>(rowp, p.V / EPV, sh);
             Sp = 1.0;
             trial = Mp > -INFINITY && Mp < INFINITY;  // block-uniform
         }
@@ -642,12 +659,14 @@ extern "C" respec_status_t respec_tree_rejection_sample(
     p.ld_t = ld_t;
     p.ld_d = ld_d;
     set_row_math(p, temperature);
-    p.aligned = aligned_to(target_logits, 16) && (ld_t * esz) % 16 == 0 && aligned_to(draft_logits, 16) &&
-                (ld_d * esz) % 16 == 0;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int epv = logits_dt == RESPEC_BF16 ? 8 : 4;
-    const bool full = p.aligned && V % epv == 0 && knobs().get(&Knobs::sampler_guarded, 0) == 0;
+    const bool full = V >= epv && knobs().get(&Knobs::sampler_guarded, 0) == 0;
+    // (rows of whole, aligned slots take fp32 weights, the others keep fp64 ones, as in the chain sampler)
+    const bool whole_rows = V % epv == 0 && aligned_to(target_logits, 16) && (ld_t * esz) % 16 == 0 &&
+                            aligned_to(draft_logits, 16) && (ld_d * esz) % 16 == 0;
+    p.one_term = p.one_term && whole_rows;
     const bool bf = logits_dt == RESPEC_BF16, one = p.one_term != 0;
 #define RESPEC_LAUNCH_TREE(BF, ONE, FULL)                                                                       \
     hipLaunchKernelGGL((tree_rejection_sample_kernel<BF, ONE, FULL>), dim3((unsigned)B), dim3(kThreads), 0,    \

@@ -1,0 +1,85 @@
+"""Logits rows that are not whole 16-byte pieces: odd vocabularies, row strides that leave the rows
+2- or 4-byte aligned, bases that start inside a piece.  Chain (one work-group per sequence and
+shared), per-sequence and tree samplers against the CPU oracle: tokens and counts exact on
+sequences that the oracle does not flag.  Whatever lies between the rows and around the matrix holds
+NaN (bf16 and fp32), so an element read past a row's end would show.
+"""
+import numpy as np
+import pytest
+import torch
+
+import helpers
+from helpers import compare_sampler, compare_tree_sampler, gpu_sample, gpu_tree_sample, oracle_sample, oracle_tree_sample
+from paper_2510_26475_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+KS = [3, 0, 2, 1, 3, 2, 3, 0] * 4
+
+
+def _wl(V, dtype, T):
+    return synth.Workload("rows", B=0, k=0, Hq=1, Hkv=1, D=64, V=V, dtype=dtype, len_dist="uniform", len_lo=1, len_hi=1,
+                          sigma=1.5, temperature=T)
+
+
+def _spread(t, gap, shift):
+    """The same rows `gap` elements further apart, starting `shift` elements into NaN."""
+    rows, V = t.shape
+    flat = torch.full((shift + rows * (V + gap) + 64,), float("nan"), dtype=t.dtype, device=t.device)
+    view = flat[shift:shift + rows * (V + gap)].view(rows, V + gap)[:, :V]
+    view.copy_(t)
+    return view
+
+
+# the last slot holds one element, one short of all, or is whole but unaligned; a vocabulary smaller
+# than a slot; one slot and a bit; a part of a shared row that would hold the partial slot alone
+SHAPES = [(8 * 300 + 1, 0, 0), (8 * 300 + 7, 0, 0), (2400, 1, 0), (2400, 0, 3), (1001, 3, 1), (9, 2, 0), (7, 1, 0), (3, 0, 0),
+          (8 * 64 + 5, 0, 0), (50257, 0, 0)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T", [1.0, 1.3])
+@pytest.mark.parametrize("V,gap,shift", SHAPES)
+@pytest.mark.parametrize("split", [1, 2, 8])
+def test_chain(oracle, V, gap, shift, dtype, T, split):
+    wl = _wl(V, dtype, T)
+    batch = synth.make_batch(wl, device="cuda", kv_lens=[k + 1 for k in KS], k_per_seq=KS, seed=V + split, with_attention=False)
+    ref = oracle_sample(oracle, batch)
+    batch.target_logits, batch.draft_logits = _spread(batch.target_logits, gap, shift), _spread(batch.draft_logits, gap, shift)
+    with helpers.sampler_split(split):
+        tally = compare_sampler(gpu_sample(batch), ref)
+    assert tally["flagged"] <= max(3, 0.25 * len(KS)), tally
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,gap,shift", SHAPES)
+def test_per_sequence_temperatures(oracle, V, gap, shift, dtype):
+    wl = _wl(V, dtype, 1.0)
+    batch = synth.make_batch(wl, device="cuda", kv_lens=[k + 1 for k in KS], k_per_seq=KS, seed=V, with_attention=False)
+    temps = np.array([(0.0, 0.6, 1.0, 1.3)[b % 4] for b in range(len(KS))], dtype=np.float32)
+    for b, qi in enumerate(batch.q_indptr.tolist()[:-1]):  # a tie that straddles the last slot, greedy rows
+        if temps[b] == 0:
+            batch.target_logits[qi, V - 1] = batch.target_logits[qi, V // 2] = 40.0
+    odt = oracle.F32 if dtype == "f32" else oracle.BF16
+    ref = oracle.rejection_sample_per_seq(
+        synth.to_host_array(batch.target_logits), synth.to_host_array(batch.draft_logits), batch.draft_tokens.cpu().numpy(),
+        batch.q_indptr.cpu().numpy(), batch.u_accept.cpu().numpy(), batch.u_final.cpu().numpy(), batch.max_k, temps, odt)
+    target, draft = _spread(batch.target_logits, gap, shift), _spread(batch.draft_logits, gap, shift)
+    B = len(KS)
+    toks = torch.full((B, batch.max_k + 1), -7, dtype=torch.int32, device="cuda")
+    n, flags = (torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+    binding.respec_rejection_sample_per_seq(target, draft, batch.draft_tokens, batch.q_indptr, batch.u_accept, batch.u_final,
+                                            torch.from_numpy(temps).cuda(), toks, n, flags, batch.max_k)
+    torch.cuda.synchronize()
+    compare_sampler((toks.cpu().numpy(), n.cpu().numpy(), flags.cpu().numpy()), ref)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T", [1.0, 1.3])
+@pytest.mark.parametrize("V,gap,shift", SHAPES)
+def test_tree(oracle, V, gap, shift, dtype, T):
+    parents = [synth.caterpillar_parents(2, 3), [-1, 0, 0], [-1], [-1, 0, 1, 2]] * 6
+    tb = synth.make_tree_batch(_wl(V, dtype, T), parents, device="cuda", kv_lens=[len(p) for p in parents], seed=V, with_attention=False)
+    ref = oracle_tree_sample(oracle, tb)
+    tb.target_logits, tb.draft_logits = _spread(tb.target_logits, gap, shift), _spread(tb.draft_logits, gap, shift)
+    compare_tree_sampler(gpu_tree_sample(tb), ref)
