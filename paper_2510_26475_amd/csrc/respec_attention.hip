@@ -523,7 +523,7 @@ struct Bf16Form {
 // (B = 256 at the 7B shape, trees of 91 columns: 409 -> 340 us per call by HIP events, 311 us with
 // the shorter loop below as well).
 template <int D, int NT, typename OutT, int CW, int NC>
-__global__ __launch_bounds__((NC + kProducers) * 64, 1) void attn_bf16_kernel(AttnParams p) {
+__device__ __forceinline__ void attn_bf16(const AttnParams &p) {
     using C = Bf16Cfg<D>;
     static_assert(CW == 1 || CW == 2 || CW == 4, "one, two or four consumers per range");
     constexpr int kStreams = NC / CW;             // ranges per work-group
@@ -1157,42 +1157,43 @@ __global__ __launch_bounds__((NC + kProducers) * 64, 1) void attn_bf16_kernel(At
     }
 }
 
+// Consumers of a work-group: one per range and SIMD, or two per SIMD where they share ranges.
+constexpr int consumers_of(int cw) { return cw == 1 ? 4 : 8; }
+
+template <int D, int NT, typename OutT, int CW>
+__global__ __launch_bounds__((consumers_of(CW) + kProducers) * 64, 1) void attn_bf16_kernel(AttnParams p) {
+    attn_bf16<D, NT, OutT, CW, consumers_of(CW)>(p);
+}
+
+// The form for the smallest batches: one column tile per consumer, four consumers on one range.
+template <int D, typename OutT>
+__global__ __launch_bounds__((4 + kProducers) * 64, 1) void attn_bf16_small_kernel(AttnParams p) {
+    attn_bf16<D, 1, OutT, 4, 4>(p);
+}
+
 // ------------------------------------------------------------------------------------------
 // fp32 kernel: one work-group per (sequence, query head, query row), no split
 // ------------------------------------------------------------------------------------------
+// A chunk of 256 keys at a time: each thread forms one key's score, a wave's scores are reduced in
+// the wave, and the probabilities of the chunk, relative to their wave's maximum, go through LDS
+// (two buffers in turn: one barrier per chunk) to the threads that own four values of d of every
+// sixteenth (D = 64) or eighth key.  The workloads that run in fp32 are small, so what bounds the
+// kernel is the chain of latencies: index arrays, query row, key rows, barrier, value rows, merge.
+// Sixteen loads of a key row and eight value rows are in flight together (with one value per thread,
+// one load in flight and six barriers per chunk: B = 4, k = 4, 4 heads of 64, up to 256 keys
+// 11.1 us; now 7.4 us).
 constexpr int kF32Threads = 256;
-
-__device__ inline float block_reduce_max(float x, float *scratch) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) scratch[wave] = x;
-    __syncthreads();
-    float r = scratch[0];
-    for (int w = 1; w < kF32Threads / 64; ++w) r = fmaxf(r, scratch[w]);
-    return r;
-}
-
-__device__ inline float block_reduce_sum(float x, float *scratch) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) scratch[wave] = x;
-    __syncthreads();
-    float r = scratch[0];
-    for (int w = 1; w < kF32Threads / 64; ++w) r += scratch[w];
-    return r;
-}
+constexpr int kF32Waves = kF32Threads / 64;
 
 template <int D>
 __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
-    __shared__ float sh_q[D];
-    __shared__ float sh_p[kF32Threads];
-    __shared__ float sh_red[kF32Threads / 64];
-    __shared__ float sh_part[kF32Threads];
-    constexpr int kParts = kF32Threads / D;
+    constexpr int kLanesPerKey = D / 4;                       // threads that cover a value row, four values each
+    constexpr int kGroups = kF32Threads / kLanesPerKey;       // keys handled at a time in the second product
+    constexpr int kDepth = 8;                                 // value rows in flight per thread
+    __shared__ floatx4 sh_q[D / 4];
+    __shared__ float sh_p[2][kF32Threads];
+    __shared__ float sh_m[2][kF32Waves], sh_l[2][kF32Waves];
+    __shared__ floatx4 sh_part[kGroups][kLanesPerKey];
 
     const int h = blockIdx.x % p.Hq;
     const int b = blockIdx.x / p.Hq;
@@ -1205,7 +1206,6 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
     const int first_new = si.L - si.R;
     const int k_end = tree ? si.L : min(si.L, si.L - si.R + i + 1);  // one past the last visible key
     const int64_t qrow = (int64_t)(si.q0 + i) * p.Hq + h;
-    const float *q = static_cast<const float *>(p.q) + qrow * D;
     const bool paged = p.page_table != nullptr;
     // element offset of key j's row of this KV head in the K or V buffer
     auto key_row = [&](int j) __attribute__((always_inline)) -> int64_t {
@@ -1215,50 +1215,80 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
     };
     const float *kb = static_cast<const float *>(p.k);
     const float *vb = static_cast<const float *>(p.v);
-    for (int d = threadIdx.x; d < D; d += kF32Threads) sh_q[d] = q[d];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x < D / 4) sh_q[threadIdx.x] = reinterpret_cast<const floatx4 *>(static_cast<const float *>(p.q) + qrow * D)[threadIdx.x];
     __syncthreads();
 
-    const int d_own = threadIdx.x % D, part = threadIdx.x / D;
-    float m_run = -INFINITY, l_run = 0.f, acc = 0.f;
-    for (int t0 = 0; t0 < k_end; t0 += kF32Threads) {
+    const int d4 = threadIdx.x % kLanesPerKey, group = threadIdx.x / kLanesPerKey;
+    float m_run = -INFINITY, l_run = 0.f;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    int turn = 0;
+    for (int t0 = 0; t0 < k_end; t0 += kF32Threads, turn ^= 1) {
         const int key = t0 + threadIdx.x;
-        float s = -INFINITY;
-        const bool seen = key < k_end && (!tree || key < first_new || ((row_mask >> (key - first_new)) & 1u));
-        if (seen) {
-            const float4 *kr = reinterpret_cast<const float4 *>(kb + key_row(key));
-            float dot = 0.f;
-#pragma unroll 8
-            for (int d4 = 0; d4 < D / 4; ++d4) {
-                const float4 x = kr[d4];
-                dot = fmaf(x.x, sh_q[4 * d4], dot);
-                dot = fmaf(x.y, sh_q[4 * d4 + 1], dot);
-                dot = fmaf(x.z, sh_q[4 * d4 + 2], dot);
-                dot = fmaf(x.w, sh_q[4 * d4 + 3], dot);
-            }
-            s = dot * p.scale2;
+        // (keys past the end read the last visible one; their score is dropped)
+        const floatx4 *kr = reinterpret_cast<const floatx4 *>(kb + key_row(min(key, k_end - 1)));
+        floatx4 dot4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 16
+        for (int c = 0; c < D / 4; ++c) {
+            const floatx4 x = kr[c], y = sh_q[c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dot4[e] = fmaf(x[e], y[e], dot4[e]);
         }
-        const float m_tile = block_reduce_max(s, sh_red);
-        const float m_new = fmaxf(m_run, m_tile);  // finite: the tile holds at least one key
-        const float pr = seen ? exp2f(s - m_new) : 0.f;
-        const float l_tile = block_reduce_sum(pr, sh_red);
-        const float alpha = exp2f(m_run - m_new);
-        l_run = l_run * alpha + l_tile;
+        const bool seen = key < k_end && (!tree || key < first_new || ((row_mask >> (key - first_new)) & 1u));
+        const float s = seen ? ((dot4[0] + dot4[1]) + (dot4[2] + dot4[3])) * p.scale2 : -INFINITY;
+        float m_w = s;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) m_w = fmaxf(m_w, __shfl_xor(m_w, o));
+        const float pr = seen ? exp2f(s - m_w) : 0.f;
+        float l_w = pr;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) l_w += __shfl_xor(l_w, o);
+        sh_p[turn][threadIdx.x] = pr;
+        if (lane == 0) {
+            sh_m[turn][wave] = m_w;
+            sh_l[turn][wave] = l_w;
+        }
+        __syncthreads();  // (a buffer is written again two chunks later, behind the next chunk's barrier)
+        float m_new = m_run;
+#pragma unroll
+        for (int w = 0; w < kF32Waves; ++w) m_new = fmaxf(m_new, sh_m[turn][w]);
+        // (no key of the row seen so far, a tree's mask may hide a whole chunk: nothing to add)
+        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = exp2f(m_run - m_safe);
+        float wgt[kF32Waves];
+        l_run *= alpha;
+#pragma unroll
+        for (int w = 0; w < kF32Waves; ++w) {
+            wgt[w] = exp2f(sh_m[turn][w] - m_safe);
+            l_run += sh_l[turn][w] * wgt[w];
+        }
         acc *= alpha;
         m_run = m_new;
-        __syncthreads();
-        sh_p[threadIdx.x] = pr;
-        __syncthreads();
         const int nk = min(kF32Threads, k_end - t0);
-        float a = 0.f;
-        for (int j = part; j < nk; j += kParts) a = fmaf(sh_p[j], vb[key_row(t0 + j) + d_own], a);
-        acc += a;
+        for (int j0 = group; j0 < nk; j0 += kGroups * kDepth) {
+            floatx4 v[kDepth];
+            float pj[kDepth];
+#pragma unroll
+            for (int e = 0; e < kDepth; ++e) {
+                const int j = j0 + e * kGroups;
+                v[e] = *reinterpret_cast<const floatx4 *>(vb + key_row(t0 + min(j, nk - 1)) + d4 * 4);
+                const int w = min(j, kF32Threads - 1) >> 6;
+                const float f = w == 0 ? wgt[0] : w == 1 ? wgt[1] : w == 2 ? wgt[2] : wgt[3];
+                pj[e] = j < nk ? sh_p[turn][j] * f : 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < kDepth; ++e)
+                if (j0 + e * kGroups < nk)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc[c] = fmaf(pj[e], v[e][c], acc[c]);
+        }
     }
-    __syncthreads();
-    sh_part[threadIdx.x] = acc;
+    sh_part[group][d4] = acc;
     __syncthreads();
     if (threadIdx.x < D) {
         float o = 0.f;
-        for (int pz = 0; pz < kParts; ++pz) o += sh_part[pz * D + threadIdx.x];
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) o += sh_part[g][threadIdx.x / 4][threadIdx.x % 4];
         static_cast<float *>(p.out)[qrow * D + threadIdx.x] = l_run > 0.f ? o / l_run : 0.f;
         if (p.lse && threadIdx.x == 0)
             p.lse[qrow] = l_run > 0.f ? (m_run + log2f(l_run)) * 0.6931471805599453f : -INFINITY;
@@ -1502,19 +1532,19 @@ int compute_units() {
     return cached[dev];
 }
 
-template <int D, int NT, int CW, int NC>
+// One launch of a form of the main kernel (Form: its LDS, NC: its consumers).
+template <auto kernel, typename Form, int NC>
 hipError_t launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream) {
-    const size_t smem = Bf16Form<D, NT, NC>::kBytes;
-    static bool configured[64] = {false};  // per device; benign race: the attribute is idempotent
+    static bool configured[64] = {false};  // per kernel and device; benign race: the attribute is idempotent
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
     if (dev < 0 || !configured[dev]) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_kernel<D, NT, uint16_t, CW, NC>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, Form::kBytes);
         if (e != hipSuccess) return e;
         if (dev >= 0) configured[dev] = true;
     }
-    hipLaunchKernelGGL((attn_bf16_kernel<D, NT, uint16_t, CW, NC>), grid, dim3((NC + kProducers) * 64), smem, stream, p);
+    hipLaunchKernelGGL(kernel, grid, dim3((NC + kProducers) * 64), Form::kBytes, stream, p);
     return hipGetLastError();
 }
 
@@ -1543,14 +1573,15 @@ hipError_t launch_combine(const AttnParams &p, int M, int64_t kv_tokens, long fo
 // nt: column tiles of a column block; cw: consumers that share a range; nc: consumers of a work-group
 template <int D>
 hipError_t launch_bf16_nt(int nt, int cw, int nc, const AttnParams &p, dim3 grid, hipStream_t stream) {
-    if (cw == 4 && nc == 8) return nt <= 4 ? launch_bf16<D, 1, 4, 8>(p, grid, stream) : launch_bf16<D, 2, 4, 8>(p, grid, stream);
-    if (cw == 2) return nt <= 2 ? launch_bf16<D, 1, 2, 8>(p, grid, stream) : launch_bf16<D, 2, 2, 8>(p, grid, stream);
-    if (cw == 4) return launch_bf16<D, 1, 4, 4>(p, grid, stream);
+#define RESPEC_FORM(NT, CW) launch_bf16<&attn_bf16_kernel<D, NT, uint16_t, CW>, Bf16Form<D, NT, consumers_of(CW)>, consumers_of(CW)>(p, grid, stream)
+    if (cw == 4 && nc == 4) return launch_bf16<&attn_bf16_small_kernel<D, uint16_t>, Bf16Form<D, 1, 4>, 4>(p, grid, stream);
+    if (cw == 4) return nt <= 4 ? RESPEC_FORM(1, 4) : RESPEC_FORM(2, 4);
+    if (cw == 2) return nt <= 2 ? RESPEC_FORM(1, 2) : RESPEC_FORM(2, 2);
     switch (nt) {
-        case 1: return launch_bf16<D, 1, 1, 4>(p, grid, stream);
-        case 2: return launch_bf16<D, 2, 1, 4>(p, grid, stream);
-        case 3: return launch_bf16<D, 3, 1, 4>(p, grid, stream);
-        default: return launch_bf16<D, 4, 1, 4>(p, grid, stream);
+        case 1: return RESPEC_FORM(1, 1);
+        case 2: return RESPEC_FORM(2, 1);
+        case 3: return RESPEC_FORM(3, 1);
+        default: return RESPEC_FORM(4, 1);
     }
 }
 
@@ -1758,8 +1789,18 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     const int streams = nc / cw;  // ranges per work-group
     // the split width: one range per consumer (or group of consumers) of the device
     // (RESPEC_ATTN_WGS overrides it, for tests and sweeps)
+    // A range of a tiny batch gets two tiles at least, were all sequences as long as the longest may
+    // be (a bound that the contiguous and the paged entry point share, so that both split alike): the
+    // partials that the combine kernel folds halve with the ranges, and a second tile takes 0.5 us (2
+    // sequences of 2300 tokens: k = 0 at the 3B shape 21.7 us per call with 1024 ranges, 16.3 us with
+    // 128; k = 6, 4 query heads of 64, 17.0 us with 256, 14.6 with 128)
     long W = kn.get(&Knobs::attn_wgs, 0);
-    if (W <= 0) W = (long)streams * compute_units() / col_blocks;
+    if (W <= 0) {
+        W = (long)streams * compute_units() / col_blocks;
+        const int64_t tile_bound = (int64_t)B * ((max_kv_len + kTileKeys - 1) / kTileKeys) * Hkv;
+        const int64_t most = ((tile_bound + 1) / 2 + streams - 1) / streams * streams;
+        if (W > most) W = (long)most;
+    }
     if (W < 1) W = 1;
     if (W > max_waves) W = max_waves;
     p.W = (int32_t)W;

@@ -892,8 +892,9 @@ __device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, 
     }
 }
 
-template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED>
-__global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParams p) {
+// SHORT: the form for rows of at most kShortSlots slots (one work-group per sequence).
+template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED, bool SHORT>
+__device__ __forceinline__ void rejection_sample(SamplerParams p) {
     __shared__ SharedState sh;
     __shared__ uint32_t sh_epoch;
     constexpr int EPV = Elem<BF16>::EPV;
@@ -970,25 +971,67 @@ __global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParam
     const char *scan_row = tbase;  // row, reference and sum of the final inverse-CDF walk over p
     float scan_M = 0.f;
     double scan_S = 1.0;
+    // Eq. 1 in fp64: rho = p(x)/q(x) = exp(((zp-Mp) - (zq-Mq))/T) * Sq/Sp
+    auto ratio = [&](float zpx, float zqx, float Mp, double Sp, float Mq, double Sq) __attribute__((always_inline)) {
+        if (zqx == -INFINITY) return (zpx == -INFINITY) ? 0.0 : (double)INFINITY;
+        return exp((((double)zpx - (double)Mp) - ((double)zqx - (double)Mq)) * p.inv_T) * (Sq / Sp);
+    };
+    // Short rows: a position's chain of loads, reductions and barriers takes 3 us whatever the row's
+    // length, so eight positions are taken at a time, one per wave, rows behind a rejected position
+    // read for nothing (never used).  Up to kShortSlots a wave's walk over a row pair costs less
+    // than the block's passes it replaces (B = 4, k = 4, V = 1024 fp32: kernel 17.2 -> 11.3 us).
+    // (An instantiation of its own: tested at run time it cost the long rows 1-2 %.)
+    static_assert(!SHORT || !SHARED, "short rows are not shared");
     for (int i = 0; i < k; ++i) {
         const char *rowp = tbase + (size_t)(row0 + i) * p.ld_t * esz;
         const char *rowq = dbase + (size_t)(drow0 + i) * p.ld_d * esz;
+        if constexpr (SHORT) {
+            const int wave = threadIdx.x >> 6;
+            if ((i & (kWaves - 1)) == 0) {
+                __syncthreads();  // (the numbers of the eight positions before have been read)
+                if (i + wave < k) {
+                    const char *rp = rowp + (size_t)wave * p.ld_t * esz, *rq = rowq + (size_t)wave * p.ld_d * esz;
+                    const int x = max(0, min(p.draft_tokens[drow0 + i + wave], p.V - 1));
+                    const float zpx = logit_at<BF16>(rp, x), zqx = logit_at<BF16>(rq, x);
+                    const double u = (double)p.u_accept[drow0 + i + wave];
+                    float Mp, Mq;
+                    double Sp, Sq;
+                    wave_row_stats<BF16>(rp, nslots, Vrow, p, Mp, Sp);
+                    wave_row_stats<BF16>(rq, nslots, Vrow, p, Mq, Sq);
+                    const double rho = ratio(zpx, zqx, Mp, Sp, Mq, Sq);
+                    if ((threadIdx.x & 63) == 0) {
+                        sh.pos_m[0][wave] = Mp;
+                        sh.pos_m[1][wave] = Mq;
+                        sh.pos_s[0][wave] = Sp;
+                        sh.pos_s[1][wave] = Sq;
+                        sh.pos_rho[wave] = rho;
+                        sh.pos_u[wave] = u;
+                        sh.pos_x[wave] = x;
+                    }
+                }
+                __syncthreads();
+            }
+        }
         // the drafted token's two logits and the uniform are requested before the streaming
         // pass, so that the acceptance test does not start with a chain of dependent loads
-        int x = p.draft_tokens[drow0 + i];
-        x = max(0, min(x, p.V - 1));  // memory safety only; ids outside [0,V) are a caller error
-        float zpx, zqx;
-        if constexpr (BF16) {
-            zpx = as_f32((uint32_t) reinterpret_cast<const uint16_t *>(rowp)[x] << 16);
-            zqx = as_f32((uint32_t) reinterpret_cast<const uint16_t *>(rowq)[x] << 16);
-        } else {
-            zpx = reinterpret_cast<const float *>(rowp)[x];
-            zqx = reinterpret_cast<const float *>(rowq)[x];
-        }
-        const double u = (double)p.u_accept[drow0 + i];
+        int x = 0;
+        float zpx = 0.f, zqx = 0.f;
+        double u = 0.0;
         float Mp = 0.f, Mq = 0.f;
         double Sp = 0.0, Sq = 0.0;
         bool have = false;
+        if constexpr (SHORT) {
+            const int w = i & (kWaves - 1);
+            x = sh.pos_x[w];
+            u = sh.pos_u[w];
+            Mp = sh.pos_m[0][w], Sp = sh.pos_s[0][w], Mq = sh.pos_m[1][w], Sq = sh.pos_s[1][w];
+            have = true;
+        } else {
+            x = max(0, min(p.draft_tokens[drow0 + i], p.V - 1));  // memory safety only; ids outside [0,V) are a caller error
+            zpx = logit_at<BF16>(rowp, x);
+            zqx = logit_at<BF16>(rowq, x);
+            u = (double)p.u_accept[drow0 + i];
+        }
         if constexpr (kTwoItems) {
             if (ahead_of == i) {  // this position's normalisers came with the previous stage (block-uniform)
                 Mp = ahead.Mp, Sp = ahead.Sp, Mq = ahead.Mq, Sq = ahead.Sq;
@@ -1014,13 +1057,9 @@ __global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParam
             row_stats_any<BF16, true, ONE_TERM, FULL, SHARED>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow, sh,
                                                       i & 1, mb, p, Mp, Sp, Mq, Sq);
         last_Mp = Mp;
-        // Eq. 1 in fp64: rho = p(x)/q(x) = exp(((zp-Mp) - (zq-Mq))/T) * Sq/Sp
         double rho;
-        if (zqx == -INFINITY)
-            rho = (zpx == -INFINITY) ? 0.0 : (double)INFINITY;
-        else
-            rho = exp((((double)zpx - (double)Mp) - ((double)zqx - (double)Mq)) * p.inv_T) *
-                  (Sq / Sp);
+        if constexpr (SHORT) rho = sh.pos_rho[i & (kWaves - 1)];
+        else rho = ratio(zpx, zqx, Mp, Sp, Mq, Sq);
         const double thr = rho < 1.0 ? rho : 1.0;
         if (fabs(u - thr) <= kBoundaryEps) flag_accept = 1;
         if (u < thr) {
@@ -1126,6 +1165,16 @@ __global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParam
             }
         }
     }
+}
+
+template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED>
+__global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, ONE_TERM, FULL, SHARED, false>(p);
+}
+
+template <bool BF16, bool ONE_TERM>
+__global__ __launch_bounds__(kThreads) void short_rows_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, ONE_TERM, true, false, true>(p);
 }
 
 // Both entry points: `temps` NULL = one temperature for the batch (`temperature`), else one per
@@ -1243,17 +1292,27 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
             hipLaunchKernelGGL((rejection_sample_kernel<BF, ONE, FULL, true>), dim3((unsigned)(B * split)),        \
                                dim3(kThreads), smem, stream, p);                                                   \
         } else {                                                                                                   \
-            if (smem > 0 &&                                                                                        \
-                hipFuncSetAttribute(reinterpret_cast<const void *>(&rejection_sample_kernel<BF, ONE, FULL, false>), \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) {        \
-                smem = 0;                                                                                          \
-                p.tab_slots = 0;                                                                                   \
-            }                                                                                                      \
-            hipLaunchKernelGGL((rejection_sample_kernel<BF, ONE, FULL, false>), dim3((unsigned)B), dim3(kThreads), \
-                               smem, stream, p);                                                                   \
+            RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, ONE, FULL, false>));                            \
         }                                                                                                          \
     } while (0)
-    if (!full) {
+// one work-group per sequence
+#define RESPEC_LAUNCH_SAMPLER_ONE(KERNEL)                                                                           \
+    do {                                                                                                           \
+        if (smem > 0 && hipFuncSetAttribute(reinterpret_cast<const void *>(&KERNEL),                               \
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess) { \
+            smem = 0;                                                                                              \
+            p.tab_slots = 0;                                                                                       \
+        }                                                                                                          \
+        hipLaunchKernelGGL(KERNEL, dim3((unsigned)B), dim3(kThreads), smem, stream, p);                            \
+    } while (0)
+    const bool short_rows = full && split == 1 && max_k > 0 && ((int64_t)V + epv - 1) / epv <= kShortSlots;
+    if (short_rows && bf) {
+        if (one) RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<true, true>));
+        else RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<true, false>));
+    } else if (short_rows) {
+        if (one) RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<false, true>));
+        else RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<false, false>));
+    } else if (!full) {
         if (bf) RESPEC_LAUNCH_SAMPLER(true, false, false); else RESPEC_LAUNCH_SAMPLER(false, false, false);
     } else if (bf) {
         if (one) RESPEC_LAUNCH_SAMPLER(true, true, true); else RESPEC_LAUNCH_SAMPLER(true, false, true);
@@ -1261,6 +1320,7 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         if (one) RESPEC_LAUNCH_SAMPLER(false, true, true); else RESPEC_LAUNCH_SAMPLER(false, false, true);
     }
 #undef RESPEC_LAUNCH_SAMPLER
+#undef RESPEC_LAUNCH_SAMPLER_ONE
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess)
         return fail(RESPEC_ERR_HIP, "rejection_sample: launch failed: %s", hipGetErrorString(err));

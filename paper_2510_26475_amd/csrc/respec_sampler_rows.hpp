@@ -26,6 +26,7 @@ constexpr int kSetsDraw = 2;     // the final draw's pass over the row pair
 constexpr int kChunk = 5;   // slots of a thread's run in the inverse-CDF walk that are loaded together
 constexpr float kRefInit = -1.0e30f;
 constexpr double kBoundaryEps = 1e-6;
+constexpr int kShortSlots = 1024;     // rows up to this many slots: a wave walks a row pair, eight positions at a time
 constexpr int kMaxSplit = 8;          // work-groups that can share one sequence
 constexpr int kBoxHeaderBytes = 128;                      // epoch at word 0
 constexpr int kBoxPayload = kMaxSplit * 2 * 16;           // [part][stage parity][8 doubles as 16 tagged words]
@@ -130,6 +131,14 @@ __device__ inline u32x4 load_slot(const void *row, int slot, int V) {
         for (int j = 0; j < 4; ++j) w[j] = (e0 + j < V) ? r[e0 + j] : 0xff800000u;
     }
     return u32x4{w[0], w[1], w[2], w[3]};
+}
+
+template <bool BF16>
+__device__ inline float logit_at(const char *row, int x) {
+    if constexpr (BF16)
+        return as_f32((uint32_t) reinterpret_cast<const uint16_t *>(row)[x] << 16);
+    else
+        return reinterpret_cast<const float *>(row)[x];
 }
 
 // Of nslots slots from the start of a row (or of a part of one) with Vrow elements to the row's end,
@@ -251,6 +260,10 @@ struct SharedState {
     int failed;                            // a bounded wait for a partner ran out
     float arg_val[kWaves];                 // per-wave (largest logit, its first token) of an argmax pass
     int arg_idx[kWaves];
+    float pos_m[2][kWaves];                // short rows: [p/q][position] references and sums, ...
+    double pos_s[2][kWaves];
+    double pos_rho[kWaves], pos_u[kWaves]; // ... acceptance ratios, uniforms and tokens of eight positions
+    int pos_x[kWaves];
     int token;
     int near_edge;
     int last_positive;
@@ -509,6 +522,33 @@ __device__ inline void row_stats(const void *rowp, const void *rowq, int nslots,
     }
     block_combine(tp.ref, tp.total(), sh, parity, 0, p, Mp, Sp);
     if constexpr (TWO) block_combine(tq.ref, tq.total(), sh, parity, 1, p, Mq, Sq);
+}
+
+// (M, S) of one short row in one wave: its largest logit and S = sum_x exp((z_x - M)/T); an empty
+// row gives (kRefInit, 0), as the guarded pass does.  The second walk finds the row in the caches.
+template <bool BF16>
+__device__ inline void wave_row_stats(const void *row, int nslots, int Vrow, const RowMath &p, float &M, double &S) {
+    constexpr int EPV = Elem<BF16>::EPV;
+    const int lane = threadIdx.x & 63;
+    float m = -INFINITY;
+#pragma unroll 4
+    for (int s = lane; s < nslots; s += 64) m = fmaxf(m, slot_max<BF16>(load_slot<BF16>(row, s, Vrow)));
+    m = wave_max(m);
+    M = m > -INFINITY ? m : kRefInit;
+    float acc[EPV];
+#pragma unroll
+    for (int j = 0; j < EPV; ++j) acc[j] = 0.f;
+#pragma unroll 4
+    for (int s = lane; s < nslots; s += 64) {
+        float z[EPV];
+        unpack<BF16>(load_slot<BF16>(row, s, Vrow), z);
+#pragma unroll
+        for (int j = 0; j < EPV; ++j) acc[j] += hw_exp2(exp2_arg(z[j], M, p.c_hi, p.c_lo));
+    }
+    double t = 0.0;
+#pragma unroll
+    for (int j = 0; j < EPV; ++j) t += (double)acc[j];
+    S = wave_sum(t);
 }
 
 // fp32 form of a normalised probability, for calls whose exponent constant rounds well

@@ -429,14 +429,6 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     return tok;
 }
 
-template <bool BF16>
-__device__ inline float logit_at(const char *row, int x) {
-    if constexpr (BF16)
-        return as_f32((uint32_t) reinterpret_cast<const uint16_t *>(row)[x] << 16);
-    else
-        return reinterpret_cast<const float *>(row)[x];
-}
-
 template <bool BF16, bool ONE_TERM, bool FULL>
 __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreeParams p) {
     __shared__ SharedState sh;
