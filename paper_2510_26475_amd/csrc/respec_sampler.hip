@@ -135,13 +135,13 @@ __device__ inline void exchange(Mailbox &mb, const double (&mine)[8], SharedStat
 // streams its own part (`rowp`, `rowq` point at the part's first slot, `nslots` and `Vrow`
 // are the part's); with several parts the partial results are exchanged and combined in part
 // order, so every part holds the same bits afterwards.
-template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED>
+template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL>
 __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nslots, int Vrow, SharedState &sh,
                                      int parity, Mailbox &mb, const SamplerParams &p, float &Mp,
                                      double &Sp, float &Mq, double &Sq) {
     if constexpr (!SHARED) {
         if constexpr (FULL) {
-            if (row_stats_fast<BF16, TWO, ONE_TERM>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq))
+            if (row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq))
                 return;        // block-uniform
             __syncthreads();   // every thread has read the combine buffers of this parity
         }
@@ -154,7 +154,7 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
         Sp = Sq = 0.0;
         ok = FULL;
     } else if constexpr (FULL) {
-        ok = row_stats_fast<BF16, TWO, ONE_TERM>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
+        ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
     }
     if constexpr (FULL) {
         const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, ok ? 1.0 : 0.0, 0.0, 0.0, 0.0};
@@ -206,7 +206,7 @@ struct DrawNorm {
 // than a part's pass over a row pair, and this halves the exchanges of a chain.  Returns bit 0 if
 // A's numbers are valid and bit 1 if B's are (every part returns the same); an item whose fast
 // pass overflowed or came out empty in some part is repeated by the caller the ordinary way.
-template <bool BF16, bool ONE_TERM>
+template <bool BF16, bool ONE_TERM, bool PARTIAL>
 __device__ inline int row_stats_two_items(const void *pa, const void *qa, const void *pb, const void *qb,
                                           bool b_pair, int nslots, int Vrow, SharedState &sh, Mailbox &mb,
                                           const SamplerParams &p, DrawNorm &A, DrawNorm &Bn) {
@@ -214,11 +214,11 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
     A.Mp = A.Mq = Bn.Mp = Bn.Mq = kRefInit;
     A.Sp = A.Sq = Bn.Sp = Bn.Sq = 0.0;
     if (nslots > 0) {  // (a part without slots has nothing to read and no mass)
-        ok_a = row_stats_fast<BF16, true, ONE_TERM>(pa, qa, nslots, Vrow, sh, 0, p, A.Mp, A.Sp, A.Mq, A.Sq);
+        ok_a = row_stats_fast<BF16, true, ONE_TERM, PARTIAL>(pa, qa, nslots, Vrow, sh, 0, p, A.Mp, A.Sp, A.Mq, A.Sq);
         if (b_pair)  // block-uniform
-            ok_b = row_stats_fast<BF16, true, ONE_TERM>(pb, qb, nslots, Vrow, sh, 1, p, Bn.Mp, Bn.Sp, Bn.Mq, Bn.Sq);
+            ok_b = row_stats_fast<BF16, true, ONE_TERM, PARTIAL>(pb, qb, nslots, Vrow, sh, 1, p, Bn.Mp, Bn.Sp, Bn.Mq, Bn.Sq);
         else
-            ok_b = row_stats_fast<BF16, false, ONE_TERM>(pb, pb, nslots, Vrow, sh, 1, p, Bn.Mp, Bn.Sp, Bn.Mq, Bn.Sq);
+            ok_b = row_stats_fast<BF16, false, ONE_TERM, PARTIAL>(pb, pb, nslots, Vrow, sh, 1, p, Bn.Mp, Bn.Sp, Bn.Mq, Bn.Sq);
     }
     // two binary32 references travel as the halves of one 8-byte word (moved, never computed with)
     auto pack = [](float lo, float hi) {
@@ -343,7 +343,7 @@ struct RowPart {
 
 // Phase A over one part: leaves the eight region totals in sh.wave_total (no barrier), and with
 // a table every slot's total in part.tab.
-template <bool BF16, bool RESID, bool FULL, bool FAST>
+template <bool BF16, bool RESID, bool FULL, bool FAST, bool PARTIAL>
 __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &nm, SharedState &sh,
                                           const RowMath &p) {
     constexpr int EPV = Elem<BF16>::EPV;
@@ -359,7 +359,7 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
     const double Cp = 1.0 / Sp, Cq = RESID ? 1.0 / Sq : 0.0;
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, RESID ? Sq : Sp, p);
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
-    const int whole = FULL && !FAST ? whole_slots<BF16>(nslots, Vrow) : nslots;
+    const int whole = PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots;
     const int beg = min(wave * span, nslots), end_all = min(beg + span, nslots), end = min(end_all, whole);
 
     // phase A: region totals (the next batch of slots is in flight while one is summed; batches
@@ -371,8 +371,8 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
 #pragma unroll
         for (int c = 0; c < kUnroll; ++c) {
             const int slot = s0 + c * 64 + lane;
-            vp[c] = load_slot<BF16, FULL, true, FAST>(rowp, slot < end ? slot : beg, Vrow);
-            if constexpr (RESID) vq[c] = load_slot<BF16, FULL, true, FAST>(rowq, slot < end ? slot : beg, Vrow);
+            vp[c] = load_slot<BF16, FULL, true, !PARTIAL>(rowp, slot < end ? slot : beg, Vrow);
+            if constexpr (RESID) vq[c] = load_slot<BF16, FULL, true, !PARTIAL>(rowq, slot < end ? slot : beg, Vrow);
         }
     };
     if (beg < end) {  // wave-uniform
@@ -422,9 +422,9 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
         for (int s = 0; s < NSETS; ++s)
             if (s < rem) sum_batch(beg + (ib + s) * kStep, rp[s], rq[s], std::false_type{});
     }
-    if constexpr (FULL && !FAST) {  // (the fp32 form serves rows of whole slots only)
+    if constexpr (PARTIAL) {
         if (beg <= whole && whole < end_all && lane == 0) {  // the row's partial slot
-            const u32x4 a = load_slot<BF16>(rowp, whole, Vrow), b = RESID ? load_slot<BF16>(rowq, whole, Vrow) : a;
+            const u32x4 a = load_partial_slot<BF16>(rowp, whole, Vrow), b = RESID ? load_partial_slot<BF16>(rowq, whole, Vrow) : a;
             double w[EPV];
             slot_weights<BF16, RESID>(a, b, Mp, Cp, Mq, Cq, p, w);
 #pragma unroll
@@ -439,7 +439,7 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
 // (LDS); the regions [my_reg0, my_reg0 + kWaves) are those of `part`, this block's part of the
 // row.  Returns the token, or -1 with mine = false when another block holds the crossing, or
 // -1 with Z_out <= 0 when the row carries no mass.  Ends with a barrier.
-template <bool BF16, bool RESID, bool FULL, bool FAST, bool KEEP_SLOTS>
+template <bool BF16, bool RESID, bool FULL, bool FAST, bool KEEP_SLOTS, bool PARTIAL>
 __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, const RowPart &part,
                                   const DrawNorm &nm, double u, SharedState &sh, const RowMath &p, int &near_edge,
                                   double &Z_out, bool &mine) {
@@ -491,11 +491,14 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
     float *tab = part.tab;
     const bool use_tab = FAST && tab != nullptr;  // block-uniform
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
-    const int whole = FULL && !FAST ? whole_slots<BF16>(nslots, Vrow) : nslots;
+    const int whole = PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots;
     // one slot, the partial one included (a single thread's read)
     auto any_slot = [&](const void *row, int sidx) {
-        if constexpr (FAST) return load_slot<BF16, FULL, false, true>(row, sidx, Vrow);
-        else return load_slot<BF16>(row, sidx, Vrow);
+        if constexpr (FULL && !PARTIAL) return load_slot<BF16, FULL, false, true>(row, sidx, Vrow);
+        else if constexpr (FULL) {
+            const u32x4 v = load_slot_or_last<BF16>(row, sidx, Vrow);
+            return sidx < whole ? v : partial_slot<BF16>(v, whole, Vrow);
+        } else return load_slot<BF16>(row, sidx, Vrow);
     };
     const int wstar = rstar % kWaves;
 
@@ -587,21 +590,26 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
     auto load_chunk = [&](int c0, u32x4 (&vp)[kChunk], u32x4 (&vq)[kChunk]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < kChunk; ++j) {
-            const int slot = FULL && !FAST ? max(0, min(c0 + j < my1 ? c0 + j : rb, whole - 1)) : c0 + j < my1 ? c0 + j : rb;
-            vp[j] = load_slot<BF16, FULL, false, FAST>(rowp, slot, Vrow);
-            if constexpr (RESID) vq[j] = load_slot<BF16, FULL, false, FAST>(rowq, slot, Vrow);
+            const int slot = c0 + j < my1 ? c0 + j : rb;
+            if constexpr (PARTIAL) {
+                vp[j] = load_slot_or_last<BF16>(rowp, slot, Vrow);
+                if constexpr (RESID) vq[j] = load_slot_or_last<BF16>(rowq, slot, Vrow);
+            } else {
+                vp[j] = load_slot<BF16, FULL, false, !PARTIAL>(rowp, slot, Vrow);
+                if constexpr (RESID) vq[j] = load_slot<BF16, FULL, false, !PARTIAL>(rowq, slot, Vrow);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < kChunk; ++j) {
             const bool in = c0 + j < my1;
+            if (PARTIAL && c0 + j == whole) {  // (whole == nslots: there is no such slot, and no such j inside the run)
+                vp[j] = partial_slot<BF16>(vp[j], whole, Vrow);
+                if constexpr (RESID) vq[j] = partial_slot<BF16>(vq[j], whole, Vrow);
+            }
             vp[j] = in ? vp[j] : neg_inf_slot<BF16>();
             if constexpr (RESID) vq[j] = in ? vq[j] : neg_inf_slot<BF16>();
-            if (FULL && !FAST && in && c0 + j >= whole) {  // the row's partial slot
-                vp[j] = load_slot<BF16>(rowp, c0 + j, Vrow);
-                if constexpr (RESID) vq[j] = load_slot<BF16>(rowq, c0 + j, Vrow);
-            }
-            if constexpr (!RESID) vq[j] = vp[j];
+            else vq[j] = vp[j];
         }
     };
     // the totals of the slots of the first chunk are kept for the walk, and (when the registers
@@ -730,14 +738,14 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
 // The draw of a block that sees one part of the row: its own share of a sequence that several
 // work-groups walk together (SHARED: the region totals are exchanged, and the block that holds
 // the crossing finishes), or the whole row.
-template <bool BF16, bool RESID, bool FULL, bool SHARED, bool FAST = false>
+template <bool BF16, bool RESID, bool FULL, bool SHARED, bool FAST, bool PARTIAL>
 __device__ inline int inverse_cdf_pass(const void *rowp, const void *rowq, int nslots, int Vrow, int tok_off,
                                        float Mp, double Sp, float Mq, double Sq, double u, SharedState &sh,
                                        Mailbox &mb, const SamplerParams &p, int &near_edge, double &Z_out,
                                        bool &mine, float *tab = nullptr) {
     const RowPart part{rowp, rowq, nslots, Vrow, tok_off, tab};
     const DrawNorm nm{Mp, Mq, Sp, Sq};
-    draw_region_totals<BF16, RESID, FULL, FAST>(part, nm, sh, p);
+    draw_region_totals<BF16, RESID, FULL, FAST, PARTIAL>(part, nm, sh, p);
     __syncthreads();
     // the region totals of all parts, in vocabulary order
     const int n_reg = SHARED ? mb.split * kWaves : kWaves;
@@ -750,7 +758,7 @@ __device__ inline int inverse_cdf_pass(const void *rowp, const void *rowq, int n
         __syncthreads();
     }
     const double *totals = SHARED ? sh.all_total : sh.wave_total;
-    return draw_finish<BF16, RESID, FULL, FAST, !SHARED>(totals, n_reg, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
+    return draw_finish<BF16, RESID, FULL, FAST, !SHARED, PARTIAL>(totals, n_reg, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
                                                          p, near_edge, Z_out, mine);
 }
 
@@ -774,10 +782,10 @@ __device__ inline void device_row_math(RowMath &m, float temperature) {
 
 // The first argmax of a row: its largest logit, the lowest token id among equal ones (an
 // all -inf row gives token 0).  Every thread returns the same value.  Ends with a barrier.
-template <bool BF16, bool FULL>
+template <bool BF16, bool FULL, bool PARTIAL>
 __device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedState &sh) {
     constexpr int EPV = Elem<BF16>::EPV;
-    const int nslots = FULL ? whole_slots<BF16>(nslots_all, V) : nslots_all;
+    const int nslots = PARTIAL ? whole_slots<BF16>(nslots_all, V) : nslots_all;
     constexpr int kBatch = kThreads * kUnroll;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     const int n_iter = (nslots + kBatch - 1) / kBatch;
@@ -787,7 +795,7 @@ __device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedS
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int slot = it * kBatch + u * kThreads + (int)threadIdx.x;
-            v[u] = load_slot<BF16, FULL>(row, it + 1 < n_iter ? slot : max(0, min(slot, nslots - 1)), V);
+            v[u] = load_slot<BF16, FULL, false, !PARTIAL>(row, it + 1 < n_iter ? slot : max(0, min(slot, nslots - 1)), V);
         }
     };
     float best = -INFINITY;
@@ -825,9 +833,9 @@ __device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedS
     } else {
         compare_batch(it, v);
     }
-    if (nslots < nslots_all && threadIdx.x == 0) {  // the row's partial slot (the highest ids)
+    if (PARTIAL && nslots < nslots_all && threadIdx.x == 0) {  // the row's partial slot (the highest ids)
         float z[EPV];
-        unpack<BF16>(load_slot<BF16>(row, nslots, V), z);
+        unpack<BF16>(load_partial_slot<BF16>(row, nslots, V), z);
 #pragma unroll
         for (int j = 0; j < EPV; ++j)
             if (z[j] > best) {
@@ -868,7 +876,7 @@ __device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedS
 // accepted iff it is the first argmax of its target row; the first one that is not is replaced
 // by that argmax; if all are accepted the bonus token is the argmax of row k.  Reads target
 // rows 0..n only, no drafter logits and no uniforms.
-template <bool BF16, bool FULL>
+template <bool BF16, bool FULL, bool PARTIAL>
 __device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, int drow0, int k, SharedState &sh) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int nslots = (p.V + EPV - 1) / EPV;
@@ -877,7 +885,7 @@ __device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, 
     int n = 0, a;
     for (;;) {
         const char *rowp = static_cast<const char *>(p.target) + (size_t)(row0 + n) * p.ld_t * esz;
-        a = row_argmax<BF16, FULL>(rowp, nslots, p.V, sh);
+        a = row_argmax<BF16, FULL, PARTIAL>(rowp, nslots, p.V, sh);
         if (n >= k) break;
         const int x = p.draft_tokens[drow0 + n];
         if (x != a) break;
@@ -893,8 +901,8 @@ __device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, 
 }
 
 // SHORT: the form for rows of at most kShortSlots slots (one work-group per sequence).
-template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED, bool SHORT>
-__device__ __forceinline__ void rejection_sample(SamplerParams p) {
+template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED, bool SHORT, bool PARTIAL>
+__device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     __shared__ SharedState sh;
     __shared__ uint32_t sh_epoch;
     constexpr int EPV = Elem<BF16>::EPV;
@@ -937,7 +945,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
                 return;
             }
             if (T == 0.f) {
-                greedy_sequence<BF16, FULL>(p, b, row0, drow0, k, sh);
+                greedy_sequence<BF16, FULL, PARTIAL>(p, b, row0, drow0, k, sh);
                 return;
             }
             device_row_math(p, T);
@@ -979,7 +987,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
     // Short rows: a position's chain of loads, reductions and barriers takes 3 us whatever the row's
     // length, so eight positions are taken at a time, one per wave, rows behind a rejected position
     // read for nothing (never used).  Up to kShortSlots a wave's walk over a row pair costs less
-    // than the block's passes it replaces (B = 4, k = 4, V = 1024 fp32: kernel 17.2 -> 11.3 us).
+    // than the block's passes it replaces (B = 4, k = 4, V = 1024 fp32: kernel 17.2 -> 10.8 us).
     // (An instantiation of its own: tested at run time it cost the long rows 1-2 %.)
     static_assert(!SHORT || !SHARED, "short rows are not shared");
     for (int i = 0; i < k; ++i) {
@@ -1043,7 +1051,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
                 const char *rowpb = tbase + (size_t)(row0 + i + 1) * p.ld_t * esz;
                 const char *rowqb = b_pair ? dbase + (size_t)(drow0 + i + 1) * p.ld_d * esz : rowpb;
                 DrawNorm a;
-                const int ok = row_stats_two_items<BF16, ONE_TERM>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16,
+                const int ok = row_stats_two_items<BF16, ONE_TERM, PARTIAL>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16,
                                                                    rowpb + (size_t)lo * 16, rowqb + (size_t)lo * 16, b_pair,
                                                                    nslots, Vrow, sh, mb, p, a, ahead);
                 ahead_of = (ok & 2) ? i + 1 : -1;
@@ -1054,7 +1062,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
             }
         }
         if (!have)
-            row_stats_any<BF16, true, ONE_TERM, FULL, SHARED>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow, sh,
+            row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow, sh,
                                                       i & 1, mb, p, Mp, Sp, Mq, Sq);
         last_Mp = Mp;
         double rho;
@@ -1070,7 +1078,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
         // first rejection: one draw from the residual distribution (Eq. 2)
         double Z;
         int edge = 0;
-        final_token = inverse_cdf_pass<BF16, true, FULL, SHARED, kFastScan>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow,
+        final_token = inverse_cdf_pass<BF16, true, FULL, SHARED, kFastScan, PARTIAL>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow,
                                                          tok_off, Mp, Sp, Mq, Sq, u_fin, sh, mb, p, edge, Z, mine, tab);
         flag_cdf = edge;
         rejected = true;
@@ -1083,7 +1091,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
     }
     bool scan_target = false;
     bool drawn = false;
-    if constexpr (FULL && kFastScan) {
+    if constexpr (FULL) {
         // The bonus token's draw needs no normaliser: it compares running sums of weights with u
         // times their total, so exp((z - M0)/T) serves for any reference M0 that keeps the
         // weights in range: one pass over the row instead of two.  With one work-group per
@@ -1101,7 +1109,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
             if (M0 > -INFINITY && M0 < INFINITY) {  // block-uniform
                 double Z;
                 int edge = 0;
-                const int tok = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots, Vrow, tok_off,
+                const int tok = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots, Vrow, tok_off,
                                                                                M0, 1.0, M0, 1.0, u_fin, sh, mb, p, edge, Z, mine, tab);
                 if (Z > 0.0 && Z < 1.0e300) {
                     final_token = tok;
@@ -1123,7 +1131,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
             scan_M = ahead.Mp;
             scan_S = ahead.Sp;
         } else {
-            row_stats_any<BF16, false, ONE_TERM, FULL, SHARED>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
+            row_stats_any<BF16, false, ONE_TERM, FULL, SHARED, PARTIAL>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
                                                        Vrow, sh, k & 1, mb, p, scan_M, scan_S, Mq, Sq);
         }
         scan_target = true;
@@ -1133,7 +1141,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
     if (scan_target) {
         double Z;
         int edge = 0;
-        final_token = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
+        final_token = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
                                                           Vrow, tok_off, scan_M, scan_S, scan_M, scan_S, u_fin, sh,
                                                           mb, p, edge, Z, mine, tab);
         flag_cdf = rejected ? 1 : edge;
@@ -1169,12 +1177,18 @@ __device__ __forceinline__ void rejection_sample(SamplerParams p) {
 
 template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED>
 __global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParams p) {
-    rejection_sample<BF16, ONE_TERM, FULL, SHARED, false>(p);
+    rejection_sample<BF16, ONE_TERM, FULL, SHARED, false, false>(p);
+}
+
+// Rows that are not whole aligned slots (fp64 weights).
+template <bool BF16, bool SHARED>
+__global__ __launch_bounds__(kThreads) void partial_rows_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, false, true, SHARED, false, true>(p);
 }
 
 template <bool BF16, bool ONE_TERM>
 __global__ __launch_bounds__(kThreads) void short_rows_sample_kernel(SamplerParams p) {
-    rejection_sample<BF16, ONE_TERM, true, false, true>(p);
+    rejection_sample<BF16, ONE_TERM, true, false, true, !ONE_TERM>(p);
 }
 
 // Both entry points: `temps` NULL = one temperature for the batch (`temperature`), else one per
@@ -1282,19 +1296,21 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
             p.tab_slots = (int)slots_part;
         }
     }
-#define RESPEC_LAUNCH_SAMPLER(BF, ONE, FULL)                                                                        \
+// with or without sharing
+#define RESPEC_LAUNCH_SAMPLER(SHARED_KERNEL, ONE_KERNEL)                                                            \
     do {                                                                                                           \
         if (split > 1) {                                                                                           \
             if (smem > 48 * 1024) { /* (only whole rows need more than the default limit) */                      \
                 smem = 0;                                                                                          \
                 p.tab_slots = 0;                                                                                   \
             }                                                                                                      \
-            hipLaunchKernelGGL((rejection_sample_kernel<BF, ONE, FULL, true>), dim3((unsigned)(B * split)),        \
-                               dim3(kThreads), smem, stream, p);                                                   \
+            hipLaunchKernelGGL(SHARED_KERNEL, dim3((unsigned)(B * split)), dim3(kThreads), smem, stream, p);       \
         } else {                                                                                                   \
-            RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, ONE, FULL, false>));                            \
+            RESPEC_LAUNCH_SAMPLER_ONE(ONE_KERNEL);                                                                 \
         }                                                                                                          \
     } while (0)
+#define RESPEC_LAUNCH_FORM(BF, ONE, FULL)                                                                           \
+    RESPEC_LAUNCH_SAMPLER((rejection_sample_kernel<BF, ONE, FULL, true>), (rejection_sample_kernel<BF, ONE, FULL, false>))
 // one work-group per sequence
 #define RESPEC_LAUNCH_SAMPLER_ONE(KERNEL)                                                                           \
     do {                                                                                                           \
@@ -1313,12 +1329,16 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         if (one) RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<false, true>));
         else RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<false, false>));
     } else if (!full) {
-        if (bf) RESPEC_LAUNCH_SAMPLER(true, false, false); else RESPEC_LAUNCH_SAMPLER(false, false, false);
+        if (bf) RESPEC_LAUNCH_FORM(true, false, false); else RESPEC_LAUNCH_FORM(false, false, false);
+    } else if (!whole_rows) {
+        if (bf) RESPEC_LAUNCH_SAMPLER((partial_rows_sample_kernel<true, true>), (partial_rows_sample_kernel<true, false>));
+        else RESPEC_LAUNCH_SAMPLER((partial_rows_sample_kernel<false, true>), (partial_rows_sample_kernel<false, false>));
     } else if (bf) {
-        if (one) RESPEC_LAUNCH_SAMPLER(true, true, true); else RESPEC_LAUNCH_SAMPLER(true, false, true);
+        if (one) RESPEC_LAUNCH_FORM(true, true, true); else RESPEC_LAUNCH_FORM(true, false, true);
     } else {
-        if (one) RESPEC_LAUNCH_SAMPLER(false, true, true); else RESPEC_LAUNCH_SAMPLER(false, false, true);
+        if (one) RESPEC_LAUNCH_FORM(false, true, true); else RESPEC_LAUNCH_FORM(false, false, true);
     }
+#undef RESPEC_LAUNCH_FORM
 #undef RESPEC_LAUNCH_SAMPLER
 #undef RESPEC_LAUNCH_SAMPLER_ONE
     const hipError_t err = hipGetLastError();

@@ -99,7 +99,7 @@ __device__ inline u32x4 neg_inf_slot() {
 // Rows start wherever their element type may (an odd vocabulary leaves them 2 or 4 bytes aligned):
 // the 16-byte loads of this device take any address, a wave's 1 KiB then touches one cache line more.
 // (Element loads for such rows took 2 to 8 times the instructions: B = 32, k = 2, fp32, V = 50,257
-// 43.6 -> 29.1 us per call.)
+// 43.5 -> 26.8 us per call.)
 // LAST_USE: the pass that reads the row for the last time marks its loads non-temporal, which
 // leaves the caches to rows that are still to be read again (3 % of the sampler's time, 6 % of
 // the distillation kernel's; the same hint on a row's first read costs 5 %: the second read
@@ -139,6 +139,42 @@ __device__ inline float logit_at(const char *row, int x) {
         return as_f32((uint32_t) reinterpret_cast<const uint16_t *>(row)[x] << 16);
     else
         return reinterpret_cast<const float *>(row)[x];
+}
+
+// The partial slot behind `whole` whole ones from the row's last 16 bytes (what it is loaded as: the
+// same kind of load as every other slot's, so that a batch of loads needs no condition): its
+// elements moved to the front, -inf behind them.
+template <bool BF16>
+__device__ inline u32x4 partial_slot(const u32x4 &last, int whole, int Vrow) {
+    const uint32_t fill = neg_inf_slot<BF16>()[0];
+    const int bytes = (Elem<BF16>::EPV - (Vrow - whole * Elem<BF16>::EPV)) * (BF16 ? 2 : 4);  // to drop
+    uint32_t w[5];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        w[j] = fill;
+#pragma unroll
+        for (int i = j; i < 4; ++i) w[j] = j + bytes / 4 == i ? last[i] : w[j];
+    }
+    w[4] = fill;
+    u32x4 v;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = (bytes & 2) ? (w[j] >> 16) | (w[j + 1] << 16) : w[j];
+    return v;
+}
+
+// 16 bytes of slot `slot` of a row with Vrow elements (at least one slot's worth), the row's last 16
+// bytes for its partial slot.
+template <bool BF16>
+__device__ inline u32x4 load_slot_or_last(const void *row, int slot, int Vrow) {
+    typedef u32x4 u32x4_elem __attribute__((aligned(2)));
+    const uint32_t off = min((uint32_t)slot * 16u, (uint32_t)Vrow * (BF16 ? 2u : 4u) - 16u);
+    return *reinterpret_cast<const u32x4_elem *>(static_cast<const char *>(row) + off);
+}
+
+// The partial slot itself.
+template <bool BF16>
+__device__ inline u32x4 load_partial_slot(const void *row, int whole, int Vrow) {
+    return partial_slot<BF16>(load_slot_or_last<BF16>(row, whole, Vrow), whole, Vrow);
 }
 
 // Of nslots slots from the start of a row (or of a part of one) with Vrow elements to the row's end,
@@ -382,14 +418,14 @@ __device__ inline float block_max_of_row_start(const void *row, int nslots, Shar
 // exp2 keeps full relative precision for any offset, only a logit more than ~88/c above the
 // reference would overflow.  Returns false (every thread alike) when a sum came out
 // non-finite or empty, and the caller then repeats the row with the guarded pass below.
-// The row has at least one whole slot.
-template <bool BF16, bool TWO, bool ONE_TERM>
+// PARTIAL: the row need not be aligned nor hold whole slots only (it has at least one); an
+// instantiation of its own, since what it adds cost whole rows 1-2 %.
+template <bool BF16, bool TWO, bool ONE_TERM, bool PARTIAL = false>
 __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int nslots_all, int Vrow,
                                       SharedState &sh, int parity, const RowMath &p, float &Mp,
                                       double &Sp, float &Mq, double &Sq) {
     constexpr int EPV = Elem<BF16>::EPV;
-    // (the one-term form serves rows of whole slots only)
-    const int nslots = ONE_TERM ? nslots_all : whole_slots<BF16>(nslots_all, Vrow);
+    const int nslots = PARTIAL ? whole_slots<BF16>(nslots_all, Vrow) : nslots_all;
     constexpr int kBatch = kThreads * kUnroll;  // slots per block iteration
     const int tid = opaque_thread_index();
     float accp[EPV], accq[EPV];
@@ -406,15 +442,15 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
         if (it + 1 < n_iter) {
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
-                vp[u] = load_slot<BF16, true, false, ONE_TERM>(rowp, s0 + u * kThreads, Vrow);
-                if constexpr (TWO) vq[u] = load_slot<BF16, true, false, ONE_TERM>(rowq, s0 + u * kThreads, Vrow);
+                vp[u] = load_slot<BF16, true, false, !PARTIAL>(rowp, s0 + u * kThreads, Vrow);
+                if constexpr (TWO) vq[u] = load_slot<BF16, true, false, !PARTIAL>(rowq, s0 + u * kThreads, Vrow);
             }
         } else {
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
                 const int safe = max(0, min(s0 + u * kThreads, nslots - 1));
-                vp[u] = load_slot<BF16, true, false, ONE_TERM>(rowp, safe, Vrow);
-                if constexpr (TWO) vq[u] = load_slot<BF16, true, false, ONE_TERM>(rowq, safe, Vrow);
+                vp[u] = load_slot<BF16, true, false, !PARTIAL>(rowp, safe, Vrow);
+                if constexpr (TWO) vq[u] = load_slot<BF16, true, false, !PARTIAL>(rowq, safe, Vrow);
             }
         }
     };
@@ -478,9 +514,9 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
             absorb_batch(rp[s], rq[s]);
         }
     }
-    if (!ONE_TERM && nslots < nslots_all && tid == 0) {  // the row's partial slot
-        fast_absorb<BF16, ONE_TERM>(load_slot<BF16>(rowp, nslots, Vrow), accp, refp, Kp, p);
-        if constexpr (TWO) fast_absorb<BF16, ONE_TERM>(load_slot<BF16>(rowq, nslots, Vrow), accq, refq, Kq, p);
+    if (PARTIAL && nslots < nslots_all && tid == 0) {  // the row's partial slot
+        fast_absorb<BF16, ONE_TERM>(load_partial_slot<BF16>(rowp, nslots, Vrow), accp, refp, Kp, p);
+        if constexpr (TWO) fast_absorb<BF16, ONE_TERM>(load_partial_slot<BF16>(rowq, nslots, Vrow), accq, refq, Kq, p);
     }
     double sp = 0.0, sq = 0.0;
 #pragma unroll

@@ -167,7 +167,7 @@ __device__ inline float tree_slot_weights_f32(const u32x4 &vp, const u32x4 &vq, 
 // and streams it with coalesced loads; lanes keep their own fp64 sums, one reduction per wave
 // gives the region total (left in sh.wave_total).  Returns Z = the ordered sum of the region
 // totals, the same bits in every thread.  At depth 0 only the target row is read.
-template <bool BF16, bool FULL, bool FAST, int KIND>
+template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND>
 __device__ inline double tree_region_totals(const void *rowp, const void *rowq, int nslots, int V, float Mp,
                                             double Sp, float Mq, double Sq, const Depth &d, double raw_1, SharedState &sh,
                                             const RowMath &p) {
@@ -178,7 +178,7 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, two ? Sq : Sp, p);
     const FastDepth fd = make_fast_depth(d, raw_1, fn);
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
-    const int whole = FULL && !FAST ? whole_slots<BF16>(nslots, V) : nslots;
+    const int whole = PARTIAL ? whole_slots<BF16>(nslots, V) : nslots;
     const int beg = min(wave * span, nslots), end_all = min(beg + span, nslots), end = min(end_all, whole);
     __syncthreads();  // the totals of an earlier pass have been read by everyone
     double lane_sum = 0.0;
@@ -186,8 +186,8 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
 #pragma unroll
         for (int c = 0; c < kUnroll; ++c) {  // no select behind a load: the loads of a batch go out together
             const int slot = s0 + c * 64 + lane;
-            vp[c] = load_slot<BF16, FULL, false, FAST>(rowp, slot < end ? slot : beg, V);
-            if constexpr (two) vq[c] = load_slot<BF16, FULL, false, FAST>(rowq, slot < end ? slot : beg, V);
+            vp[c] = load_slot<BF16, FULL, false, !PARTIAL>(rowp, slot < end ? slot : beg, V);
+            if constexpr (two) vq[c] = load_slot<BF16, FULL, false, !PARTIAL>(rowq, slot < end ? slot : beg, V);
             else vq[c] = vp[c];
         }
     };
@@ -230,9 +230,9 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
             sum_batch(s0, vp, vq, std::false_type{});
         }
     }
-    if constexpr (FULL && !FAST) {  // (the fp32 form serves rows of whole slots only)
+    if constexpr (PARTIAL) {
         if (beg <= whole && whole < end_all && lane == 0) {  // the row's partial slot
-            const u32x4 a = load_slot<BF16>(rowp, whole, V), b = two ? load_slot<BF16>(rowq, whole, V) : a;
+            const u32x4 a = load_partial_slot<BF16>(rowp, whole, V), b = two ? load_partial_slot<BF16>(rowq, whole, V) : a;
             double w[EPV];
             tree_slot_weights<BF16, KIND>(a, b, Mp, Cp, Mq, Cq, d, p, w);
 #pragma unroll
@@ -254,7 +254,7 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
 // thread whose running sum passes u*Z walks its run element by element.  The re-read adds
 // the same numbers in another order than the region pass, so at the last bit a crossing can
 // fall off the end of the region; that draw takes the last token with mass and is flagged.
-template <bool BF16, bool FULL, bool FAST, int KIND>
+template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND>
 __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, int V, float Mp, double Sp,
                                 float Mq, double Sq, const Depth &d, double raw_1, double u, SharedState &sh,
                                 const RowMath &p, int &near_edge) {
@@ -290,10 +290,13 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     if (forced) rstar = rlast;
     __syncthreads();
 
-    const int whole = FULL && !FAST ? whole_slots<BF16>(nslots, V) : nslots;
+    const int whole = PARTIAL ? whole_slots<BF16>(nslots, V) : nslots;
     auto any_slot = [&](const void *row, int sidx) {
-        if constexpr (FAST) return load_slot<BF16, FULL, false, true>(row, sidx, V);
-        else return load_slot<BF16>(row, sidx, V);
+        if constexpr (FULL && !PARTIAL) return load_slot<BF16, FULL, false, true>(row, sidx, V);
+        else if constexpr (FULL) {
+            const u32x4 v = load_slot_or_last<BF16>(row, sidx, V);
+            return sidx < whole ? v : partial_slot<BF16>(v, whole, V);
+        } else return load_slot<BF16>(row, sidx, V);
     };
     const int rb = min(rstar * span, nslots), re = min(rb + span, nslots);
     const int per = (re - rb + kThreads - 1) / kThreads;
@@ -303,21 +306,26 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     auto load_chunk = [&](int c0, u32x4 (&vp)[kChunk], u32x4 (&vq)[kChunk]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < kChunk; ++j) {  // no select behind a load: the loads go out together
-            const int slot = FULL && !FAST ? max(0, min(c0 + j < my1 ? c0 + j : rb, whole - 1)) : c0 + j < my1 ? c0 + j : rb;
-            vp[j] = load_slot<BF16, FULL, false, FAST>(rowp, slot, V);
-            if constexpr (two) vq[j] = load_slot<BF16, FULL, false, FAST>(rowq, slot, V);
+            const int slot = c0 + j < my1 ? c0 + j : rb;
+            if constexpr (PARTIAL) {
+                vp[j] = load_slot_or_last<BF16>(rowp, slot, V);
+                if constexpr (two) vq[j] = load_slot_or_last<BF16>(rowq, slot, V);
+            } else {
+                vp[j] = load_slot<BF16, FULL, false, !PARTIAL>(rowp, slot, V);
+                if constexpr (two) vq[j] = load_slot<BF16, FULL, false, !PARTIAL>(rowq, slot, V);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < kChunk; ++j) {  // slots past the run count as -inf
             const bool in = c0 + j < my1;
+            if (PARTIAL && c0 + j == whole) {
+                vp[j] = partial_slot<BF16>(vp[j], whole, V);
+                if constexpr (two) vq[j] = partial_slot<BF16>(vq[j], whole, V);
+            }
             vp[j] = in ? vp[j] : neg_inf_slot<BF16>();
             if constexpr (two) vq[j] = in ? vq[j] : neg_inf_slot<BF16>();
-            if (FULL && !FAST && in && c0 + j >= whole) {  // the row's partial slot
-                vp[j] = load_slot<BF16>(rowp, c0 + j, V);
-                if constexpr (two) vq[j] = load_slot<BF16>(rowq, c0 + j, V);
-            }
-            if constexpr (!two) vq[j] = vp[j];
+            else vq[j] = vp[j];
         }
     };
     double slot_total[kChunk];
@@ -429,8 +437,8 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     return tok;
 }
 
-template <bool BF16, bool ONE_TERM, bool FULL>
-__global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreeParams p) {
+template <bool BF16, bool ONE_TERM, bool FULL, bool PARTIAL>
+__device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
     __shared__ SharedState sh;
     __shared__ int sh_parent[kMaxTreeRows];
     __shared__ double sh_inv_z[kMaxTreeRows];
@@ -473,7 +481,7 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
         while (c < R && sh_parent[c] != cur) ++c;
         if (c >= R || n >= p.max_depth) break;  // a leaf (or the output row is full): draw from the target
         if constexpr (FULL) {
-            if (!row_stats_fast<BF16, true, ONE_TERM>(rowp, rowq, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq)) {
+            if (!row_stats_fast<BF16, true, ONE_TERM, PARTIAL>(rowp, rowq, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq)) {
                 __syncthreads();
                 row_stats<BF16, true>(rowp, rowq, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
             }
@@ -523,14 +531,14 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
             {
                 const Depth d{depth, sh_inv_z[1], sh_inv_z[2], sh_inv_z};
                 if (depth == 1) {
-                    raw_1 = tree_region_totals<BF16, FULL, ONE_TERM, 1>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                    raw_1 = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 1>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
                     Zd = raw_1;
                     if constexpr (ONE_TERM) Zd += raw_1 * (double)make_fast_norm(Mp, Sp, Mq, Sq, p).ep;
                 } else if (depth == 2) {
-                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, 2>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 2>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
                     if constexpr (ONE_TERM) Zd /= raw_1;
                 } else {
-                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, kAnyDepth>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
                 }
             }
             if (Zd > 0.0) {
@@ -554,7 +562,7 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
         // At a leaf one pass serves instead of two: the draw compares running sums with u times
         // their total, so any reference that keeps the weights in range will do; a total that is
         // not a positive finite number sends the draw the ordinary way (normalisers first).
-        bool trial = FULL && ONE_TERM && !have_norm;
+        bool trial = FULL && !have_norm;
         if (trial) {
             Mp = block_max_of_row_start<BF16>(rowp, p.V / EPV, sh);
             Sp = 1.0;
@@ -564,13 +572,13 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
             if (!trial && !have_norm) {
                 bool ok = false;
                 if constexpr (FULL) {
-                    ok = row_stats_fast<BF16, false, ONE_TERM>(rowp, rowp, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
+                    ok = row_stats_fast<BF16, false, ONE_TERM, PARTIAL>(rowp, rowp, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
                     if (!ok) __syncthreads();
                 }
                 if (!ok) row_stats<BF16, false>(rowp, rowp, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
                 have_norm = true;
             }
-            Z = tree_region_totals<BF16, FULL, ONE_TERM, 0>(rowp, rowp, nslots, p.V, Mp, Sp, Mp, Sp, d, raw_1, sh, p);
+            Z = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 0>(rowp, rowp, nslots, p.V, Mp, Sp, Mp, Sp, d, raw_1, sh, p);
             if (!trial || (Z > 0.0 && Z < 1.0e300)) break;
             trial = false;
         }
@@ -579,13 +587,13 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
         const double u = (double)p.u_final[b];
         int edge = 0;
         if (depth == 0)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, 0>(rowp, rowp, nslots, p.V, Mp, Sp, Mp, Sp, d, raw_1, u, sh, p, edge);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 0>(rowp, rowp, nslots, p.V, Mp, Sp, Mp, Sp, d, raw_1, u, sh, p, edge);
         else if (depth == 1)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, 1>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 1>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
         else if (depth == 2)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, 2>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 2>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
         else
-            final_token = tree_draw<BF16, FULL, ONE_TERM, kAnyDepth>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
         flag_cdf |= edge;
     } else {  // row without any finite logit: report the last token
         final_token = p.V - 1;
@@ -599,6 +607,17 @@ __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreePar
         p.out_num_accepted[b] = n;
         if (p.out_flags) p.out_flags[b] = (flag_accept ? 1 : 0) | (flag_cdf ? 2 : 0);
     }
+}
+
+template <bool BF16, bool ONE_TERM, bool FULL>
+__global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreeParams p) {
+    tree_rejection_sample<BF16, ONE_TERM, FULL, false>(p);
+}
+
+// Rows that are not whole aligned slots (fp64 weights).
+template <bool BF16>
+__global__ __launch_bounds__(kThreads) void tree_partial_rows_kernel(TreeParams p) {
+    tree_rejection_sample<BF16, false, true, true>(p);
 }
 
 }  // namespace
@@ -660,15 +679,19 @@ extern "C" respec_status_t respec_tree_rejection_sample(
                             aligned_to(draft_logits, 16) && (ld_d * esz) % 16 == 0;
     p.one_term = p.one_term && whole_rows;
     const bool bf = logits_dt == RESPEC_BF16, one = p.one_term != 0;
-#define RESPEC_LAUNCH_TREE(BF, ONE, FULL)                                                                       \
-    hipLaunchKernelGGL((tree_rejection_sample_kernel<BF, ONE, FULL>), dim3((unsigned)B), dim3(kThreads), 0,    \
-                       stream, p)
+#define RESPEC_LAUNCH_TREE(KERNEL) hipLaunchKernelGGL(KERNEL, dim3((unsigned)B), dim3(kThreads), 0, stream, p)
     if (!full) {
-        if (bf) RESPEC_LAUNCH_TREE(true, false, false); else RESPEC_LAUNCH_TREE(false, false, false);
+        if (bf) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<true, false, false>));
+        else RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<false, false, false>));
+    } else if (!whole_rows) {
+        if (bf) RESPEC_LAUNCH_TREE((tree_partial_rows_kernel<true>));
+        else RESPEC_LAUNCH_TREE((tree_partial_rows_kernel<false>));
     } else if (bf) {
-        if (one) RESPEC_LAUNCH_TREE(true, true, true); else RESPEC_LAUNCH_TREE(true, false, true);
+        if (one) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<true, true, true>));
+        else RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<true, false, true>));
     } else {
-        if (one) RESPEC_LAUNCH_TREE(false, true, true); else RESPEC_LAUNCH_TREE(false, false, true);
+        if (one) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<false, true, true>));
+        else RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<false, false, true>));
     }
 #undef RESPEC_LAUNCH_TREE
     const hipError_t err = hipGetLastError();
