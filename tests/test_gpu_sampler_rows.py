@@ -83,3 +83,27 @@ def test_tree(oracle, V, gap, shift, dtype, T):
     ref = oracle_tree_sample(oracle, tb)
     tb.target_logits, tb.draft_logits = _spread(tb.target_logits, gap, shift), _spread(tb.draft_logits, gap, shift)
     compare_tree_sampler(gpu_tree_sample(tb), ref)
+
+
+# Short rows are read eight positions at a time: what lies behind a rejected position is read and must
+# not matter (10 drafts: two groups of positions)
+@pytest.mark.parametrize("dtype,V", [("bf16", 1000), ("f32", 1001), ("f32", 4096)])
+@pytest.mark.parametrize("T", [1.0, 1.3])
+def test_rows_behind_a_rejection_of_a_short_row_may_hold_anything(oracle, dtype, V, T):
+    ks = [10, 9, 8, 7, 1, 0] * 5
+    batch = synth.make_batch(_wl(V, dtype, T), device="cuda", kv_lens=[k + 1 for k in ks], k_per_seq=ks, seed=V, with_attention=False)
+    batch.draft_logits.copy_((batch.target_logits[[q for b, k in enumerate(ks) for q in range(int(batch.q_indptr[b]), int(batch.q_indptr[b]) + k)]]
+                              .float() + 0.1 * torch.randn_like(batch.draft_logits.float())).to(batch.draft_logits.dtype))
+    ref = oracle_sample(oracle, batch)
+    clean = gpu_sample(batch, workspace=None)
+    compare_sampler(clean, ref)
+    assert clean[1].max() >= 8                     # a chain that reaches the second group
+    qi = batch.q_indptr.tolist()
+    for b, k in enumerate(ks):
+        n = int(clean[1][b])
+        if n < k:
+            batch.target_logits[qi[b] + n + 1:qi[b + 1]] = float("nan")
+            batch.draft_logits[qi[b] - b + n + 1:qi[b + 1] - (b + 1)] = float("nan")
+    poisoned = gpu_sample(batch, workspace=None)
+    for x, y in zip(clean, poisoned):
+        np.testing.assert_array_equal(x, y)
