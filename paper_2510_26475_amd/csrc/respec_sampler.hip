@@ -438,12 +438,13 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
 
 // Choice and phase B.  `totals` are the n_reg region totals of the whole row in vocabulary order
 // (LDS); the regions [my_reg0, my_reg0 + kWaves) are those of `part`, this block's part of the
-// row.  Returns the token, or -1 with mine = false when another block holds the crossing, or
+// row.  SHARED: the totals are this block's weights times `scale` (and the other blocks' times
+// theirs).  Returns the token, or -1 with mine = false when another block holds the crossing, or
 // -1 with Z_out <= 0 when the row carries no mass.  Ends with a barrier.
-template <bool BF16, bool RESID, bool FULL, bool FAST, bool KEEP_SLOTS, bool PARTIAL>
+template <bool BF16, bool RESID, bool FULL, bool FAST, bool SHARED, bool PARTIAL>
 __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, const RowPart &part,
                                   const DrawNorm &nm, double u, SharedState &sh, const RowMath &p, int &near_edge,
-                                  double &Z_out, bool &mine) {
+                                  double &Z_out, bool &mine, double scale) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     const float Mp = nm.Mp, Mq = nm.Mq;
@@ -466,7 +467,7 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
         near_edge = 1;
         return -1;
     }
-    const double t = u * Z;
+    double t = u * Z;
     int rstar = -1, rlast = 0;
     double base = 0.0, prefix = 0.0;
     for (int w = 0; w < n_reg; ++w) {
@@ -487,6 +488,11 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
         return -1;
     }
     mine = true;
+    if constexpr (SHARED) {  // from here on in the units of this block's own weights
+        t /= scale;
+        base /= scale;
+        Z /= scale;
+    }
     const void *rowp = part.rowp, *rowq = part.rowq;
     const int nslots = part.nslots, Vrow = part.Vrow, tok_off = part.tok_off;
     float *tab = part.tab;
@@ -615,7 +621,7 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
     };
     // the totals of the slots of the first chunk are kept for the walk, and (when the registers
     // allow: not in the form that several work-groups share) so are the slots themselves
-    constexpr bool kKeepSlots = KEEP_SLOTS;
+    constexpr bool kKeepSlots = !SHARED;
     double slot_total[kChunk];
     u32x4 keep_p[kKeepSlots ? kChunk : 1], keep_q[kKeepSlots ? kChunk : 1];
 #pragma unroll
@@ -738,12 +744,14 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
 
 // The draw of a block that sees one part of the row: its own share of a sequence that several
 // work-groups walk together (SHARED: the region totals are exchanged, and the block that holds
-// the crossing finishes), or the whole row.
+// the crossing finishes), or the whole row.  scale: what brings the weights of this block, formed
+// against its own reference, to the scale that the blocks of a sequence share (NaN: no usable
+// reference; every block then finds Z_out NaN).
 template <bool BF16, bool RESID, bool FULL, bool SHARED, bool FAST, bool PARTIAL>
 __device__ inline int inverse_cdf_pass(const void *rowp, const void *rowq, int nslots, int Vrow, int tok_off,
                                        float Mp, double Sp, float Mq, double Sq, double u, SharedState &sh,
                                        Mailbox &mb, const SamplerParams &p, int &near_edge, double &Z_out,
-                                       bool &mine, float *tab = nullptr) {
+                                       bool &mine, float *tab = nullptr, double scale = 1.0) {
     const RowPart part{rowp, rowq, nslots, Vrow, tok_off, tab};
     const DrawNorm nm{Mp, Mq, Sp, Sq};
     draw_region_totals<BF16, RESID, FULL, FAST, PARTIAL>(part, nm, sh, p);
@@ -753,14 +761,14 @@ __device__ inline int inverse_cdf_pass(const void *rowp, const void *rowq, int n
     if constexpr (SHARED) {
         double pub[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) pub[w] = sh.wave_total[w];
+        for (int w = 0; w < kWaves; ++w) pub[w] = sh.wave_total[w] * scale;
         exchange(mb, pub, sh);
         if ((int)threadIdx.x < n_reg) sh.all_total[threadIdx.x] = sh.xchg[threadIdx.x / kWaves][threadIdx.x % kWaves];
         __syncthreads();
     }
     const double *totals = SHARED ? sh.all_total : sh.wave_total;
-    return draw_finish<BF16, RESID, FULL, FAST, !SHARED, PARTIAL>(totals, n_reg, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
-                                                         p, near_edge, Z_out, mine);
+    return draw_finish<BF16, RESID, FULL, FAST, SHARED, PARTIAL>(totals, n_reg, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
+                                                        p, near_edge, Z_out, mine, scale);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -976,7 +984,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     constexpr bool kTwoItems = SHARED && FULL;
     DrawNorm ahead{};
     int ahead_of = -1;
-    float last_Mp = -INFINITY;  // reference of the target row of the position tested last
+    float last_Mp = 0.f;  // reference of the target row of the position tested last
     const char *scan_row = tbase;  // row, reference and sum of the final inverse-CDF walk over p
     float scan_M = 0.f;
     double scan_S = 1.0;
@@ -1094,25 +1102,38 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     bool drawn = false;
     if constexpr (FULL) {
         // The bonus token's draw needs no normaliser: it compares running sums of weights with u
-        // times their total, so exp((z - M0)/T) serves for any reference M0 that keeps the
-        // weights in range: one pass over the row instead of two.  With one work-group per
-        // sequence M0 is the largest logit among the row's first 512 slots; the parts of a shared
-        // sequence need the same M0 and take the reference of the last draft's target row, which
-        // they all hold (a sequence without drafts, or whose bonus row came with the last stage,
-        // goes the ordinary way).  A total that is not a positive finite number (an outlier far
-        // above M0, a row start without any finite logit) leaves the draw to the two passes below;
-        // every part sees the same total and decides alike.
+        // times their total, so exp((z - M0)/T) serves for any reference M0 that keeps the weights in
+        // range: one pass over the row instead of two.  M0 is the largest logit among the first 512
+        // slots of the row, or of this block's part of it, so no total is small beside its largest
+        // weight.  (A reference of another row may lie far above this one: the small weights are then
+        // lost below 2^-126 while the total is still positive.)  The blocks of a shared sequence bring
+        // their fp64 totals to one scale, weights against last_Mp, which all of them hold (a sequence
+        // without drafts, or whose bonus row came with the last stage, goes the ordinary way).  A total
+        // that is not a positive number in the middle of the fp64 range (an outlier far above M0, a
+        // part that starts without any finite logit) leaves the draw to the two passes below; every
+        // block sees the same total and decides alike.
         if (!rejected && (!SHARED || (k > 0 && ahead_of != k))) {
             scan_row = tbase + (size_t)(row0 + k) * p.ld_t * esz;
-            float M0;
-            if constexpr (SHARED) M0 = last_Mp;
-            else M0 = block_max_of_row_start<BF16>(scan_row, p.V / EPV, sh);
-            if (M0 > -INFINITY && M0 < INFINITY) {  // block-uniform
+            const char *part_row = scan_row + (size_t)lo * 16;
+            float M0 = block_max_of_row_start<BF16>(part_row, PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots, sh);
+            const bool usable = M0 > -INFINITY && M0 < INFINITY;  // block-uniform
+            double scale = 1.0;
+            if constexpr (SHARED) {
+                if (usable) {
+                    // what the weights are formed with: exp2(z c_f + K) or exp2((z - M0) c)
+                    if constexpr (kFastScan) scale = exp2_f64(-(double)make_fast_norm(M0, 1.0, M0, 1.0, p).Kp - (double)last_Mp * (double)p.c_f);
+                    else scale = exp2_f64(((double)M0 - (double)last_Mp) * p.c_d);
+                } else {
+                    M0 = 0.f;
+                    scale = nslots > 0 ? (double)NAN : 1.0;  // (a part without slots has no mass)
+                }
+            }
+            if (SHARED || usable) {
                 double Z;
                 int edge = 0;
-                const int tok = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots, Vrow, tok_off,
-                                                                               M0, 1.0, M0, 1.0, u_fin, sh, mb, p, edge, Z, mine, tab);
-                if (Z > 0.0 && Z < 1.0e300) {
+                const int tok = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL>(part_row, part_row, nslots, Vrow, tok_off,
+                                                                               M0, 1.0, M0, 1.0, u_fin, sh, mb, p, edge, Z, mine, tab, scale);
+                if (Z > 1.0e-280 && Z < 1.0e280) {
                     final_token = tok;
                     flag_cdf = edge;
                     drawn = true;

@@ -439,3 +439,29 @@ def test_temperatures_on_both_sides_of_the_one_term_criterion(oracle, T):
     wl = _wl("temps", 151936, "bf16", sigma=1.0, T=T)
     _, ref, _ = _parity(oracle, _batch(wl, [3] * 20 + [0, 1, 2, 4], seed=int(100 * T)))
     assert len(set(ref[1].tolist())) >= 2
+
+
+@pytest.mark.parametrize("dtype,V", [("f32", 50257), ("f32", 49152), ("bf16", 50257), ("bf16", 49152)])
+@pytest.mark.parametrize("T", [1.0, 0.6, 0.4, 0.1])
+@pytest.mark.parametrize("split", [1, 4])
+def test_bonus_rows_at_another_level_than_the_drafts_rows(oracle, dtype, V, T, split):
+    """A constant added to a row changes no probability, so the level of the bonus token's row
+    beside the last draft's row must not matter: levels across the band in which binary32 weights
+    against the wrong row's reference lose the small ones (2^-126 is 87 T below it) and far past it,
+    above and below.  One-term (T = 1, 0.4) and two-term temperatures, whole rows and odd ones, one
+    work-group per sequence and shared ones that walk one item per stage."""
+    levels = [-400, -100, -86, -84, -82, -79, -75, -70, -60, -20, 0, 60, 86, 100, 400]
+    wl = _wl("level", V, dtype, sigma=1.0, T=T)
+    ks = [1] * (4 * len(levels))
+    batch = _batch(wl, ks, seed=int(V + 100 * T + split))
+    B = len(ks)
+    rows = batch.target_logits.float()
+    rows[1::2] += T * torch.tensor([levels[b % len(levels)] for b in range(B)], device="cuda")[:, None]
+    batch.target_logits.copy_(rows.to(batch.target_logits.dtype))
+    batch.draft_logits.copy_(batch.target_logits[0::2])  # every draft is accepted
+    batch.u_accept.mul_(0.999)
+    ref = oracle_sample(oracle, batch)
+    assert (ref[1] == 1).all()
+    with sampler_split(split), env_setting("RESPEC_SAMPLER_TWO_ITEMS", 0):
+        tally = compare_sampler(gpu_sample(batch), ref)
+    assert tally["flagged"] <= max(3, 0.25 * B), tally
