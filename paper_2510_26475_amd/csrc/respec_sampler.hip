@@ -372,8 +372,8 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
 #pragma unroll
         for (int c = 0; c < kUnroll; ++c) {
             const int slot = s0 + c * 64 + lane;
-            vp[c] = load_slot<BF16, FULL, true, !PARTIAL>(rowp, slot < end ? slot : beg, Vrow);
-            if constexpr (RESID) vq[c] = load_slot<BF16, FULL, true, !PARTIAL>(rowq, slot < end ? slot : beg, Vrow);
+            vp[c] = load_slot<BF16, FULL, true, FULL && !PARTIAL>(rowp, slot < end ? slot : beg, Vrow);
+            if constexpr (RESID) vq[c] = load_slot<BF16, FULL, true, FULL && !PARTIAL>(rowq, slot < end ? slot : beg, Vrow);
         }
     };
     if (beg < end) {  // wave-uniform
@@ -602,8 +602,8 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
                 vp[j] = load_slot_or_last<BF16>(rowp, slot, Vrow);
                 if constexpr (RESID) vq[j] = load_slot_or_last<BF16>(rowq, slot, Vrow);
             } else {
-                vp[j] = load_slot<BF16, FULL, false, !PARTIAL>(rowp, slot, Vrow);
-                if constexpr (RESID) vq[j] = load_slot<BF16, FULL, false, !PARTIAL>(rowq, slot, Vrow);
+                vp[j] = load_slot<BF16, FULL, false, FULL && !PARTIAL>(rowp, slot, Vrow);
+                if constexpr (RESID) vq[j] = load_slot<BF16, FULL, false, FULL && !PARTIAL>(rowq, slot, Vrow);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -804,7 +804,7 @@ __device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedS
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int slot = it * kBatch + u * kThreads + (int)threadIdx.x;
-            v[u] = load_slot<BF16, FULL, false, !PARTIAL>(row, it + 1 < n_iter ? slot : max(0, min(slot, nslots - 1)), V);
+            v[u] = load_slot<BF16, FULL, false, FULL && !PARTIAL>(row, it + 1 < n_iter ? slot : max(0, min(slot, nslots - 1)), V);
         }
     };
     float best = -INFINITY;
@@ -1115,7 +1115,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         if (!rejected && (!SHARED || (k > 0 && ahead_of != k))) {
             scan_row = tbase + (size_t)(row0 + k) * p.ld_t * esz;
             const char *part_row = scan_row + (size_t)lo * 16;
-            float M0 = block_max_of_row_start<BF16>(part_row, PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots, sh);
+            float M0 = block_max_of_row_start<BF16, !PARTIAL>(part_row, PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots, sh);
             const bool usable = M0 > -INFINITY && M0 < INFINITY;  // block-uniform
             double scale = 1.0;
             if constexpr (SHARED) {

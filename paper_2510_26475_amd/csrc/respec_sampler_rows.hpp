@@ -397,11 +397,11 @@ __device__ inline float slot_max(const u32x4 &v) {
 
 // The largest logit among the first kThreads of a row's nslots whole slots; every
 // thread returns the same value (-inf when none of them is finite).  Ends with a barrier.
-template <bool BF16>
+template <bool BF16, bool ALIGNED>
 __device__ inline float block_max_of_row_start(const void *row, int nslots, SharedState &sh) {
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     float m = -INFINITY;
-    if ((int)threadIdx.x < nslots) m = slot_max<BF16>(load_slot<BF16, true, false, true>(row, threadIdx.x, 0));
+    if ((int)threadIdx.x < nslots) m = slot_max<BF16>(load_slot<BF16, true, false, ALIGNED>(row, threadIdx.x, 0));
     m = wave_max(m);
     __syncthreads();  // (earlier readers of arg_val are done)
     if (lane == 0) sh.arg_val[wave] = m;

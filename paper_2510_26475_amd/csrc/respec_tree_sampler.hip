@@ -186,8 +186,8 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
 #pragma unroll
         for (int c = 0; c < kUnroll; ++c) {  // no select behind a load: the loads of a batch go out together
             const int slot = s0 + c * 64 + lane;
-            vp[c] = load_slot<BF16, FULL, false, !PARTIAL>(rowp, slot < end ? slot : beg, V);
-            if constexpr (two) vq[c] = load_slot<BF16, FULL, false, !PARTIAL>(rowq, slot < end ? slot : beg, V);
+            vp[c] = load_slot<BF16, FULL, false, FULL && !PARTIAL>(rowp, slot < end ? slot : beg, V);
+            if constexpr (two) vq[c] = load_slot<BF16, FULL, false, FULL && !PARTIAL>(rowq, slot < end ? slot : beg, V);
             else vq[c] = vp[c];
         }
     };
@@ -311,8 +311,8 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
                 vp[j] = load_slot_or_last<BF16>(rowp, slot, V);
                 if constexpr (two) vq[j] = load_slot_or_last<BF16>(rowq, slot, V);
             } else {
-                vp[j] = load_slot<BF16, FULL, false, !PARTIAL>(rowp, slot, V);
-                if constexpr (two) vq[j] = load_slot<BF16, FULL, false, !PARTIAL>(rowq, slot, V);
+                vp[j] = load_slot<BF16, FULL, false, FULL && !PARTIAL>(rowp, slot, V);
+                if constexpr (two) vq[j] = load_slot<BF16, FULL, false, FULL && !PARTIAL>(rowq, slot, V);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -564,7 +564,7 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
         // not a positive finite number sends the draw the ordinary way (normalisers first).
         bool trial = FULL && !have_norm;
         if (trial) {
-            Mp = block_max_of_row_start<BF16>(rowp, p.V / EPV, sh);
+            Mp = block_max_of_row_start<BF16, !PARTIAL>(rowp, p.V / EPV, sh);
             Sp = 1.0;
             trial = Mp > -INFINITY && Mp < INFINITY;  // block-uniform
         }

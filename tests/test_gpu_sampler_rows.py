@@ -85,6 +85,24 @@ def test_tree(oracle, V, gap, shift, dtype, T):
     compare_tree_sampler(gpu_tree_sample(tb), ref)
 
 
+# The guarded form (running references per thread) on the same rows: it too must not count on rows
+# that start on 16 bytes
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V,gap,shift", SHAPES)
+@pytest.mark.parametrize("split", [1, 2])
+def test_guarded_form(oracle, V, gap, shift, dtype, split):
+    wl = _wl(V, dtype, 1.3)
+    batch = synth.make_batch(wl, device="cuda", kv_lens=[k + 1 for k in KS], k_per_seq=KS, seed=V + split, with_attention=False)
+    parents = [synth.caterpillar_parents(2, 3), [-1, 0, 0], [-1], [-1, 0, 1, 2]] * 6
+    tb = synth.make_tree_batch(wl, parents, device="cuda", kv_lens=[len(p) for p in parents], seed=V, with_attention=False)
+    ref, tree_ref = oracle_sample(oracle, batch), oracle_tree_sample(oracle, tb)
+    for t in (batch, tb):
+        t.target_logits, t.draft_logits = _spread(t.target_logits, gap, shift), _spread(t.draft_logits, gap, shift)
+    with helpers.sampler_split(split), helpers.env_setting("RESPEC_SAMPLER_GUARDED", 1):
+        compare_sampler(gpu_sample(batch), ref)
+        compare_tree_sampler(gpu_tree_sample(tb), tree_ref)
+
+
 # Short rows are read eight positions at a time: what lies behind a rejected position is read and must
 # not matter (10 drafts: two groups of positions)
 @pytest.mark.parametrize("dtype,V", [("bf16", 1000), ("f32", 1001), ("f32", 4096)])
