@@ -1103,8 +1103,8 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     if constexpr (FULL) {
         // The bonus token's draw needs no normaliser: it compares running sums of weights with u
         // times their total, so exp((z - M0)/T) serves for any reference M0 that keeps the weights in
-        // range: one pass over the row instead of two.  M0 is the largest logit among the first 512
-        // slots of the row, or of this block's part of it, so no total is small beside its largest
+        // range: one pass over the row instead of two.  M0 is the largest logit among the first slots
+        // of the row, or of this block's part of it, so no total is small beside its largest
         // weight.  (A reference of another row may lie far above this one: the small weights are then
         // lost below 2^-126 while the total is still positive.)  The blocks of a shared sequence bring
         // their fp64 totals to one scale, weights against last_Mp, which all of them hold (a sequence
@@ -1115,7 +1115,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         if (!rejected && (!SHARED || (k > 0 && ahead_of != k))) {
             scan_row = tbase + (size_t)(row0 + k) * p.ld_t * esz;
             const char *part_row = scan_row + (size_t)lo * 16;
-            float M0 = block_max_of_row_start<BF16, !PARTIAL>(part_row, PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots, sh);
+            float M0 = block_max_of_row_start<BF16, !PARTIAL, kRefSlots<ONE_TERM>>(part_row, PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots, sh);
             const bool usable = M0 > -INFINITY && M0 < INFINITY;  // block-uniform
             double scale = 1.0;
             if constexpr (SHARED) {

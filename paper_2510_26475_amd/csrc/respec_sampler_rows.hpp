@@ -395,13 +395,20 @@ __device__ inline float slot_max(const u32x4 &v) {
     return m;
 }
 
-// The largest logit among the first kThreads of a row's nslots whole slots; every
+// The largest logit among the first kThreads x PER of a row's nslots whole slots; every
 // thread returns the same value (-inf when none of them is finite).  Ends with a barrier.
-template <bool BF16, bool ALIGNED>
+template <bool BF16, bool ALIGNED, int PER>
 __device__ inline float block_max_of_row_start(const void *row, int nslots, SharedState &sh) {
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     float m = -INFINITY;
-    if ((int)threadIdx.x < nslots) m = slot_max<BF16>(load_slot<BF16, true, false, ALIGNED>(row, threadIdx.x, 0));
+    if ((int)threadIdx.x < nslots) {
+        u32x4 v[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u)  // (slots past the row's end: its last one again)
+            v[u] = load_slot<BF16, true, false, ALIGNED>(row, min((int)threadIdx.x + u * kThreads, nslots - 1), 0);
+#pragma unroll
+        for (int u = 0; u < PER; ++u) m = fmaxf(m, slot_max<BF16>(v[u]));
+    }
     m = wave_max(m);
     __syncthreads();  // (earlier readers of arg_val are done)
     if (lane == 0) sh.arg_val[wave] = m;
@@ -412,6 +419,13 @@ __device__ inline float block_max_of_row_start(const void *row, int nslots, Shar
     __syncthreads();
     return r;
 }
+
+// Slots per thread that the one-pass draws take their reference from.  A binary32 exponent is exact to
+// 2^-24 of its own size, so a weight loses accuracy with its distance from the reference.  The forms
+// with fp64 weights look as far into the row as the normaliser pass (whose reference they would
+// otherwise have) does; the fp32 forms, whose weights carry a few 1e-7 in any case, at one slot.
+template <bool ONE_TERM>
+constexpr int kRefSlots = ONE_TERM ? 1 : kUnroll;
 
 // Fast streaming pass over a target row (and, if TWO, the matching drafter row).  The
 // reference of a wave is the maximum of the first slots it reads, not the row maximum:

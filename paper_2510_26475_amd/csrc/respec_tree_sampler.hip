@@ -564,7 +564,7 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
         // not a positive finite number sends the draw the ordinary way (normalisers first).
         bool trial = FULL && !have_norm;
         if (trial) {
-            Mp = block_max_of_row_start<BF16, !PARTIAL>(rowp, p.V / EPV, sh);
+            Mp = block_max_of_row_start<BF16, !PARTIAL, kRefSlots<ONE_TERM>>(rowp, p.V / EPV, sh);
             Sp = 1.0;
             trial = Mp > -INFINITY && Mp < INFINITY;  // block-uniform
         }

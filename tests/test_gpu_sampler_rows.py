@@ -125,3 +125,54 @@ def test_rows_behind_a_rejection_of_a_short_row_may_hold_anything(oracle, dtype,
     poisoned = gpu_sample(batch, workspace=None)
     for x, y in zip(clean, poisoned):
         np.testing.assert_array_equal(x, y)
+
+
+def _two_heavy_tokens(first, last, V, B, T, k, seed):
+    """B row blocks (k + 1 rows of V fp32 logits) whose last row holds its mass in two tokens about
+    84 T above the rest, between the indices first and last: nearly the largest distance at which a
+    weight against the rest's level is finite in binary32.  Returns (target rows, the indices, the share
+    of the first heavy token)."""
+    gen = torch.Generator().manual_seed(seed)
+    rows = torch.randn((B * (k + 1), V), generator=gen)
+    level = rows[k::k + 1].amax(1)
+    at = torch.sort(first + torch.rand((B, 2), generator=gen).mul(last - first - 1).long(), dim=1).values
+    at[:, 1] = torch.maximum(at[:, 1], at[:, 0] + 1)
+    z = (level[:, None] + T * (84.0 + torch.rand((B, 2), generator=gen))).float()
+    rows[torch.arange(k, B * (k + 1), k + 1)[:, None], at] = z
+    share = 1.0 / (1.0 + torch.exp((z[:, 1].double() - z[:, 0].double()) / float(np.float32(T))))
+    return rows, at, share.numpy()
+
+
+# A weight 121 binary orders above the reference that it is formed against has an exponent rounded to
+# 2^-18, so the edge between two such tokens can be off by 1.3e-6, more than the band that is flagged.
+# Uniforms just outside the band show it (in 1 to 2 % of the rows).  The heavy tokens lie behind the
+# first 512 slots and within the first 2048 (1024 in a part of a shared row).
+@pytest.mark.parametrize("T", [0.85, 1.3])
+@pytest.mark.parametrize("form", ["one work-group", "shared", "per sequence", "tree"])
+def test_draws_with_64_bit_weights_look_as_far_for_their_reference_as_a_normaliser_pass(oracle, form, T):
+    V, B, k = (8192, 128, 1) if form == "shared" else (8192, 1024, 0)
+    rows, _, share = _two_heavy_tokens(4 * 512, 4 * (1024 if k else 2048), V, B, T, k, seed=int(100 * T))
+    batch = synth.make_batch(_wl(V, "f32", T), device="cuda", kv_lens=[k + 1] * B, k_per_seq=[k] * B, seed=1, with_attention=False)
+    batch.target_logits.copy_(rows)
+    if k:
+        batch.draft_logits.copy_(rows[0::2])
+        batch.u_accept.mul_(0.999)
+    batch.u_final.copy_(torch.from_numpy((share + np.where(np.arange(B) % 2, 1.05e-6, -1.05e-6)).astype(np.float32)))
+    ref = oracle_sample(oracle, batch)
+    assert (ref[2] != 0).sum() <= B // 8
+    if form == "tree":
+        tb = synth.make_tree_batch(_wl(V, "f32", T), [[-1]] * B, device="cuda", kv_lens=[1] * B, seed=1, with_attention=False)
+        tb.target_logits.copy_(rows)
+        tb.u_final.copy_(batch.u_final)
+        toks, _, n, flags = gpu_tree_sample(tb)
+        compare_sampler((toks, n, flags), ref)
+    elif form == "per sequence":
+        toks = torch.full((B, 1), -7, dtype=torch.int32, device="cuda")
+        n, flags = (torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+        binding.respec_rejection_sample_per_seq(batch.target_logits, None, None, batch.q_indptr, None, batch.u_final,
+                                                torch.full((B,), T, device="cuda"), toks, n, flags, 0)
+        torch.cuda.synchronize()
+        compare_sampler((toks.cpu().numpy(), n.cpu().numpy(), flags.cpu().numpy()), ref)
+    else:
+        with helpers.sampler_split(2 if form == "shared" else 1), helpers.env_setting("RESPEC_SAMPLER_TWO_ITEMS", 0):
+            compare_sampler(gpu_sample(batch), ref)
