@@ -432,7 +432,8 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
             for (int j = 0; j < EPV; ++j) lane_sum += w[j];
         }
     }
-    const double region_total = wave_sum(lane_sum);
+    double region_total = wave_sum(lane_sum);
+    if (PARTIAL && region_total > kFastMost) region_total = (double)INFINITY;
     if (lane == 0) sh.wave_total[wave] = region_total;
 }
 

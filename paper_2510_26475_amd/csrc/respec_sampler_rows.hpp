@@ -420,6 +420,12 @@ __device__ inline float block_max_of_row_start(const void *row, int nslots, Shar
     return r;
 }
 
+// The guarded pass moves a reference once an element lies 40 binary orders above it (RowMath::gap). The
+// fast passes over rows that are not whole aligned slots leave to it what it would have handled that
+// way: a thread's or a region's sum above this counts as an overflow.  (Without the bound elements up
+// to 127 orders above their reference were summed, with exponents rounded to 2^-18 instead of 2^-20.)
+constexpr double kFastMost = 0x1p40;
+
 // Slots per thread that the one-pass draws take their reference from.  A binary32 exponent is exact to
 // 2^-24 of its own size, so a weight loses accuracy with its distance from the reference.  The forms
 // with fp64 weights look as far into the row as the normaliser pass (whose reference they would
@@ -537,6 +543,10 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
     for (int j = 0; j < EPV; ++j) {
         sp += (double)accp[j];
         sq += (double)accq[j];
+    }
+    if constexpr (PARTIAL) {
+        if (sp > kFastMost) sp = (double)INFINITY;
+        if (TWO && sq > kFastMost) sq = (double)INFINITY;
     }
     // (ONE_TERM: exp2(z c + K) = exp2((z - ref) c) * exp2(K + ref c); the combine undoes the residue)
     block_combine_fast<TWO, ONE_TERM>(refp, sp, refq, sq, sh, parity, p, Mp, Sp, Mq, Sq);

@@ -239,7 +239,8 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
             for (int j = 0; j < EPV; ++j) lane_sum += w[j];
         }
     }
-    const double region_total = wave_sum(lane_sum);
+    double region_total = wave_sum(lane_sum);
+    if (PARTIAL && region_total > kFastMost) region_total = (double)INFINITY;
     if (lane == 0) sh.wave_total[wave] = region_total;
     __syncthreads();
     double Z = 0.0;

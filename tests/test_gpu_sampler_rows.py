@@ -143,6 +143,31 @@ def _two_heavy_tokens(first, last, V, B, T, k, seed):
     return rows, at, share.numpy()
 
 
+def _compare_forms(form, batch, ref):
+    """The batch through one form of the samplers (a tree of root nodes for "tree") against the oracle."""
+    B, k, T, V = len(batch.k_per_seq), batch.max_k, batch.wl.temperature, batch.wl.V
+    if form == "tree":
+        tb = synth.make_tree_batch(batch.wl, [list(range(-1, k))] * B, device="cuda", kv_lens=[k + 1] * B, seed=1, with_attention=False)
+        tb.target_logits.copy_(batch.target_logits)
+        tb.u_final.copy_(batch.u_final)
+        if k:  # (k = 1: the root's row pair, the leaf's target row)
+            tb.draft_logits[0::2] = batch.draft_logits
+            tb.node_tokens[1::2] = batch.draft_tokens
+            tb.u_accept[1::2] = batch.u_accept
+        toks, _, n, flags = gpu_tree_sample(tb)
+        compare_sampler((toks, n, flags), ref)
+    elif form == "per sequence":
+        toks = torch.full((B, k + 1), -7, dtype=torch.int32, device="cuda")
+        n, flags = (torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
+        binding.respec_rejection_sample_per_seq(batch.target_logits, batch.draft_logits, batch.draft_tokens, batch.q_indptr,
+                                                batch.u_accept, batch.u_final, torch.full((B,), T, device="cuda"), toks, n, flags, k)
+        torch.cuda.synchronize()
+        compare_sampler((toks.cpu().numpy(), n.cpu().numpy(), flags.cpu().numpy()), ref)
+    else:
+        with helpers.sampler_split(2 if form == "shared" else 1), helpers.env_setting("RESPEC_SAMPLER_TWO_ITEMS", 0):
+            compare_sampler(gpu_sample(batch), ref)
+
+
 # A weight 121 binary orders above the reference that it is formed against has an exponent rounded to
 # 2^-18, so the edge between two such tokens can be off by 1.3e-6, more than the band that is flagged.
 # Uniforms just outside the band show it (in 1 to 2 % of the rows).  The heavy tokens lie behind the
@@ -160,19 +185,39 @@ def test_draws_with_64_bit_weights_look_as_far_for_their_reference_as_a_normalis
     batch.u_final.copy_(torch.from_numpy((share + np.where(np.arange(B) % 2, 1.05e-6, -1.05e-6)).astype(np.float32)))
     ref = oracle_sample(oracle, batch)
     assert (ref[2] != 0).sum() <= B // 8
-    if form == "tree":
-        tb = synth.make_tree_batch(_wl(V, "f32", T), [[-1]] * B, device="cuda", kv_lens=[1] * B, seed=1, with_attention=False)
-        tb.target_logits.copy_(rows)
-        tb.u_final.copy_(batch.u_final)
-        toks, _, n, flags = gpu_tree_sample(tb)
-        compare_sampler((toks, n, flags), ref)
-    elif form == "per sequence":
-        toks = torch.full((B, 1), -7, dtype=torch.int32, device="cuda")
-        n, flags = (torch.full((B,), -7, dtype=torch.int32, device="cuda") for _ in range(2))
-        binding.respec_rejection_sample_per_seq(batch.target_logits, None, None, batch.q_indptr, None, batch.u_final,
-                                                torch.full((B,), T, device="cuda"), toks, n, flags, 0)
-        torch.cuda.synchronize()
-        compare_sampler((toks.cpu().numpy(), n.cpu().numpy(), flags.cpu().numpy()), ref)
+    _compare_forms(form, batch, ref)
+
+
+# The same distance in rows that are not whole aligned slots, heavy tokens anywhere: these rows had the
+# guarded pass, which moves its reference, and must not do worse in the fast ones.  Draws at the edge
+# between the two tokens, and acceptance tests of the first of them (its share is exact here, the sum
+# it is divided by is what can be off).
+@pytest.mark.parametrize("T", [0.6, 1.3])
+@pytest.mark.parametrize("what", ["draw", "accept"])
+@pytest.mark.parametrize("form", ["one work-group", "shared", "per sequence", "tree"])
+def test_heavy_tokens_far_behind_the_start_of_an_odd_row(oracle, form, what, T):
+    V, B, k = 50257, 128, 1
+    rows, at, share = _two_heavy_tokens(4 * 2100, 4 * 6200, V, B, T, k, seed=int(100 * T))
+    side = np.where(np.arange(B) % 2, 1.05e-6, -1.05e-6)
+    wl = _wl(V, "f32", T)
+    batch = synth.make_batch(wl, device="cuda", kv_lens=[k + 1] * B, k_per_seq=[k] * B, seed=1, with_attention=False)
+    batch.target_logits.copy_(rows)
+    if what == "draw":
+        batch.draft_logits.copy_(rows[0::2])  # every draft is accepted, the heavy row is the bonus row
+        batch.u_accept.mul_(0.999)
+        batch.u_final.copy_(torch.from_numpy((share + side).astype(np.float32)))
     else:
-        with helpers.sampler_split(2 if form == "shared" else 1), helpers.env_setting("RESPEC_SAMPLER_TWO_ITEMS", 0):
-            compare_sampler(gpu_sample(batch), ref)
+        batch.target_logits.copy_(rows.view(B, 2, V).flip(1).reshape(2 * B, V))  # the heavy row is the draft's
+        q = torch.randn((B, V), generator=torch.Generator().manual_seed(3))
+        ar, x, T64 = torch.arange(B), at[:, 0], float(np.float32(T))
+        rest = torch.exp(q.double() / T64).sum(1) - torch.exp(q[ar, x].double() / T64)
+        q[ar, x] = (T64 * torch.log(3.0 * rest)).float()  # q(x) about 0.75
+        qx = 1.0 / (1.0 + rest * torch.exp(-q[ar, x].double() / T64)).numpy()
+        batch.draft_logits.copy_(q)
+        batch.draft_tokens.copy_(x.to(torch.int32))
+        batch.u_accept.copy_(torch.from_numpy((share / qx + side).astype(np.float32)))
+    ref = oracle_sample(oracle, batch)
+    assert (ref[2] != 0).sum() <= B // 8
+    if what == "accept":
+        assert B // 5 < ref[1].sum() < B  # (uniforms above 1 among them: never accepted)
+    _compare_forms(form, batch, ref)
