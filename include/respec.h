@@ -309,7 +309,7 @@ size_t respec_rejection_sample_workspace_bytes(int32_t B, int32_t total_q, int32
  * sum exceeds u_final[b]*Z.  Rows after the first rejection are never used, but some
  * may have been read ahead of the test: with a workspace (sequences shared by several
  * work-groups) the row pair right behind a rejected position, and with or without one, in
- * vocabularies of up to 1024 16-byte pieces, up to seven row pairs behind it.  Those rows have
+ * vocabularies of up to 512 16-byte pieces, up to seven row pairs behind it.  Those rows have
  * to be readable memory of the logits buffers, which they are by the layout above, but may
  * hold anything.
  *

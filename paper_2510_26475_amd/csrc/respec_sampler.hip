@@ -996,9 +996,8 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     };
     // Short rows: a position's chain of loads, reductions and barriers takes 3 us whatever the row's
     // length, so eight positions are taken at a time, one per wave, rows behind a rejected position
-    // read for nothing (never used).  Up to kShortSlots a wave's walk over a row pair costs less
-    // than the block's passes it replaces (B = 4, k = 4, V = 1024 fp32: kernel 17.2 -> 10.8 us).
-    // (An instantiation of its own: tested at run time it cost the long rows 1-2 %.)
+    // read for nothing (never used).  (An instantiation of its own: tested at run time it cost the
+    // long rows 1-2 %.)  Where the line lies stands at the launch.
     static_assert(!SHORT || !SHARED, "short rows are not shared");
     for (int i = 0; i < k; ++i) {
         const char *rowp = tbase + (size_t)(row0 + i) * p.ld_t * esz;
@@ -1012,16 +1011,15 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                     const int x = max(0, min(p.draft_tokens[drow0 + i + wave], p.V - 1));
                     const float zpx = logit_at<BF16>(rp, x), zqx = logit_at<BF16>(rq, x);
                     const double u = (double)p.u_accept[drow0 + i + wave];
-                    float Mp, Mq;
-                    double Sp, Sq;
-                    wave_row_stats<BF16>(rp, nslots, Vrow, p, Mp, Sp);
-                    wave_row_stats<BF16>(rq, nslots, Vrow, p, Mq, Sq);
-                    const double rho = ratio(zpx, zqx, Mp, Sp, Mq, Sq);
+                    float M[2];
+                    double S[2];
+                    wave_row_pair_stats<BF16>(rp, rq, nslots, Vrow, p, M, S);
+                    const double rho = ratio(zpx, zqx, M[0], S[0], M[1], S[1]);
                     if ((threadIdx.x & 63) == 0) {
-                        sh.pos_m[0][wave] = Mp;
-                        sh.pos_m[1][wave] = Mq;
-                        sh.pos_s[0][wave] = Sp;
-                        sh.pos_s[1][wave] = Sq;
+                        sh.pos_m[0][wave] = M[0];
+                        sh.pos_m[1][wave] = M[1];
+                        sh.pos_s[0][wave] = S[0];
+                        sh.pos_s[1][wave] = S[1];
                         sh.pos_rho[wave] = rho;
                         sh.pos_u[wave] = u;
                         sh.pos_x[wave] = x;
@@ -1344,7 +1342,13 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         }                                                                                                          \
         hipLaunchKernelGGL(KERNEL, dim3((unsigned)B), dim3(kThreads), smem, stream, p);                            \
     } while (0)
-    const bool short_rows = full && split == 1 && max_k > 0 && ((int64_t)V + epv - 1) / epv <= kShortSlots;
+    // Short rows eight positions at a time (long form / this one, us per call, fp32, k = 4 unless said):
+    // V = 1024, B = 4 17.4 / 10.1, B = 512 34.3 / 19.5; V = 2048, B = 4 18.1 / 11.5, B = 512 35.1 / 23.8.
+    // It takes the same time however early the chains end, so it loses where every sequence of the
+    // batch rejects its first draft (V = 1024, B = 4 8.9 / 9.4, V = 2048 9.6 / 10.8; not at B = 512, where
+    // some sequence goes on: 24.2 / 23.2), with a single draft (V = 2048 9.5 / 10.6) and at 1024 slots
+    // (V = 4096, B = 2048 128 / 135, drafts rarely accepted 87 / 133).
+    const bool short_rows = full && split == 1 && max_k > 1 && ((int64_t)V + epv - 1) / epv <= kShortSlots;
     if (short_rows && bf) {
         if (one) RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<true, true>));
         else RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<true, false>));

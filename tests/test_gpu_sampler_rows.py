@@ -103,9 +103,9 @@ def test_guarded_form(oracle, V, gap, shift, dtype, split):
         compare_tree_sampler(gpu_tree_sample(tb), tree_ref)
 
 
-# Short rows are read eight positions at a time: what lies behind a rejected position is read and must
+# Short rows are taken eight positions at a time: what lies behind a rejected position is read and must
 # not matter (10 drafts: two groups of positions)
-@pytest.mark.parametrize("dtype,V", [("bf16", 1000), ("f32", 1001), ("f32", 4096)])
+@pytest.mark.parametrize("dtype,V", [("bf16", 1000), ("f32", 1001), ("f32", 2048), ("f32", 4096)])
 @pytest.mark.parametrize("T", [1.0, 1.3])
 def test_rows_behind_a_rejection_of_a_short_row_may_hold_anything(oracle, dtype, V, T):
     ks = [10, 9, 8, 7, 1, 0] * 5
@@ -221,3 +221,32 @@ def test_heavy_tokens_far_behind_the_start_of_an_odd_row(oracle, form, what, T):
     if what == "accept":
         assert B // 5 < ref[1].sum() < B  # (uniforms above 1 among them: never accepted)
     _compare_forms(form, batch, ref)
+
+
+# Short rows are summed by one wave, long ones by the block; neither may be the less exact one.  The
+# acceptance test is taken in 64 bits, so uniforms one binary32 step from the ratio show the error of
+# the normalisers: their sums over 2048 elements are good to about 3e-9 (exp2's last bit, averaged over
+# the heavy tokens), so at relative distances of 1.5e-8 and more (three deviations of two such sums)
+# less than one in a hundred falls on the wrong side; the block's sums put up to 1.7 % there, binary32
+# accumulators of up to eight terms per lane 3 to 9 %.
+@pytest.mark.parametrize("dtype,V", [("f32", 2048), ("f32", 1999), ("bf16", 4096)])
+@pytest.mark.parametrize("T", [1.0, 1.3])
+def test_normalisers_of_short_rows_are_as_exact_as_those_of_long_ones(dtype, V, T):
+    B, k, T64 = 2048, 2, float(np.float32(T))
+    batch = synth.make_batch(_wl(V, dtype, T), device="cuda", kv_lens=[k + 1] * B, k_per_seq=[k] * B, seed=V, with_attention=False)
+    zp, zq = batch.target_logits[0::3].double().cpu() / T64, batch.draft_logits[0::2].double().cpu() / T64
+    ratio = torch.exp((zp - zp.logsumexp(1, keepdim=True)) - (zq - zq.logsumexp(1, keepdim=True)))
+    x = ((ratio > 0.5) & (ratio < 1.0)).int().argmax(1)
+    rho = ratio[torch.arange(B), x].numpy()
+    u = rho.astype(np.float32)
+    above = np.arange(B) % 2 == 1
+    wrong_side = (u.astype(np.float64) > rho) != above
+    u = np.where(wrong_side, np.nextafter(u, np.where(above, np.float32(2), np.float32(0)), dtype=np.float32), u)
+    batch.draft_tokens[0::2] = x.to(torch.int32).cuda()
+    batch.u_accept[0::2] = torch.from_numpy(u).cuda()
+    n = gpu_sample(batch, workspace=None)[1]
+    far = (np.abs(u.astype(np.float64) - rho) >= 1.5e-8 * rho) & (rho > 0.5) & (rho < 1.0)
+    assert far.sum() > B // 2
+    wrong = ((n > 0) == above) & far
+    print(f"{wrong.sum()} of {far.sum()} on the wrong side")
+    assert wrong.sum() <= 0.01 * far.sum()
