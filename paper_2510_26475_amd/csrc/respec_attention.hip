@@ -1797,7 +1797,7 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     long W = kn.get(&Knobs::attn_wgs, 0);
     if (W <= 0) {
         W = (long)streams * compute_units() / col_blocks;
-        const int64_t tile_bound = (int64_t)B * ((max_kv_len + kTileKeys - 1) / kTileKeys) * Hkv;
+        const int64_t tile_bound = (int64_t)B * (((int64_t)max_kv_len + kTileKeys - 1) / kTileKeys) * Hkv;  // (a caller without a bound passes the largest int32)
         const int64_t most = ((tile_bound + 1) / 2 + streams - 1) / streams * streams;
         if (W > most) W = (long)most;
     }

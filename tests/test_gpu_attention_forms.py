@@ -111,3 +111,22 @@ def test_paged_and_trees_are_bit_equal_to_contiguous(form, page_size):
             outs.append(out)
     assert torch.isfinite(outs[0].float()).all()
     assert torch.equal(outs[0], outs[1])
+
+
+# A caller without a bound on the lengths passes the largest int32: the same split, the same bits (the
+# combine kernel's form follows the bound and is held)
+def test_no_bound_on_the_lengths(oracle):
+    batch = synth.make_batch(_wl(28, 4, 128), device="cuda", kv_lens=[4096, 3000, 4095, 31, 2048, 4000, 4096, 3500],
+                             k_per_seq=[0] * 8, seed=4, with_logits=False)
+    outs = []
+    with env_setting("RESPEC_ATTN_COMBINE", 1):
+        for bound in (4096, 2 ** 31 - 1):
+            out = torch.full_like(batch.q, float("nan"))
+            ws = torch.empty(binding.respec_verify_attention_workspace_bytes(
+                8, batch.total_q, batch.total_kv, 1, bound, 28, 4, 128, binding.RESPEC_BF16), dtype=torch.uint8, device="cuda")
+            binding.respec_verify_attention(batch.q, batch.k_cache, batch.v_cache, batch.q_indptr, batch.kv_indptr, out, None,
+                                            1, bound, 0.088, ws)
+            torch.cuda.synchronize()
+            outs.append(out)
+    assert torch.isfinite(outs[0].float()).all()
+    assert torch.equal(outs[0], outs[1])
