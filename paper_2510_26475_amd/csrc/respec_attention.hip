@@ -489,8 +489,10 @@ __device__ inline void wait_at_least(LdsCounter flag, uint32_t need, bool &alive
 
 // LDS of one form of the kernel.  Eight consumers beside the four producers leave a wave 168
 // registers; two column tiles at D = 128 do not fit with their query rows (32 registers), which
-// then live in LDS, in the room of every producer's second slot: the range's tiles still
-// alternate between its producers' slots.
+// then live in LDS, in the room of every producer's second slot.  A range of four consumers has two
+// producers, whose slots alternate; a range of two has one, whose next tiles wait in its registers
+// until the slot is free (k = 9, B = 512 at the 14B shape 826 us per call; 860 with two slots, query
+// rows in registers and one consumer per SIMD).
 template <int D, int NT, int NC>
 struct Bf16Form {
     using C = Bf16Cfg<D>;
@@ -1577,12 +1579,9 @@ hipError_t launch_bf16_nt(int nt, int cw, int nc, const AttnParams &p, dim3 grid
     if (cw == 4 && nc == 4) return launch_bf16<&attn_bf16_small_kernel<D, uint16_t>, Bf16Form<D, 1, 4>, 4>(p, grid, stream);
     if (cw == 4) return nt <= 4 ? RESPEC_FORM(1, 4) : RESPEC_FORM(2, 4);
     if (cw == 2) return nt <= 2 ? RESPEC_FORM(1, 2) : RESPEC_FORM(2, 2);
-    switch (nt) {
-        case 1: return RESPEC_FORM(1, 1);
-        case 2: return RESPEC_FORM(2, 1);
-        case 3: return RESPEC_FORM(3, 1);
-        default: return RESPEC_FORM(4, 1);
-    }
+    if constexpr (D == 128)
+        if (nt == 3) return RESPEC_FORM(3, 1);
+    return RESPEC_FORM(1, 1);
 }
 
 }  // namespace
@@ -1744,46 +1743,49 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     }
 
     // The form of the main kernel: consumers that share a range (cw, each with its own column
-    // tiles), consumers of a work-group (nc) and, from them, the split.  Times are per call, main
-    // and combine kernel, by rocprofv3.
+    // tiles), consumers of a work-group (nc) and, from them, the split.  Times are us per call, main and
+    // combine kernel, medians over calls in turn (lengths 512 to 4096; they scatter by 1-2 %); "tiles"
+    // are those per consumer of the device.
     // One column tile: a range per consumer; bound by HBM.
-    // Two tiles: two consumers per range, eight per work-group (two per SIMD hide each other's
-    // dependent phases): 66.5 us against 69.1 us with two tiles in one consumer at B = 64, k = 3 and
-    // the 7B shape, 241.8 / 242.7 us at B = 256; with 96 or more tiles per consumer of the device
-    // HBM is all that counts and the eight pollers cost more than they give (k = 4, B = 512 at the
-    // 14B shape 922 / 918 us).
-    // Three and four tiles: four consumers per range, eight per work-group (k = 4 at the 3B shape, 40
-    // columns, B = 256: 118.7 us, 128.3 with two, 138.5 with one; k = 5 and 8 at the 7B shape 261 and
-    // 270 us, 265 and 275 with two).  But that form's two ranges read two neighbouring heads of a
-    // cache row at a time where the others read four, which shows when a row is 2 KiB or more and
-    // HBM is the bound: k = 7, B = 512 at the 14B shape 980 us, 963 with one consumer per range.
+    // Two tiles: two consumers per range, eight per work-group (two per SIMD hide each other's dependent
+    // phases; one consumer per range with both tiles / two): B = 8, 64, 256, 512 at the 7B shape, k = 3,
+    // 31.1 / 25.0, 67.2 / 63.7, 219 / 217, 405 / 405; B = 512 at the 14B shape, k = 4, 785 / 782; B = 768 at the
+    // 3B shape, k = 3, 318 / 312, and with heads of 64 167 / 163.  With fewer than two tiles four
+    // consumers of one tile each share a range, four per work-group: a quarter of the ranges and of the
+    // partials to fold (two consumers / four: 24.8 / 23.4 at B = 6, 21.8 / 18.2 at B = 2, 7B; 19.5 / 18.1 at
+    // B = 8, 3B with heads of 64; from two tiles on 28.1 / 28.9 at B = 12, 7B; 29.7 / 32.0 at B = 32, 3B).
+    // Three and four tiles: four consumers per range, eight per work-group (one, two and four consumers
+    // per range: k = 4, B = 256 and 768 at the 3B shape 135, 133, 124 and 336, 331, 318; k = 5, B = 256 at the
+    // 7B shape 239, 237, 233; k = 7, B = 64 at the 14B shape 125, 121, 117).  But that form's two ranges
+    // read two neighbouring heads of a cache row at a time where the others read four, which shows with
+    // eight KV heads or more and a batch that HBM bounds.  Heads of 64 from 32 tiles on (19 tiles 48.6, 48.1
+    // with two and four, 34 tiles 72.0, 73.7, 146 tiles 235, 250; one, two and four, 45 columns, 146 tiles
+    // 234, 232, 246; with two KV heads, 109 tiles, 178, 174, 171).  Heads of 128 from 64 on (14B shape; k = 7:
+    // 52 tiles 179, 176, 171, 71 tiles 226, 224, 224, 288 tiles 806, 815, 824; k = 10: 34 tiles -, 126, 122,
+    // 71 tiles -, 227, 230, 146 tiles -, 437, 443): three tiles then in one consumer, four in two.
     // More than 64 columns: blocks of 128, four consumers of 32 columns per range, K and V read once
-    // per block (91 columns, B = 256 at the 7B shape: 306 us against 410 us with four consumers per
+    // per block (91 columns, B = 256 at the 7B shape: 272 us against 380 us with four consumers per
     // work-group and the longer loop).
-    // Small batches: with fewer than four tiles per consumer of the device two tiles are spread
-    // over four consumers as well (a quarter of the ranges: a quarter of the partials to fold), and
-    // with fewer than two four consumers per work-group do (half of the ranges again: B = 8, k = 4
-    // at the 3B shape 20.5 us per call against 24.0 us; from two tiles on the eight are ahead,
-    // 22.7 us against 24.1 us at B = 8 and the 7B shape).
     // (cached tokens: the host-side total, for a paged cache what its page-table entries can hold)
     const Knobs kn = knobs();
     const int64_t kv_tokens = paged ? (int64_t)pg.table_len * pg.page_size : total_kv;
     const int64_t tiles = (kv_tokens / kTileKeys + B) * (int64_t)Hkv;  // of all (head, sequence) pairs, about
     const int64_t tiles_per_consumer = tiles / ((int64_t)kProducers * compute_units());
     const long quad_env = kn.get(&Knobs::attn_quad, 1);  // 0: never, 2: always four consumers per range
-    const long wide = kn.get(&Knobs::attn_wide, -1);     // 0 / 1: one / two consumers per range up to 64 columns
+    const long wide = kn.get(&Knobs::attn_wide, -1);     // 0 / 1: one (three tiles, D = 128) / two consumers per range up to 64 columns
     const bool quad = M > kMaxColsPerBlock && quad_env != 0;
     const int block_cols = quad ? 2 * kMaxColsPerBlock : kMaxColsPerBlock;
     const int col_blocks = (M + block_cols - 1) / block_cols;
     const int cols = col_blocks == 1 ? M : kMaxColsPerBlock;
     const int nt = quad ? 8 : (cols + kColTile - 1) / kColTile;  // column tiles of a block
-    const bool wide_rows = (int64_t)Hkv * D * 2 >= 2048 && tiles_per_consumer >= 48;
+    const bool many_heads = Hkv >= 8 && tiles_per_consumer >= (D == 64 ? 32 : 64);
+    const bool one = nt == 1 || (nt == 3 && D == 128 && wide != 1 && (wide == 0 || many_heads));
     int cw;
     if (quad || (quad_env == 2 && nt >= 2 && M <= kMaxColsPerBlock)) cw = 4;
-    else if (nt == 1 || wide == 0) cw = 1;
-    else if (wide > 0 || quad_env == 0 || M > kMaxColsPerBlock) cw = 2;
-    else if (nt == 2) cw = tiles_per_consumer < 4 ? 4 : tiles_per_consumer < 96 ? 2 : 1;
-    else cw = !wide_rows ? 4 : nt == 3 ? 1 : 2;
+    else if (one) cw = 1;
+    else if (wide >= 0 || quad_env == 0 || M > kMaxColsPerBlock) cw = 2;
+    else if (nt == 2) cw = tiles_per_consumer < 2 ? 4 : 2;
+    else cw = many_heads ? 2 : 4;
     const long nc_env = kn.get(&Knobs::attn_consumers, 0);  // 4 / 8: the narrow four-way form's consumers
     const int nc = cw == 1 ? 4 : cw == 4 && nt <= 4 && (nc_env ? nc_env == 4 : tiles_per_consumer < 2) ? 4 : 8;
     const int streams = nc / cw;  // ranges per work-group

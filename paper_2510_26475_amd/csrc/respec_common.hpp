@@ -30,7 +30,7 @@ struct Knobs {
     static constexpr long kUnset = -0x7fffffffL;
     long attn_wgs;          // RESPEC_ATTN_WGS: ranges the attention's tile lists are split over
     long attn_head_major;   // RESPEC_ATTN_HEAD_MAJOR: one head-major tile list
-    long attn_wide;         // RESPEC_ATTN_WIDE: 0/1 always one or two consumer waves per range (2-4 column tiles)
+    long attn_wide;         // RESPEC_ATTN_WIDE: 0/1 one (three column tiles at D = 128) or two consumer waves per range (2-4 column tiles)
     long attn_quad;         // RESPEC_ATTN_QUAD: 0/1/2 four consumers per range never / by rule / also narrow blocks
     long attn_inline;       // RESPEC_ATTN_INLINE: 0 = the set-up kernel also for small batches
     long attn_consumers;    // RESPEC_ATTN_CONSUMERS: 4/8 consumer waves per work-group of the four-way form up to 64 columns
