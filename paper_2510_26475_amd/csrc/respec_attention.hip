@@ -24,6 +24,7 @@
 // case), one work-group per (sequence, query head, query row).
 #include "respec_common.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -1766,9 +1767,11 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     // More than 64 columns: blocks of 128, four consumers of 32 columns per range, K and V read once
     // per block (91 columns, B = 256 at the 7B shape: 272 us against 380 us with four consumers per
     // work-group and the longer loop).
-    // (cached tokens: the host-side total, for a paged cache what its page-table entries can hold)
+    // (cached tokens: the host-side total, for a paged cache what its page-table entries can hold, in
+    // either case no more than the longest length allows: a table with room to grow takes the form of the
+    // tokens it may hold, not of its room)
     const Knobs kn = knobs();
-    const int64_t kv_tokens = paged ? (int64_t)pg.table_len * pg.page_size : total_kv;
+    const int64_t kv_tokens = std::min(paged ? (int64_t)pg.table_len * pg.page_size : total_kv, (int64_t)B * max_kv_len);
     const int64_t tiles = (kv_tokens / kTileKeys + B) * (int64_t)Hkv;  // of all (head, sequence) pairs, about
     const int64_t tiles_per_consumer = tiles / ((int64_t)kProducers * compute_units());
     const long quad_env = kn.get(&Knobs::attn_quad, 1);  // 0: never, 2: always four consumers per range
@@ -1792,7 +1795,7 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     // the split width: one range per consumer (or group of consumers) of the device
     // (RESPEC_ATTN_WGS overrides it, for tests and sweeps)
     // A range of a tiny batch gets two tiles at least, were all sequences as long as the longest may
-    // be (a bound that the contiguous and the paged entry point share, so that both split alike): the
+    // be (a bound that the contiguous and the paged entry point share): the
     // partials that the combine kernel folds halve with the ranges, and a second tile takes 0.5 us (2
     // sequences of 2300 tokens: k = 0 at the 3B shape 21.7 us per call with 1024 ranges, 16.3 us with
     // 128; k = 6, 4 query heads of 64, 17.0 us with 256, 14.6 with 128)

@@ -6,8 +6,8 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import (attn_wgs, gpu_attention, gpu_paged_attention, gpu_tree_attention, gpu_tree_sample,
-                     oracle_paged_attention, oracle_tree_sample)
+from helpers import (attn_wgs, check_bf16_attention_rows, gpu_attention, gpu_paged_attention, gpu_tree_attention,
+                     gpu_tree_sample, oracle_attention, oracle_paged_attention, oracle_tree_sample)
 from paper_2510_26475_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
@@ -229,6 +229,24 @@ def test_next_layer_on_a_paged_cache_is_bit_equal_to_a_full_call(oracle):
         pk.page_indptr.cpu().numpy(), pk.page_table.cpu().numpy(), pk.kv_len.cpu().numpy(), wl.Hq, wl.Hkv, wl.D,
         float(np.float32(1.0 / math.sqrt(wl.D))), oracle.BF16, tree_mask=None, want_lse=True, n_threads=0)
     _check(next2[0], next2[1], ref, ref_lse, "bf16")
+
+
+# The form of the attention kernel follows the cached tokens; a page table with room to grow must not
+# count as a larger batch.  Equal lengths: the longest length bounds both entry points alike, and the
+# results are the same bits.  Ragged ones may take another form: the oracle's bounds.
+@pytest.mark.parametrize("lens", [[2304] * 8, [2304, 40, 700, 1500, 9, 333, 64, 2000]])
+def test_pages_in_reserve(oracle, lens):
+    wl = synth.Workload("reserve", B=0, k=0, Hq=16, Hkv=2, D=128, V=8, dtype="bf16", len_dist="uniform", len_lo=1, len_hi=1)
+    batch = synth.make_batch(wl, device="cuda", kv_lens=lens, k_per_seq=[4] * 8, seed=6, with_logits=False)
+    outs = []
+    for reserve in (0, 400):
+        pk = synth.paginate(batch.k_cache, batch.v_cache, lens, 16, seed=2, extra_pages_per_seq=reserve)
+        outs.append(gpu_paged_attention(batch, pk)[0])
+    ref, _ = oracle_attention(oracle, batch)
+    for out in outs:
+        check_bf16_attention_rows(out.double().cpu().numpy(), ref)
+    if len(set(lens)) == 1:
+        assert torch.equal(gpu_attention(batch)[0], outs[0]) and torch.equal(outs[0], outs[1])
 
 
 def test_bad_arguments_are_rejected_before_any_launch():
