@@ -88,13 +88,13 @@ def test_identical_drafter_accepts_everything(oracle):
 
 
 @pytest.mark.parametrize("env", ["RESPEC_SAMPLER_GUARDED", "RESPEC_SAMPLER_TWO_TERM", "RESPEC_SAMPLER_NO_TABLE"])
-def test_alternative_normaliser_passes_agree(oracle, env, monkeypatch):
+def test_alternative_normaliser_passes_agree(oracle, env):
     # the guarded pass (running per-thread references) and the two-term exponent are the paths
-    # taken for unaligned rows / temperatures whose log2(e)/T rounds badly; without the table of
+    # taken for rows with outliers / temperatures whose log2(e)/T rounds badly; without the table of
     # slot totals the final draw reads its region again (rows too wide for LDS); force them here
-    monkeypatch.setenv(env, "1")
     wl = _wl("alt", 151936, "bf16", sigma=1.0)
-    _parity(oracle, _batch(wl, [3] * 16 + [0, 1, 2, 4], seed=21))
+    with env_setting(env, 1):
+        _parity(oracle, _batch(wl, [3] * 16 + [0, 1, 2, 4], seed=21))
 
 
 def test_f32_logits_full_vocab_are_too_wide_for_the_slot_table(oracle):
@@ -400,12 +400,10 @@ def test_bad_arguments_are_rejected_before_any_launch():
 
 
 @pytest.mark.parametrize("no_table", [0, 1])
-def test_extreme_final_uniforms_pick_tokens_with_mass(oracle, no_table, monkeypatch):
+def test_extreme_final_uniforms_pick_tokens_with_mass(oracle, no_table):
     """u_final = 0 and the largest binary32 below 1 sit on a CDF edge by construction (always
     flagged, so parity says nothing): the token drawn must still carry mass, the first such
     token for u = 0 and one at the far end of the support for u -> 1."""
-    if no_table:
-        monkeypatch.setenv("RESPEC_SAMPLER_NO_TABLE", "1")
     wl = _wl("extreme", 151936, "bf16", sigma=1.0)
     ks = [2] * 16 + [0] * 4
     batch = _batch(wl, ks, seed=31)
@@ -413,7 +411,8 @@ def test_extreme_final_uniforms_pick_tokens_with_mass(oracle, no_table, monkeypa
     u = np.zeros(B, dtype=np.float32)
     u[1::2] = np.float32(1.0) - np.float32(2.0 ** -24)
     batch.u_final.copy_(torch.from_numpy(u))
-    toks, n, _ = gpu_sample(batch, workspace=None)
+    with env_setting("RESPEC_SAMPLER_NO_TABLE", no_table or None):
+        toks, n, _ = gpu_sample(batch, workspace=None)
     ref_t, ref_n, ref_f = oracle_sample(oracle, batch)
     assert np.array_equal(n, ref_n)                      # the acceptance tests do not involve u_final
     P = oracle.softmax_rows(synth.to_host_array(batch.target_logits), 1.0, oracle.BF16)
