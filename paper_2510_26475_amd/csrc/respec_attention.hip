@@ -1185,29 +1185,39 @@ __global__ __launch_bounds__((4 + kProducers) * 64, 1) void attn_bf16_small_kern
 // Sixteen loads of a key row and eight value rows are in flight together (with one value per thread,
 // one load in flight and six barriers per chunk: B = 4, k = 4, 4 heads of 64, up to 256 keys
 // 11.1 us; now 7.4 us).
+// A row of at most 64 visible keys is one wave's work: the other three leave at once, and a wave without
+// keys reads none (with all four at work on rows of a few keys the loads of keys that nobody has took
+// most of the time).  The registers are held at four waves per SIMD, between the loads in flight that
+// small grids want and the work-groups that large ones do.  D = 64, k = 3, us per call (one value per
+// thread, then, now): B = 128, 16 keys 7.2, 13.8, 6.4; 80 keys 13.7, 16.2, 13.0; 256 keys 40.9, 38.5, 36.5;
+// 1000 keys 144, 143, 149; B = 512, 16 keys 18.8, 44.0, 15.6; B = 4, k = 4, 16 keys 5.3, 5.5, 4.6; 256 keys 14.6,
+// 7.8, 7.7.
 constexpr int kF32Threads = 256;
-constexpr int kF32Waves = kF32Threads / 64;
 
-template <int D>
-__global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
+// One row: query row i and head h of a sequence, by THREADS threads (a whole number of waves).
+template <int D, int THREADS>
+__device__ __forceinline__ void attn_f32_row(const AttnParams &p, const SeqInfo &si, int h, int i, int k_end) {
+    constexpr int kWaves = THREADS / 64;
     constexpr int kLanesPerKey = D / 4;                       // threads that cover a value row, four values each
-    constexpr int kGroups = kF32Threads / kLanesPerKey;       // keys handled at a time in the second product
+    constexpr int kGroups = THREADS / kLanesPerKey;           // keys handled at a time in the second product
     constexpr int kDepth = 8;                                 // value rows in flight per thread
     __shared__ floatx4 sh_q[D / 4];
-    __shared__ float sh_p[2][kF32Threads];
-    __shared__ float sh_m[2][kF32Waves], sh_l[2][kF32Waves];
+    __shared__ float sh_p[2][THREADS];
+    __shared__ float sh_m[2][kWaves], sh_l[2][kWaves];
     __shared__ floatx4 sh_part[kGroups][kLanesPerKey];
 
-    const int h = blockIdx.x % p.Hq;
-    const int b = blockIdx.x / p.Hq;
-    const int i = blockIdx.y;
-    const SeqInfo si = seq_info(p, b);
-    if (i >= si.R || si.L <= 0) return;
+    auto sync = [&]() __attribute__((always_inline)) {  // (one wave: its LDS operations run in order)
+        if constexpr (THREADS > 64) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
     const int kvh = h / p.G;
     const bool tree = p.tree_mask != nullptr;
     const uint64_t row_mask = tree ? p.tree_mask[si.q0 + i] : 0;
     const int first_new = si.L - si.R;
-    const int k_end = tree ? si.L : min(si.L, si.L - si.R + i + 1);  // one past the last visible key
     const int64_t qrow = (int64_t)(si.q0 + i) * p.Hq + h;
     const bool paged = p.page_table != nullptr;
     // element offset of key j's row of this KV head in the K or V buffer
@@ -1220,22 +1230,24 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
     const float *vb = static_cast<const float *>(p.v);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (threadIdx.x < D / 4) sh_q[threadIdx.x] = reinterpret_cast<const floatx4 *>(static_cast<const float *>(p.q) + qrow * D)[threadIdx.x];
-    __syncthreads();
+    sync();
 
     const int d4 = threadIdx.x % kLanesPerKey, group = threadIdx.x / kLanesPerKey;
     float m_run = -INFINITY, l_run = 0.f;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
     int turn = 0;
-    for (int t0 = 0; t0 < k_end; t0 += kF32Threads, turn ^= 1) {
+    for (int t0 = 0; t0 < k_end; t0 += THREADS, turn ^= 1) {
         const int key = t0 + threadIdx.x;
-        // (keys past the end read the last visible one; their score is dropped)
-        const floatx4 *kr = reinterpret_cast<const floatx4 *>(kb + key_row(min(key, k_end - 1)));
         floatx4 dot4 = {0.f, 0.f, 0.f, 0.f};
+        if (THREADS == 64 || t0 + wave * 64 < k_end) {  // (a wave without keys reads nothing)
+            // (keys past the end read the last visible one; their score is dropped)
+            const floatx4 *kr = reinterpret_cast<const floatx4 *>(kb + key_row(min(key, k_end - 1)));
 #pragma unroll 16
-        for (int c = 0; c < D / 4; ++c) {
-            const floatx4 x = kr[c], y = sh_q[c];
+            for (int c = 0; c < D / 4; ++c) {
+                const floatx4 x = kr[c], y = sh_q[c];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dot4[e] = fmaf(x[e], y[e], dot4[e]);
+                for (int e = 0; e < 4; ++e) dot4[e] = fmaf(x[e], y[e], dot4[e]);
+            }
         }
         const bool seen = key < k_end && (!tree || key < first_new || ((row_mask >> (key - first_new)) & 1u));
         const float s = seen ? ((dot4[0] + dot4[1]) + (dot4[2] + dot4[3])) * p.scale2 : -INFINITY;
@@ -1251,23 +1263,23 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
             sh_m[turn][wave] = m_w;
             sh_l[turn][wave] = l_w;
         }
-        __syncthreads();  // (a buffer is written again two chunks later, behind the next chunk's barrier)
+        sync();  // (a buffer is written again two chunks later, behind the next chunk's barrier)
         float m_new = m_run;
 #pragma unroll
-        for (int w = 0; w < kF32Waves; ++w) m_new = fmaxf(m_new, sh_m[turn][w]);
+        for (int w = 0; w < kWaves; ++w) m_new = fmaxf(m_new, sh_m[turn][w]);
         // (no key of the row seen so far, a tree's mask may hide a whole chunk: nothing to add)
         const float m_safe = m_new == -INFINITY ? 0.f : m_new;
         const float alpha = exp2f(m_run - m_safe);
-        float wgt[kF32Waves];
+        float wgt[kWaves];
         l_run *= alpha;
 #pragma unroll
-        for (int w = 0; w < kF32Waves; ++w) {
+        for (int w = 0; w < kWaves; ++w) {
             wgt[w] = exp2f(sh_m[turn][w] - m_safe);
             l_run += sh_l[turn][w] * wgt[w];
         }
         acc *= alpha;
         m_run = m_new;
-        const int nk = min(kF32Threads, k_end - t0);
+        const int nk = min(THREADS, k_end - t0);
         for (int j0 = group; j0 < nk; j0 += kGroups * kDepth) {
             floatx4 v[kDepth];
             float pj[kDepth];
@@ -1275,8 +1287,10 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
             for (int e = 0; e < kDepth; ++e) {
                 const int j = j0 + e * kGroups;
                 v[e] = *reinterpret_cast<const floatx4 *>(vb + key_row(t0 + min(j, nk - 1)) + d4 * 4);
-                const int w = min(j, kF32Threads - 1) >> 6;
-                const float f = w == 0 ? wgt[0] : w == 1 ? wgt[1] : w == 2 ? wgt[2] : wgt[3];
+                const int w = min(j, THREADS - 1) >> 6;
+                float f = wgt[0];
+#pragma unroll
+                for (int x = 1; x < kWaves; ++x) f = w == x ? wgt[x] : f;
                 pj[e] = j < nk ? sh_p[turn][j] * f : 0.f;
             }
 #pragma unroll
@@ -1287,14 +1301,29 @@ __global__ __launch_bounds__(kF32Threads) void attn_f32_kernel(AttnParams p) {
         }
     }
     sh_part[group][d4] = acc;
-    __syncthreads();
-    if (threadIdx.x < D) {
+    sync();
+    for (int d = threadIdx.x; d < D; d += THREADS) {
         float o = 0.f;
 #pragma unroll
-        for (int g = 0; g < kGroups; ++g) o += sh_part[g][threadIdx.x / 4][threadIdx.x % 4];
-        static_cast<float *>(p.out)[qrow * D + threadIdx.x] = l_run > 0.f ? o / l_run : 0.f;
-        if (p.lse && threadIdx.x == 0)
+        for (int g = 0; g < kGroups; ++g) o += sh_part[g][d / 4][d % 4];
+        static_cast<float *>(p.out)[qrow * D + d] = l_run > 0.f ? o / l_run : 0.f;
+        if (p.lse && d == 0)
             p.lse[qrow] = l_run > 0.f ? (m_run + log2f(l_run)) * 0.6931471805599453f : -INFINITY;
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(1, 4))) void attn_f32_kernel(AttnParams p) {
+    const int h = blockIdx.x % p.Hq;
+    const int b = blockIdx.x / p.Hq;
+    const int i = blockIdx.y;
+    const SeqInfo si = seq_info(p, b);
+    if (i >= si.R || si.L <= 0) return;
+    const int k_end = p.tree_mask ? si.L : min(si.L, si.L - si.R + i + 1);  // one past the last visible key
+    if (k_end <= 64) {  // block-uniform
+        if (threadIdx.x < 64) attn_f32_row<D, 64>(p, si, h, i, k_end);
+    } else {
+        attn_f32_row<D, kF32Threads>(p, si, h, i, k_end);
     }
 }
 

@@ -62,6 +62,15 @@ def test_f32_longer_contexts(oracle):
     _run(oracle, wl, [257, 31, 640], [2, 4, 0], seed=4)
 
 
+# One wave takes a row of up to 64 visible keys, four waves longer ones: the rows of one sequence fall on
+# both sides of the line
+@pytest.mark.parametrize("D", [64, 128])
+def test_f32_rows_around_one_wave_of_keys(oracle, D):
+    wl = _wl("f32_edges", 6, 2, D, "f32")
+    _run(oracle, wl, [1, 5, 16, 17, 63, 64, 65, 66, 68, 127, 128, 129, 255, 256, 257, 320], [0, 4, 3, 4, 4, 0, 4, 4, 4, 2, 4, 4, 0, 4, 4, 4],
+         seed=70 + D)
+
+
 @pytest.mark.parametrize("heads", [(28, 4), (16, 2), (40, 8), (4, 1), (8, 8), (7, 1)])
 @pytest.mark.parametrize("wgs", [None, 1, 3, 64])
 def test_bf16_d128_shapes(oracle, heads, wgs):
