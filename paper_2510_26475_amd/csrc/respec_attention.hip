@@ -1337,10 +1337,9 @@ __global__ __launch_bounds__(kF32Threads) __attribute__((amdgpu_waves_per_eu(1, 
 // the slices are merged through LDS in part order.  A short batch cuts every sequence into many
 // parts (one sequence: all of the split), which one wave per column walks four at a time, a round
 // trip each.  Measured (3B shape, k = 4; PW = 1 / 4 / 8): 8 sequences of 2304 tokens, 16 parts
-// each, 7.3 / 4.2 / 5.1 us; one sequence of 4096 tokens, 128 parts, 41 / 9.8 / 7.4 us (7B shape,
-// 64 parts: 22 / 6.0 / 5.6 us); 14B shape, 32 sequences of 5 parts each, 4.8 / 9.8 / 13.8 us.
-// (With the loads of a batch behind conditions and one fold per part the first two took 13-20 and
-// 85 us.)
+// each, 7.5 / 4.3 / 5.2 us; one sequence of 4096 tokens, 64 parts, 21.7 / 5.9 / 5.2 us, of 16,384
+// tokens, 128 parts, 41.6 / 9.3 / 7.3 us; 14B shape, 32 sequences of 5 parts each, 4.9 / 9.9 / 14.2 us.
+// (With the loads of a batch behind conditions and one fold per part the first took 13 to 20 us.)
 template <int D, typename OutT, int PW>
 __global__ __launch_bounds__(PW == 1 ? 256 : 64 * PW) void attn_combine_kernel(AttnParams p) {
     constexpr int kTpc = D / 8;                   // lanes per column
@@ -1583,8 +1582,8 @@ hipError_t launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream) {
 // The combine kernel's form (see there), by the parts that the longest sequence's heads have: the
 // average, times how much longer than the average the longest can be (at most twice that is
 // counted: the bound is the caller's and may be the model's).  Sharing them between waves wins from
-// 16 parts on (7.3 -> 4.2 us) and loses at 8 (5.5 -> 6.8 us); eight waves win over four from 64 on
-// (6.0 -> 5.6 us).  forced: 1, 4 or 8 (RESPEC_ATTN_COMBINE), 0 = by this rule.
+// 16 parts on (7.5 -> 4.3 us) and loses at 8 (5.5 -> 6.8 us); eight waves win over four from 64 on
+// (5.9 -> 5.2 us).  forced: 1, 4 or 8 (RESPEC_ATTN_COMBINE), 0 = by this rule.
 template <int D>
 hipError_t launch_combine(const AttnParams &p, int M, int64_t kv_tokens, long forced, hipStream_t stream) {
     const int cols_per_wave = 64 / (D / 8);
