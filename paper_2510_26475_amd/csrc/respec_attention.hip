@@ -785,6 +785,8 @@ __device__ __forceinline__ void attn_bf16(const AttnParams &p) {
         }
     };
 
+    // (the rows as they are: their sign is applied where they are first used, for an operation
+    // right behind a load waits for it)
     auto load_q = [&](bf16x8(&dst)[NT][C::kKSteps], const SeqInfo &s, int kvh) __attribute__((always_inline)) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -795,10 +797,12 @@ __device__ __forceinline__ void attn_bf16(const AttnParams &p) {
             for (int t = 0; t < C::kKSteps; ++t) {
                 u32x4 raw = {0u, 0u, 0u, 0u};
                 if (valid) raw = *reinterpret_cast<const u32x4 *>(qrow + (t * 32 + g4 * 8) * 2);
-                raw ^= p.q_sign;  // (a negative scale: the rows are negated, which is exact)
                 dst[nt][t] = __builtin_bit_cast(bf16x8, raw);
             }
         }
+    };
+    auto signed_q = [&](const bf16x8 &x) __attribute__((always_inline)) {  // (a negative scale: the rows are negated, which is exact)
+        return __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, x) ^ p.q_sign);
     };
 
     bf16x8 qreg[NT][C::kKSteps];  // query rows of the segment at hand (F::kQueryInLds: in LDS instead)
@@ -812,6 +816,7 @@ __device__ __forceinline__ void attn_bf16(const AttnParams &p) {
     bf16x8 qnext[kPrefetchQ ? NT : 1][C::kKSteps];
     bool qnext_valid = false;
     bool q_in_place = false;  // qreg already holds the rows of the segment that begins
+    bool q_unsigned = !F::kQueryInLds && p.q_sign != 0;  // ... without their sign
 
     // per-segment state
     int seg_t_first = 0;
@@ -850,16 +855,17 @@ __device__ __forceinline__ void attn_bf16(const AttnParams &p) {
 #pragma unroll
                     for (int t = 0; t < C::kKSteps; ++t)
                         *reinterpret_cast<u32x4 *>(q_lds + (nt * kColTile + c16) * C::kRowBytes + (t * 32 + g4 * 8) * 2) =
-                            __builtin_bit_cast(u32x4, qrow[nt][t]);
+                            __builtin_bit_cast(u32x4, signed_q(qrow[nt][t]));
             } else if (q_in_place) {
                 // (moved over at the end of the previous segment)
             } else if (kPrefetchQ && qnext_valid) {
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int t = 0; t < C::kKSteps; ++t) qreg[nt][t] = qnext[kPrefetchQ ? nt : 0][t];
+                    for (int t = 0; t < C::kKSteps; ++t) qreg[nt][t] = signed_q(qnext[kPrefetchQ ? nt : 0][t]);
             } else if (idx > 0) {
                 load_q(qreg, cp.si, cp.h);
+                q_unsigned = p.q_sign != 0;
             }
             q_in_place = false;
             if constexpr (kPrefetchQ) {
@@ -870,6 +876,15 @@ __device__ __forceinline__ void attn_bf16(const AttnParams &p) {
 
         wait_at_least(filled + src, (uint32_t)(idx / PW + 1), alive, p.error_flag);
         asm volatile("" ::: "memory");
+        if constexpr (!F::kQueryInLds) {
+            if (q_unsigned) {  // wave-uniform
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int t = 0; t < C::kKSteps; ++t) qreg[nt][t] = signed_q(qreg[nt][t]);
+                q_unsigned = false;
+            }
+        }
 
         // S^T[key, col] = sum_d K[key, d] Q[col, d]; two 16-key sub-tiles
         floatx4 s_acc[NT][2];
@@ -1048,7 +1063,7 @@ __device__ __forceinline__ void attn_bf16(const AttnParams &p) {
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                        for (int t = 0; t < C::kKSteps; ++t) qreg[nt][t] = qnext[nt][t];
+                        for (int t = 0; t < C::kKSteps; ++t) qreg[nt][t] = signed_q(qnext[nt][t]);
                     q_in_place = true;
                 }
                 __builtin_amdgcn_sched_barrier(0);

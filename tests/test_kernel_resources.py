@@ -30,10 +30,9 @@ NO_SCRATCH = [
 ]
 
 
-# What the other kernels may take, bytes per lane: the three-tile form and the two-term trees reload a
-# few values; the one-term short rows only reserve room (their scalar spills go to vector lanes).
+# What the other kernels may take, bytes per lane: the two-term trees reload a few values; the one-term
+# short rows only reserve room (their scalar spills go to vector lanes).
 SCRATCH = {
-    "attn_bf16_kernelILi128ELi3EtLi1E": 16,
     "short_rows_sample_kernelILb1ELb1E": 20,
     "short_rows_sample_kernelILb0ELb1E": 20,
     "tree_rejection_sample_kernelILb1ELb0ELb0E": 8,
