@@ -1837,17 +1837,25 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     const int streams = nc / cw;  // ranges per work-group
     // the split width: one range per consumer (or group of consumers) of the device
     // (RESPEC_ATTN_WGS overrides it, for tests and sweeps)
-    // A range of a tiny batch gets two tiles at least, were all sequences as long as the longest may
-    // be (a bound that the contiguous and the paged entry point share): the
-    // partials that the combine kernel folds halve with the ranges, and a second tile takes 0.5 us (2
-    // sequences of 2300 tokens: k = 0 at the 3B shape 21.7 us per call with 1024 ranges, 16.3 us with
-    // 128; k = 6, 4 query heads of 64, 17.0 us with 256, 14.6 with 128)
+    // A tiny batch gets no more ranges than it can have tiles, were all sequences as long as the longest
+    // may be (a bound that the contiguous and the paged entry point share): ranges without a tile cost
+    // their launch, and every part the combine kernel walks.  us per call at the 3B shape with as many
+    // ranges as the device takes (1024 at k = 0, 256 at k = 4), with as many as tiles, and with half as
+    // many: 4 sequences of 8 to 64 tokens, k = 0 15.2, 12.1, 14.2, k = 4 14.7, 13.5, 17.1; 48 of 8 to 32
+    // tokens, k = 4 11.8, 11.9, 15.6 (a second tile in a range is a second sequence there); one of 60 to
+    // 70 tokens, k = 0 20.5, 11.1, 11.5.  Half as many are better where each range is one whole sequence,
+    // which no bound tells: 4 of 33 to 64 tokens, k = 0 15.0, 12.2, 10.9, k = 4 14.8, 13.2, 11.8.
+    // Of long sequences a range gets two tiles at least: the partials that the combine kernel folds
+    // halve with the ranges, a second tile of the same sequence takes 0.5 us, and few ranges cross from
+    // one sequence to the next (2 sequences of 2300 tokens: k = 0 at the 3B shape 21.7 us per call with
+    // 1024 ranges, 16.3 us with 128; k = 6, 4 query heads of 64, 17.0 us with 256, 14.6 with 128)
     long W = kn.get(&Knobs::attn_wgs, 0);
     if (W <= 0) {
         W = (long)streams * compute_units() / col_blocks;
-        const int64_t tile_bound = (int64_t)B * (((int64_t)max_kv_len + kTileKeys - 1) / kTileKeys) * Hkv;  // (a caller without a bound passes the largest int32)
-        const int64_t most = ((tile_bound + 1) / 2 + streams - 1) / streams * streams;
-        if (W > most) W = (long)most;
+        const int64_t longest = ((int64_t)max_kv_len + kTileKeys - 1) / kTileKeys;  // (a caller without a bound passes the largest int32)
+        const int per = longest > 64 ? 2 : 1;
+        const int64_t most = ((int64_t)B * longest * Hkv + per - 1) / per;
+        if (W > most) W = (long)((most + streams - 1) / streams * streams);
     }
     if (W < 1) W = 1;
     if (W > max_waves) W = max_waves;
