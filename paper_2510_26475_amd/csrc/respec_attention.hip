@@ -1798,6 +1798,10 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     // consumers of one tile each share a range, four per work-group: a quarter of the ranges and of the
     // partials to fold (two consumers / four: 24.8 / 23.4 at B = 6, 21.8 / 18.2 at B = 2, 7B; 19.5 / 18.1 at
     // B = 8, 3B with heads of 64; from two tiles on 28.1 / 28.9 at B = 12, 7B; 29.7 / 32.0 at B = 32, 3B).
+    // Where 16 (sequence, head) pairs or fewer share the ranges, folding the partials weighs more and the
+    // line is at four tiles (two consumers / four at 2 and 3 tiles, k = 3, 3B shape: one sequence of 39,000
+    // and 57,000 tokens 35.0 / 27.7 and 37.6 / 30.1, four of 9,800 and 14,300 23.7 / 21.9 and 26.4 / 24.2,
+    // eight of 4,900 and 7,200 22.4 / 21.5 and 24.7 / 23.7; heads of 64, eight, 17.2 / 17.4 and 18.0 / 18.7).
     // Three and four tiles: four consumers per range, eight per work-group (one, two and four consumers
     // per range: k = 4, B = 256 and 768 at the 3B shape 135, 133, 124 and 336, 331, 318; k = 5, B = 256 at the
     // 7B shape 239, 237, 233; k = 7, B = 64 at the 14B shape 125, 121, 117).  But that form's two ranges
@@ -1826,11 +1830,12 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     const int nt = quad ? 8 : (cols + kColTile - 1) / kColTile;  // column tiles of a block
     const bool many_heads = Hkv >= 8 && tiles_per_consumer >= (D == 64 ? 32 : 64);
     const bool one = nt == 1 || (nt == 3 && D == 128 && wide != 1 && (wide == 0 || many_heads));
+    const bool few_pairs = (int64_t)B * Hkv * 16 <= compute_units();
     int cw;
     if (quad || (quad_env == 2 && nt >= 2 && M <= kMaxColsPerBlock)) cw = 4;
     else if (one) cw = 1;
     else if (wide >= 0 || quad_env == 0 || M > kMaxColsPerBlock) cw = 2;
-    else if (nt == 2) cw = tiles_per_consumer < 2 ? 4 : 2;
+    else if (nt == 2) cw = tiles_per_consumer < (few_pairs ? 4 : 2) ? 4 : 2;
     else cw = many_heads ? 2 : 4;
     const long nc_env = kn.get(&Knobs::attn_consumers, 0);  // 4 / 8: the narrow four-way form's consumers
     const int nc = cw == 1 ? 4 : cw == 4 && nt <= 4 && (nc_env ? nc_env == 4 : tiles_per_consumer < 2) ? 4 : 8;

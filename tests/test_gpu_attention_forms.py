@@ -61,6 +61,17 @@ def test_forms_agree_with_the_oracle(oracle, shape, wgs, form):
         _check(oracle, batch)
 
 
+# The form by size where few sequences share all ranges: on both sides of each of its lines (two tiles
+# per consumer of the device, and four for 16 pairs of a sequence and a KV head or fewer)
+@pytest.mark.parametrize("pairs,tiles", [(1, 1), (1, 2), (1, 3), (4, 2), (4, 3), (4, 4), (16, 3), (18, 2)])
+def test_few_long_sequences(oracle, pairs, tiles):
+    B, Hkv = {1: (1, 1), 4: (2, 2), 16: (8, 2), 18: (9, 2)}[pairs]
+    consumers = 4 * torch.cuda.get_device_properties(0).multi_processor_count
+    lens = [(2 * tiles + 1) * consumers * 16 // pairs - 3 * i for i in range(B)]
+    batch = synth.make_batch(_wl(8 * Hkv, Hkv, 64), device="cuda", kv_lens=lens, k_per_seq=[2] * B, seed=pairs + tiles, with_logits=False)
+    _check(oracle, batch)
+
+
 # The scale is folded into the exponent: its sign, a value of zero (uniform attention over the
 # visible keys), large ones (one key dominates, references move often) and tiny ones
 @pytest.mark.parametrize("form", list(FORMS))
