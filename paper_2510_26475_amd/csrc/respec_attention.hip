@@ -1850,15 +1850,18 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     // tokens, k = 4 11.8, 11.9, 15.6 (a second tile in a range is a second sequence there); one of 60 to
     // 70 tokens, k = 0 20.5, 11.1, 11.5.  Half as many are better where each range is one whole sequence,
     // which no bound tells: 4 of 33 to 64 tokens, k = 0 15.0, 12.2, 10.9, k = 4 14.8, 13.2, 11.8.
-    // Of long sequences a range gets two tiles at least: the partials that the combine kernel folds
+    // Where sequences may have more than 16 tiles a range gets two tiles at least: the partials that the combine kernel folds
     // halve with the ranges, a second tile of the same sequence takes 0.5 us, and few ranges cross from
     // one sequence to the next (2 sequences of 2300 tokens: k = 0 at the 3B shape 21.7 us per call with
-    // 1024 ranges, 16.3 us with 128; k = 6, 4 query heads of 64, 17.0 us with 256, 14.6 with 128)
+    // 1024 ranges, 16.3 us with 128; k = 6, 4 query heads of 64, 17.0 us with 256, 14.6 with 128).
+    // Between 512 and 2048 tokens the two are even on the whole, by how the ends of the ranges meet those
+    // of the sequences (k = 4, 3B shape, one tile / two: 2 of 300 to 512 tokens 15.5 / 19.4; 2 of 512 to 1024
+    // 17.7 / 15.7, of 1024 to 2048 19.2 / 15.8; 4 of 520 15.4 / 20.1, of 512 to 1024 17.4 / 18.4)
     long W = kn.get(&Knobs::attn_wgs, 0);
     if (W <= 0) {
         W = (long)streams * compute_units() / col_blocks;
         const int64_t longest = ((int64_t)max_kv_len + kTileKeys - 1) / kTileKeys;  // (a caller without a bound passes the largest int32)
-        const int per = longest > 64 ? 2 : 1;
+        const int per = longest > 16 ? 2 : 1;
         const int64_t most = ((int64_t)B * longest * Hkv + per - 1) / per;
         if (W > most) W = (long)((most + streams - 1) / streams * streams);
     }
