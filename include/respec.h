@@ -430,8 +430,9 @@ respec_status_t respec_tree_rejection_sample(const void *target_logits, const vo
  * w_r = row_weight[r] is the weight w(reward) of the sample the row belongs to; the paper's
  * default w(r) = r, its normalisation and its clipping are the caller's (they are not
  * specified).  Rows with weight 0 are not read; their gradient is written as zero.
- * The rows are the [rows, V] logits the sampler reads.  A row pair is streamed twice (once for
- * its normalisers, once for the gradient) by one work-group; rows are independent.
+ * The rows are the [rows, V] logits the sampler reads.  A row pair is kept in LDS between the pass
+ * for its normalisers and the one for its gradient, by one work-group or by several that exchange
+ * their parts' sums through the workspace; where that does not pay it is streamed twice by one work-group.
  *
  *   target_logits, draft_logits [rows, V] logits_dt, row strides ld_t, ld_d elements
  *   row_weight    [rows] f32
@@ -440,7 +441,8 @@ respec_status_t respec_tree_rejection_sample(const void *target_logits, const vo
  *   V * sizeof(element), the strides in bytes and the three base pointers must be multiples of
  *   16 (RESPEC_ERR_UNSUPPORTED otherwise).
  *   workspace     respec_kd_rows_workspace_bytes(rows, V, logits_dt) bytes, 256-byte aligned,
- *                 scratch (nothing to prepare, nothing survives).
+ *                 scratch (nothing to prepare, nothing survives).  8 * rows bytes (rounded up to 256) are
+ *                 accepted too: the rows are then streamed twice.
  * Asynchronous on hip_stream like every other call; sums are formed in a fixed order, so a call
  * repeated on the same inputs gives the same bits.
  */

@@ -41,6 +41,8 @@ struct Knobs {
     long sampler_no_table;  // RESPEC_SAMPLER_NO_TABLE: the final draw without its table of slot totals
     long sampler_two_items; // RESPEC_SAMPLER_TWO_ITEMS: 0/1 shared sequences walk one or two chain items per stage
     long kd_wgs;            // RESPEC_KD_WGS: work-groups of the distillation kernel
+    long kd_team;           // RESPEC_KD_TEAM: 0 = one work-group per row pair, which it streams twice
+    long kd_spin;           // RESPEC_KD_SPIN: 10 ns ticks that a member's part of a row is waited for
     long get(long Knobs::*field, long fallback) const { return this->*field == kUnset ? fallback : this->*field; }
 };
 Knobs knobs();

@@ -4,17 +4,25 @@
 // and the gradient with respect to the drafter's logits, w * (q - p).  w is the weight w(r) of
 // the row's sample, supplied per row.
 //
-// The gradient of a row needs both normalisers of the row first.  One 512-thread work-group
-// takes a row pair at a time: pass 1 streams both rows for their normalisers (the sampler's
-// streaming pass), pass 2 streams them again, back to front, and writes the gradient; the KL
-// terms are summed on the way.  Work-groups are independent (no exchange, no waiting).
+// The gradient of a row needs both normalisers of the row first, so a row pair has to be kept, or
+// read twice, between the two passes over it.  kd_team_kernel keeps it: a team of work-groups holds
+// a row pair in its LDS, a part each, and exchanges the parts' normalisers through the workspace.
+// kd_stream_kernel is the form for rows too long for any team, and for workspaces without
+// room for the exchange: one work-group per row pair, which it streams twice.
 //
 // Numerics: exp2 of one element in fp32 (hardware exp2, two-term constant), row sums carried in
 // fp64, p and q formed in the log2 domain in fp32 (relative error about 2e-6), the KL terms
 // summed per thread in fp32 over one batch of slots (at most 32 terms) and in fp64 from there on.
 #include "respec_sampler_rows.hpp"
 
+#include <algorithm>
 #include <type_traits>
+#include <utility>
+
+// v_mul_legacy_f32: zero times anything is zero.  (The intrinsic and not an asm statement: its operand comes
+// straight from v_exp_f32, whose result the next vector instruction may not read; the compiler
+// puts the wait state between the two only where it knows both instructions.)
+extern "C" __device__ float legacy_mul(float, float) __asm("llvm.amdgcn.fmul.legacy");
 
 namespace respec {
 namespace {
@@ -26,9 +34,13 @@ struct KdParams : RowMath {
     void *grad;
     float *row_loss;
     double *total_loss;
-    double *row_kl;      // [rows] unweighted KL of every row
+    double *row_kl;      // [rows][team] unweighted KL of every row, by parts
+    uint64_t *box;       // [rows][team][kKdBoxWords] tagged words: the parts' normalisers
     int32_t rows, V;
     int64_t ld_t, ld_d, ld_g;
+    int32_t team;        // work-groups that share a row pair (1 in kd_stream_kernel)
+    int32_t part_slots;  // 16-byte slots of a row that each of them takes
+    int32_t spin;        // 10 ns ticks that a part is waited for before it is computed here
 };
 
 struct KdShared {
@@ -133,9 +145,7 @@ __global__ __launch_bounds__(kThreads) void kd_stream_kernel(KdParams p) {
                         const float pe = hw_exp2(a), qe = hw_exp2(b);
                         // (a token without target mass adds nothing, whatever a - b is then, -inf
                         // minus -inf included: the legacy multiply takes 0 times anything as 0)
-                        float term;
-                        asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(term) : "v"(pe), "v"(a - b));
-                        klb += term;
+                        klb += legacy_mul(pe, a - b);
                         gr[j] = w * (qe - pe);
                     }
                     store_grad<BF16>(g + (size_t)s * 16, gr);
@@ -188,12 +198,474 @@ __global__ __launch_bounds__(kThreads) void kd_stream_kernel(KdParams p) {
     }
 }
 
+// ---------------------------------------------------------------- a row pair kept in a team's LDS
+constexpr int kKdThreads = kThreads + 64;  // eight streaming waves and the one that exchanges normalisers
+constexpr int kKdChunk = 64;               // slots of a wave's piece: a lane's 16 bytes each
+constexpr int kKdMaxChunks = 38;           // pieces of a part: two rows, two buffers, 152 KiB of LDS
+constexpr int kKdMaxTeam = 32;
+constexpr int kKdFill = 256;               // compute units that few rows are spread over
+constexpr int kKdBoxWords = 8;             // a part's sums (two words each) and references; two words spare: 64 bytes
+constexpr uint32_t kKdTag = 1u;            // in the upper half of every word (the words are cleared ahead of the kernel)
+
+struct KdTeamShared {
+    float m[2][2][kWaves];        // [row parity][p/q][wave]: reference and sum of a wave's pieces
+    double s[2][2][kWaves];
+    double kl[2][kWaves];
+    uint32_t pay[kKdMaxTeam][kKdBoxWords];
+    float K[2][2];                // [row parity][p/q]: constants of the gradient pass
+    double shift[2];              // [row parity]: what the row's KL gets for their rounding
+    int row[2];                   // [row parity]: the row
+    uint32_t stats_seq[kWaves];   // rows whose m, s (kl) a wave has left, and whose K is there
+    uint32_t kl_seq[kWaves];
+    uint32_t const_seq;
+};
+
+typedef volatile uint32_t __attribute__((address_space(3))) *KdCounter;
+
+// (a wave's LDS operations execute in order: a counter written after the data needs no fence, only
+// the compiler kept from moving it)
+__device__ inline void kd_set(uint32_t &word, uint32_t v) {
+    asm volatile("" ::: "memory");
+    *(KdCounter)&word = v;
+}
+
+__device__ inline void kd_wait(uint32_t &word, uint32_t v) {
+    while (*(KdCounter)&word < v) __builtin_amdgcn_s_sleep(1);
+    asm volatile("" ::: "memory");
+}
+
+// 16 bytes per lane, global memory to LDS (lane i to lds + 16 i), counted by vmcnt.  Non-temporal:
+// every row is read once.  (No result register, so nothing to keep alive; the instruction takes the LDS address
+// from m0, whose write needs one wait state.)
+__device__ inline void kd_load_to_lds(uint32_t lds, const char *base, uint32_t off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+
+// Waits until at most n vector memory operations of the wave are outstanding (they complete in issue order).
+__device__ inline void kd_wait_vm(int n) {
+    switch (n) {  // wave-uniform
+        case 0: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+        case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
+        case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
+        case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
+        case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+        case 5: asm volatile("s_waitcnt vmcnt(5)" ::: "memory"); break;
+        case 6: asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); break;
+        case 7: asm volatile("s_waitcnt vmcnt(7)" ::: "memory"); break;
+        case 8: asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); break;
+        case 9: asm volatile("s_waitcnt vmcnt(9)" ::: "memory"); break;
+        case 10: asm volatile("s_waitcnt vmcnt(10)" ::: "memory"); break;
+        case 11: asm volatile("s_waitcnt vmcnt(11)" ::: "memory"); break;
+        case 12: asm volatile("s_waitcnt vmcnt(12)" ::: "memory"); break;
+        case 13: asm volatile("s_waitcnt vmcnt(13)" ::: "memory"); break;
+        default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); break;
+    }
+}
+
+// Sum and maximum over a wave by lane-permuting adds (no LDS round trip); every lane gets the result.
+template <int CTRL>
+__device__ inline double kd_dpp_add(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return x + __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+__device__ inline double kd_lane(double x, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, lane), hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+__device__ inline double kd_wave_sum(double x) {
+    x = kd_dpp_add<0xB1>(x);   // lane ^ 1
+    x = kd_dpp_add<0x4E>(x);   // lane ^ 2
+    x = kd_dpp_add<0x141>(x);  // the other quad of eight lanes
+    x = kd_dpp_add<0x140>(x);  // the other eight lanes of sixteen
+    return (kd_lane(x, 0) + kd_lane(x, 16)) + (kd_lane(x, 32) + kd_lane(x, 48));
+}
+
+template <int CTRL>
+__device__ inline float kd_dpp_max(float x) {
+    return fmaxf(x, as_f32(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true)));
+}
+
+__device__ inline float kd_wave_max(float x) {
+    x = kd_dpp_max<0xB1>(x);
+    x = kd_dpp_max<0x4E>(x);
+    x = kd_dpp_max<0x141>(x);
+    x = kd_dpp_max<0x140>(x);
+    auto at = [&](int lane) { return as_f32(__builtin_amdgcn_readlane((int)__float_as_uint(x), lane)); };
+    return fmaxf(fmaxf(at(0), at(16)), fmaxf(at(32), at(48)));
+}
+
+// Reference and sum of one wave's pieces of a row pair: S = sum exp(z - M), the same bits wherever
+// the pieces are read from.  load(c, vp, vq) gives piece c, -inf past the part's end.  The
+// reference is the largest element of the first piece; a wave whose first piece has no finite element, or
+// whose sum overflows, takes its pieces again with running references (kRefInit, 0 for none at all).
+template <bool BF16, class Load>
+__device__ inline void kd_wave_stats(int n_pieces, const RowMath &p, float (&M)[2], double (&S)[2], Load &&load) {
+    constexpr int EPV = Elem<BF16>::EPV;
+    float acc[2][EPV], K[2] = {0.f, 0.f};
+    bool ok = true;
+    M[0] = M[1] = kRefInit;
+    S[0] = S[1] = 0.0;
+    if (n_pieces == 0) return;
+#pragma unroll
+    for (int j = 0; j < EPV; ++j) acc[0][j] = acc[1][j] = 0.f;
+    for (int c = 0; c < n_pieces; ++c) {
+        u32x4 v[2];
+        load(c, v[0], v[1], true);
+        if (c == 0) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                M[r] = kd_wave_max(slot_max<BF16>(v[r]));
+                ok = ok && M[r] > -INFINITY && M[r] < INFINITY;
+                K[r] = -M[r] * p.c_f;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) fast_absorb<BF16, true>(v[r], acc[r], M[r], K[r], p);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < EPV; ++j) t += (double)acc[r][j];
+        S[r] = kd_wave_sum(t);
+        ok = ok && S[r] < 1.0e300;
+    }
+    if (ok) {  // wave-uniform
+        // exp2(z c_f + K) with K rounded: the residue, at most 2^-24 of |K|, is put back to second order
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const double d = 0.69314718055994530942 * ((double)K[r] + (double)M[r] * (double)p.c_f);
+            S[r] *= 1.0 - d + 0.5 * d * d;
+        }
+        return;
+    }
+    ThreadSum<BF16> t[2];
+    t[0].init();
+    t[1].init();
+    for (int c = 0; c < n_pieces; ++c) {
+        u32x4 v[2];
+        load(c, v[0], v[1], false);
+        t[0].absorb(v[0], p);
+        t[1].absorb(v[1], p);
+    }
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        M[r] = kd_wave_max(t[r].ref);
+        S[r] = kd_wave_sum(t[r].total() * exp2_f64((double)(t[r].ref - M[r]) * p.c_d));
+    }
+}
+
+// (M, S) over groups of LANES neighbouring lanes; every lane of a group gets the same bits.
+template <int LANES>
+__device__ inline void kd_fold(float &M, double &S, const RowMath &p) {
+    static_assert(LANES == 8 || LANES == 32);
+    float mm = kd_dpp_max<0x141>(kd_dpp_max<0x4E>(kd_dpp_max<0xB1>(M)));
+    if constexpr (LANES == 32) {
+        mm = kd_dpp_max<0x140>(mm);
+        const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(mm), __float_as_uint(mm), false, false);
+        mm = fmaxf(as_f32(x[0]), as_f32(x[1]));
+    }
+    double t = S * exp2_f64((double)(M - mm) * p.c_d);
+    t = kd_dpp_add<0x141>(kd_dpp_add<0x4E>(kd_dpp_add<0xB1>(t)));
+    if constexpr (LANES == 32) {
+        t = kd_dpp_add<0x140>(t);
+        const uint64_t u = __builtin_bit_cast(uint64_t, t);
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+        t = __builtin_bit_cast(double, (uint64_t)lo[0] | ((uint64_t)hi[0] << 32)) + __builtin_bit_cast(double, (uint64_t)lo[1] | ((uint64_t)hi[1] << 32));
+    }
+    M = mm;
+    S = t;
+}
+
+// Team t takes the rows t, t + teams, ... of those whose weight is not zero; member m of it the slots
+// [m, m + 1) * part_slots of each.  A streaming wave goes through its pieces of row i + 1 (sums for the
+// normalisers), then of row i (gradient, whose constants have had that long to arrive); a piece
+// of row i + 2 is requested into the same place as soon as one of row i has been read, so a row is read from
+// memory once and the exchange is not waited for.  Nothing but counters in LDS orders the waves.
+//
+// What bounds it: HBM.  2048 rows of 151,936 bf16 logits 438 us (one work-group per row pair, read twice) -> 370 us; a
+// kernel that reads two arrays of that size and writes a third takes 328 us, this one without its wait for the other
+// members 352, without its stores as well 237, the arithmetic alone 199.
+// Also measured: all requests of a row ahead of its gradients' stores 402 us (their issue blocks), requests from three
+// waves of their own, so that no streaming wave waits for its stores' acknowledgements 465 us; plain instead of
+// non-temporal stores 404 us, plain loads 387 us.
+//
+// A member that does not answer within `spin` (its work-group is not running yet: another stream's kernels
+// hold the device) is not needed: its part is computed from the rows, with the same operations in the same order.
+template <bool BF16>
+__global__ __launch_bounds__(kKdThreads) void kd_team_kernel(KdParams p) {
+    constexpr int EPV = Elem<BF16>::EPV;
+    extern __shared__ u32x4 kd_rows_lds[];  // [buffer][piece][p/q][lane]
+    __shared__ KdTeamShared sh;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int member = (int)(blockIdx.x % (unsigned)p.team), first_row = (int)(blockIdx.x / (unsigned)p.team);
+    const int teams = (int)(gridDim.x / (unsigned)p.team);
+    const size_t esz = BF16 ? 2 : 4;
+    const int nslots = p.V / EPV;
+    const int n_pieces = (p.part_slots + kKdChunk - 1) / kKdChunk;
+    typedef const float __attribute__((address_space(4))) *ConstWeight;  // scalar loads: they do not count with the pieces'
+    const ConstWeight weight = (ConstWeight)(uintptr_t)p.weight;
+    if (threadIdx.x < kWaves) sh.stats_seq[threadIdx.x] = sh.kl_seq[threadIdx.x] = 0;
+    if (threadIdx.x == 0) sh.const_seq = 0;
+    __syncthreads();
+    auto row_of = [&](const void *base, int64_t ld, int r) { return static_cast<const char *>(base) + (size_t)r * ld * esz; };
+
+    if (wave < kWaves) {
+        const int begin = member * p.part_slots, end = min(begin + p.part_slots, nslots);  // (end <= begin: nothing)
+        const int mine = end > begin ? ((end - begin + kKdChunk - 1) / kKdChunk - wave + kWaves - 1) / kWaves : 0;
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)kd_rows_lds;
+        auto slot_of = [&](int c) { return begin + (c * kWaves + wave) * kKdChunk + lane; };
+        auto place = [&](int buf, int c) { return ((buf * n_pieces + c * kWaves + wave) * 2) * kKdChunk; };  // in slots
+        auto request = [&](int r, int buf, int c) __attribute__((always_inline)) {
+            const uint32_t off = (uint32_t)min(slot_of(c), end - 1) * 16u;
+            const uint32_t at = lds0 + (uint32_t)place(buf, c) * 16u;
+            kd_load_to_lds(at, row_of(p.target, p.ld_t, r), off);
+            kd_load_to_lds(at + kKdChunk * 16u, row_of(p.draft, p.ld_d, r), off);
+        };
+        // the next of the team's rows from r on whose weight is not zero; gradients of the others are zero
+        auto next_row = [&](int r) __attribute__((always_inline)) {
+            while (r < p.rows && weight[r] == 0.f) {
+                char *g = static_cast<char *>(p.grad) + (size_t)r * p.ld_g * esz;
+                for (int c = 0; c < mine; ++c)
+                    if (slot_of(c) < end) *reinterpret_cast<u32x4 *>(g + (size_t)slot_of(c) * 16) = u32x4{0u, 0u, 0u, 0u};
+                r += teams;
+            }
+            return r;
+        };
+        // the sums over row number i (the i-th with a weight)
+        auto stats = [&](int i) __attribute__((always_inline)) {
+            float M[2];
+            double S[2];
+            kd_wave_stats<BF16>(mine, p, M, S, [&](int c, u32x4 &vp, u32x4 &vq, bool first) __attribute__((always_inline)) {
+                // (behind piece c's requests: two for each further piece, and where they were made by the
+                // gradient pass a store for each and for c)
+                if (first) kd_wait_vm((mine - 1 - c) * (i < 2 ? 2 : 3) + (i < 2 ? 0 : 1));
+                vp = kd_rows_lds[place(i & 1, c) + lane];
+                vq = kd_rows_lds[place(i & 1, c) + kKdChunk + lane];
+                if (slot_of(c) - lane + kKdChunk > end) {  // the part's last, ragged piece
+                    vp = slot_of(c) < end ? vp : neg_inf_slot<BF16>();
+                    vq = slot_of(c) < end ? vq : neg_inf_slot<BF16>();
+                }
+            });
+            if (lane < 2) {
+                sh.m[i & 1][lane][wave] = lane ? M[1] : M[0];
+                sh.s[i & 1][lane][wave] = lane ? S[1] : S[0];
+            }
+            kd_set(sh.stats_seq[wave], (uint32_t)i + 1);
+        };
+        // the gradient of row number i, at r, and its KL terms; requests row r2 into the places that become free
+        auto gradient = [&](int i, int r, int r2) __attribute__((always_inline)) {
+            kd_wait(sh.const_seq, (uint32_t)i + 1);
+            const float Ka = as_f32(__builtin_amdgcn_readfirstlane((int)__float_as_uint(sh.K[i & 1][0])));
+            const float Kb = as_f32(__builtin_amdgcn_readfirstlane((int)__float_as_uint(sh.K[i & 1][1])));
+            const float w = weight[r];
+            char *g = static_cast<char *>(p.grad) + (size_t)r * p.ld_g * esz;
+            double kl = 0.0;
+            for (int c = 0; c < mine; ++c) {
+                const u32x4 vp = kd_rows_lds[place(i & 1, c) + lane];
+                const u32x4 vq = kd_rows_lds[place(i & 1, c) + kKdChunk + lane];
+                if (r2 < p.rows) {
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::"v"(vp), "v"(vq) : "memory");  // the piece has left LDS
+                    request(r2, i & 1, c);
+                }
+                float zp[EPV], zq[EPV], gr[EPV], klc = 0.f;
+                unpack<BF16>(vp, zp);
+                unpack<BF16>(vq, zq);
+#pragma unroll
+                for (int j = 0; j < EPV; ++j) {
+                    const float a = fmaf(zp[j], p.c_f, Ka), b = fmaf(zq[j], p.c_f, Kb);
+                    const float pe = hw_exp2(a), qe = hw_exp2(b);
+                    // (a token without target mass adds nothing, whatever a - b is then, -inf
+                    // minus -inf included: the legacy multiply takes 0 times anything as 0)
+                    klc += legacy_mul(pe, a - b);
+                    gr[j] = w * (qe - pe);
+                }
+                if (slot_of(c) < end) {
+                    store_grad<BF16>(g + (size_t)slot_of(c) * 16, gr);
+                    kl += (double)klc;
+                }
+            }
+            kl = kd_wave_sum(kl);
+            if (lane == 0) sh.kl[i & 1][wave] = kl;
+            kd_set(sh.kl_seq[wave], (uint32_t)i + 1);
+        };
+        int r0 = next_row(first_row);
+        if (r0 >= p.rows) return;
+        for (int c = 0; c < mine; ++c) request(r0, 0, c);
+        int r1 = next_row(r0 + teams);
+        if (r1 < p.rows)
+            for (int c = 0; c < mine; ++c) request(r1, 1, c);
+        stats(0);
+        for (int i = 0; r0 < p.rows; ++i) {
+            const int r2 = r1 < p.rows ? next_row(r1 + teams) : p.rows;
+            if (r1 < p.rows) stats(i + 1);
+            gradient(i, r0, r2);
+            r0 = r1;
+            r1 = r2;
+        }
+        return;
+    }
+
+    // the exchanging wave
+    auto next_row = [&](int r) {
+        while (r < p.rows && weight[r] == 0.f) r += teams;
+        return r;
+    };
+    uint32_t absent = 0;  // members that did not answer in time
+    auto write_kl = [&](int i) {  // of row number i
+        double t = lane < kWaves ? sh.kl[i & 1][lane] : 0.0;
+#pragma unroll
+        for (int o = kWaves / 2; o >= 1; o >>= 1) t += __shfl_xor(t, o);
+        if (lane == 0) p.row_kl[(size_t)sh.row[i & 1] * p.team + member] = (member == 0 ? t + sh.shift[i & 1] : t) * 0.69314718055994530942;
+    };
+    auto fold_waves = [&](float M, double S) {  // lanes 0..7: the p row's waves, 8..15: the q row's
+        kd_fold<kWaves>(M, S, p);
+        return std::pair<float, double>(M, S);
+    };
+    auto set_pay = [&](int m, float M, double S) {
+        if (lane == 0 || lane == 8) {
+            const int r = lane >> 3;
+            const uint64_t u = __builtin_bit_cast(uint64_t, S);
+            sh.pay[m][2 * r] = (uint32_t)u;
+            sh.pay[m][2 * r + 1] = (uint32_t)(u >> 32);
+            sh.pay[m][4 + r] = __float_as_uint(M);
+        }
+        asm volatile("" ::: "memory");
+    };
+    int i = 0;
+    for (int r = next_row(first_row); r < p.rows; r = next_row(r + teams), ++i) {
+        while (__any(*(KdCounter)&sh.stats_seq[lane & 7] < (uint32_t)i + 1)) {}
+        asm volatile("" ::: "memory");
+        const auto own = fold_waves(sh.m[i & 1][(lane >> 3) & 1][lane & 7], sh.s[i & 1][(lane >> 3) & 1][lane & 7]);
+        set_pay(member, own.first, own.second);
+        if (p.team == 1) {
+            if (i >= 2) write_kl(i);
+        } else {
+            uint64_t *box = p.box + (size_t)r * p.team * kKdBoxWords;
+            if (lane < 6)
+                __hip_atomic_store(box + member * kKdBoxWords + lane, (uint64_t)sh.pay[member][lane] | ((uint64_t)kKdTag << 32),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            constexpr int kPer = kKdMaxTeam * kKdBoxWords / 64;
+            uint32_t missing = 0;  // bit u: this lane's word u
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int idx = u * 64 + lane, m = idx / kKdBoxWords;
+                if (m < p.team && m != member && idx % kKdBoxWords < 6) missing |= 1u << u;
+            }
+            if (i >= 2) write_kl(i);  // of row number i - 2, which all waves have passed
+            const uint64_t t0 = wall_clock64();
+            for (;;) {
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    if (u * 64 >= p.team * kKdBoxWords) break;
+                    if (missing & (1u << u)) {
+                        const int idx = u * 64 + lane;
+                        const uint64_t v = __hip_atomic_load(box + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if ((uint32_t)(v >> 32) == kKdTag) {
+                            sh.pay[idx / kKdBoxWords][idx % kKdBoxWords] = (uint32_t)v;
+                            missing &= ~(1u << u);
+                        }
+                    }
+                }
+                if (!__any(missing != 0)) {
+                    absent = 0;
+                    break;
+                }
+                const bool out_of_time = wall_clock64() - t0 >= (uint64_t)p.spin;
+                uint32_t give_up = 0;
+                if (out_of_time || absent != 0) {
+                    uint32_t late = 0;  // members with a missing word
+#pragma unroll
+                    for (int u = 0; u < kPer; ++u) {
+                        const unsigned long long b = __ballot((missing & (1u << u)) != 0);
+#pragma unroll
+                        for (int x = 0; x < 64 / kKdBoxWords; ++x)
+                            if ((b >> (x * kKdBoxWords)) & 0xff) late |= 1u << (u * (64 / kKdBoxWords) + x);
+                    }
+                    absent = out_of_time ? late : late & absent;
+                    give_up = absent;
+                }
+                while (give_up != 0) {
+                    const int m = __builtin_ctz(give_up);
+                    give_up &= give_up - 1;
+                    const int b0 = m * p.part_slots, e0 = min(b0 + p.part_slots, nslots);
+                    const char *rp = row_of(p.target, p.ld_t, r), *rq = row_of(p.draft, p.ld_d, r);
+                    float Ml = kRefInit;
+                    double Sl = 0.0;
+                    for (int w = 0; w < kWaves; ++w) {
+                        float M[2];
+                        double S[2];
+                        const int n = e0 > b0 ? ((e0 - b0 + kKdChunk - 1) / kKdChunk - w + kWaves - 1) / kWaves : 0;
+                        kd_wave_stats<BF16>(n, p, M, S, [&](int c, u32x4 &vp, u32x4 &vq, bool) __attribute__((always_inline)) {
+                            const int s = b0 + (c * kWaves + w) * kKdChunk + lane;
+                            vp = load_slot<BF16, true, false, true>(rp, min(s, e0 - 1), 0);
+                            vq = load_slot<BF16, true, false, true>(rq, min(s, e0 - 1), 0);
+                            vp = s < e0 ? vp : neg_inf_slot<BF16>();
+                            vq = s < e0 ? vq : neg_inf_slot<BF16>();
+                        });
+                        if ((lane & 7) == w) {
+                            Ml = lane & 8 ? M[1] : M[0];
+                            Sl = lane & 8 ? S[1] : S[0];
+                        }
+                    }
+                    const auto part = fold_waves(Ml, Sl);
+                    set_pay(m, part.first, part.second);
+#pragma unroll
+                    for (int u = 0; u < kPer; ++u)
+                        if ((u * 64 + lane) / kKdBoxWords == m) missing &= ~(1u << u);
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+        // lanes 0..31: the members' p parts, 32..63: the q parts
+        const int m = lane & 31, which = lane >> 5;
+        float M = kRefInit;
+        double S = 0.0;
+        if (m < p.team) {
+            M = as_f32(sh.pay[m][4 + which]);
+            S = __builtin_bit_cast(double, (uint64_t)sh.pay[m][2 * which] | ((uint64_t)sh.pay[m][2 * which + 1] << 32));
+        }
+        kd_fold<32>(M, S, p);
+        // The log2 of a probability is one multiply-add, z c_f + K with K = -M c_f - log2(S) rounded to
+        // binary32; what the rounding leaves out (a few 1e-7) shifts every term of the row's KL alike
+        // and is put back once per row, since the probabilities sum to one.
+        const double k = -(double)M * (double)p.c_f - log2(S);
+        const float K = (float)k;
+        const double rest = k - (double)K;
+        sh.shift[i & 1] = kd_lane(rest, 0) - kd_lane(rest, 32);
+        sh.row[i & 1] = r;
+        if (m == 0) sh.K[i & 1][which] = K;
+        kd_set(sh.const_seq, (uint32_t)i + 1);
+    }
+    for (int x = max(0, i - 2); x < i; ++x) {
+        for (int w = 0; w < kWaves; ++w) kd_wait(sh.kl_seq[w], (uint32_t)x + 1);
+        write_kl(x);
+    }
+}
+
+// The words that the members exchange, cleared ahead of the kernel.
+__global__ __launch_bounds__(256) void kd_clear_kernel(u32x4 *words, size_t n) {
+    for (size_t x = blockIdx.x * 256u + threadIdx.x; x < n; x += (size_t)gridDim.x * 256u) words[x] = u32x4{0u, 0u, 0u, 0u};
+}
+
 // row_loss[r] = w[r] * KL of the row; total = sum over rows in a fixed order.  One work-group.
 __global__ __launch_bounds__(1024) void kd_finish_kernel(KdParams p) {
     __shared__ double sh[1024];
     double acc = 0.0;
     for (int r = threadIdx.x; r < p.rows; r += 1024) {
-        const double l = (double)p.weight[r] == 0.0 ? 0.0 : (double)p.weight[r] * p.row_kl[r];
+        double l = 0.0;
+        if (p.weight[r] != 0.f) {
+            double kl = 0.0;
+#pragma unroll 8
+            for (int m = 0; m < p.team; ++m) kl += p.row_kl[(size_t)r * p.team + m];
+            l = (double)p.weight[r] * kl;
+        }
         p.row_loss[r] = (float)l;
         acc += l;
     }
@@ -206,14 +678,73 @@ __global__ __launch_bounds__(1024) void kd_finish_kernel(KdParams p) {
     if (threadIdx.x == 0 && p.total_loss) *p.total_loss = sh[0];
 }
 
+// Work-groups that share a row pair, 0 for one that streams it twice.  The smallest power of two whose
+// members' parts fit their LDS; few rows are shared by more, as long as every streaming wave
+// keeps a piece of its own, until the device is full.  Times in us, streamed twice / by a team:
+//   - a row pair that one work-group can keep needs no exchange and is always better kept: bf16, V = 8000, 100 rows
+//     11.5 / 10.3, 2048 rows 57 / 35; V = 16,000, 2048 rows 70 / 50;
+//   - longer ones cost the exchange and one more small kernel (about 4 us): worth it where rows are few (V = 64,000, 32
+//     rows 20.4 / 14.3; V = 151,936, 8 rows 35 / 15; but fp32, V = 16,000, 8 rows 11.8 / 12.7), where the row pairs under way do not fit the L2s, so
+//     that the second read is one from memory (V = 128,000, 512 rows 100 / 97; fp32, 240 / 162; V = 151,936, 2048
+//     rows 441 / 375; but V = 64,000, 512 rows 51.6 / 53.6), and over many rows (V = 32,000, 2048 rows 104 / 96,
+//     256 rows 20 / 23; fp32, 1024 rows 88 / 83).
+int kd_team(int32_t rows, int32_t V, bool bf16) {
+    const int64_t slots = V / (bf16 ? 8 : 4);
+    int team = 1;
+    while (team <= kKdMaxTeam && (slots + team - 1) / team > kKdMaxChunks * kKdChunk) team *= 2;
+    if (team == 1) return 1;
+    if (team > kKdMaxTeam) return 0;
+    const bool few = rows <= 64 && V >= 32000;
+    if (!few && slots < 12000 && rows < (bf16 ? 2048 : 1024)) return 0;
+    while (team < kKdMaxTeam && (int64_t)rows * team * 2 <= kKdFill && slots / (2 * team) >= kThreads) team *= 2;
+    return team;
+}
+
+size_t kd_kl_bytes(int32_t rows, int team) { return round_up((size_t)rows * team * sizeof(double), 256); }
+size_t kd_box_bytes(int32_t rows, int team) { return team > 1 ? (size_t)rows * team * kKdBoxWords * 8 : 0; }
+
+template <bool BF16>
+hipError_t launch_kd_team(KdParams &p, int cus, hipStream_t stream) {
+    static bool configured[64] = {false};  // per device; benign race: the attribute is idempotent
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
+    if (dev < 0 || !configured[dev]) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kd_team_kernel<BF16>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kKdMaxChunks * kKdChunk * 64);
+        if (e != hipSuccess) return e;
+        if (dev >= 0) configured[dev] = true;
+    }
+    const int slots = p.V / Elem<BF16>::EPV;
+    p.part_slots = ((slots + p.team - 1) / p.team + 7) / 8 * 8;  // (whole 128-byte lines)
+    const int pieces = (p.part_slots + kKdChunk - 1) / kKdChunk;
+    long teams = knobs().get(&Knobs::kd_wgs, (long)cus) / p.team;
+    if (teams > p.rows) teams = p.rows;
+    if (teams < 1) teams = 1;
+    p.spin = (int32_t)knobs().get(&Knobs::kd_spin, 5000);  // 50 us
+    if (p.team > 1) {
+        const size_t words = kd_box_bytes(p.rows, p.team) / 16;
+        hipLaunchKernelGGL(kd_clear_kernel, dim3((unsigned)std::min<size_t>((words + 255) / 256, (size_t)cus)), dim3(256), 0, stream,
+                           reinterpret_cast<u32x4 *>(p.box), words);
+    }
+    hipLaunchKernelGGL((kd_team_kernel<BF16>), dim3((unsigned)(teams * p.team)), dim3(kKdThreads), (size_t)pieces * kKdChunk * 64, stream, p);
+    return hipGetLastError();
+}
+
 template <bool BF16>
 hipError_t launch_kd(KdParams &p, hipStream_t stream) {
     int cus = 256, dev = 0;
     if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    long wgs = knobs().get(&Knobs::kd_wgs, (long)cus);  // tests and sweeps
-    if (wgs > p.rows) wgs = p.rows;
-    if (wgs < 1) wgs = 1;
-    hipLaunchKernelGGL((kd_stream_kernel<BF16>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, p);
+    hipError_t err = hipSuccess;
+    if (p.team > 0) {
+        err = launch_kd_team<BF16>(p, cus, stream);
+    } else {
+        p.team = 1;
+        long wgs = knobs().get(&Knobs::kd_wgs, (long)cus);  // tests and sweeps
+        if (wgs > p.rows) wgs = p.rows;
+        if (wgs < 1) wgs = 1;
+        hipLaunchKernelGGL((kd_stream_kernel<BF16>), dim3((unsigned)wgs), dim3(kThreads), 0, stream, p);
+    }
+    if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kd_finish_kernel, dim3(1), dim3(1024), 0, stream, p);
     return hipGetLastError();
 }
@@ -226,7 +757,8 @@ extern "C" {
 size_t respec_kd_rows_workspace_bytes(int32_t rows, int32_t V, respec_dtype_t dt) {
     using namespace respec;
     if (rows <= 0 || V <= 0 || (dt != RESPEC_F32 && dt != RESPEC_BF16)) return 0;
-    return round_up((size_t)rows * sizeof(double), 256);
+    const int team = kd_team(rows, V, dt == RESPEC_BF16);
+    return kd_kl_bytes(rows, std::max(team, 1)) + round_up(kd_box_bytes(rows, team), 256);
 }
 
 respec_status_t respec_kd_rows(const void *target_logits, const void *draft_logits, const float *row_weight,
@@ -246,7 +778,7 @@ respec_status_t respec_kd_rows(const void *target_logits, const void *draft_logi
     if ((V * esz) % 16 != 0 || (ld_t * esz) % 16 != 0 || (ld_d * esz) % 16 != 0 || (ld_g * esz) % 16 != 0 ||
         !aligned_to(target_logits, 16) || !aligned_to(draft_logits, 16) || !aligned_to(grad_draft_logits, 16))
         return fail(RESPEC_ERR_UNSUPPORTED, "kd_rows: rows must be whole 16-byte pieces (V, strides and base pointers)");
-    const size_t need = respec_kd_rows_workspace_bytes(rows, V, logits_dt);
+    const size_t need = kd_kl_bytes(rows, 1);  // (less than the size function asks for: one work-group per row pair)
     if (!workspace || workspace_bytes < need || !aligned_to(workspace, 256))
         return fail(RESPEC_ERR_WORKSPACE, "kd_rows: workspace of %zu bytes (256-byte aligned) needed, got %zu", need,
                     workspace ? workspace_bytes : (size_t)0);
@@ -260,6 +792,9 @@ respec_status_t respec_kd_rows(const void *target_logits, const void *draft_logi
     p.row_loss = row_loss;
     p.total_loss = total_loss;
     p.row_kl = static_cast<double *>(workspace);
+    p.team = kd_team(rows, V, logits_dt == RESPEC_BF16);
+    if (knobs().get(&Knobs::kd_team, 1) == 0 || workspace_bytes < respec_kd_rows_workspace_bytes(rows, V, logits_dt)) p.team = 0;
+    p.box = reinterpret_cast<uint64_t *>(static_cast<char *>(workspace) + kd_kl_bytes(rows, std::max((int)p.team, 1)));
     p.rows = rows;
     p.V = V;
     p.ld_t = ld_t;

@@ -144,3 +144,77 @@ def test_bad_arguments_are_rejected_before_any_launch():
     with pytest.raises(binding.RespecError) as e:
         binding.respec_kd_rows(t2.contiguous(), d2.contiguous(), w, torch.empty((4, 1022), device="cuda"), loss, None, ws)
     assert e.value.status == 2
+
+
+# ---- row pairs kept by teams of work-groups (a part: at most 38 pieces of 64 16-byte slots; streaming wave w takes the pieces
+# w, w + 8, ...; few rows are shared by more work-groups than one part each would need)
+@pytest.mark.parametrize("dtype,V,rows", [
+    ("bf16", 8 * 2432, 300),      # the longest row of one work-group, more rows than work-groups
+    ("bf16", 8 * 2433, 2048),     # one slot more: two members, the second part ragged
+    ("bf16", 8 * 511, 700),       # eight pieces, the last one a slot short
+    ("bf16", 8 * 513, 5),         # ... and one of a single slot
+    ("f32", 4 * 2440, 1030),      # two members
+    ("f32", 50256, 6),            # few rows: four-way and wider parts of 64 to 512 slots
+    ("bf16", 151936, 1),          # a single row: 32 members, the last one's part short
+    ("f32", 151936, 33),          # several rows per team, not the same number for all
+])
+def test_row_pairs_kept_by_teams(oracle, dtype, V, rows):
+    target, draft, w = _inputs(rows, V, dtype, seed=V + rows, zero_rows=(rows // 2,) if rows > 2 else ())
+    _parity(oracle, target, draft, w)
+
+
+@pytest.mark.parametrize("rows", [3, 200])
+def test_a_member_that_is_not_heard_of_is_computed_to_the_same_bits(rows):
+    target, draft, w = _inputs(rows, 151936, "bf16", seed=21)
+    a = gpu_kd(target, draft, w)
+    with env_setting("RESPEC_KD_SPIN", 0):  # nobody is waited for
+        b = gpu_kd(target, draft, w)
+    for x, y in zip(a, b):
+        assert torch.equal(x.view(torch.int16) if x.dtype == torch.bfloat16 else x, y.view(torch.int16) if y.dtype == torch.bfloat16 else y)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_references_of_a_wave_that_do_not_hold(oracle, dtype):
+    # a wave's first piece masked, without any piece at all, and an element 2^128 above the wave's first piece
+    target, draft, w = _inputs(12, 151936, dtype, seed=22)
+    target[0, :40000] = float("-inf")
+    target[1, 70000:] = float("-inf")
+    draft[2, 5000:9000] -= 300.0
+    target[3, 120000] = 200.0
+    draft[3, 120000] = 200.0
+    target[4] -= 25.0   # (the constant of the exponent stays below 64: it is rounded to 2^-19, 1.3e-6 of a probability)
+    draft[4] += 25.0
+    _parity(oracle, target, draft, w)
+
+
+def test_the_smallest_workspace_is_still_accepted(oracle):
+    target, draft, w = _inputs(300, 151936, "bf16", seed=23)
+    big = gpu_kd(target, draft, w)
+    ws = torch.empty((300 * 8 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+    grad, loss, total = torch.empty_like(draft), torch.empty(300, device="cuda"), torch.empty(1, dtype=torch.float64, device="cuda")
+    binding.respec_kd_rows(target, draft, w, grad, loss, total, ws)
+    torch.cuda.synchronize()
+    # (the bounds of the other tests twice: both sides are rounded)
+    assert float((grad.double() - big[0].double()).abs().max()) <= 2 * (2.0 ** -8 + 5e-6) * 2.0
+    assert bool(((loss - big[1]).abs() <= 4e-5 * (big[1].abs() + 0.05 * w)).all())
+
+
+def test_replays_of_a_captured_call_see_their_own_inputs(oracle):
+    target, draft, w = _inputs(40, 151936, "bf16", seed=24)
+    ws = torch.empty(binding.respec_kd_rows_workspace_bytes(40, 151936, binding.RESPEC_BF16), dtype=torch.uint8, device="cuda")
+    grad, loss, total = torch.empty_like(draft), torch.empty(40, device="cuda"), torch.empty(1, dtype=torch.float64, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        binding.respec_kd_rows(target, draft, w, grad, loss, total, ws)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(g, stream=s):
+            binding.respec_kd_rows(target, draft, w, grad, loss, total, ws)
+    for seed in (25, 26, 27):
+        t2, d2, w2 = _inputs(40, 151936, "bf16", seed=seed)
+        target.copy_(t2), draft.copy_(d2), w.copy_(w2)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        eager = gpu_kd(t2, d2, w2)
+        assert torch.equal(grad.view(torch.int16), eager[0].view(torch.int16)) and torch.equal(loss, eager[1]) and torch.equal(total, eager[2])
