@@ -262,43 +262,6 @@ __device__ inline void kd_wait_vm(int n) {
     }
 }
 
-// Sum and maximum over a wave by lane-permuting adds (no LDS round trip); every lane gets the result.
-template <int CTRL>
-__device__ inline double kd_dpp_add(double x) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
-    return x + __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-}
-
-__device__ inline double kd_lane(double x, int lane) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, lane), hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
-}
-
-__device__ inline double kd_wave_sum(double x) {
-    x = kd_dpp_add<0xB1>(x);   // lane ^ 1
-    x = kd_dpp_add<0x4E>(x);   // lane ^ 2
-    x = kd_dpp_add<0x141>(x);  // the other quad of eight lanes
-    x = kd_dpp_add<0x140>(x);  // the other eight lanes of sixteen
-    return (kd_lane(x, 0) + kd_lane(x, 16)) + (kd_lane(x, 32) + kd_lane(x, 48));
-}
-
-template <int CTRL>
-__device__ inline float kd_dpp_max(float x) {
-    return fmaxf(x, as_f32(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true)));
-}
-
-__device__ inline float kd_wave_max(float x) {
-    x = kd_dpp_max<0xB1>(x);
-    x = kd_dpp_max<0x4E>(x);
-    x = kd_dpp_max<0x141>(x);
-    x = kd_dpp_max<0x140>(x);
-    auto at = [&](int lane) { return as_f32(__builtin_amdgcn_readlane((int)__float_as_uint(x), lane)); };
-    return fmaxf(fmaxf(at(0), at(16)), fmaxf(at(32), at(48)));
-}
-
 // Reference and sum of one wave's pieces of a row pair: S = sum exp(z - M), the same bits wherever
 // the pieces are read from.  load(c, vp, vq) gives piece c, -inf past the part's end.  The
 // reference is the largest element of the first piece; a wave whose first piece has no finite element, or
@@ -319,7 +282,7 @@ __device__ inline void kd_wave_stats(int n_pieces, const RowMath &p, float (&M)[
         if (c == 0) {
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
-                M[r] = kd_wave_max(slot_max<BF16>(v[r]));
+                M[r] = wave_max(slot_max<BF16>(v[r]));
                 ok = ok && M[r] > -INFINITY && M[r] < INFINITY;
                 K[r] = -M[r] * p.c_f;
             }
@@ -332,7 +295,7 @@ __device__ inline void kd_wave_stats(int n_pieces, const RowMath &p, float (&M)[
         double t = 0.0;
 #pragma unroll
         for (int j = 0; j < EPV; ++j) t += (double)acc[r][j];
-        S[r] = kd_wave_sum(t);
+        S[r] = wave_sum(t);
         ok = ok && S[r] < 1.0e300;
     }
     if (ok) {  // wave-uniform
@@ -355,8 +318,8 @@ __device__ inline void kd_wave_stats(int n_pieces, const RowMath &p, float (&M)[
     }
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        M[r] = kd_wave_max(t[r].ref);
-        S[r] = kd_wave_sum(t[r].total() * exp2_f64((double)(t[r].ref - M[r]) * p.c_d));
+        M[r] = wave_max(t[r].ref);
+        S[r] = wave_sum(t[r].total() * exp2_f64((double)(t[r].ref - M[r]) * p.c_d));
     }
 }
 
@@ -364,16 +327,16 @@ __device__ inline void kd_wave_stats(int n_pieces, const RowMath &p, float (&M)[
 template <int LANES>
 __device__ inline void kd_fold(float &M, double &S, const RowMath &p) {
     static_assert(LANES == 8 || LANES == 32);
-    float mm = kd_dpp_max<0x141>(kd_dpp_max<0x4E>(kd_dpp_max<0xB1>(M)));
+    float mm = dpp_max<kDppOtherQuad>(dpp_max<kDppXor2>(dpp_max<kDppXor1>(M)));
     if constexpr (LANES == 32) {
-        mm = kd_dpp_max<0x140>(mm);
+        mm = dpp_max<kDppOtherEight>(mm);
         const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(mm), __float_as_uint(mm), false, false);
         mm = fmaxf(as_f32(x[0]), as_f32(x[1]));
     }
     double t = S * exp2_f64((double)(M - mm) * p.c_d);
-    t = kd_dpp_add<0x141>(kd_dpp_add<0x4E>(kd_dpp_add<0xB1>(t)));
+    t = dpp_add<kDppOtherQuad>(dpp_add<kDppXor2>(dpp_add<kDppXor1>(t)));
     if constexpr (LANES == 32) {
-        t = kd_dpp_add<0x140>(t);
+        t = dpp_add<kDppOtherEight>(t);
         const uint64_t u = __builtin_bit_cast(uint64_t, t);
         const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
         const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
@@ -491,7 +454,7 @@ __global__ __launch_bounds__(kKdThreads) void kd_team_kernel(KdParams p) {
                     kl += (double)klc;
                 }
             }
-            kl = kd_wave_sum(kl);
+            kl = wave_sum(kl);
             if (lane == 0) sh.kl[i & 1][wave] = kl;
             kd_set(sh.kl_seq[wave], (uint32_t)i + 1);
         };
@@ -638,7 +601,7 @@ __global__ __launch_bounds__(kKdThreads) void kd_team_kernel(KdParams p) {
         const double k = -(double)M * (double)p.c_f - log2(S);
         const float K = (float)k;
         const double rest = k - (double)K;
-        sh.shift[i & 1] = kd_lane(rest, 0) - kd_lane(rest, 32);
+        sh.shift[i & 1] = lane_value(rest, 0) - lane_value(rest, 32);
         sh.row[i & 1] = r;
         if (m == 0) sh.K[i & 1][which] = K;
         kd_set(sh.const_seq, (uint32_t)i + 1);

@@ -10,7 +10,7 @@
 // Parallelisation.  The chain of positions of one sequence is sequential and its length
 // differs from sequence to sequence, so one work-group per sequence leaves most of the
 // device idle when there are fewer sequences than compute units.  A sequence can therefore
-// be shared by SPLIT work-groups of 512 threads (one per compute unit), each owning a
+// be shared by SPLIT work-groups of 256 threads (one per compute unit), each owning a
 // contiguous part of the vocabulary.  After every streaming pass the parts exchange their
 // partial results (a few numbers) through a small mailbox in the workspace and then take
 // the same decision from the same numbers.  An exchange costs a few memory round trips, so
@@ -32,6 +32,14 @@
 
 namespace respec {
 namespace {
+
+// Threads of a work-group that shares its sequence with others.  Its passes are short (a part of a row) and
+// lie between reductions, barriers and exchanges, which cost less with half the waves, while four
+// waves, one per SIMD, still reach nine tenths of the issue rate of eight: bf16, V = 151,936, k = 4, T = 0.6, B = 64
+// 50.1 -> 45.8 us per call; fp32, V = 50,257, B = 32, k = 2 27.4 -> 24.4 (and 42.5 and 22.3 with the items of a
+// stage in one stream and reductions without LDS round trips).  Sequences with a work-group of their own keep 512: their
+// passes are long (mixed temperatures, B = 256 96 us, 110 with 256 threads; trees 97 / 112).
+constexpr int kSharedThreads = 256;
 
 struct SamplerParams : RowMath {
     const void *target;
@@ -136,17 +144,17 @@ __device__ inline void exchange(Mailbox &mb, const double (&mine)[8], SharedStat
 // streams its own part (`rowp`, `rowq` point at the part's first slot, `nslots` and `Vrow`
 // are the part's); with several parts the partial results are exchanged and combined in part
 // order, so every part holds the same bits afterwards.
-template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL>
+template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL, int TH>
 __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nslots, int Vrow, SharedState &sh,
                                      int parity, Mailbox &mb, const SamplerParams &p, float &Mp,
                                      double &Sp, float &Mq, double &Sq) {
     if constexpr (!SHARED) {
         if constexpr (FULL) {
-            if (row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq))
+            if (row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq))
                 return;        // block-uniform
             __syncthreads();   // every thread has read the combine buffers of this parity
         }
-        row_stats<BF16, TWO>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
+        row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
         return;
     }
     bool ok = false;
@@ -155,7 +163,7 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
         Sp = Sq = 0.0;
         ok = FULL;
     } else if constexpr (FULL) {
-        ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
+        ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
     }
     if constexpr (FULL) {
         const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, ok ? 1.0 : 0.0, 0.0, 0.0, 0.0};
@@ -166,7 +174,7 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
     }
     if (!ok) {  // some part saw an overflow or an empty sum: all repeat with the guarded pass
         __syncthreads();
-        row_stats<BF16, TWO>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
+        row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
         const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, 1.0, 0.0, 0.0, 0.0};
         exchange(mb, mine, sh);
     }
@@ -174,12 +182,8 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
         const int r = threadIdx.x / kMaxSplit, j = threadIdx.x % kMaxSplit;
         const bool have = j < mb.split;
         const float m_j = have ? (float)sh.xchg[j][2 * r] : -INFINITY;
-        float M = m_j;
-#pragma unroll
-        for (int o = kMaxSplit / 2; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-        double S = have ? sh.xchg[j][2 * r + 1] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0;
-#pragma unroll
-        for (int o = kMaxSplit / 2; o >= 1; o >>= 1) S += __shfl_xor(S, o);
+        const float M = group_max<kMaxSplit>(m_j);
+        const double S = group_sum<kMaxSplit>(have ? sh.xchg[j][2 * r + 1] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0);
         if (j == 0) {
             sh.comb_m[r] = M;
             sh.comb_s[r] = S;
@@ -207,19 +211,135 @@ struct DrawNorm {
 // than a part's pass over a row pair, and this halves the exchanges of a chain.  Returns bit 0 if
 // A's numbers are valid and bit 1 if B's are (every part returns the same); an item whose fast
 // pass overflowed or came out empty in some part is repeated by the caller the ordinary way.
-template <bool BF16, bool ONE_TERM, bool PARTIAL>
+//
+// The two items are one stream of batches: B's first batch is requested ahead of A's last, and the
+// four sums are reduced together behind one barrier (one pass after the other left the memory pipeline
+// empty for 3 us of every stage).
+template <bool BF16, bool ONE_TERM, bool PARTIAL, int TH>
 __device__ inline int row_stats_two_items(const void *pa, const void *qa, const void *pb, const void *qb,
-                                          bool b_pair, int nslots, int Vrow, SharedState &sh, Mailbox &mb,
+                                          bool b_pair, int nslots_all, int Vrow, SharedState &sh, Mailbox &mb,
                                           const SamplerParams &p, DrawNorm &A, DrawNorm &Bn) {
+    constexpr int EPV = Elem<BF16>::EPV, kThreads = TH, kWaves = TH / 64, kBatch = kThreads * kUnroll;
     bool ok_a = true, ok_b = true;
     A.Mp = A.Mq = Bn.Mp = Bn.Mq = kRefInit;
     A.Sp = A.Sq = Bn.Sp = Bn.Sq = 0.0;
-    if (nslots > 0) {  // (a part without slots has nothing to read and no mass)
-        ok_a = row_stats_fast<BF16, true, ONE_TERM, PARTIAL>(pa, qa, nslots, Vrow, sh, 0, p, A.Mp, A.Sp, A.Mq, A.Sq);
-        if (b_pair)  // block-uniform
-            ok_b = row_stats_fast<BF16, true, ONE_TERM, PARTIAL>(pb, qb, nslots, Vrow, sh, 1, p, Bn.Mp, Bn.Sp, Bn.Mq, Bn.Sq);
-        else
-            ok_b = row_stats_fast<BF16, false, ONE_TERM, PARTIAL>(pb, pb, nslots, Vrow, sh, 1, p, Bn.Mp, Bn.Sp, Bn.Mq, Bn.Sq);
+    if (nslots_all > 0) {  // (a part without slots has nothing to read and no mass)
+        const int nslots = PARTIAL ? whole_slots<BF16>(nslots_all, Vrow) : nslots_all;
+        const int tid = opaque_thread_index(), lane = tid & 63, wave = threadIdx.x >> 6;
+        const int n = (nslots + kBatch - 1) / kBatch;  // batches of an item; block-uniform, >= 1
+        float ref[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, acc[2][EPV], K[2] = {0.f, 0.f};  // [item][p/q]; acc, K: the current item's
+        double sum[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
+        u32x4 part_slot[2][2];
+        if constexpr (PARTIAL) {
+            if (nslots < nslots_all) {  // block-uniform
+                part_slot[0][0] = load_slot_or_last<BF16>(pa, nslots, Vrow);
+                part_slot[0][1] = load_slot_or_last<BF16>(qa, nslots, Vrow);
+                part_slot[1][0] = load_slot_or_last<BF16>(pb, nslots, Vrow);
+                part_slot[1][1] = load_slot_or_last<BF16>(qb, nslots, Vrow);
+            }
+        }
+        // batch `it` of the stream, clamped to the rows; unconditional (see row_stats_fast).  Without a
+        // drafter row in B its target row is requested twice, the second time from a cache.
+        auto load_batch = [&](int it, u32x4 (&vp)[kUnroll], u32x4 (&vq)[kUnroll]) __attribute__((always_inline)) {
+            it = min(it, 2 * n - 1);
+            const void *rowp = it < n ? pa : pb, *rowq = it < n ? qa : qb;
+            const int s0 = (it < n ? it : it - n) * kBatch + tid;
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                const int safe = max(0, min(s0 + u * kThreads, nslots - 1));
+                vp[u] = load_slot<BF16, true, false, !PARTIAL>(rowp, safe, Vrow);
+                vq[u] = load_slot<BF16, true, false, !PARTIAL>(rowq, safe, Vrow);
+            }
+        };
+        // every condition below is block-uniform
+        auto sum_batch = [&](int it, u32x4 (&vp)[kUnroll], u32x4 (&vq)[kUnroll]) __attribute__((always_inline)) {
+            const int item = it < n ? 0 : 1, at = it - item * n;
+            const bool two = item == 0 || b_pair;
+            if (at == n - 1) {  // an item's last batch: slots past the row are inert
+                const int s0 = at * kBatch + tid;
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) {
+                    const bool in = s0 + u * kThreads < nslots;
+                    vp[u] = in ? vp[u] : neg_inf_slot<BF16>();
+                    vq[u] = in ? vq[u] : neg_inf_slot<BF16>();
+                }
+            }
+            if (at == 0) {  // its first: the references
+                float m[2] = {-INFINITY, -INFINITY};
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) {
+                    m[0] = fmaxf(m[0], slot_max<BF16>(vp[u]));
+                    m[1] = fmaxf(m[1], slot_max<BF16>(vq[u]));
+                }
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    const float w = wave_max(m[r]);
+                    const float f = (w > -INFINITY && w < INFINITY) ? w : 0.f;
+                    K[r] = -f * p.c_f;
+                    if (item == 0) ref[0][r] = f; else ref[1][r] = f;
+#pragma unroll
+                    for (int j = 0; j < EPV; ++j) acc[r][j] = 0.f;
+                }
+            }
+            const float rp = item == 0 ? ref[0][0] : ref[1][0], rq = item == 0 ? ref[0][1] : ref[1][1];
+            if (two) {
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) {
+                    fast_absorb<BF16, ONE_TERM>(vp[u], acc[0], rp, K[0], p);
+                    fast_absorb<BF16, ONE_TERM>(vq[u], acc[1], rq, K[1], p);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u) fast_absorb<BF16, ONE_TERM>(vp[u], acc[0], rp, K[0], p);
+            }
+            if (at == n - 1) {
+                if (PARTIAL && nslots < nslots_all && tid == 0) {
+                    fast_absorb<BF16, ONE_TERM>(partial_slot<BF16>(item == 0 ? part_slot[0][0] : part_slot[1][0], nslots, Vrow), acc[0], rp, K[0], p);
+                    if (two) fast_absorb<BF16, ONE_TERM>(partial_slot<BF16>(item == 0 ? part_slot[0][1] : part_slot[1][1], nslots, Vrow), acc[1], rq, K[1], p);
+                }
+#pragma unroll
+                for (int r = 0; r < 2; ++r) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int j = 0; j < EPV; ++j) t += (double)acc[r][j];
+                    if (PARTIAL && t > kFastMost) t = (double)INFINITY;
+                    if (item == 0) sum[0][r] = t; else sum[1][r] = t;
+                }
+            }
+        };
+        u32x4 vp[2][kUnroll], vq[2][kUnroll];  // one set is summed while the other's loads are in flight
+        load_batch(0, vp[0], vq[0]);
+        for (int it = 0; it < 2 * n; it += 2) {
+            load_batch(it + 1, vp[1], vq[1]);
+            sum_batch(it, vp[0], vq[0]);
+            load_batch(it + 2, vp[0], vq[0]);
+            sum_batch(it + 1, vp[1], vq[1]);
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const double s = wave_sum(sum[x >> 1][x & 1]);
+            if (lane == 0) {
+                sh.m[x >> 1][x & 1][wave] = ref[x >> 1][x & 1];
+                sh.s[x >> 1][x & 1][wave] = s;
+            }
+        }
+        __syncthreads();
+        // lane group x: (item, p/q) = x; one exp2 per lane (see block_combine_fast)
+        const int x = (lane / kWaves) & 3, w = lane & (kWaves - 1);
+        const float my_m = sh.m[x >> 1][x & 1][w], mm = group_max<kWaves>(my_m);
+        double e = (double)(my_m - mm) * p.c_d;
+        if constexpr (ONE_TERM) e -= (double)(-my_m * p.c_f) + (double)my_m * (double)p.c_f;
+        const double part = group_sum<kWaves>(sh.s[x >> 1][x & 1][w] * exp2_f64(e));
+        A.Mp = lane_value(mm, 0), A.Mq = lane_value(mm, kWaves), Bn.Mp = lane_value(mm, 2 * kWaves);
+        A.Sp = lane_value(part, 0), A.Sq = lane_value(part, kWaves), Bn.Sp = lane_value(part, 2 * kWaves);
+        auto sound = [](double S) { return S > 0.0 && S < 1.0e300; };
+        ok_a = sound(A.Sp) && sound(A.Sq);
+        ok_b = sound(Bn.Sp);
+        if (b_pair) {
+            Bn.Mq = lane_value(mm, 3 * kWaves);
+            Bn.Sq = lane_value(part, 3 * kWaves);
+            ok_b = ok_b && sound(Bn.Sq);
+        }
     }
     // two binary32 references travel as the halves of one 8-byte word (moved, never computed with)
     auto pack = [](float lo, float hi) {
@@ -240,12 +360,8 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
             const unsigned long long w = __builtin_bit_cast(unsigned long long, sh.xchg[j][3 * item]);
             m_j = __uint_as_float((uint32_t)(r ? w >> 32 : w & 0xffffffffull));
         }
-        float M = m_j;
-#pragma unroll
-        for (int o = kMaxSplit / 2; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-        double S = have ? sh.xchg[j][3 * item + 1 + r] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0;
-#pragma unroll
-        for (int o = kMaxSplit / 2; o >= 1; o >>= 1) S += __shfl_xor(S, o);
+        const float M = group_max<kMaxSplit>(m_j);
+        const double S = group_sum<kMaxSplit>(have ? sh.xchg[j][3 * item + 1 + r] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0);
         if (j == 0) {
             sh.comb2_m[item][r] = M;
             sh.comb2_s[item][r] = S;
@@ -342,11 +458,12 @@ struct RowPart {
     float *tab;   // LDS room for one float per slot of the part (fp32 form of the weights), or NULL
 };
 
-// Phase A over one part: leaves the eight region totals in sh.wave_total (no barrier), and with
+// Phase A over one part: leaves the waves' region totals in sh.wave_total (no barrier), and with
 // a table every slot's total in part.tab.
-template <bool BF16, bool RESID, bool FULL, bool FAST, bool PARTIAL>
+template <bool BF16, bool RESID, bool FULL, bool FAST, bool PARTIAL, int TH>
 __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &nm, SharedState &sh,
                                           const RowMath &p) {
+    constexpr int kWaves = TH / 64;
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     const void *rowp = part.rowp, *rowq = part.rowq;
@@ -442,11 +559,13 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
 // row.  SHARED: the totals are this block's weights times `scale` (and the other blocks' times
 // theirs).  Returns the token, or -1 with mine = false when another block holds the crossing, or
 // -1 with Z_out <= 0 when the row carries no mass.  Ends with a barrier.
-template <bool BF16, bool RESID, bool FULL, bool FAST, bool SHARED, bool PARTIAL>
+template <bool BF16, bool RESID, bool FULL, bool FAST, bool SHARED, bool PARTIAL, int TH>
 __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, const RowPart &part,
                                   const DrawNorm &nm, double u, SharedState &sh, const RowMath &p, int &near_edge,
                                   double &Z_out, bool &mine, double scale) {
     constexpr int EPV = Elem<BF16>::EPV;
+    constexpr int kThreads = TH, kWaves = TH / 64;
+    static_assert(kMaxSplit * kWaves <= 64, "a wave holds the totals of all regions");
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     const float Mp = nm.Mp, Mq = nm.Mq;
     const double Sp = nm.Sp, Sq = nm.Sq;
@@ -458,9 +577,11 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
         sh.first_thread = kThreads;
         sh.last_positive = -1;
     }
-    // every thread: ordered prefix over the regions, find the region holding the crossing
-    double Z = 0.0;
-    for (int w = 0; w < n_reg; ++w) Z += totals[w];
+    // every wave: ordered prefix over the regions, a lane each, and the region holding the crossing (one
+    // thread after the other through 32 totals took 2 us of a shared draw)
+    const double tot = lane < n_reg ? totals[lane] : 0.0;
+    const double incl = wave_inclusive_scan(tot, lane);
+    double Z = lane_value(incl, 63);
     Z_out = Z;
     mine = false;
     if (!(Z > 0.0)) {  // caller falls back (residual of an exact tie) or reports the last token
@@ -469,18 +590,10 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
         return -1;
     }
     double t = u * Z;
-    int rstar = -1, rlast = 0;
-    double base = 0.0, prefix = 0.0;
-    for (int w = 0; w < n_reg; ++w) {
-        const double tot = totals[w];
-        const double next = prefix + tot;  // same additions, same order as Z above
-        if (rstar < 0 && next > t) {
-            rstar = w;
-            base = prefix;
-        }
-        if (tot > 0.0) rlast = w;
-        prefix = next;
-    }
+    const unsigned long long with_mass = __ballot(tot > 0.0), past = with_mass & __ballot(incl > t);
+    const int rlast = with_mass != 0ull ? 63 - __builtin_clzll(with_mass) : 0;
+    int rstar = past != 0ull ? __builtin_ctzll(past) : -1;
+    double base = rstar > 0 ? lane_value(incl, rstar - 1) : 0.0;
     const bool forced = rstar < 0;  // u*Z rounded up to Z: take the last token with mass
     if (forced) rstar = rlast;
     __syncthreads();  // the totals may be rewritten from here on; sh.token and friends are set
@@ -748,14 +861,15 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
 // the crossing finishes), or the whole row.  scale: what brings the weights of this block, formed
 // against its own reference, to the scale that the blocks of a sequence share (NaN: no usable
 // reference; every block then finds Z_out NaN).
-template <bool BF16, bool RESID, bool FULL, bool SHARED, bool FAST, bool PARTIAL>
+template <bool BF16, bool RESID, bool FULL, bool SHARED, bool FAST, bool PARTIAL, int TH>
 __device__ inline int inverse_cdf_pass(const void *rowp, const void *rowq, int nslots, int Vrow, int tok_off,
                                        float Mp, double Sp, float Mq, double Sq, double u, SharedState &sh,
                                        Mailbox &mb, const SamplerParams &p, int &near_edge, double &Z_out,
                                        bool &mine, float *tab = nullptr, double scale = 1.0) {
+    constexpr int kWaves = TH / 64;
     const RowPart part{rowp, rowq, nslots, Vrow, tok_off, tab};
     const DrawNorm nm{Mp, Mq, Sp, Sq};
-    draw_region_totals<BF16, RESID, FULL, FAST, PARTIAL>(part, nm, sh, p);
+    draw_region_totals<BF16, RESID, FULL, FAST, PARTIAL, TH>(part, nm, sh, p);
     __syncthreads();
     // the region totals of all parts, in vocabulary order
     const int n_reg = SHARED ? mb.split * kWaves : kWaves;
@@ -768,7 +882,7 @@ __device__ inline int inverse_cdf_pass(const void *rowp, const void *rowq, int n
         __syncthreads();
     }
     const double *totals = SHARED ? sh.all_total : sh.wave_total;
-    return draw_finish<BF16, RESID, FULL, FAST, SHARED, PARTIAL>(totals, n_reg, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
+    return draw_finish<BF16, RESID, FULL, FAST, SHARED, PARTIAL, TH>(totals, n_reg, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
                                                         p, near_edge, Z_out, mine, scale);
 }
 
@@ -913,6 +1027,7 @@ __device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, 
 // SHORT: the form for rows of at most kShortSlots slots (one work-group per sequence).
 template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED, bool SHORT, bool PARTIAL>
 __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
+    constexpr int kThreads = SHARED ? kSharedThreads : respec::kThreads, kWaves = kThreads / 64, TH = kThreads;
     __shared__ SharedState sh;
     __shared__ uint32_t sh_epoch;
     constexpr int EPV = Elem<BF16>::EPV;
@@ -1059,7 +1174,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                 const char *rowpb = tbase + (size_t)(row0 + i + 1) * p.ld_t * esz;
                 const char *rowqb = b_pair ? dbase + (size_t)(drow0 + i + 1) * p.ld_d * esz : rowpb;
                 DrawNorm a;
-                const int ok = row_stats_two_items<BF16, ONE_TERM, PARTIAL>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16,
+                const int ok = row_stats_two_items<BF16, ONE_TERM, PARTIAL, TH>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16,
                                                                    rowpb + (size_t)lo * 16, rowqb + (size_t)lo * 16, b_pair,
                                                                    nslots, Vrow, sh, mb, p, a, ahead);
                 ahead_of = (ok & 2) ? i + 1 : -1;
@@ -1070,7 +1185,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
             }
         }
         if (!have)
-            row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow, sh,
+            row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, TH>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow, sh,
                                                       i & 1, mb, p, Mp, Sp, Mq, Sq);
         last_Mp = Mp;
         double rho;
@@ -1086,7 +1201,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         // first rejection: one draw from the residual distribution (Eq. 2)
         double Z;
         int edge = 0;
-        final_token = inverse_cdf_pass<BF16, true, FULL, SHARED, kFastScan, PARTIAL>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow,
+        final_token = inverse_cdf_pass<BF16, true, FULL, SHARED, kFastScan, PARTIAL, TH>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow,
                                                          tok_off, Mp, Sp, Mq, Sq, u_fin, sh, mb, p, edge, Z, mine, tab);
         flag_cdf = edge;
         rejected = true;
@@ -1114,7 +1229,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         if (!rejected && (!SHARED || (k > 0 && ahead_of != k))) {
             scan_row = tbase + (size_t)(row0 + k) * p.ld_t * esz;
             const char *part_row = scan_row + (size_t)lo * 16;
-            float M0 = block_max_of_row_start<BF16, !PARTIAL, kRefSlots<ONE_TERM>>(part_row, PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots, sh);
+            float M0 = block_max_of_row_start<BF16, !PARTIAL, kRefSlots<ONE_TERM>, TH>(part_row, PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots, sh);
             const bool usable = M0 > -INFINITY && M0 < INFINITY;  // block-uniform
             double scale = 1.0;
             if constexpr (SHARED) {
@@ -1130,7 +1245,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
             if (SHARED || usable) {
                 double Z;
                 int edge = 0;
-                const int tok = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL>(part_row, part_row, nslots, Vrow, tok_off,
+                const int tok = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL, TH>(part_row, part_row, nslots, Vrow, tok_off,
                                                                                M0, 1.0, M0, 1.0, u_fin, sh, mb, p, edge, Z, mine, tab, scale);
                 if (Z > 1.0e-280 && Z < 1.0e280) {
                     final_token = tok;
@@ -1152,7 +1267,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
             scan_M = ahead.Mp;
             scan_S = ahead.Sp;
         } else {
-            row_stats_any<BF16, false, ONE_TERM, FULL, SHARED, PARTIAL>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
+            row_stats_any<BF16, false, ONE_TERM, FULL, SHARED, PARTIAL, TH>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
                                                        Vrow, sh, k & 1, mb, p, scan_M, scan_S, Mq, Sq);
         }
         scan_target = true;
@@ -1162,7 +1277,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     if (scan_target) {
         double Z;
         int edge = 0;
-        final_token = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
+        final_token = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL, TH>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
                                                           Vrow, tok_off, scan_M, scan_S, scan_M, scan_S, u_fin, sh,
                                                           mb, p, edge, Z, mine, tab);
         flag_cdf = rejected ? 1 : edge;
@@ -1197,13 +1312,13 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
 }
 
 template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED>
-__global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParams p) {
+__global__ __launch_bounds__(SHARED ? kSharedThreads : kThreads) void rejection_sample_kernel(SamplerParams p) {
     rejection_sample<BF16, ONE_TERM, FULL, SHARED, false, false>(p);
 }
 
 // Rows that are not whole aligned slots (fp64 weights).
 template <bool BF16, bool SHARED>
-__global__ __launch_bounds__(kThreads) void partial_rows_sample_kernel(SamplerParams p) {
+__global__ __launch_bounds__(SHARED ? kSharedThreads : kThreads) void partial_rows_sample_kernel(SamplerParams p) {
     rejection_sample<BF16, false, true, SHARED, false, true>(p);
 }
 
@@ -1266,15 +1381,26 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
     // work-groups per sequence: as many as there are otherwise idle compute units, as long as a
     // part keeps a useful share of the row; one (and no mailbox) without a workspace
     int split = 1, cus = 256;
+    bool two_items = false;
     if (workspace) {
         if (workspace_bytes < (size_t)B * kBoxBytes || !aligned_to(workspace, 16))
             return fail(RESPEC_ERR_WORKSPACE, "rejection_sample: workspace of %zu bytes (16-byte aligned) needed, got %zu",
                         (size_t)B * kBoxBytes, workspace_bytes);
         int dev = 0;
         if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        // Two chain items per stage read a row pair that the chain may not need.  That pays while
+        // the extra bytes are cheaper than the exchange they save: up to a quarter as many sequences
+        // as compute units (one item / two, us per call: bf16, V = 151,936, B = 96 63.0 / 60.6, B = 128 56.6 / 64.4;
+        // fp32, V = 50,257, B = 100 40.3 / 43.7).
+        two_items = kn.get(&Knobs::sampler_two_items, (long)B * 4 <= cus ? 1 : 0) != 0;
+        // A stage of two items costs little beside its pass, so parts may be shorter there (one work-group / parts of
+        // 1000 slots / of 500: bf16, V = 32,000, B = 64 29.7 / 25.6, B = 32 27.6 / 23.5 / 24.2; V = 60,000, B = 32 parts
+        // of 1875 / 938 28.4 / 25.4); with one item per stage they may not (V = 32,000, B = 100 30.2 / 33.5 in
+        // parts of 2000), nor where a chain has one stage (V = 32,000, B = 64, k = 1 15.2 / 16.4, k = 0 10.2 / 12.7).
         const int epv0 = logits_dt == RESPEC_BF16 ? 8 : 4;
         const long slots_row = ((long)V + epv0 - 1) / epv0;
-        while (split < kMaxSplit && (long)B * split * 2 <= cus && slots_row / (split * 2) >= 2048) split *= 2;
+        const long least = two_items && max_k >= 3 ? 768 : 2048;  // slots of a part
+        while (split < kMaxSplit && (long)B * split * 2 <= cus && slots_row / (split * 2) >= least) split *= 2;
         const long forced = kn.get(&Knobs::sampler_split, 0);
         if (forced == 1 || forced == 2 || forced == 4 || forced == 8) split = (int)forced;
         // The parts of a sequence wait for one another, so all of them have to be on the device at
@@ -1290,10 +1416,7 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         return fail(RESPEC_ERR_UNSUPPORTED, "rejection_sample: too many work-groups");
     p.split = split;
     p.boxes = static_cast<char *>(workspace);
-    // Two chain items per stage read a row pair that the chain may not need.  That pays while
-    // the extra bytes are cheaper than the exchange they save: up to a quarter as many sequences
-    // as compute units (measured: B = 8..64 gain 3-6 us per call, B = 128 loses 3).
-    p.two_items = split > 1 && kn.get(&Knobs::sampler_two_items, (long)B * 4 <= cus ? 1 : 0) != 0;
+    p.two_items = split > 1 && two_items;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int epv = logits_dt == RESPEC_BF16 ? 8 : 4;
@@ -1325,7 +1448,7 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
                 smem = 0;                                                                                          \
                 p.tab_slots = 0;                                                                                   \
             }                                                                                                      \
-            hipLaunchKernelGGL(SHARED_KERNEL, dim3((unsigned)(B * split)), dim3(kThreads), smem, stream, p);       \
+            hipLaunchKernelGGL(SHARED_KERNEL, dim3((unsigned)(B * split)), dim3(kSharedThreads), smem, stream, p);       \
         } else {                                                                                                   \
             RESPEC_LAUNCH_SAMPLER_ONE(ONE_KERNEL);                                                                 \
         }                                                                                                          \

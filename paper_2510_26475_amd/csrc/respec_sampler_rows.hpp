@@ -236,25 +236,52 @@ struct ThreadSum {
     }
 };
 
+// Sums, maxima and prefix sums over a wave by lane-permuting adds (DPP): no LDS round trip per step,
+// as the shuffles have (six of them in a row, two words each, took 0.3 us of every pass).  All 64
+// lanes have to be active.  Lanes a row shift reads from outside its sixteen count as zero.
+template <int CTRL>
+__device__ inline double dpp_add(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+    return x + __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+__device__ inline double lane_value(double x, int lane) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, lane), hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+__device__ inline float lane_value(float x, int lane) {
+    return as_f32((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), lane));
+}
+
+template <int CTRL>
+__device__ inline float dpp_max(float x) {
+    return fmaxf(x, as_f32(__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true)));
+}
+
+// (control words of the permutations)
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;              // lane ^ 1, lane ^ 2
+constexpr int kDppOtherQuad = 0x141, kDppOtherEight = 0x140; // the other quad of eight lanes, the other eight of sixteen
+constexpr int kDppShr1 = 0x111, kDppShr2 = 0x112, kDppShr4 = 0x114, kDppShr8 = 0x118;  // lane - 1, ... of sixteen
+
 __device__ inline float wave_max(float x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
+    x = dpp_max<kDppOtherEight>(dpp_max<kDppOtherQuad>(dpp_max<kDppXor2>(dpp_max<kDppXor1>(x))));
+    return fmaxf(fmaxf(lane_value(x, 0), lane_value(x, 16)), fmaxf(lane_value(x, 32), lane_value(x, 48)));
 }
 
 __device__ inline double wave_sum(double x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-    return x;
+    x = dpp_add<kDppOtherEight>(dpp_add<kDppOtherQuad>(dpp_add<kDppXor2>(dpp_add<kDppXor1>(x))));
+    return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
 }
 
 __device__ inline double wave_inclusive_scan(double x, int lane) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const double y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    return x;
+    x = dpp_add<kDppShr8>(dpp_add<kDppShr4>(dpp_add<kDppShr2>(dpp_add<kDppShr1>(x))));
+    const double s1 = lane_value(x, 15), s2 = s1 + lane_value(x, 31), s3 = s2 + lane_value(x, 47);
+    const double before = lane < 32 ? (lane < 16 ? 0.0 : s1) : (lane < 48 ? s2 : s3);
+    return before + x;
 }
 
 // The block-wide "first thread for which `hit` holds" and "largest `last` (a value that grows
@@ -306,10 +333,29 @@ struct SharedState {
     int first_thread;
 };
 
+// Maximum and sum over groups of N neighbouring lanes (N = waves of a block); every lane of a group gets
+// the same bits.
+template <int N>
+__device__ inline float group_max(float x) {
+    static_assert(N == 4 || N == 8);
+    x = dpp_max<kDppXor2>(dpp_max<kDppXor1>(x));
+    return N == 8 ? dpp_max<kDppOtherQuad>(x) : x;
+}
+
+template <int N>
+__device__ inline double group_sum(double x) {
+    static_assert(N == 4 || N == 8);
+    x = dpp_add<kDppXor2>(dpp_add<kDppXor1>(x));
+    if constexpr (N == 8) x = dpp_add<kDppOtherQuad>(x);
+    return x;
+}
+
 // Combine the per-thread (ref, sum) pairs of the block into one (M, S) with
 // S = sum_x exp((z_x - M)/T).  Every thread returns the same bits.
+template <int TH = kThreads>
 __device__ inline void block_combine(float ref, double sum, SharedState &sh, int parity, int which,
                                      const RowMath &p, float &M, double &S) {
+    constexpr int kWaves = TH / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float mw = wave_max(ref);
     const double sw = wave_sum(sum * exp2_f64((double)(ref - mw) * p.c_d));
@@ -320,14 +366,9 @@ __device__ inline void block_combine(float ref, double sum, SharedState &sh, int
     __syncthreads();
     const int w = lane & (kWaves - 1);
     const float my_m = sh.m[parity][which][w];
-    float mm = my_m;
-#pragma unroll
-    for (int o = kWaves / 2; o >= 1; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
-    double part = sh.s[parity][which][w] * exp2_f64((double)(my_m - mm) * p.c_d);
-#pragma unroll
-    for (int o = kWaves / 2; o >= 1; o >>= 1) part += __shfl_xor(part, o);
+    const float mm = group_max<kWaves>(my_m);
     M = mm;
-    S = part;
+    S = group_sum<kWaves>(sh.s[parity][which][w] * exp2_f64((double)(my_m - mm) * p.c_d));
 }
 
 // The same for the fast pass, both rows at once.  The threads of a wave share one reference
@@ -335,9 +376,10 @@ __device__ inline void block_combine(float ref, double sum, SharedState &sh, int
 // reconcile the eight (reference, sum) pairs of each row behind a single barrier, with one fp64
 // exp2 each.  ONE_TERM: the sums were taken as exp2(z c_f + K) with K = -ref c_f rounded; the
 // residue K + ref c_f is undone in the same exp2.  Every thread returns the same bits.
-template <bool TWO, bool ONE_TERM>
+template <bool TWO, bool ONE_TERM, int TH = kThreads>
 __device__ inline void block_combine_fast(float refp, double sp, float refq, double sq, SharedState &sh, int parity,
                                           const RowMath &p, float &Mp, double &Sp, float &Mq, double &Sq) {
+    constexpr int kWaves = TH / 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const double swp = wave_sum(sp);
     const double swq = TWO ? wave_sum(sq) : 0.0;
@@ -350,21 +392,17 @@ __device__ inline void block_combine_fast(float refp, double sp, float refq, dou
         }
     }
     __syncthreads();
-    const int w = lane & (kWaves - 1), r = TWO ? (lane >> 3) & 1 : 0;  // lanes 8..15 (mod 16): the q row
+    const int w = lane & (kWaves - 1), r = TWO ? (lane / kWaves) & 1 : 0;  // (the second group of lanes: the q row)
     const float my_m = sh.m[parity][r][w];
-    float mm = my_m;
-#pragma unroll
-    for (int o = kWaves / 2; o >= 1; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
+    const float mm = group_max<kWaves>(my_m);
     double e = (double)(my_m - mm) * p.c_d;
     if constexpr (ONE_TERM) e -= (double)(-my_m * p.c_f) + (double)my_m * (double)p.c_f;
-    double part = sh.s[parity][r][w] * exp2_f64(e);
-#pragma unroll
-    for (int o = kWaves / 2; o >= 1; o >>= 1) part += __shfl_xor(part, o);
-    Mp = __shfl(mm, 0);
-    Sp = __shfl(part, 0);
+    const double part = group_sum<kWaves>(sh.s[parity][r][w] * exp2_f64(e));
+    Mp = lane_value(mm, 0);
+    Sp = lane_value(part, 0);
     if constexpr (TWO) {
-        Mq = __shfl(mm, 8);
-        Sq = __shfl(part, 8);
+        Mq = lane_value(mm, kWaves);
+        Sq = lane_value(part, kWaves);
     }
 }
 
@@ -397,8 +435,9 @@ __device__ inline float slot_max(const u32x4 &v) {
 
 // The largest logit among the first kThreads x PER of a row's nslots whole slots; every
 // thread returns the same value (-inf when none of them is finite).  Ends with a barrier.
-template <bool BF16, bool ALIGNED, int PER>
+template <bool BF16, bool ALIGNED, int PER, int TH = kThreads>
 __device__ inline float block_max_of_row_start(const void *row, int nslots, SharedState &sh) {
+    constexpr int kThreads = TH, kWaves = TH / 64;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     float m = -INFINITY;
     if ((int)threadIdx.x < nslots) {
@@ -440,12 +479,13 @@ constexpr int kRefSlots = ONE_TERM ? 1 : kUnroll;
 // non-finite or empty, and the caller then repeats the row with the guarded pass below.
 // PARTIAL: the row need not be aligned nor hold whole slots only (it has at least one); an
 // instantiation of its own, since what it adds cost whole rows 1-2 %.
-template <bool BF16, bool TWO, bool ONE_TERM, bool PARTIAL = false>
+template <bool BF16, bool TWO, bool ONE_TERM, bool PARTIAL = false, int TH = kThreads>
 __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int nslots_all, int Vrow,
                                       SharedState &sh, int parity, const RowMath &p, float &Mp,
                                       double &Sp, float &Mq, double &Sq) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int nslots = PARTIAL ? whole_slots<BF16>(nslots_all, Vrow) : nslots_all;
+    constexpr int kThreads = TH;
     constexpr int kBatch = kThreads * kUnroll;  // slots per block iteration
     const int tid = opaque_thread_index();
     float accp[EPV], accq[EPV];
@@ -549,7 +589,7 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
         if (TWO && sq > kFastMost) sq = (double)INFINITY;
     }
     // (ONE_TERM: exp2(z c + K) = exp2((z - ref) c) * exp2(K + ref c); the combine undoes the residue)
-    block_combine_fast<TWO, ONE_TERM>(refp, sp, refq, sq, sh, parity, p, Mp, Sp, Mq, Sq);
+    block_combine_fast<TWO, ONE_TERM, TH>(refp, sp, refq, sq, sh, parity, p, Mp, Sp, Mq, Sq);
     bool ok = Sp > 0.0 && Sp < 1.0e300;
     if constexpr (TWO) ok = ok && Sq > 0.0 && Sq < 1.0e300;
     return ok;
@@ -557,10 +597,11 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
 
 // Guarded streaming pass (any finite or -inf logits): per-thread references that follow the
 // running maximum.  Used when the fast pass reports an overflow or an empty sum.
-template <bool BF16, bool TWO>
+template <bool BF16, bool TWO, int TH = kThreads>
 __device__ inline void row_stats(const void *rowp, const void *rowq, int nslots, int Vrow, SharedState &sh,
                                  int parity, const RowMath &p, float &Mp, double &Sp,
                                  float &Mq, double &Sq) {
+    constexpr int kThreads = TH;
     ThreadSum<BF16> tp, tq;
     tp.init();
     tq.init();
@@ -580,8 +621,8 @@ __device__ inline void row_stats(const void *rowp, const void *rowq, int nslots,
             if constexpr (TWO) tq.absorb(vq[u], p);
         }
     }
-    block_combine(tp.ref, tp.total(), sh, parity, 0, p, Mp, Sp);
-    if constexpr (TWO) block_combine(tq.ref, tq.total(), sh, parity, 1, p, Mq, Sq);
+    block_combine<TH>(tp.ref, tp.total(), sh, parity, 0, p, Mp, Sp);
+    if constexpr (TWO) block_combine<TH>(tq.ref, tq.total(), sh, parity, 1, p, Mq, Sq);
 }
 
 // (M, S) of a short row pair in one wave: a reference and S = sum_x exp((z_x - M)/T) for each row; an

@@ -250,3 +250,41 @@ def test_normalisers_of_short_rows_are_as_exact_as_those_of_long_ones(dtype, V, 
     wrong = ((n > 0) == above) & far
     print(f"{wrong.sum()} of {far.sum()} on the wrong side")
     assert wrong.sum() <= 0.01 * far.sum()
+
+
+# Shared sequences stream two chain items as one run of batches (256 threads, four slots each): an item of one batch, of
+# exactly one, of two and three, a last batch of a slot; chains that end on either item, or on the bonus row.
+# Item two of some sequences overflows its reference (an outlier far above its first batch), or has no finite logit there.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T", [1.0, 1.3])
+@pytest.mark.parametrize("slots", [1984, 2048, 2112, 4096, 4160, 6144, 6200])
+@pytest.mark.parametrize("short", [0, 1])
+def test_two_items_of_a_shared_chain_are_one_stream(oracle, slots, short, dtype, T):
+    V = slots * (8 if dtype == "bf16" else 4) - short
+    batch = synth.make_batch(_wl(V, dtype, T), device="cuda", kv_lens=[k + 1 for k in KS], k_per_seq=KS, seed=slots + short, with_attention=False)
+    for b, qi in enumerate(batch.q_indptr.tolist()[:-1]):
+        if KS[b] == 3 and b % 8 == 0:
+            batch.target_logits[qi + 1, V - 3] = 250.0
+        if KS[b] == 2 and b % 8 == 2:
+            batch.target_logits[qi + 2, :V // 2 + 64] = float("-inf")
+    ref = oracle_sample(oracle, batch)
+    with helpers.sampler_split(2):
+        tally = compare_sampler(gpu_sample(batch), ref)
+    assert tally["flagged"] <= max(3, 0.25 * len(KS)), tally
+
+
+# The region totals of a shared draw are searched by one scan over a wave: crossings in every region, none below, and
+# regions without mass in between
+@pytest.mark.parametrize("split", [1, 2, 4, 8])
+@pytest.mark.parametrize("T", [1.0, 1.3])
+def test_crossings_in_every_region(oracle, split, T):
+    ks, V = [0] * 32, 8 * 64 * 32
+    batch = synth.make_batch(_wl(V, "bf16", T), device="cuda", kv_lens=[1] * 32, k_per_seq=ks, seed=split, with_attention=False)
+    for b in range(32):
+        if b % 2:  # mass in every third region of 64 slots only
+            keep = (torch.arange(V, device="cuda") // 512) % 3 == b % 3
+            batch.target_logits[b, ~keep] = float("-inf")
+        batch.u_final[b] = (b + 0.5) / 32 if b < 30 else (0.0, 1.0 - 2.0 ** -24)[b - 30]
+    ref = oracle_sample(oracle, batch)
+    with helpers.sampler_split(split):
+        compare_sampler(gpu_sample(batch), ref)
