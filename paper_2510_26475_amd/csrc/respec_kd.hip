@@ -663,6 +663,13 @@ int kd_team(int32_t rows, int32_t V, bool bf16) {
     return team;
 }
 
+// Whether the bytes of two [rows, V] matrices have an address in common, as far as their ends tell.
+bool ranges_meet(const void *a, int64_t ld_a, const void *b, int64_t ld_b, int32_t rows, int32_t V, size_t esz) {
+    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
+    const uintptr_t a1 = a0 + ((size_t)(rows - 1) * ld_a + V) * esz, b1 = b0 + ((size_t)(rows - 1) * ld_b + V) * esz;
+    return a0 < b1 && b0 < a1;
+}
+
 size_t kd_kl_bytes(int32_t rows, int team) { return round_up((size_t)rows * team * sizeof(double), 256); }
 size_t kd_box_bytes(int32_t rows, int team) { return team > 1 ? (size_t)rows * team * kKdBoxWords * 8 : 0; }
 
@@ -757,6 +764,11 @@ respec_status_t respec_kd_rows(const void *target_logits, const void *draft_logi
     p.row_kl = static_cast<double *>(workspace);
     p.team = kd_team(rows, V, logits_dt == RESPEC_BF16);
     if (knobs().get(&Knobs::kd_team, 1) == 0 || workspace_bytes < respec_kd_rows_workspace_bytes(rows, V, logits_dt)) p.team = 0;
+    // A gradient written over one of its inputs: a member computes an absent one's part from the rows, which
+    // that one may overwrite by then.  (One work-group per row pair reads what it writes over before.)
+    if (p.team > 1 && (ranges_meet(grad_draft_logits, ld_g, target_logits, ld_t, rows, V, esz) ||
+                       ranges_meet(grad_draft_logits, ld_g, draft_logits, ld_d, rows, V, esz)))
+        p.team = 0;
     p.box = reinterpret_cast<uint64_t *>(static_cast<char *>(workspace) + kd_kl_bytes(rows, std::max((int)p.team, 1)));
     p.rows = rows;
     p.V = V;

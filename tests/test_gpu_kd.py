@@ -218,3 +218,19 @@ def test_replays_of_a_captured_call_see_their_own_inputs(oracle):
         torch.cuda.synchronize()
         eager = gpu_kd(t2, d2, w2)
         assert torch.equal(grad.view(torch.int16), eager[0].view(torch.int16)) and torch.equal(loss, eager[1]) and torch.equal(total, eager[2])
+
+
+@pytest.mark.parametrize("dtype,V,rows", [("bf16", 151936, 20), ("bf16", 8 * 1000, 300)])
+@pytest.mark.parametrize("over", ["draft", "target"])
+def test_a_gradient_may_be_written_over_its_inputs(dtype, V, rows, over):
+    # (spin 0: members of a team would compute one another's parts from rows that are being overwritten)
+    target, draft, w = _inputs(rows, V, dtype, seed=31, zero_rows=(1,))
+    ref = gpu_kd(target, draft, w)
+    grad = draft.clone() if over == "draft" else target.clone()
+    ws = torch.empty(binding.respec_kd_rows_workspace_bytes(rows, V, binding.RESPEC_BF16), dtype=torch.uint8, device="cuda")
+    loss, total = torch.empty(rows, device="cuda"), torch.empty(1, dtype=torch.float64, device="cuda")
+    with env_setting("RESPEC_KD_SPIN", 0):
+        binding.respec_kd_rows(grad if over == "target" else target, grad if over == "draft" else draft, w, grad, loss, total, ws)
+    torch.cuda.synchronize()
+    assert float((grad.double() - ref[0].double()).abs().max()) <= 2 * (2.0 ** -8 + 5e-6) * 2.0
+    assert bool(((loss - ref[1]).abs() <= 4e-5 * (ref[1].abs() + 0.05 * w)).all())
