@@ -33,13 +33,15 @@
 namespace respec {
 namespace {
 
-// Threads of a work-group that shares its sequence with others.  Its passes are short (a part of a row) and
-// lie between reductions, barriers and exchanges, which cost less with half the waves, while four
-// waves, one per SIMD, still reach nine tenths of the issue rate of eight: bf16, V = 151,936, k = 4, T = 0.6, B = 64
-// 50.1 -> 45.8 us per call; fp32, V = 50,257, B = 32, k = 2 27.4 -> 24.4 (and 42.5 and 22.3 with the items of a
-// stage in one stream and reductions without LDS round trips).  Sequences with a work-group of their own keep 512: their
-// passes are long (mixed temperatures, B = 256 96 us, 110 with 256 threads; trees 97 / 112).
-constexpr int kSharedThreads = 256;
+// How a sequence is walked: by a work-group of its own, or by several that take one or two items of its chain per stage.
+enum Share { kOwn, kOneAtATime, kTwoAtATime };
+
+// Threads of a work-group.  The stages of two items share short passes that lie between reductions, barriers and
+// exchanges, which cost less with half the waves, while four waves, one per SIMD, still reach most of the
+// issue rate of eight (256 / 512 threads, us per call: bf16, V = 151,936, k = 4, T = 0.6, B = 64 43.1 / 45.7; V = 32,000
+// 24.8 / 28.7; fp32, V = 50,257, B = 32, k = 2 22.9 / 23.8).  Longer passes want the eight (V = 151,936 in two parts, B = 128
+// 56.0 / 53.7; whole rows at mixed temperatures, B = 256 110 / 96; trees 112 / 97).
+constexpr int share_threads(int share) { return share == kTwoAtATime ? 256 : kThreads; }
 
 struct SamplerParams : RowMath {
     const void *target;
@@ -57,7 +59,6 @@ struct SamplerParams : RowMath {
     char *boxes;       // [B] mailboxes of kBoxBytes (split > 1)
     const float *temps;  // [B] one temperature per sequence (0: greedy), or NULL: the RowMath constants hold
     int tab_slots;       // > 0: the launch carries dynamic LDS for one float per slot of a row
-    int two_items;       // shared sequences: two chain items per stage (row_stats_two_items)
 };
 
 
@@ -82,14 +83,26 @@ struct SamplerParams : RowMath {
 struct Mailbox {
     uint32_t *words;
     unsigned long long *payload;
-    uint32_t base;
+    uint32_t base;          // valid from the first exchange on
     int part, split, stage;
+    uint32_t epoch;         // thread 0: the box's epoch, requested at the start of the kernel
+    uint32_t *sh_epoch;     // LDS word it is handed to the block in
 };
 
 // One exchange.  Every thread of the block calls it with the same `mine`; afterwards
 // sh.xchg[j] holds what part j published.  Ends with a barrier.  A wait that runs out of its
 // (very large) spin budget marks the block as failed and goes on, so that every block ends.
 __device__ inline void exchange(Mailbox &mb, const double (&mine)[8], SharedState &sh) {
+    if (mb.stage == 0) {  // block-uniform; (by now the epoch has arrived: the first pass did not wait for it)
+        if (threadIdx.x == 0) {
+            *mb.sh_epoch = mb.epoch;
+            // a box that an earlier call left poisoned (one of its waits ran out) cannot be trusted
+            // until the caller has zeroed it again: every part reports failure without waiting
+            if (mb.epoch == kBoxPoison) sh.failed = 1;
+        }
+        __syncthreads();
+        mb.base = *mb.sh_epoch * 1024u;
+    }
     const int parity = mb.stage & 1;
     const uint32_t mark = mb.base + (uint32_t)mb.stage + 1u;
     const unsigned long long tag = (unsigned long long)mark << 32;
@@ -144,13 +157,14 @@ __device__ inline void exchange(Mailbox &mb, const double (&mine)[8], SharedStat
 // streams its own part (`rowp`, `rowq` point at the part's first slot, `nslots` and `Vrow`
 // are the part's); with several parts the partial results are exchanged and combined in part
 // order, so every part holds the same bits afterwards.
-template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL, int TH>
+template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL, int TH, class Meanwhile = Nothing>
 __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nslots, int Vrow, SharedState &sh,
                                      int parity, Mailbox &mb, const SamplerParams &p, float &Mp,
-                                     double &Sp, float &Mq, double &Sq) {
+                                     double &Sp, float &Mq, double &Sq, Meanwhile &&meanwhile = Nothing{}) {
+    if constexpr (!FULL) meanwhile();
     if constexpr (!SHARED) {
         if constexpr (FULL) {
-            if (row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq))
+            if (row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile))
                 return;        // block-uniform
             __syncthreads();   // every thread has read the combine buffers of this parity
         }
@@ -159,18 +173,18 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
     }
     bool ok = false;
     if (nslots <= 0) {  // a part without slots (tiny vocabulary): nothing to read, no mass
+        if constexpr (FULL) meanwhile();
         Mp = Mq = kRefInit;
         Sp = Sq = 0.0;
         ok = FULL;
     } else if constexpr (FULL) {
-        ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
+        ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile);
     }
     if constexpr (FULL) {
         const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, ok ? 1.0 : 0.0, 0.0, 0.0, 0.0};
         exchange(mb, mine, sh);
-        bool all_ok = true;
-        for (int j = 0; j < mb.split; ++j) all_ok = all_ok && sh.xchg[j][4] != 0.0;
-        ok = all_ok;   // the same in every part
+        const int j = threadIdx.x & (kMaxSplit - 1);
+        ok = __all(j >= mb.split || sh.xchg[j][4] != 0.0);   // the same in every part
     }
     if (!ok) {  // some part saw an overflow or an empty sum: all repeat with the guarded pass
         __syncthreads();
@@ -178,23 +192,17 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
         const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, 1.0, 0.0, 0.0, 0.0};
         exchange(mb, mine, sh);
     }
-    if (threadIdx.x < 2 * kMaxSplit) {  // lane 8 r + j: row r (p, q) of part j; one exp2 per lane
-        const int r = threadIdx.x / kMaxSplit, j = threadIdx.x % kMaxSplit;
-        const bool have = j < mb.split;
-        const float m_j = have ? (float)sh.xchg[j][2 * r] : -INFINITY;
-        const float M = group_max<kMaxSplit>(m_j);
-        const double S = group_sum<kMaxSplit>(have ? sh.xchg[j][2 * r + 1] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0);
-        if (j == 0) {
-            sh.comb_m[r] = M;
-            sh.comb_s[r] = S;
-        }
-    }
-    __syncthreads();
-    Mp = sh.comb_m[0];
-    Sp = sh.comb_s[0];
-    Mq = sh.comb_m[1];
-    Sq = sh.comb_s[1];
-    __syncthreads();  // comb_* and xchg may be rewritten by the next stage
+    // In every wave, so that no barrier is needed (the next exchange has one ahead of it): lane 8 r + j: row r (p, q)
+    // of part j; one exp2 per lane.
+    const int r = (threadIdx.x / kMaxSplit) & 1, j = threadIdx.x & (kMaxSplit - 1);
+    const bool have = j < mb.split;
+    const float m_j = have ? (float)sh.xchg[j][2 * r] : -INFINITY;
+    const float M = group_max<kMaxSplit>(m_j);
+    const double S = group_sum<kMaxSplit>(have ? sh.xchg[j][2 * r + 1] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0);
+    Mp = lane_value(M, 0);
+    Sp = lane_value(S, 0);
+    Mq = lane_value(M, kMaxSplit);
+    Sq = lane_value(S, kMaxSplit);
 }
 
 // The normalisers of one row pair: references and sums of the p row and the q row.
@@ -215,10 +223,10 @@ struct DrawNorm {
 // The two items are one stream of batches: B's first batch is requested ahead of A's last, and the
 // four sums are reduced together behind one barrier (one pass after the other left the memory pipeline
 // empty for 3 us of every stage).
-template <bool BF16, bool ONE_TERM, bool PARTIAL, int TH>
+template <bool BF16, bool ONE_TERM, bool PARTIAL, int TH, class Meanwhile>
 __device__ inline int row_stats_two_items(const void *pa, const void *qa, const void *pb, const void *qb,
                                           bool b_pair, int nslots_all, int Vrow, SharedState &sh, Mailbox &mb,
-                                          const SamplerParams &p, DrawNorm &A, DrawNorm &Bn) {
+                                          const SamplerParams &p, DrawNorm &A, DrawNorm &Bn, Meanwhile &&meanwhile) {
     constexpr int EPV = Elem<BF16>::EPV, kThreads = TH, kWaves = TH / 64, kBatch = kThreads * kUnroll;
     bool ok_a = true, ok_b = true;
     A.Mp = A.Mq = Bn.Mp = Bn.Mq = kRefInit;
@@ -282,7 +290,7 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
                 }
             }
             const float rp = item == 0 ? ref[0][0] : ref[1][0], rq = item == 0 ? ref[0][1] : ref[1][1];
-            if (two) {
+            if (two && at < n - 1) {
 #pragma unroll
                 for (int u = 0; u < kUnroll; ++u) {
                     fast_absorb<BF16, ONE_TERM>(vp[u], acc[0], rp, K[0], p);
@@ -290,7 +298,11 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
                 }
             } else {
 #pragma unroll
-                for (int u = 0; u < kUnroll; ++u) fast_absorb<BF16, ONE_TERM>(vp[u], acc[0], rp, K[0], p);
+                for (int u = 0; u < kUnroll; ++u) {
+                    if (at * kBatch + u * kThreads >= nslots) break;  // (nothing of the row in this group of slots)
+                    fast_absorb<BF16, ONE_TERM>(vp[u], acc[0], rp, K[0], p);
+                    if (two) fast_absorb<BF16, ONE_TERM>(vq[u], acc[1], rq, K[1], p);
+                }
             }
             if (at == n - 1) {
                 if (PARTIAL && nslots < nslots_all && tid == 0) {
@@ -309,6 +321,7 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
         };
         u32x4 vp[2][kUnroll], vq[2][kUnroll];  // one set is summed while the other's loads are in flight
         load_batch(0, vp[0], vq[0]);
+        meanwhile();
         for (int it = 0; it < 2 * n; it += 2) {
             load_batch(it + 1, vp[1], vq[1]);
             sum_batch(it, vp[0], vq[0]);
@@ -340,6 +353,8 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
             Bn.Sq = lane_value(part, 3 * kWaves);
             ok_b = ok_b && sound(Bn.Sq);
         }
+    } else {
+        meanwhile();
     }
     // two binary32 references travel as the halves of one 8-byte word (moved, never computed with)
     auto pack = [](float lo, float hi) {
@@ -349,35 +364,24 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
     const double mine[8] = {pack(A.Mp, A.Mq), A.Sp, A.Sq, pack(Bn.Mp, Bn.Mq), Bn.Sp, Bn.Sq,
                             (double)((ok_a ? 1 : 0) | (ok_b ? 2 : 0)), 0.0};
     exchange(mb, mine, sh);
-    int ok = 3;
-    for (int j = 0; j < mb.split; ++j) ok &= (int)sh.xchg[j][6];
-    if (threadIdx.x < 4 * kMaxSplit) {  // lane 8 (2 item + row) + j: part j; one exp2 per lane
-        const int g = threadIdx.x / kMaxSplit, j = threadIdx.x % kMaxSplit;
-        const int item = g >> 1, r = g & 1;
-        const bool have = j < mb.split;
-        float m_j = -INFINITY;
-        if (have) {
-            const unsigned long long w = __builtin_bit_cast(unsigned long long, sh.xchg[j][3 * item]);
-            m_j = __uint_as_float((uint32_t)(r ? w >> 32 : w & 0xffffffffull));
-        }
-        const float M = group_max<kMaxSplit>(m_j);
-        const double S = group_sum<kMaxSplit>(have ? sh.xchg[j][3 * item + 1 + r] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0);
-        if (j == 0) {
-            sh.comb2_m[item][r] = M;
-            sh.comb2_s[item][r] = S;
-        }
+    // in every wave (see row_stats_any): lane 8 (2 item + row) + j: part j; one exp2 per lane
+    const int g = (threadIdx.x / kMaxSplit) & 3, j = threadIdx.x & (kMaxSplit - 1);
+    const int item = g >> 1, r = g & 1;
+    const bool have = j < mb.split;
+    float m_j = -INFINITY;
+    int good = 3;
+    if (have) {
+        const unsigned long long w = __builtin_bit_cast(unsigned long long, sh.xchg[j][3 * item]);
+        m_j = __uint_as_float((uint32_t)(r ? w >> 32 : w & 0xffffffffull));
+        good = (int)sh.xchg[j][6];
     }
-    __syncthreads();
-    A.Mp = sh.comb2_m[0][0];
-    A.Sp = sh.comb2_s[0][0];
-    A.Mq = sh.comb2_m[0][1];
-    A.Sq = sh.comb2_s[0][1];
-    Bn.Mp = sh.comb2_m[1][0];
-    Bn.Sp = sh.comb2_s[1][0];
-    Bn.Mq = sh.comb2_m[1][1];
-    Bn.Sq = sh.comb2_s[1][1];
-    __syncthreads();  // comb2_* and xchg may be rewritten by the next stage
-    return ok;
+    const float M = group_max<kMaxSplit>(m_j);
+    const double S = group_sum<kMaxSplit>(have ? sh.xchg[j][3 * item + 1 + r] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0);
+    A.Mp = lane_value(M, 0), A.Mq = lane_value(M, kMaxSplit);
+    A.Sp = lane_value(S, 0), A.Sq = lane_value(S, kMaxSplit);
+    Bn.Mp = lane_value(M, 2 * kMaxSplit), Bn.Mq = lane_value(M, 3 * kMaxSplit);
+    Bn.Sp = lane_value(S, 2 * kMaxSplit), Bn.Sq = lane_value(S, 3 * kMaxSplit);
+    return (__all((good & 1) != 0) ? 1 : 0) | (__all((good & 2) != 0) ? 2 : 0);
 }
 
 // fp64 weights of one slot: p(x) (RESID = false) or max(0, p(x) - q(x)) (Eq. 2).
@@ -475,7 +479,6 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
     // table instead of reading the region again.
     const bool use_tab = FAST && tab != nullptr;  // block-uniform
     const double Cp = 1.0 / Sp, Cq = RESID ? 1.0 / Sq : 0.0;
-    const FastNorm fn = make_fast_norm(Mp, Sp, Mq, RESID ? Sq : Sp, p);
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
     const int whole = PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots;
     const int beg = min(wave * span, nslots), end_all = min(beg + span, nslots), end = min(end_all, whole);
@@ -497,11 +500,19 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
         // a ring of register sets: all but one are in flight while one is summed
         constexpr int NSETS = FULL ? kSetsDraw : 2;  // (the guarded loads of the general form need the registers)
         u32x4 rp[NSETS][kUnroll], rq[NSETS][kUnroll];
+        // (the loads of the steady state are unconditional: behind a condition, the wait for the
+        // batch in front of a load becomes a wait for everything in flight; batches past the
+        // region read its first slot again and are never summed)
+        constexpr int kStep = 64 * kUnroll;
+#pragma unroll
+        for (int s = 0; s + 1 < NSETS; ++s) load_batch(beg + s * kStep, rp[s], rq[s]);
+        const FastNorm fn = make_fast_norm(Mp, Sp, Mq, RESID ? Sq : Sp, p);  // (two logarithms in the loads' shadow)
         // (whole: every slot of the batch lies inside the region, which holds for all batches but
         // a region's last; the selects that a ragged batch needs are a tenth of the loop)
         auto sum_batch = [&](int s0, const u32x4 (&xp)[kUnroll], const u32x4 (&xq)[kUnroll], auto whole) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < kUnroll; ++c) {
+                if (!decltype(whole)::value && s0 + c * 64 >= end) break;  // wave-uniform
                 const bool in = decltype(whole)::value || s0 + c * 64 + lane < end;
                 const u32x4 a = in ? xp[c] : neg_inf_slot<BF16>();
                 const u32x4 b = RESID ? (in ? xq[c] : neg_inf_slot<BF16>()) : a;
@@ -518,13 +529,7 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
                 }
             }
         };
-        constexpr int kStep = 64 * kUnroll;
         const int n_b = (end - beg + kStep - 1) / kStep;  // wave-uniform, >= 1
-        // (the loads of the steady state are unconditional: behind a condition, the wait for the
-        // batch in front of a load becomes a wait for everything in flight; batches past the
-        // region read its first slot again and are never summed)
-#pragma unroll
-        for (int s = 0; s + 1 < NSETS; ++s) load_batch(beg + s * kStep, rp[s], rq[s]);
         int ib = 0;  // set s holds batch ib + s for s < NSETS - 1
         for (; ib + NSETS < n_b; ib += NSETS) {
 #pragma unroll
@@ -554,13 +559,13 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
     if (lane == 0) sh.wave_total[wave] = region_total;
 }
 
-// Choice and phase B.  `totals` are the n_reg region totals of the whole row in vocabulary order
-// (LDS); the regions [my_reg0, my_reg0 + kWaves) are those of `part`, this block's part of the
+// Choice and phase B.  `tot` are the region totals of the whole row in vocabulary order, a lane each
+// (zero in the lanes behind them); the regions [my_reg0, my_reg0 + kWaves) are those of `part`, this block's part of the
 // row.  SHARED: the totals are this block's weights times `scale` (and the other blocks' times
 // theirs).  Returns the token, or -1 with mine = false when another block holds the crossing, or
 // -1 with Z_out <= 0 when the row carries no mass.  Ends with a barrier.
 template <bool BF16, bool RESID, bool FULL, bool FAST, bool SHARED, bool PARTIAL, int TH>
-__device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, const RowPart &part,
+__device__ inline int draw_finish(double tot, int my_reg0, const RowPart &part,
                                   const DrawNorm &nm, double u, SharedState &sh, const RowMath &p, int &near_edge,
                                   double &Z_out, bool &mine, double scale) {
     constexpr int EPV = Elem<BF16>::EPV;
@@ -579,7 +584,6 @@ __device__ inline int draw_finish(const double *totals, int n_reg, int my_reg0, 
     }
     // every wave: ordered prefix over the regions, a lane each, and the region holding the crossing (one
     // thread after the other through 32 totals took 2 us of a shared draw)
-    const double tot = lane < n_reg ? totals[lane] : 0.0;
     const double incl = wave_inclusive_scan(tot, lane);
     double Z = lane_value(incl, 63);
     Z_out = Z;
@@ -872,17 +876,17 @@ __device__ inline int inverse_cdf_pass(const void *rowp, const void *rowq, int n
     draw_region_totals<BF16, RESID, FULL, FAST, PARTIAL, TH>(part, nm, sh, p);
     __syncthreads();
     // the region totals of all parts, in vocabulary order
+    const int lane = threadIdx.x & 63;
     const int n_reg = SHARED ? mb.split * kWaves : kWaves;
     if constexpr (SHARED) {
         double pub[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) pub[w] = sh.wave_total[w] * scale;
         exchange(mb, pub, sh);
-        if ((int)threadIdx.x < n_reg) sh.all_total[threadIdx.x] = sh.xchg[threadIdx.x / kWaves][threadIdx.x % kWaves];
-        __syncthreads();
     }
-    const double *totals = SHARED ? sh.all_total : sh.wave_total;
-    return draw_finish<BF16, RESID, FULL, FAST, SHARED, PARTIAL, TH>(totals, n_reg, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
+    double tot = 0.0;
+    if (lane < n_reg) tot = SHARED ? sh.xchg[lane / kWaves][lane % kWaves] : sh.wave_total[lane];
+    return draw_finish<BF16, RESID, FULL, FAST, SHARED, PARTIAL, TH>(tot, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
                                                         p, near_edge, Z_out, mine, scale);
 }
 
@@ -1025,9 +1029,10 @@ __device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, 
 }
 
 // SHORT: the form for rows of at most kShortSlots slots (one work-group per sequence).
-template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED, bool SHORT, bool PARTIAL>
+template <bool BF16, bool ONE_TERM, bool FULL, int SHARE, bool SHORT, bool PARTIAL>
 __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
-    constexpr int kThreads = SHARED ? kSharedThreads : respec::kThreads, kWaves = kThreads / 64, TH = kThreads;
+    constexpr bool SHARED = SHARE != kOwn;
+    constexpr int kThreads = share_threads(SHARE), kWaves = kThreads / 64, TH = kThreads;
     __shared__ SharedState sh;
     __shared__ uint32_t sh_epoch;
     constexpr int EPV = Elem<BF16>::EPV;
@@ -1078,26 +1083,20 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     }
     const double u_fin = (double)p.u_final[b];
 
-    Mailbox mb{nullptr, nullptr, 0u, part, split, 0};
+    Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch};
     if (threadIdx.x == 0) sh.failed = 0;
     if constexpr (SHARED) {
         mb.words = reinterpret_cast<uint32_t *>(p.boxes + (size_t)b * kBoxBytes);
         mb.payload = reinterpret_cast<unsigned long long *>(p.boxes + (size_t)b * kBoxBytes + kBoxHeaderBytes);
-        if (threadIdx.x == 0) {
-            sh_epoch = load_dev(mb.words);
-            // a box that an earlier call left poisoned (one of its waits ran out) cannot be trusted
-            // until the caller has zeroed it again: every part reports failure without waiting
-            if (sh_epoch == kBoxPoison) sh.failed = 1;
-        }
+        if (threadIdx.x == 0) mb.epoch = load_dev(mb.words);
     }
-    __syncthreads();
-    if constexpr (SHARED) mb.base = sh_epoch * 1024u;
 
     int n = 0, flag_accept = 0, flag_cdf = 0, final_token = -1;
     bool rejected = false, mine = false;
     // shared sequences walk their chain two items per stage (see row_stats_two_items); `ahead`
     // holds the normalisers of item `ahead_of` (a position, or k for the bonus token's row)
-    constexpr bool kTwoItems = SHARED && FULL;
+    constexpr bool kTwoItems = SHARE == kTwoAtATime;
+    static_assert(!kTwoItems || FULL, "the guarded form takes one item at a time");
     DrawNorm ahead{};
     int ahead_of = -1;
     float last_Mp = 0.f;  // reference of the target row of the position tested last
@@ -1109,6 +1108,22 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         if (zqx == -INFINITY) return (zpx == -INFINITY) ? 0.0 : (double)INFINITY;
         return exp((((double)zpx - (double)Mp) - ((double)zqx - (double)Mq)) * p.inv_T) * (Sq / Sp);
     };
+    // A drafted token, its two logits and the uniform of its test: requested while the position's first batch is on its
+    // way, so that neither the pass nor the test waits for a chain of dependent loads.
+    struct Draft {
+        int x;
+        float zpx, zqx;
+        double u;
+    };
+    auto draft_at = [&](int i) __attribute__((always_inline)) {
+        Draft d;
+        d.x = max(0, min(p.draft_tokens[drow0 + i], p.V - 1));  // memory safety only; ids outside [0,V) are a caller error
+        d.zpx = logit_at<BF16>(tbase + (size_t)(row0 + i) * p.ld_t * esz, d.x);
+        d.zqx = logit_at<BF16>(dbase + (size_t)(drow0 + i) * p.ld_d * esz, d.x);
+        d.u = (double)p.u_accept[drow0 + i];
+        return d;
+    };
+    Draft d{}, d_ahead{};
     // Short rows: a position's chain of loads, reductions and barriers takes 3 us whatever the row's
     // length, so eight positions are taken at a time, one per wave, rows behind a rejected position
     // read for nothing (never used).  (An instantiation of its own: tested at run time it cost the
@@ -1143,40 +1158,34 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                 __syncthreads();
             }
         }
-        // the drafted token's two logits and the uniform are requested before the streaming
-        // pass, so that the acceptance test does not start with a chain of dependent loads
-        int x = 0;
-        float zpx = 0.f, zqx = 0.f;
-        double u = 0.0;
         float Mp = 0.f, Mq = 0.f;
         double Sp = 0.0, Sq = 0.0;
         bool have = false;
         if constexpr (SHORT) {
             const int w = i & (kWaves - 1);
-            x = sh.pos_x[w];
-            u = sh.pos_u[w];
+            d.x = sh.pos_x[w];
+            d.u = sh.pos_u[w];
             Mp = sh.pos_m[0][w], Sp = sh.pos_s[0][w], Mq = sh.pos_m[1][w], Sq = sh.pos_s[1][w];
             have = true;
-        } else {
-            x = max(0, min(p.draft_tokens[drow0 + i], p.V - 1));  // memory safety only; ids outside [0,V) are a caller error
-            zpx = logit_at<BF16>(rowp, x);
-            zqx = logit_at<BF16>(rowq, x);
-            u = (double)p.u_accept[drow0 + i];
         }
         if constexpr (kTwoItems) {
-            if (ahead_of == i) {  // this position's normalisers came with the previous stage (block-uniform)
+            if (ahead_of == i) {  // this position's numbers came with the previous stage (block-uniform)
                 Mp = ahead.Mp, Sp = ahead.Sp, Mq = ahead.Mq, Sq = ahead.Sq;
+                d = d_ahead;
                 have = true;
-            } else if (p.two_items) {
+            } else {
                 // one stage for this position and the next item of the chain: position i + 1, or
                 // the bonus token's row when this is the last draft
                 const bool b_pair = i + 1 < k;
                 const char *rowpb = tbase + (size_t)(row0 + i + 1) * p.ld_t * esz;
                 const char *rowqb = b_pair ? dbase + (size_t)(drow0 + i + 1) * p.ld_d * esz : rowpb;
                 DrawNorm a;
-                const int ok = row_stats_two_items<BF16, ONE_TERM, PARTIAL, TH>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16,
-                                                                   rowpb + (size_t)lo * 16, rowqb + (size_t)lo * 16, b_pair,
-                                                                   nslots, Vrow, sh, mb, p, a, ahead);
+                const int ok = row_stats_two_items<BF16, ONE_TERM, PARTIAL, TH>(
+                    rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, rowpb + (size_t)lo * 16, rowqb + (size_t)lo * 16, b_pair,
+                    nslots, Vrow, sh, mb, p, a, ahead, [&]() __attribute__((always_inline)) {
+                        d = draft_at(i);
+                        if (b_pair) d_ahead = draft_at(i + 1);
+                    });
                 ahead_of = (ok & 2) ? i + 1 : -1;
                 if (ok & 1) {
                     Mp = a.Mp, Sp = a.Sp, Mq = a.Mq, Sq = a.Sq;
@@ -1186,15 +1195,15 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         }
         if (!have)
             row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, TH>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow, sh,
-                                                      i & 1, mb, p, Mp, Sp, Mq, Sq);
+                                                      i & 1, mb, p, Mp, Sp, Mq, Sq, [&]() __attribute__((always_inline)) { d = draft_at(i); });
         last_Mp = Mp;
         double rho;
         if constexpr (SHORT) rho = sh.pos_rho[i & (kWaves - 1)];
-        else rho = ratio(zpx, zqx, Mp, Sp, Mq, Sq);
+        else rho = ratio(d.zpx, d.zqx, Mp, Sp, Mq, Sq);
         const double thr = rho < 1.0 ? rho : 1.0;
-        if (fabs(u - thr) <= kBoundaryEps) flag_accept = 1;
-        if (u < thr) {
-            if (threadIdx.x == 0 && part == 0) out[i] = x;
+        if (fabs(d.u - thr) <= kBoundaryEps) flag_accept = 1;
+        if (d.u < thr) {
+            if (threadIdx.x == 0 && part == 0) out[i] = d.x;
             n = i + 1;
             continue;
         }
@@ -1305,26 +1314,26 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
             if (failed) {
                 __hip_atomic_fetch_max(mb.words, kBoxPoison, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             } else if (part == 0) {
-                __hip_atomic_fetch_max(mb.words, sh_epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_max(mb.words, mb.epoch + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     }
 }
 
-template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED>
-__global__ __launch_bounds__(SHARED ? kSharedThreads : kThreads) void rejection_sample_kernel(SamplerParams p) {
-    rejection_sample<BF16, ONE_TERM, FULL, SHARED, false, false>(p);
+template <bool BF16, bool ONE_TERM, bool FULL, int SHARE>
+__global__ __launch_bounds__(share_threads(SHARE)) void rejection_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, ONE_TERM, FULL, SHARE, false, false>(p);
 }
 
 // Rows that are not whole aligned slots (fp64 weights).
-template <bool BF16, bool SHARED>
-__global__ __launch_bounds__(SHARED ? kSharedThreads : kThreads) void partial_rows_sample_kernel(SamplerParams p) {
-    rejection_sample<BF16, false, true, SHARED, false, true>(p);
+template <bool BF16, int SHARE>
+__global__ __launch_bounds__(share_threads(SHARE)) void partial_rows_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, false, true, SHARE, false, true>(p);
 }
 
 template <bool BF16, bool ONE_TERM>
 __global__ __launch_bounds__(kThreads) void short_rows_sample_kernel(SamplerParams p) {
-    rejection_sample<BF16, ONE_TERM, true, false, true, !ONE_TERM>(p);
+    rejection_sample<BF16, ONE_TERM, true, kOwn, true, !ONE_TERM>(p);
 }
 
 // Both entry points: `temps` NULL = one temperature for the batch (`temperature`), else one per
@@ -1416,8 +1425,6 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         return fail(RESPEC_ERR_UNSUPPORTED, "rejection_sample: too many work-groups");
     p.split = split;
     p.boxes = static_cast<char *>(workspace);
-    p.two_items = split > 1 && two_items;
-
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const int epv = logits_dt == RESPEC_BF16 ? 8 : 4;
     const bool full = V >= epv && kn.get(&Knobs::sampler_guarded, 0) == 0;
@@ -1440,21 +1447,32 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
             p.tab_slots = (int)slots_part;
         }
     }
-// with or without sharing
-#define RESPEC_LAUNCH_SAMPLER(SHARED_KERNEL, ONE_KERNEL)                                                            \
+// several work-groups per sequence
+#define RESPEC_LAUNCH_SAMPLER_SHARED(KERNEL, SHARE)                                                                 \
     do {                                                                                                           \
-        if (split > 1) {                                                                                           \
-            if (smem > 48 * 1024) { /* (only whole rows need more than the default limit) */                      \
-                smem = 0;                                                                                          \
-                p.tab_slots = 0;                                                                                   \
-            }                                                                                                      \
-            hipLaunchKernelGGL(SHARED_KERNEL, dim3((unsigned)(B * split)), dim3(kSharedThreads), smem, stream, p);       \
-        } else {                                                                                                   \
-            RESPEC_LAUNCH_SAMPLER_ONE(ONE_KERNEL);                                                                 \
+        if (smem > 48 * 1024) { /* (only whole rows need more than the default limit) */                          \
+            smem = 0;                                                                                              \
+            p.tab_slots = 0;                                                                                       \
         }                                                                                                          \
+        hipLaunchKernelGGL(KERNEL, dim3((unsigned)(B * split)), dim3(share_threads(SHARE)), smem, stream, p);      \
     } while (0)
-#define RESPEC_LAUNCH_FORM(BF, ONE, FULL)                                                                           \
-    RESPEC_LAUNCH_SAMPLER((rejection_sample_kernel<BF, ONE, FULL, true>), (rejection_sample_kernel<BF, ONE, FULL, false>))
+#define RESPEC_LAUNCH_FORM(BF, ONE)                                                                                 \
+    do {                                                                                                           \
+        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, ONE, true, kOwn>));                 \
+        else if (two_items) RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, ONE, true, kTwoAtATime>), kTwoAtATime); \
+        else RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, ONE, true, kOneAtATime>), kOneAtATime);     \
+    } while (0)
+#define RESPEC_LAUNCH_GUARDED(BF)                                                                                   \
+    do {                                                                                                           \
+        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, false, false, kOwn>));              \
+        else RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, false, false, kOneAtATime>), kOneAtATime);  \
+    } while (0)
+#define RESPEC_LAUNCH_PARTIAL(BF)                                                                                   \
+    do {                                                                                                           \
+        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((partial_rows_sample_kernel<BF, kOwn>));                         \
+        else if (two_items) RESPEC_LAUNCH_SAMPLER_SHARED((partial_rows_sample_kernel<BF, kTwoAtATime>), kTwoAtATime); \
+        else RESPEC_LAUNCH_SAMPLER_SHARED((partial_rows_sample_kernel<BF, kOneAtATime>), kOneAtATime);             \
+    } while (0)
 // one work-group per sequence
 #define RESPEC_LAUNCH_SAMPLER_ONE(KERNEL)                                                                           \
     do {                                                                                                           \
@@ -1479,17 +1497,18 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         if (one) RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<false, true>));
         else RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<false, false>));
     } else if (!full) {
-        if (bf) RESPEC_LAUNCH_FORM(true, false, false); else RESPEC_LAUNCH_FORM(false, false, false);
+        if (bf) RESPEC_LAUNCH_GUARDED(true); else RESPEC_LAUNCH_GUARDED(false);
     } else if (!whole_rows) {
-        if (bf) RESPEC_LAUNCH_SAMPLER((partial_rows_sample_kernel<true, true>), (partial_rows_sample_kernel<true, false>));
-        else RESPEC_LAUNCH_SAMPLER((partial_rows_sample_kernel<false, true>), (partial_rows_sample_kernel<false, false>));
+        if (bf) RESPEC_LAUNCH_PARTIAL(true); else RESPEC_LAUNCH_PARTIAL(false);
     } else if (bf) {
-        if (one) RESPEC_LAUNCH_FORM(true, true, true); else RESPEC_LAUNCH_FORM(true, false, true);
+        if (one) RESPEC_LAUNCH_FORM(true, true); else RESPEC_LAUNCH_FORM(true, false);
     } else {
-        if (one) RESPEC_LAUNCH_FORM(false, true, true); else RESPEC_LAUNCH_FORM(false, false, true);
+        if (one) RESPEC_LAUNCH_FORM(false, true); else RESPEC_LAUNCH_FORM(false, false);
     }
 #undef RESPEC_LAUNCH_FORM
-#undef RESPEC_LAUNCH_SAMPLER
+#undef RESPEC_LAUNCH_GUARDED
+#undef RESPEC_LAUNCH_PARTIAL
+#undef RESPEC_LAUNCH_SAMPLER_SHARED
 #undef RESPEC_LAUNCH_SAMPLER_ONE
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess)

@@ -314,12 +314,7 @@ struct SharedState {
     double s[2][2][kWaves];
     double wave_total[kWaves];
     double scan_total[kWaves];
-    double all_total[kMaxSplit * kWaves];  // region totals of every part, in vocabulary order
     double xchg[kMaxSplit][8];             // what the parts published in the current stage
-    float comb_m[2];                       // combined (M, S) of the p row and the q row
-    double comb_s[2];
-    float comb2_m[2][2];                   // the same for the two items of a double stage: [item][p/q]
-    double comb2_s[2][2];
     int failed;                            // a bounded wait for a partner ran out
     float arg_val[kWaves];                 // per-wave (largest logit, its first token) of an argmax pass
     int arg_idx[kWaves];
@@ -478,11 +473,16 @@ constexpr int kRefSlots = ONE_TERM ? 1 : kUnroll;
 // reference would overflow.  Returns false (every thread alike) when a sum came out
 // non-finite or empty, and the caller then repeats the row with the guarded pass below.
 // PARTIAL: the row need not be aligned nor hold whole slots only (it has at least one); an
-// instantiation of its own, since what it adds cost whole rows 1-2 %.
-template <bool BF16, bool TWO, bool ONE_TERM, bool PARTIAL = false, int TH = kThreads>
+// instantiation of its own, since what it adds cost whole rows 1-2 %.  `meanwhile` is called once the
+// first batch has been requested.
+struct Nothing {
+    __device__ inline void operator()() const {}
+};
+
+template <bool BF16, bool TWO, bool ONE_TERM, bool PARTIAL = false, int TH = kThreads, class Meanwhile = Nothing>
 __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int nslots_all, int Vrow,
                                       SharedState &sh, int parity, const RowMath &p, float &Mp,
-                                      double &Sp, float &Mq, double &Sq) {
+                                      double &Sp, float &Mq, double &Sq, Meanwhile &&meanwhile = Nothing{}) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int nslots = PARTIAL ? whole_slots<BF16>(nslots_all, Vrow) : nslots_all;
     constexpr int kThreads = TH;
@@ -532,6 +532,7 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
     u32x4 rp[NSETS][kUnroll], rq[NSETS][kUnroll];
 #pragma unroll
     for (int s = 0; s + 1 < NSETS; ++s) load_batch(s, rp[s], rq[s]);
+    meanwhile();
     if (n_iter == 1) mask_last(rp[0], rq[0]);  // block-uniform
     {   // references from the first batch
         float mp = slot_max<BF16>(rp[0][0]), mq = -INFINITY;
@@ -548,9 +549,11 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
             Kq = -refq * p.c_f;
         }
     }
-    auto absorb_batch = [&](const u32x4 (&xp)[kUnroll], const u32x4 (&xq)[kUnroll]) __attribute__((always_inline)) {
+    // (live: of the batch's kUnroll groups of slots, those with a slot inside the row; block-uniform)
+    auto absorb_batch = [&](const u32x4 (&xp)[kUnroll], const u32x4 (&xq)[kUnroll], int live) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
+            if (u >= live) break;
             fast_absorb<BF16, ONE_TERM>(xp[u], accp, refp, Kp, p);
             if constexpr (TWO) fast_absorb<BF16, ONE_TERM>(xq[u], accq, refq, Kq, p);
         }
@@ -561,7 +564,7 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
         for (int s = 0; s < NSETS; ++s) {
             constexpr int kAhead = NSETS - 1;
             load_batch(it + s + kAhead, rp[(s + kAhead) % NSETS], rq[(s + kAhead) % NSETS]);
-            absorb_batch(rp[s], rq[s]);
+            absorb_batch(rp[s], rq[s], kUnroll);
         }
     }
     // the last 1..NSETS batches
@@ -570,8 +573,12 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
 #pragma unroll
     for (int s = 0; s < NSETS; ++s) {
         if (s < rem) {
-            if (s == rem - 1) mask_last(rp[s], rq[s]);  // (a second time when the row has one batch: harmless)
-            absorb_batch(rp[s], rq[s]);
+            if (s == rem - 1) {
+                mask_last(rp[s], rq[s]);  // (a second time when the row has one batch: harmless)
+                absorb_batch(rp[s], rq[s], (nslots - (n_iter - 1) * kBatch + kThreads - 1) / kThreads);
+            } else {
+                absorb_batch(rp[s], rq[s], kUnroll);
+            }
         }
     }
     if (PARTIAL && nslots < nslots_all && tid == 0) {  // the row's partial slot

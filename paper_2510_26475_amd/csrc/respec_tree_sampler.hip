@@ -198,6 +198,7 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
         auto sum_batch = [&](int s0, const u32x4 (&xp)[kUnroll], const u32x4 (&xq)[kUnroll], auto whole) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < kUnroll; ++c) {
+                if (!decltype(whole)::value && s0 + c * 64 >= end) break;  // wave-uniform
                 const bool in = decltype(whole)::value || s0 + c * 64 + lane < end;  // slots past the region count as -inf
                 const u32x4 a = in ? xp[c] : neg_inf_slot<BF16>(), b = in ? xq[c] : neg_inf_slot<BF16>();
                 if constexpr (FAST) {
