@@ -384,10 +384,12 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
     return (__all((good & 1) != 0) ? 1 : 0) | (__all((good & 2) != 0) ? 2 : 0);
 }
 
-// fp64 weights of one slot: p(x) (RESID = false) or max(0, p(x) - q(x)) (Eq. 2).
+// fp64 weights of one slot, times Sp: p(x) (RESID = false) or max(0, p(x) - q(x)) (Eq. 2), that is
+// max(0, pe - qe g) with g = Sp / Sq.  (A draw only compares running sums with u times their total.  Multiplying both
+// exponentials by their normalisers' reciprocals took two operations more per element of this pass, which is
+// bound by instruction issue, and rounded twice more.)
 template <bool BF16, bool RESID>
-__device__ inline void slot_weights(const u32x4 &vp, const u32x4 &vq, float Mp, double Cp, float Mq,
-                                    double Cq, const RowMath &p,
+__device__ inline void slot_weights(const u32x4 &vp, const u32x4 &vq, float Mp, float Mq, double g, const RowMath &p,
                                     double (&w)[Elem<BF16>::EPV]) {
     constexpr int EPV = Elem<BF16>::EPV;
     float zp[EPV], zq[EPV];
@@ -395,10 +397,10 @@ __device__ inline void slot_weights(const u32x4 &vp, const u32x4 &vq, float Mp, 
     if constexpr (RESID) unpack<BF16>(vq, zq);
 #pragma unroll
     for (int j = 0; j < EPV; ++j) {
-        const double pe = (double)hw_exp2(exp2_arg(zp[j], Mp, p.c_hi, p.c_lo)) * Cp;
+        const double pe = (double)hw_exp2(exp2_arg(zp[j], Mp, p.c_hi, p.c_lo));
         if constexpr (RESID) {
-            const double qe = (double)hw_exp2(exp2_arg(zq[j], Mq, p.c_hi, p.c_lo)) * Cq;
-            w[j] = fmax(pe - qe, 0.0);
+            const double qe = (double)hw_exp2(exp2_arg(zq[j], Mq, p.c_hi, p.c_lo));
+            w[j] = fmax(fma(-qe, g, pe), 0.0);
         } else {
             w[j] = pe;
         }
@@ -478,7 +480,7 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
     // FAST with a table: phase A leaves every slot's total there, and phase B works from the
     // table instead of reading the region again.
     const bool use_tab = FAST && tab != nullptr;  // block-uniform
-    const double Cp = 1.0 / Sp, Cq = RESID ? 1.0 / Sq : 0.0;
+    const double g = RESID ? Sp / Sq : 0.0;
     const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
     const int whole = PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots;
     const int beg = min(wave * span, nslots), end_all = min(beg + span, nslots), end = min(end_all, whole);
@@ -523,7 +525,7 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
                     if (use_tab && in) tab[s0 + c * 64 + lane] = ts;
                 } else {
                     double w[EPV];
-                    slot_weights<BF16, RESID>(a, b, Mp, Cp, Mq, Cq, p, w);
+                    slot_weights<BF16, RESID>(a, b, Mp, Mq, g, p, w);
 #pragma unroll
                     for (int j = 0; j < EPV; ++j) lane_sum += w[j];
                 }
@@ -549,7 +551,7 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
         if (beg <= whole && whole < end_all && lane == 0) {  // the row's partial slot
             const u32x4 a = load_partial_slot<BF16>(rowp, whole, Vrow), b = RESID ? load_partial_slot<BF16>(rowq, whole, Vrow) : a;
             double w[EPV];
-            slot_weights<BF16, RESID>(a, b, Mp, Cp, Mq, Cq, p, w);
+            slot_weights<BF16, RESID>(a, b, Mp, Mq, g, p, w);
 #pragma unroll
             for (int j = 0; j < EPV; ++j) lane_sum += w[j];
         }
@@ -574,7 +576,7 @@ __device__ inline int draw_finish(double tot, int my_reg0, const RowPart &part,
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     const float Mp = nm.Mp, Mq = nm.Mq;
     const double Sp = nm.Sp, Sq = nm.Sq;
-    const double Cp = 1.0 / Sp, Cq = RESID ? 1.0 / Sq : 0.0;
+    const double g = RESID ? Sp / Sq : 0.0;
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, RESID ? Sq : Sp, p);
     if (threadIdx.x == 0) {
         sh.token = -1;
@@ -758,7 +760,7 @@ __device__ inline int draw_finish(double tot, int my_reg0, const RowPart &part,
                     if (w[e] > 0.f) my_last = tok_off + (c0 + j) * EPV + e;
             } else {
                 double w[EPV];
-                slot_weights<BF16, RESID>(vp[j], vq[j], Mp, Cp, Mq, Cq, p, w);
+                slot_weights<BF16, RESID>(vp[j], vq[j], Mp, Mq, g, p, w);
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) {
                     st += w[e];
@@ -798,7 +800,7 @@ __device__ inline int draw_finish(double tot, int my_reg0, const RowPart &part,
 #pragma unroll
                 for (int e = 0; e < EPV; ++e) w[e] = (double)wf[e];
             } else {
-                slot_weights<BF16, RESID>(vp, vq, Mp, Cp, Mq, Cq, p, w);
+                slot_weights<BF16, RESID>(vp, vq, Mp, Mq, g, p, w);
             }
 #pragma unroll
             for (int e = 0; e < EPV; ++e) {
