@@ -1322,15 +1322,25 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     }
 }
 
-template <bool BF16, bool ONE_TERM, bool FULL, int SHARE>
-__global__ __launch_bounds__(share_threads(SHARE)) void rejection_sample_kernel(SamplerParams p) {
-    rejection_sample<BF16, ONE_TERM, FULL, SHARE, false, false>(p);
+template <bool BF16, bool ONE_TERM, bool FULL, bool SHARED>
+__global__ __launch_bounds__(kThreads) void rejection_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, ONE_TERM, FULL, SHARED ? kOneAtATime : kOwn, false, false>(p);
+}
+
+template <bool BF16, bool ONE_TERM>
+__global__ __launch_bounds__(share_threads(kTwoAtATime)) void two_items_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, ONE_TERM, true, kTwoAtATime, false, false>(p);
 }
 
 // Rows that are not whole aligned slots (fp64 weights).
-template <bool BF16, int SHARE>
-__global__ __launch_bounds__(share_threads(SHARE)) void partial_rows_sample_kernel(SamplerParams p) {
-    rejection_sample<BF16, false, true, SHARE, false, true>(p);
+template <bool BF16, bool SHARED>
+__global__ __launch_bounds__(kThreads) void partial_rows_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, false, true, SHARED ? kOneAtATime : kOwn, false, true>(p);
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(share_threads(kTwoAtATime)) void partial_rows_two_items_kernel(SamplerParams p) {
+    rejection_sample<BF16, false, true, kTwoAtATime, false, true>(p);
 }
 
 template <bool BF16, bool ONE_TERM>
@@ -1460,20 +1470,20 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
     } while (0)
 #define RESPEC_LAUNCH_FORM(BF, ONE)                                                                                 \
     do {                                                                                                           \
-        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, ONE, true, kOwn>));                 \
-        else if (two_items) RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, ONE, true, kTwoAtATime>), kTwoAtATime); \
-        else RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, ONE, true, kOneAtATime>), kOneAtATime);     \
+        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, ONE, true, false>));                 \
+        else if (two_items) RESPEC_LAUNCH_SAMPLER_SHARED((two_items_sample_kernel<BF, ONE>), kTwoAtATime); \
+        else RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, ONE, true, true>), kOneAtATime);     \
     } while (0)
 #define RESPEC_LAUNCH_GUARDED(BF)                                                                                   \
     do {                                                                                                           \
-        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, false, false, kOwn>));              \
-        else RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, false, false, kOneAtATime>), kOneAtATime);  \
+        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, false, false, false>));              \
+        else RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, false, false, true>), kOneAtATime);  \
     } while (0)
 #define RESPEC_LAUNCH_PARTIAL(BF)                                                                                   \
     do {                                                                                                           \
-        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((partial_rows_sample_kernel<BF, kOwn>));                         \
-        else if (two_items) RESPEC_LAUNCH_SAMPLER_SHARED((partial_rows_sample_kernel<BF, kTwoAtATime>), kTwoAtATime); \
-        else RESPEC_LAUNCH_SAMPLER_SHARED((partial_rows_sample_kernel<BF, kOneAtATime>), kOneAtATime);             \
+        if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((partial_rows_sample_kernel<BF, false>));                         \
+        else if (two_items) RESPEC_LAUNCH_SAMPLER_SHARED((partial_rows_two_items_kernel<BF>), kTwoAtATime); \
+        else RESPEC_LAUNCH_SAMPLER_SHARED((partial_rows_sample_kernel<BF, true>), kOneAtATime);             \
     } while (0)
 // one work-group per sequence
 #define RESPEC_LAUNCH_SAMPLER_ONE(KERNEL)                                                                           \
