@@ -10,7 +10,7 @@
 // Parallelisation.  The chain of positions of one sequence is sequential and its length
 // differs from sequence to sequence, so one work-group per sequence leaves most of the
 // device idle when there are fewer sequences than compute units.  A sequence can therefore
-// be shared by SPLIT work-groups of 256 threads (one per compute unit), each owning a
+// be shared by SPLIT work-groups (one per compute unit), each owning a
 // contiguous part of the vocabulary.  After every streaming pass the parts exchange their
 // partial results (a few numbers) through a small mailbox in the workspace and then take
 // the same decision from the same numbers.  An exchange costs a few memory round trips, so
