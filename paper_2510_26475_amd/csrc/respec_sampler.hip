@@ -174,6 +174,7 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
     bool ok = false;
     if (nslots <= 0) {  // a part without slots (tiny vocabulary): nothing to read, no mass
         if constexpr (FULL) meanwhile();
+        __syncthreads();  // (in place of the pass's own: every wave has read what the last exchange brought)
         Mp = Mq = kRefInit;
         Sp = Sq = 0.0;
         ok = FULL;
@@ -355,6 +356,7 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
         }
     } else {
         meanwhile();
+        __syncthreads();  // (as in row_stats_any)
     }
     // two binary32 references travel as the halves of one 8-byte word (moved, never computed with)
     auto pack = [](float lo, float hi) {
