@@ -559,7 +559,10 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
         }
     }
     double region_total = wave_sum(lane_sum);
-    if (PARTIAL && region_total > kFastMost) region_total = (double)INFINITY;
+    // (The bound holds for weights against a reference that nothing is known of, those of the one-pass draw, whose
+    // normaliser is taken as 1 and whose caller falls back.  A draw that has the normaliser adds up to at most that: it has
+    // nothing to fall back to, and a sum of 2^41 may well be what the normaliser's pass found.)
+    if (PARTIAL && region_total > kFastMost * Sp) region_total = (double)INFINITY;
     if (lane == 0) sh.wave_total[wave] = region_total;
 }
 

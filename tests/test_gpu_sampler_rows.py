@@ -164,8 +164,11 @@ def _compare_forms(form, batch, ref):
         torch.cuda.synchronize()
         compare_sampler((toks.cpu().numpy(), n.cpu().numpy(), flags.cpu().numpy()), ref)
     else:
-        with helpers.sampler_split(2 if form == "shared" else 1), helpers.env_setting("RESPEC_SAMPLER_TWO_ITEMS", 0):
-            compare_sampler(gpu_sample(batch), ref)
+        with helpers.sampler_split(1 if form == "one work-group" else 2), helpers.env_setting("RESPEC_SAMPLER_TWO_ITEMS", int(form == "two items")):
+            toks, n, flags = gpu_sample(batch)
+        compare_sampler((toks, n, flags), ref)
+        return toks, n, flags
+    return (toks, n, flags) if isinstance(toks, np.ndarray) else (toks.cpu().numpy(), n.cpu().numpy(), flags.cpu().numpy())
 
 
 # A weight 121 binary orders above the reference that it is formed against has an exponent rounded to
@@ -221,6 +224,37 @@ def test_heavy_tokens_far_behind_the_start_of_an_odd_row(oracle, form, what, T):
     if what == "accept":
         assert B // 5 < ref[1].sum() < B  # (uniforms above 1 among them: never accepted)
     _compare_forms(form, batch, ref)
+
+
+# Four tokens 27.5 T (39.7 binary orders) above the rest of a row, in the slots of four threads of one region: no thread's
+# sum calls for the guarded pass, and the sum over the row is 2^41.7 of its reference.  A draw that has the
+# normaliser (the residual's, and the second of a bonus row's two) has to take such a total for what it is.  (The
+# slots lie behind the first batch of every form: 2048 slots of a row or of the second half of a shared one.)
+@pytest.mark.parametrize("T,above", [(1.0, 27.5), (0.4, 11.0)])
+@pytest.mark.parametrize("what", ["bonus", "residual"])
+@pytest.mark.parametrize("form", ["one work-group", "shared", "two items", "per sequence", "tree"])
+@pytest.mark.parametrize("dtype,V,gap,slot", [("f32", 50257, 0, 8836), ("bf16", 50257, 0, 5700), ("f32", 50256, 1, 8836)])
+def test_tokens_just_inside_the_range_of_a_reference(oracle, dtype, V, gap, slot, form, what, T, above):
+    B, epv = 32, 8 if dtype == "bf16" else 4
+    gen = torch.Generator().manual_seed(V + slot)
+    rows = -0.5 - torch.rand((2 * B, V), generator=gen)
+    rows[:, ::64] = 0.0                           # every wave's reference
+    heavy = [epv * (slot + j) + j % epv for j in range(4)]
+    hot = slice(1, None, 2) if what == "bonus" else slice(0, None, 2)
+    rows[hot, heavy] = above
+    batch = synth.make_batch(_wl(V, dtype, T), device="cuda", kv_lens=[2] * B, k_per_seq=[1] * B, seed=1, with_attention=False)
+    batch.target_logits.copy_(rows)
+    batch.draft_logits.copy_(rows[0::2] if what == "bonus" else rows[1::2])
+    batch.draft_tokens.fill_(7)
+    batch.u_accept.fill_(0.5)                     # p = q: accepted; p(7) a millionth of q(7): rejected
+    batch.u_final.copy_((torch.arange(B) + 0.5) / B)
+    ref = oracle_sample(oracle, batch)
+    assert not ref[2].any() and (ref[1] == (1 if what == "bonus" else 0)).all()
+    if gap:
+        batch.target_logits, batch.draft_logits = _spread(batch.target_logits, gap, 0), _spread(batch.draft_logits, gap, 0)
+    got = _compare_forms(form, batch, ref)
+    drawn = got[0][np.arange(B), got[1]]
+    assert set(drawn.tolist()) == set(heavy)      # (nothing else has a millionth of the mass, flagged or not)
 
 
 # Short rows are summed by one wave, long ones by the block; neither may be the less exact one.  The
