@@ -346,7 +346,7 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
         const double part = group_sum<kWaves>(sh.s[x >> 1][x & 1][w] * exp2_f64(e));
         A.Mp = lane_value(mm, 0), A.Mq = lane_value(mm, kWaves), Bn.Mp = lane_value(mm, 2 * kWaves);
         A.Sp = lane_value(part, 0), A.Sq = lane_value(part, kWaves), Bn.Sp = lane_value(part, 2 * kWaves);
-        auto sound = [](double S) { return S > 0.0 && S < 1.0e300; };
+        auto sound = [](double S) { return S > kFastLeast && S < 1.0e300; };
         ok_a = sound(A.Sp) && sound(A.Sq);
         ok_b = sound(Bn.Sp);
         if (b_pair) {

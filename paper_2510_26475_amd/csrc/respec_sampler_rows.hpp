@@ -460,6 +460,11 @@ __device__ inline float block_max_of_row_start(const void *row, int nslots, Shar
 // to 127 orders above their reference were summed, with exponents rounded to 2^-18 instead of 2^-20.)
 constexpr double kFastMost = 0x1p40;
 
+// A wave whose first slots hold no finite logit sums against 0: what lies below 2^-126 there is lost, at most 2^-108 of a
+// row.  The row's reference is then at least 0, so a sum above this bound cannot miss it; one below is left to
+// the guarded pass.  (Sums against references that are logits of the row are 1 and more.)
+constexpr double kFastLeast = 0x1p-72;
+
 // Slots per thread that the one-pass draws take their reference from.  A binary32 exponent is exact to
 // 2^-24 of its own size, so a weight loses accuracy with its distance from the reference.  The forms
 // with fp64 weights look as far into the row as the normaliser pass (whose reference they would
@@ -471,7 +476,7 @@ constexpr int kRefSlots = ONE_TERM ? 1 : kUnroll;
 // reference of a wave is the maximum of the first slots it reads, not the row maximum:
 // exp2 keeps full relative precision for any offset, only a logit more than ~88/c above the
 // reference would overflow.  Returns false (every thread alike) when a sum came out
-// non-finite or empty, and the caller then repeats the row with the guarded pass below.
+// non-finite, empty or next to empty, and the caller then repeats the row with the guarded pass below.
 // PARTIAL: the row need not be aligned nor hold whole slots only (it has at least one); an
 // instantiation of its own, since what it adds cost whole rows 1-2 %.  `meanwhile` is called once the
 // first batch has been requested.
@@ -597,8 +602,8 @@ __device__ inline bool row_stats_fast(const void *rowp, const void *rowq, int ns
     }
     // (ONE_TERM: exp2(z c + K) = exp2((z - ref) c) * exp2(K + ref c); the combine undoes the residue)
     block_combine_fast<TWO, ONE_TERM, TH>(refp, sp, refq, sq, sh, parity, p, Mp, Sp, Mq, Sq);
-    bool ok = Sp > 0.0 && Sp < 1.0e300;
-    if constexpr (TWO) ok = ok && Sq > 0.0 && Sq < 1.0e300;
+    bool ok = Sp > kFastLeast && Sp < 1.0e300;
+    if constexpr (TWO) ok = ok && Sq > kFastLeast && Sq < 1.0e300;
     return ok;
 }
 

@@ -257,6 +257,38 @@ def test_tokens_just_inside_the_range_of_a_reference(oracle, dtype, V, gap, slot
     assert set(drawn.tolist()) == set(heavy)      # (nothing else has a millionth of the mass, flagged or not)
 
 
+# Waves whose first slots hold no finite logit have no reference of their own, and most of the row's mass far below 1 in their
+# later ones (120 T: an exponential against 0 is less than binary32 has).  Acceptance tests at half and at twice the ratio; the sum
+# without those slots is a quarter of the row's.
+@pytest.mark.parametrize("T", [1.0, 1.3])
+@pytest.mark.parametrize("form", ["one work-group", "shared", "two items", "per sequence", "tree"])
+@pytest.mark.parametrize("dtype,odd", [("f32", 0), ("bf16", 0), ("f32", 1)])
+def test_waves_without_a_finite_logit_in_their_first_slots(oracle, dtype, odd, form, T):
+    B, epv, T64 = 32, 8 if dtype == "bf16" else 4, float(np.float32(T))
+    V = epv * 8192 + odd
+    gen = torch.Generator().manual_seed(V)
+    slot = torch.arange(V) // epv
+    wave = slot % 256 < 64                        # of the first batches of every form: all of their slots, and others
+    target = torch.randn((2 * B, V), generator=gen) - 120.0 * T64
+    target[:, wave] += 3.0 * T64
+    target[0::2, wave & (slot % 4096 < 2048)] = float("-inf")
+    draft = torch.randn((B, V), generator=gen)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    target, draft = target.to(dt), draft.to(dt)
+    zp, zq = target[0::2].double() / T64, draft.double() / T64
+    ratio = torch.exp((zp - zp.logsumexp(1, keepdim=True)) - (zq - zq.logsumexp(1, keepdim=True)))
+    x = ((ratio > 0.1) & (ratio < 0.45)).int().argmax(1)
+    rho = ratio[torch.arange(B), x]
+    batch = synth.make_batch(_wl(V, dtype, T), device="cuda", kv_lens=[2] * B, k_per_seq=[1] * B, seed=1, with_attention=False)
+    batch.target_logits.copy_(target)
+    batch.draft_logits.copy_(draft)
+    batch.draft_tokens.copy_(x.to(torch.int32))
+    batch.u_accept.copy_(torch.where(torch.arange(B) % 2 == 0, 0.5 * rho, 2.0 * rho))
+    ref = oracle_sample(oracle, batch)
+    assert (ref[1] == (np.arange(B) + 1) % 2).all() and (ref[2] != 0).sum() <= B // 8
+    _compare_forms(form, batch, ref)
+
+
 # Short rows are summed by one wave, long ones by the block; neither may be the less exact one.  The
 # acceptance test is taken in 64 bits, so uniforms one binary32 step from the ratio show the error of
 # the normalisers: their sums over 2048 elements are good to about 3e-9 (exp2's last bit, averaged over
