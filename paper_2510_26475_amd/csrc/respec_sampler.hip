@@ -156,7 +156,8 @@ __device__ inline void exchange(Mailbox &mb, const double (&mine)[8], SharedStat
 // (M, S) of a row (and, if TWO, of the drafter row) over the whole vocabulary.  This block
 // streams its own part (`rowp`, `rowq` point at the part's first slot, `nslots` and `Vrow`
 // are the part's); with several parts the partial results are exchanged and combined in part
-// order, so every part holds the same bits afterwards.
+// order, so every part holds the same bits afterwards.  A part whose fast pass overflowed or came out empty repeats
+// it by itself, the others wait for it in the exchange.
 template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL, int TH, class Meanwhile = Nothing>
 __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nslots, int Vrow, SharedState &sh,
                                      int parity, Mailbox &mb, const SamplerParams &p, float &Mp,
@@ -171,28 +172,20 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
         row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
         return;
     }
-    bool ok = false;
+    bool ok = false;  // block-uniform
     if (nslots <= 0) {  // a part without slots (tiny vocabulary): nothing to read, no mass
         if constexpr (FULL) meanwhile();
         __syncthreads();  // (in place of the pass's own: every wave has read what the last exchange brought)
         Mp = Mq = kRefInit;
         Sp = Sq = 0.0;
-        ok = FULL;
+        ok = true;
     } else if constexpr (FULL) {
         ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile);
+        if (!ok) __syncthreads();  // every thread has read the combine buffers of this parity
     }
-    if constexpr (FULL) {
-        const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, ok ? 1.0 : 0.0, 0.0, 0.0, 0.0};
-        exchange(mb, mine, sh);
-        const int j = threadIdx.x & (kMaxSplit - 1);
-        ok = __all(j >= mb.split || sh.xchg[j][4] != 0.0);   // the same in every part
-    }
-    if (!ok) {  // some part saw an overflow or an empty sum: all repeat with the guarded pass
-        __syncthreads();
-        row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
-        const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, 1.0, 0.0, 0.0, 0.0};
-        exchange(mb, mine, sh);
-    }
+    if (!ok) row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
+    const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, 0.0, 0.0, 0.0, 0.0};
+    exchange(mb, mine, sh);
     // In every wave, so that no barrier is needed (the next exchange has one ahead of it): lane 8 r + j: row r (p, q)
     // of part j; one exp2 per lane.
     const int r = (threadIdx.x / kMaxSplit) & 1, j = threadIdx.x & (kMaxSplit - 1);
@@ -212,30 +205,35 @@ struct DrawNorm {
     double Sp, Sq;
 };
 
-// Shared sequences, fast pass only: the normalisers of two consecutive items of a chain in one
+// Shared sequences: the normalisers of two consecutive items of a chain in one
 // stage.  Item A is the row pair of position i, item B the row pair of position i + 1 or, when
 // i + 1 is past the last draft, the target row of the bonus token alone (b_pair false).  B is
 // streamed before A's acceptance test is known: when A rejects, B's bytes were read for nothing,
 // but a shared sequence runs on compute units that would otherwise idle, an exchange costs more
-// than a part's pass over a row pair, and this halves the exchanges of a chain.  Returns bit 0 if
-// A's numbers are valid and bit 1 if B's are (every part returns the same); an item whose fast
-// pass overflowed or came out empty in some part is repeated by the caller the ordinary way.
+// than a part's pass over a row pair, and this halves the exchanges of a chain.
+//
+// Numbers that a part cannot vouch for (an overflow, or a sum of next to nothing beside a wave without a reference) are
+// taken again by that part with the guarded pass, while the others wait in the exchange.  A part without
+// any finite logit (most of the vocabulary masked) is no such case where two batches are all of it: a wave that finds none
+// in the first takes kRefInit, against which a finite logit of the second overflows, so that a sum of 0 is one.  (When every
+// part repeated such items twice, one by one: k = 4, all but the first sixth masked, bf16, V = 32,000, B = 64 83 us, now 24,
+// nothing masked 23.5, by one work-group 28; V = 151,936, B = 64 158, now 84.)
 //
 // The two items are one stream of batches: B's first batch is requested ahead of A's last, and the
 // four sums are reduced together behind one barrier (one pass after the other left the memory pipeline
 // empty for 3 us of every stage).
 template <bool BF16, bool ONE_TERM, bool PARTIAL, int TH, class Meanwhile>
-__device__ inline int row_stats_two_items(const void *pa, const void *qa, const void *pb, const void *qb,
-                                          bool b_pair, int nslots_all, int Vrow, SharedState &sh, Mailbox &mb,
-                                          const SamplerParams &p, DrawNorm &A, DrawNorm &Bn, Meanwhile &&meanwhile) {
+__device__ inline void row_stats_two_items(const void *pa, const void *qa, const void *pb, const void *qb,
+                                           bool b_pair, int nslots_all, int Vrow, SharedState &sh, Mailbox &mb,
+                                           const SamplerParams &p, DrawNorm &A, DrawNorm &Bn, Meanwhile &&meanwhile) {
     constexpr int EPV = Elem<BF16>::EPV, kThreads = TH, kWaves = TH / 64, kBatch = kThreads * kUnroll;
-    bool ok_a = true, ok_b = true;
     A.Mp = A.Mq = Bn.Mp = Bn.Mq = kRefInit;
     A.Sp = A.Sq = Bn.Sp = Bn.Sq = 0.0;
     if (nslots_all > 0) {  // (a part without slots has nothing to read and no mass)
         const int nslots = PARTIAL ? whole_slots<BF16>(nslots_all, Vrow) : nslots_all;
         const int tid = opaque_thread_index(), lane = tid & 63, wave = threadIdx.x >> 6;
         const int n = (nslots + kBatch - 1) / kBatch;  // batches of an item; block-uniform, >= 1
+        const float no_ref = n <= 2 ? kRefInit : 0.f;
         float ref[2][2] = {{0.f, 0.f}, {0.f, 0.f}}, acc[2][EPV], K[2] = {0.f, 0.f};  // [item][p/q]; acc, K: the current item's
         double sum[2][2] = {{0.0, 0.0}, {0.0, 0.0}};
         u32x4 part_slot[2][2];
@@ -283,7 +281,7 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
                     const float w = wave_max(m[r]);
-                    const float f = (w > -INFINITY && w < INFINITY) ? w : 0.f;
+                    const float f = (w > -INFINITY && w < INFINITY) ? w : no_ref;
                     K[r] = -f * p.c_f;
                     if (item == 0) ref[0][r] = f; else ref[1][r] = f;
 #pragma unroll
@@ -343,16 +341,40 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
         const float my_m = sh.m[x >> 1][x & 1][w], mm = group_max<kWaves>(my_m);
         double e = (double)(my_m - mm) * p.c_d;
         if constexpr (ONE_TERM) e -= (double)(-my_m * p.c_f) + (double)my_m * (double)p.c_f;
-        const double part = group_sum<kWaves>(sh.s[x >> 1][x & 1][w] * exp2_f64(e));
+        const double s_w = sh.s[x >> 1][x & 1][w];
+        const double part = group_sum<kWaves>(s_w != 0.0 ? s_w * exp2_f64(e) : 0.0);  // (kRefInit c_f is rounded to 2^76)
+        const bool sound = (part > kFastLeast && part < 1.0e300) || (part == 0.0 && mm == kRefInit);
+        const unsigned long long doubts = __ballot(!sound && (x < 3 || b_pair)) & ((1ull << (4 * kWaves)) - 1);
         A.Mp = lane_value(mm, 0), A.Mq = lane_value(mm, kWaves), Bn.Mp = lane_value(mm, 2 * kWaves);
         A.Sp = lane_value(part, 0), A.Sq = lane_value(part, kWaves), Bn.Sp = lane_value(part, 2 * kWaves);
-        auto sound = [](double S) { return S > kFastLeast && S < 1.0e300; };
-        ok_a = sound(A.Sp) && sound(A.Sq);
-        ok_b = sound(Bn.Sp);
         if (b_pair) {
             Bn.Mq = lane_value(mm, 3 * kWaves);
             Bn.Sq = lane_value(part, 3 * kWaves);
-            ok_b = ok_b && sound(Bn.Sq);
+        }
+#pragma unroll 1
+        for (int item = 0; item < 2; ++item) {
+            if (__builtin_expect(((doubts >> (item * 2 * kWaves)) & ((1ull << (2 * kWaves)) - 1)) == 0, 1)) continue;  // block-uniform
+            // (the guarded pass a slot at a time: as unrolled as row_stats it is 20 KB of instructions in the way of every call)
+            const void *rowp = item == 0 ? pa : pb, *rowq = item == 0 ? qa : qb;
+            ThreadSum<BF16> t[2];
+            t[0].init();
+            t[1].init();
+            auto load = [&](const void *row, int s) __attribute__((always_inline)) {
+                if constexpr (!PARTIAL) return load_slot<BF16, true, false, true>(row, s, Vrow);
+                const u32x4 v = load_slot_or_last<BF16>(row, s, Vrow);
+                return s < nslots ? v : partial_slot<BF16>(v, nslots, Vrow);
+            };
+#pragma unroll 1
+            for (int s = tid; s < nslots_all; s += kThreads) {
+                const u32x4 vp = load(rowp, s), vq = load(rowq, s);
+                t[0].absorb(vp, p);
+                t[1].absorb(vq, p);
+            }
+            __syncthreads();  // every thread has read the combine buffers
+            DrawNorm d;
+            block_combine<TH>(t[0].ref, t[0].total(), sh, item, 0, p, d.Mp, d.Sp);
+            block_combine<TH>(t[1].ref, t[1].total(), sh, item, 1, p, d.Mq, d.Sq);
+            if (item == 0) A = d; else Bn = d;
         }
     } else {
         meanwhile();
@@ -363,19 +385,16 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
         return __builtin_bit_cast(double, (unsigned long long)__float_as_uint(lo) |
                                               ((unsigned long long)__float_as_uint(hi) << 32));
     };
-    const double mine[8] = {pack(A.Mp, A.Mq), A.Sp, A.Sq, pack(Bn.Mp, Bn.Mq), Bn.Sp, Bn.Sq,
-                            (double)((ok_a ? 1 : 0) | (ok_b ? 2 : 0)), 0.0};
+    const double mine[8] = {pack(A.Mp, A.Mq), A.Sp, A.Sq, pack(Bn.Mp, Bn.Mq), Bn.Sp, Bn.Sq, 0.0, 0.0};
     exchange(mb, mine, sh);
     // in every wave (see row_stats_any): lane 8 (2 item + row) + j: part j; one exp2 per lane
     const int g = (threadIdx.x / kMaxSplit) & 3, j = threadIdx.x & (kMaxSplit - 1);
     const int item = g >> 1, r = g & 1;
     const bool have = j < mb.split;
     float m_j = -INFINITY;
-    int good = 3;
     if (have) {
         const unsigned long long w = __builtin_bit_cast(unsigned long long, sh.xchg[j][3 * item]);
         m_j = __uint_as_float((uint32_t)(r ? w >> 32 : w & 0xffffffffull));
-        good = (int)sh.xchg[j][6];
     }
     const float M = group_max<kMaxSplit>(m_j);
     const double S = group_sum<kMaxSplit>(have ? sh.xchg[j][3 * item + 1 + r] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0);
@@ -383,7 +402,6 @@ __device__ inline int row_stats_two_items(const void *pa, const void *qa, const 
     A.Sp = lane_value(S, 0), A.Sq = lane_value(S, kMaxSplit);
     Bn.Mp = lane_value(M, 2 * kMaxSplit), Bn.Mq = lane_value(M, 3 * kMaxSplit);
     Bn.Sp = lane_value(S, 2 * kMaxSplit), Bn.Sq = lane_value(S, 3 * kMaxSplit);
-    return (__all((good & 1) != 0) ? 1 : 0) | (__all((good & 2) != 0) ? 2 : 0);
 }
 
 // fp64 weights of one slot, times Sp: p(x) (RESID = false) or max(0, p(x) - q(x)) (Eq. 2), that is
@@ -1167,19 +1185,16 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         }
         float Mp = 0.f, Mq = 0.f;
         double Sp = 0.0, Sq = 0.0;
-        bool have = false;
         if constexpr (SHORT) {
             const int w = i & (kWaves - 1);
             d.x = sh.pos_x[w];
             d.u = sh.pos_u[w];
             Mp = sh.pos_m[0][w], Sp = sh.pos_s[0][w], Mq = sh.pos_m[1][w], Sq = sh.pos_s[1][w];
-            have = true;
         }
         if constexpr (kTwoItems) {
             if (ahead_of == i) {  // this position's numbers came with the previous stage (block-uniform)
                 Mp = ahead.Mp, Sp = ahead.Sp, Mq = ahead.Mq, Sq = ahead.Sq;
                 d = d_ahead;
-                have = true;
             } else {
                 // one stage for this position and the next item of the chain: position i + 1, or
                 // the bonus token's row when this is the last draft
@@ -1187,22 +1202,19 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                 const char *rowpb = tbase + (size_t)(row0 + i + 1) * p.ld_t * esz;
                 const char *rowqb = b_pair ? dbase + (size_t)(drow0 + i + 1) * p.ld_d * esz : rowpb;
                 DrawNorm a;
-                const int ok = row_stats_two_items<BF16, ONE_TERM, PARTIAL, TH>(
+                row_stats_two_items<BF16, ONE_TERM, PARTIAL, TH>(
                     rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, rowpb + (size_t)lo * 16, rowqb + (size_t)lo * 16, b_pair,
                     nslots, Vrow, sh, mb, p, a, ahead, [&]() __attribute__((always_inline)) {
                         d = draft_at(i);
                         if (b_pair) d_ahead = draft_at(i + 1);
                     });
-                ahead_of = (ok & 2) ? i + 1 : -1;
-                if (ok & 1) {
-                    Mp = a.Mp, Sp = a.Sp, Mq = a.Mq, Sq = a.Sq;
-                    have = true;
-                }
+                ahead_of = i + 1;
+                Mp = a.Mp, Sp = a.Sp, Mq = a.Mq, Sq = a.Sq;
             }
-        }
-        if (!have)
+        } else if constexpr (!SHORT) {
             row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, TH>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow, sh,
                                                       i & 1, mb, p, Mp, Sp, Mq, Sq, [&]() __attribute__((always_inline)) { d = draft_at(i); });
+        }
         last_Mp = Mp;
         double rho;
         if constexpr (SHORT) rho = sh.pos_rho[i & (kWaves - 1)];
@@ -1238,14 +1250,19 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         // weight.  (A reference of another row may lie far above this one: the small weights are then
         // lost below 2^-126 while the total is still positive.)  The blocks of a shared sequence bring
         // their fp64 totals to one scale, weights against last_Mp, which all of them hold (a sequence
-        // without drafts, or whose bonus row came with the last stage, goes the ordinary way).  A total
-        // that is not a positive number in the middle of the fp64 range (an outlier far above M0, a
-        // part that starts without any finite logit) leaves the draw to the two passes below; every
-        // block sees the same total and decides alike.
+        // without drafts, or whose bonus row came with the last stage, goes the ordinary way); a part that starts
+        // without any finite logit looks for one further on, and one that has none has no mass.  A total
+        // that is not a positive number in the middle of the fp64 range (an outlier far above M0)
+        // leaves the draw to the two passes below; every block sees the same total and decides alike.
         if (!rejected && (!SHARED || (k > 0 && ahead_of != k))) {
             scan_row = tbase + (size_t)(row0 + k) * p.ld_t * esz;
             const char *part_row = scan_row + (size_t)lo * 16;
-            float M0 = block_max_of_row_start<BF16, !PARTIAL, kRefSlots<ONE_TERM>, TH>(part_row, PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots, sh);
+            const int whole = PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots;
+            float M0 = block_max_of_row_start<BF16, !PARTIAL, kRefSlots<ONE_TERM>, TH>(part_row, whole, sh);
+            if constexpr (SHARED) {  // block-uniform
+                for (int at = kRefSlots<ONE_TERM> * TH; M0 == -INFINITY && at < whole; at += kUnroll * TH)
+                    M0 = block_max_of_row_start<BF16, !PARTIAL, kUnroll, TH>(part_row + (size_t)at * 16, whole - at, sh);
+            }
             const bool usable = M0 > -INFINITY && M0 < INFINITY;  // block-uniform
             double scale = 1.0;
             if constexpr (SHARED) {
@@ -1253,9 +1270,9 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                     // what the weights are formed with: exp2(z c_f + K) or exp2((z - M0) c)
                     if constexpr (kFastScan) scale = exp2_f64(-(double)make_fast_norm(M0, 1.0, M0, 1.0, p).Kp - (double)last_Mp * (double)p.c_f);
                     else scale = exp2_f64(((double)M0 - (double)last_Mp) * p.c_d);
-                } else {
+                } else {  // no mass, unless the partial slot has some
+                    scale = M0 == -INFINITY && whole == nslots ? 1.0 : (double)NAN;
                     M0 = 0.f;
-                    scale = nslots > 0 ? (double)NAN : 1.0;  // (a part without slots has no mass)
                 }
             }
             if (SHARED || usable) {
@@ -1431,7 +1448,7 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         if (forced == 1 || forced == 2 || forced == 4 || forced == 8) split = (int)forced;
         // The parts of a sequence wait for one another, so all of them have to be on the device at
         // once: never more work-groups than compute units, whatever the knob asks for.  And a
-        // pass's mark has ten bits for the stage: very long draft chains take one work-group.
+        // pass's mark has ten bits for the stage (at most one per position, and four): very long draft chains take one work-group.
         while (split > 1 && (long)B * split > cus) split /= 2;
         // the part that holds a row's partial slot also holds whole ones
         if (V % epv0 != 0)

@@ -354,3 +354,86 @@ def test_crossings_in_every_region(oracle, split, T):
     ref = oracle_sample(oracle, batch)
     with helpers.sampler_split(split):
         compare_sampler(gpu_sample(batch), ref)
+
+
+# Masked vocabularies: the finite logits of a row lie in one stretch (its start, its end, across the middle, one token), of a
+# target row and its drafter's row not always in the same, so that some parts of a shared row have none.  A part
+# of one batch of its work-group, of two, of three; odd rows, whose last part may hold nothing but the partial slot.
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T", [1.0, 1.3])
+@pytest.mark.parametrize("slots,split", [(1024, 2), (4096, 4), (2048, 2), (4096, 2), (6200, 2)])
+@pytest.mark.parametrize("odd", [0, 1])
+@pytest.mark.parametrize("two_items", [0, 1])
+def test_parts_without_a_finite_logit(oracle, two_items, odd, slots, split, T, dtype):
+    V = slots * (8 if dtype == "bf16" else 4) + odd
+    batch = synth.make_batch(_wl(V, dtype, T), device="cuda", kv_lens=[k + 1 for k in KS], k_per_seq=KS, seed=slots, with_attention=False)
+    keep = [slice(0, V // 6), slice(V - V // 7, V), slice(V // 2 - 100, V // 2 + 2000), slice(V - 1, V), slice(0, V), slice(3, 4)]
+    draft_row = 0
+    for b, qi in enumerate(batch.q_indptr.tolist()[:-1]):
+        for i in range(KS[b] + 1):
+            t, kept = batch.target_logits[qi + i], keep[(b + 5 * i) % 6]
+            finite = t[kept].clone()
+            t.fill_(float("-inf"))
+            t[kept] = finite
+            if i < KS[b]:
+                q = batch.draft_logits[draft_row]
+                if b % 3:                      # (b % 3 == 0: the drafter's row is not masked)
+                    q[torch.isinf(t)] = float("-inf")
+                if b % 2:                      # a token that the target allows
+                    batch.draft_tokens[draft_row] = int(torch.argmax(t.float()))
+                draft_row += 1
+    ref = oracle_sample(oracle, batch)
+    with helpers.sampler_split(split), helpers.env_setting("RESPEC_SAMPLER_TWO_ITEMS", two_items):
+        tally = compare_sampler(gpu_sample(batch), ref)
+    assert tally["flagged"] <= 0.25 * len(KS), tally
+
+
+# Such a part used to make every part of its sequence repeat its passes one by one: 83 us against 24 of an unmasked call, and 28
+# of one work-group.  (24 us now; the bound leaves room for a busy device.)
+def test_a_masked_vocabulary_does_not_slow_a_shared_sequence():
+    B, V, k = 64, 32000, 4
+    batch = synth.make_batch(_wl(V, "bf16", 1.0), device="cuda", kv_lens=[k + 1] * B, k_per_seq=[k] * B, seed=1, with_attention=False)
+    ws = helpers.sampler_workspace(B, V, binding.RESPEC_BF16, "cuda")
+    out = torch.empty((B, k + 1), dtype=torch.int32, device="cuda")
+    n, flags = (torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(2))
+
+    def us_per_call():
+        times = []
+        for _ in range(7):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            for _ in range(40):
+                binding.respec_rejection_sample(batch.target_logits, batch.draft_logits, batch.draft_tokens, batch.q_indptr, batch.u_accept,
+                                                batch.u_final, out, n, flags, k, 1.0, workspace=ws)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end) / 40 * 1e3)
+        return sorted(times)[3]
+
+    us_per_call()
+    plain = us_per_call()
+    batch.target_logits[:, V // 6:] = float("-inf")
+    batch.draft_logits[:, V // 6:] = float("-inf")
+    batch.draft_tokens.copy_(torch.multinomial(torch.softmax(batch.draft_logits.float(), 1), 1)[:, 0])
+    masked = us_per_call()
+    print(f"{plain:.1f} us, masked {masked:.1f} us")
+    assert masked <= 2.0 * plain
+
+
+# A stage's mark has ten bits.  With three exchanges per position (each of these has a part without finite logits, but the first
+# two) a chain of 342 drafts left words in the mailbox with the mark of the next call's first stage.
+def test_a_long_chain_leaves_no_words_that_the_next_call_could_take(oracle):
+    V, k = 8 * 64 * 8, 342
+    batch = synth.make_batch(_wl(V, "bf16", 1.0), device="cuda", kv_lens=[k + 1], k_per_seq=[k], seed=3, with_attention=False)
+    batch.target_logits[2:, V // 2:] = float("-inf")
+    batch.draft_logits.copy_(batch.target_logits[:k])
+    batch.draft_tokens.copy_(torch.argmax(batch.target_logits[:k].float(), 1))
+    ws = torch.zeros(binding.respec_rejection_sample_workspace_bytes(1, k + 1, V, binding.RESPEC_BF16), dtype=torch.uint8, device="cuda")
+    for u, accepted in ((0.5, k), (1.5, 0), (0.5, k)):    # (identical rows: every draft is accepted; above 1: none)
+        batch.u_accept.fill_(u)
+        ref = oracle_sample(oracle, batch)
+        assert ref[1][0] == accepted
+        with helpers.sampler_split(2), helpers.env_setting("RESPEC_SAMPLER_TWO_ITEMS", 1):
+            got = gpu_sample(batch, workspace=ws)
+        assert got[1][0] == accepted
+        compare_sampler(got, ref)
