@@ -13,6 +13,7 @@
 // Numerics: exp2 of one element in fp32 (hardware exp2, two-term constant), row sums carried in
 // fp64, p and q formed in the log2 domain in fp32 (relative error about 2e-6), the KL terms
 // summed per thread in fp32 over one batch of slots (at most 32 terms) and in fp64 from there on.
+#include "respec_kd_absent.hpp"
 #include "respec_sampler_rows.hpp"
 
 #include <algorithm>
@@ -360,7 +361,12 @@ __device__ inline void kd_fold(float &M, double &S, const RowMath &p) {
 // non-temporal stores 404 us, plain loads 387 us.
 //
 // A member that does not answer within `spin` (its work-group is not running yet: another stream's kernels
-// hold the device) is not needed: its part is computed from the rows, with the same operations in the same order.
+// hold the device) is not needed: its part is computed from the rows, with the same operations in the same order, by one wave
+// of every other member; on the rows behind that it is waited for a sixteenth as long until it answers again (KdAbsent).
+// Beside other streams' kernels the form is no slower than one work-group per row pair that streams it twice (2048 rows of 151,936
+// bf16 logits, us per call, streamed / by teams, and ms until both streams were done: beside attention over 256 sequences
+// 632 / 587, 9.9 / 8.8; samplers of 64 sequences 464 / 427, 10.3 / 9.2; bf16 products of 8192 818 / 722, 9.8 / 8.7 (9.4 to
+// 9.8 when an absent member was waited for in full on every row); scans of 32 long rows 483 / 487, 13.0 / 10.5).
 template <bool BF16>
 __global__ __launch_bounds__(kKdThreads) void kd_team_kernel(KdParams p) {
     constexpr int EPV = Elem<BF16>::EPV;
@@ -480,7 +486,7 @@ __global__ __launch_bounds__(kKdThreads) void kd_team_kernel(KdParams p) {
         while (r < p.rows && weight[r] == 0.f) r += teams;
         return r;
     };
-    uint32_t absent = 0;  // members that did not answer in time
+    KdAbsent absent;  // wave-uniform
     auto write_kl = [&](int i) {  // of row number i
         double t = lane < kWaves ? sh.kl[i & 1][lane] : 0.0;
 #pragma unroll
@@ -536,13 +542,10 @@ __global__ __launch_bounds__(kKdThreads) void kd_team_kernel(KdParams p) {
                         }
                     }
                 }
-                if (!__any(missing != 0)) {
-                    absent = 0;
-                    break;
-                }
-                const bool out_of_time = wall_clock64() - t0 >= (uint64_t)p.spin;
+                if (!__any(missing != 0)) break;
+                const uint64_t waited = wall_clock64() - t0;
                 uint32_t give_up = 0;
-                if (out_of_time || absent != 0) {
+                if (waited >= (uint64_t)p.spin || absent.known != 0) {
                     uint32_t late = 0;  // members with a missing word
 #pragma unroll
                     for (int u = 0; u < kPer; ++u) {
@@ -551,8 +554,7 @@ __global__ __launch_bounds__(kKdThreads) void kd_team_kernel(KdParams p) {
                         for (int x = 0; x < 64 / kKdBoxWords; ++x)
                             if ((b >> (x * kKdBoxWords)) & 0xff) late |= 1u << (u * (64 / kKdBoxWords) + x);
                     }
-                    absent = out_of_time ? late : late & absent;
-                    give_up = absent;
+                    give_up = absent.give_up(late, waited, (uint64_t)p.spin);
                 }
                 while (give_up != 0) {
                     const int m = __builtin_ctz(give_up);
@@ -585,6 +587,7 @@ __global__ __launch_bounds__(kKdThreads) void kd_team_kernel(KdParams p) {
                 }
                 __builtin_amdgcn_s_sleep(1);
             }
+            absent.row_done();
         }
         // lanes 0..31: the members' p parts, 32..63: the q parts
         const int m = lane & 31, which = lane >> 5;

@@ -173,6 +173,16 @@ def test_a_member_that_is_not_heard_of_is_computed_to_the_same_bits(rows):
         assert torch.equal(x.view(torch.int16) if x.dtype == torch.bfloat16 else x, y.view(torch.int16) if y.dtype == torch.bfloat16 else y)
 
 
+@pytest.mark.parametrize("spin", [16, 200])   # 160 ns and 2 us: some members are given up on some rows, and waited for again
+def test_members_that_are_late_now_and_then_change_no_bits(spin):
+    target, draft, w = _inputs(200, 151936, "bf16", seed=33, zero_rows=(5, 70))
+    a = gpu_kd(target, draft, w)
+    with env_setting("RESPEC_KD_SPIN", spin):
+        b = gpu_kd(target, draft, w)
+    for x, y in zip(a, b):
+        assert torch.equal(x.view(torch.int16) if x.dtype == torch.bfloat16 else x, y.view(torch.int16) if y.dtype == torch.bfloat16 else y)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_references_of_a_wave_that_do_not_hold(oracle, dtype):
     # a wave's first piece masked, without any piece at all, and an element 2^128 above the wave's first piece
