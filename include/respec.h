@@ -441,7 +441,8 @@ respec_status_t respec_tree_rejection_sample(const void *target_logits, const vo
  *   V * sizeof(element), the strides in bytes and the three base pointers must be multiples of
  *   16 (RESPEC_ERR_UNSUPPORTED otherwise).
  *   workspace     respec_kd_rows_workspace_bytes(rows, V, logits_dt) bytes, 256-byte aligned,
- *                 scratch (nothing to prepare, nothing survives).  8 * rows bytes (rounded up to 256) are
+ *                 scratch (nothing to prepare, nothing survives).  The size is enough for any smaller number
+ *                 of rows of the same V and type.  8 * rows bytes (rounded up to 256) are
  *                 accepted too: the rows are then streamed twice.
  * Asynchronous on hip_stream like every other call; sums are formed in a fixed order, so a call
  * repeated on the same inputs gives the same bits.

@@ -675,6 +675,11 @@ bool ranges_meet(const void *a, int64_t ld_a, const void *b, int64_t ld_b, int32
 
 size_t kd_kl_bytes(int32_t rows, int team) { return round_up((size_t)rows * team * sizeof(double), 256); }
 size_t kd_box_bytes(int32_t rows, int team) { return team > 1 ? (size_t)rows * team * kKdBoxWords * 8 : 0; }
+// What a call takes, the streaming form's share where no team does.
+size_t kd_call_bytes(int32_t rows, int32_t V, bool bf16) {
+    const int team = kd_team(rows, V, bf16);
+    return kd_kl_bytes(rows, std::max(team, 1)) + round_up(kd_box_bytes(rows, team), 256);
+}
 
 template <bool BF16>
 hipError_t launch_kd_team(KdParams &p, int cus, hipStream_t stream) {
@@ -730,8 +735,11 @@ extern "C" {
 size_t respec_kd_rows_workspace_bytes(int32_t rows, int32_t V, respec_dtype_t dt) {
     using namespace respec;
     if (rows <= 0 || V <= 0 || (dt != RESPEC_F32 && dt != RESPEC_BF16)) return 0;
-    const int team = kd_team(rows, V, dt == RESPEC_BF16);
-    return kd_kl_bytes(rows, std::max(team, 1)) + round_up(kd_box_bytes(rows, team), 256);
+    // Fewer rows may be shared by more work-groups and take more room: enough for any number up to these (from kKdFill rows on
+    // teams are as small as they get, and the call with the most rows takes the most)
+    size_t most = kd_call_bytes(rows, V, dt == RESPEC_BF16);
+    for (int32_t r = std::min(rows, (int32_t)kKdFill); r >= 1; --r) most = std::max(most, kd_call_bytes(r, V, dt == RESPEC_BF16));
+    return most;
 }
 
 respec_status_t respec_kd_rows(const void *target_logits, const void *draft_logits, const float *row_weight,
@@ -766,7 +774,7 @@ respec_status_t respec_kd_rows(const void *target_logits, const void *draft_logi
     p.total_loss = total_loss;
     p.row_kl = static_cast<double *>(workspace);
     p.team = kd_team(rows, V, logits_dt == RESPEC_BF16);
-    if (knobs().get(&Knobs::kd_team, 1) == 0 || workspace_bytes < respec_kd_rows_workspace_bytes(rows, V, logits_dt)) p.team = 0;
+    if (knobs().get(&Knobs::kd_team, 1) == 0 || workspace_bytes < kd_call_bytes(rows, V, logits_dt == RESPEC_BF16)) p.team = 0;
     // A gradient written over one of its inputs: a member computes an absent one's part from the rows, which
     // that one may overwrite by then.  (One work-group per row pair reads what it writes over before.)
     if (p.team > 1 && (ranges_meet(grad_draft_logits, ld_g, target_logits, ld_t, rows, V, esz) ||

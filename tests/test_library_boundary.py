@@ -49,6 +49,15 @@ def test_workspace_query(lib):
     assert lib.respec_rejection_sample_workspace_bytes(0, 0, 151936, binding.RESPEC_BF16) == 0
 
 
+def test_a_distillation_workspace_is_enough_for_fewer_rows(lib):
+    # (fewer rows are shared by more work-groups: a call with a buffer sized for the largest one must not lose its form)
+    size = lib.respec_kd_rows_workspace_bytes
+    for dt, epv in ((binding.RESPEC_BF16, 8), (binding.RESPEC_F32, 4)):
+        for V in (epv, 8000, 16000, 20480, 32000, 50256, 96000, 128000, 151936, 400000, 32 * 2432 * epv, 32 * 2432 * epv + epv):
+            sizes = [size(rows, V, dt) for rows in list(range(1, 600)) + [1023, 1024, 2047, 2048, 4096]]
+            assert all(s % 256 == 0 and s >= 8 for s in sizes) and sizes == sorted(sizes), (V, dt)
+
+
 def test_attention_argument_errors_need_no_gpu(lib):
     null = ctypes.c_void_p(None)
     bogus = ctypes.c_void_p(0x1000)
