@@ -7,8 +7,9 @@
 // The gradient of a row needs both normalisers of the row first, so a row pair has to be kept, or
 // read twice, between the two passes over it.  kd_team_kernel keeps it: a team of work-groups holds
 // a row pair in its LDS, a part each, and exchanges the parts' normalisers through the workspace.
-// kd_stream_kernel is the form for rows too long for any team, and for workspaces without
-// room for the exchange: one work-group per row pair, which it streams twice.
+// kd_stream_kernel is the form for rows too long for any team, for rows that a team does not pay for (kd_team), for a gradient
+// written over its inputs where a team would have several members, and for workspaces without room for the
+// exchange: one work-group per row pair, which it streams twice.
 //
 // Numerics: exp2 of one element in fp32 (hardware exp2, two-term constant), row sums carried in
 // fp64, p and q formed in the log2 domain in fp32 (relative error about 2e-6), the KL terms
@@ -27,6 +28,11 @@ extern "C" __device__ float legacy_mul(float, float) __asm("llvm.amdgcn.fmul.leg
 
 namespace respec {
 namespace {
+
+// Both kernels form an exponent's argument with one multiply-add: the temperature is 1, and log2(e) rounds well
+// (RowMath::one_term).
+constexpr double kLog2e = 1.4426950408889634074;
+static_assert((double)(float)kLog2e / kLog2e - 1.0 <= 2.0e-8 && 1.0 - (double)(float)kLog2e / kLog2e <= 2.0e-8);
 
 struct KdParams : RowMath {
     const void *target;
@@ -93,24 +99,17 @@ __global__ __launch_bounds__(kThreads) void kd_stream_kernel(KdParams p) {
         const char *rq = static_cast<const char *>(p.draft) + (size_t)r * p.ld_d * esz;
         float Mp, Mq;
         double Sp, Sq;
-        const bool ok = p.one_term
-                            ? row_stats_fast<BF16, true, true>(rp, rq, nslots, p.V, sh.rows, parity, p, Mp, Sp, Mq, Sq)
-                            : row_stats_fast<BF16, true, false>(rp, rq, nslots, p.V, sh.rows, parity, p, Mp, Sp, Mq, Sq);
-        if (!ok) {  // block-uniform: an overflow or an empty sum, repeat with running references
-            __syncthreads();
+        if (!row_stats_fast<BF16, true, true>(rp, rq, nslots, p.V, sh.rows, parity, p, Mp, Sp, Mq, Sq)) {
+            __syncthreads();  // block-uniform: an overflow or an empty sum, repeat with running references
             row_stats<BF16, true>(rp, rq, nslots, p.V, sh.rows, parity, p, Mp, Sp, Mq, Sq);
         }
         parity ^= 1;
-        // log2 of the normalisers; p = exp2((z - Mp) c - lsp), q alike
-        const float lsp = (float)log2(Sp), lsq = (float)log2(Sq);
-        // One-term form (the exponent constant rounds well, as log2(e) does): the log2 of a
-        // probability is one multiply-add, z c_f + K with K = -M c_f - log2(S) rounded to
+        // The log2 of a probability is one multiply-add, z c_f + K with K = -M c_f - log2(S) rounded to
         // binary32; what the rounding of K leaves out (dKa, dKb, a few 1e-7) shifts every term
         // of the row's KL alike and is put back once per row.
         const double ka = -(double)Mp * (double)p.c_f - log2(Sp), kb = -(double)Mq * (double)p.c_f - log2(Sq);
         const float Ka = (float)ka, Kb = (float)kb;
         const double kl_shift = (ka - (double)Ka) - (kb - (double)Kb);
-        const bool one_term = p.one_term != 0;  // block-uniform
         auto load_batch = [&](int it, u32x4 (&vp)[kUnroll], u32x4 (&vq)[kUnroll]) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
@@ -122,9 +121,8 @@ __global__ __launch_bounds__(kThreads) void kd_stream_kernel(KdParams p) {
             }
         };
         double kl = 0.0;
-        // `one`: the one-term form of the log2-probabilities; `whole`: every slot of the batch lies
-        // inside the row (all batches but the row's last, which the pass takes first)
-        auto work_batch = [&](int it, const u32x4 (&xp)[kUnroll], const u32x4 (&xq)[kUnroll], auto one, auto whole) __attribute__((always_inline)) {
+        // `whole`: every slot of the batch lies inside the row (all batches but the row's last, which the pass takes first)
+        auto work_batch = [&](int it, const u32x4 (&xp)[kUnroll], const u32x4 (&xq)[kUnroll], auto whole) __attribute__((always_inline)) {
             float klb = 0.f;
 #pragma unroll
             for (int u = 0; u < kUnroll; ++u) {
@@ -135,14 +133,7 @@ __global__ __launch_bounds__(kThreads) void kd_stream_kernel(KdParams p) {
                     unpack<BF16>(xq[u], zq);
 #pragma unroll
                     for (int j = 0; j < EPV; ++j) {
-                        float a, b;
-                        if constexpr (decltype(one)::value) {
-                            a = fmaf(zp[j], p.c_f, Ka);
-                            b = fmaf(zq[j], p.c_f, Kb);
-                        } else {
-                            a = exp2_arg(zp[j], Mp, p.c_hi, p.c_lo) - lsp;
-                            b = exp2_arg(zq[j], Mq, p.c_hi, p.c_lo) - lsq;
-                        }
+                        const float a = fmaf(zp[j], p.c_f, Ka), b = fmaf(zq[j], p.c_f, Kb);
                         const float pe = hw_exp2(a), qe = hw_exp2(b);
                         // (a token without target mass adds nothing, whatever a - b is then, -inf
                         // minus -inf included: the legacy multiply takes 0 times anything as 0)
@@ -158,33 +149,32 @@ __global__ __launch_bounds__(kThreads) void kd_stream_kernel(KdParams p) {
         // two register sets take turns: one batch is worked on while the next one's loads are in
         // flight.  (The loads of the steady state are unconditional: behind a condition the wait
         // for the batch in front of a load becomes a wait for everything in flight.)
-        auto pass2 = [&](auto one) __attribute__((always_inline)) {
+        auto pass2 = [&]() __attribute__((always_inline)) {
             constexpr std::true_type whole{};
             u32x4 vp[kUnroll], vq[kUnroll], wp[kUnroll], wq[kUnroll];
             load_batch(n_iter - 1, vp, vq);
             if (n_iter == 1) {
-                work_batch(0, vp, vq, one, std::false_type{});
+                work_batch(0, vp, vq, std::false_type{});
                 return;
             }
             load_batch(n_iter - 2, wp, wq);
-            work_batch(n_iter - 1, vp, vq, one, std::false_type{});  // the row's last, ragged batch
+            work_batch(n_iter - 1, vp, vq, std::false_type{});  // the row's last, ragged batch
             int it = n_iter - 2;  // wp holds batch `it`
             for (; it >= 2; it -= 2) {
                 load_batch(it - 1, vp, vq);
-                work_batch(it, wp, wq, one, whole);
+                work_batch(it, wp, wq, whole);
                 load_batch(it - 2, wp, wq);
-                work_batch(it - 1, vp, vq, one, whole);
+                work_batch(it - 1, vp, vq, whole);
             }
             if (it == 1) {
                 load_batch(0, vp, vq);
-                work_batch(1, wp, wq, one, whole);
-                work_batch(0, vp, vq, one, whole);
+                work_batch(1, wp, wq, whole);
+                work_batch(0, vp, vq, whole);
             } else {
-                work_batch(0, wp, wq, one, whole);
+                work_batch(0, wp, wq, whole);
             }
         };
-        if (one_term) pass2(std::true_type{});
-        else pass2(std::false_type{});
+        pass2();
         // KL(p || q) of the row in nats, summed in a fixed order
         const double kw = wave_sum(kl);
         if (lane == 0) sh.loss_wave[wave] = kw;
@@ -192,8 +182,8 @@ __global__ __launch_bounds__(kThreads) void kd_stream_kernel(KdParams p) {
         if (threadIdx.x == 0) {
             double t = 0.0;
             for (int x = 0; x < kWaves; ++x) t += sh.loss_wave[x];
-            if (one_term) t += kl_shift;  // sum_x p(x) = 1
-            p.row_kl[r] = t * 0.69314718055994530942;
+            // (sum_x p(x) = 1)
+            p.row_kl[r] = (t + kl_shift) * 0.69314718055994530942;
         }
         // (the next row's normaliser pass has a barrier before anything writes loss_wave again)
     }
