@@ -565,7 +565,10 @@ __device__ inline void draw_region_totals(const RowPart &part, const DrawNorm &n
         if (rem == NSETS) load_batch(beg + (ib + NSETS - 1) * kStep, rp[NSETS - 1], rq[NSETS - 1]);
 #pragma unroll
         for (int s = 0; s < NSETS; ++s)
-            if (s < rem) sum_batch(beg + (ib + s) * kStep, rp[s], rq[s], std::false_type{});
+            if (s < rem) {
+                if (beg + (ib + s + 1) * kStep <= end) sum_batch(beg + (ib + s) * kStep, rp[s], rq[s], std::true_type{});
+                else sum_batch(beg + (ib + s) * kStep, rp[s], rq[s], std::false_type{});
+            }
     }
     if constexpr (PARTIAL) {
         if (beg <= whole && whole < end_all && lane == 0) {  // the row's partial slot
