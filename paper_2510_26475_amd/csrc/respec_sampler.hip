@@ -1439,13 +1439,15 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         // as compute units (one item / two, us per call: bf16, V = 151,936, B = 96 63.0 / 60.6, B = 128 56.6 / 64.4;
         // fp32, V = 50,257, B = 100 40.3 / 43.7).
         two_items = kn.get(&Knobs::sampler_two_items, (long)B * 4 <= cus ? 1 : 0) != 0;
-        // A stage of two items costs little beside its pass, so parts may be shorter there (one work-group / parts of
-        // 1000 slots / of 500: bf16, V = 32,000, B = 64 29.7 / 25.6, B = 32 27.6 / 23.5 / 24.2; V = 60,000, B = 32 parts
-        // of 1875 / 938 28.4 / 25.4); with one item per stage they may not (V = 32,000, B = 100 30.2 / 33.5 in
-        // parts of 2000), nor where a chain has one stage (V = 32,000, B = 64, k = 1 15.2 / 16.4, k = 0 10.2 / 12.7).
+        // A stage of two items costs little beside its pass, so parts may be shorter there, for rows whose passes are long enough
+        // to begin with (k = 4, us per call by one work-group / two / four: bf16, B = 64, V = 18,432 23.9 / 24.8 / 22.4 but k = 3
+        // 20.4 / 24.1 / 21.7, V = 26,624 25.9 / 26.0 / 23.2, k = 3 22.2 / 25.4 / 22.4, V = 32,000 27.0 / 26.9 / 23.5, k = 3 22.8 / 25.4 / 22.4; fp32,
+        // whose slots hold half as many elements, V = 12,288 19.1 / 22.1 / 20.6, V = 16,384 20.2 / 23.1 / 21.0); with one item per
+        // stage they may not (V = 32,000, B = 100 30.2 / 33.5 in parts of 2000), nor where a chain has one stage (V = 32,000,
+        // B = 64, k = 1 15.2 / 16.4 in parts of 1000, k = 0 10.2 / 12.7).
         const int epv0 = logits_dt == RESPEC_BF16 ? 8 : 4;
         const long slots_row = ((long)V + epv0 - 1) / epv0;
-        const long least = two_items && max_k >= 3 ? 768 : 2048;  // slots of a part
+        const long least = two_items && max_k >= 3 && slots_row >= (logits_dt == RESPEC_BF16 ? 3328 : 4096) ? 768 : 2048;  // slots of a part
         while (split < kMaxSplit && (long)B * split * 2 <= cus && slots_row / (split * 2) >= least) split *= 2;
         const long forced = kn.get(&Knobs::sampler_split, 0);
         if (forced == 1 || forced == 2 || forced == 4 || forced == 8) split = (int)forced;
