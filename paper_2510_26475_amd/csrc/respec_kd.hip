@@ -643,19 +643,24 @@ __global__ __launch_bounds__(1024) void kd_finish_kernel(KdParams p) {
 // keeps a piece of its own, until the device is full.  Times in us, streamed twice / by a team:
 //   - a row pair that one work-group can keep needs no exchange and is always better kept: bf16, V = 8000, 100 rows
 //     11.5 / 10.3, 2048 rows 57 / 35; V = 16,000, 2048 rows 70 / 50;
-//   - longer ones cost the exchange and one more small kernel (about 4 us): worth it where rows are few (V = 64,000, 32
-//     rows 20.4 / 14.3; V = 151,936, 8 rows 35 / 15; but fp32, V = 16,000, 8 rows 11.8 / 12.7), where the row pairs under way do not fit the L2s, so
-//     that the second read is one from memory (V = 128,000, 512 rows 100 / 97; fp32, 240 / 162; V = 151,936, 2048
-//     rows 441 / 375; but V = 64,000, 512 rows 51.6 / 53.6), and over many rows (V = 32,000, 2048 rows 104 / 96,
-//     256 rows 20 / 23; fp32, 1024 rows 88 / 83).
+//   - longer ones cost the exchange and one more small kernel (about 4 us).  Few rows: worth it from 48,000 logits on (bf16,
+//     V = 32,000, 1 to 64 rows 13.4 / 15.3, 40,000 14.5 / 15.4, 48,000 16 / 15.2, 151,936, 8 rows 35 / 15.3; fp32, 32,000 13.2 / 15.3,
+//     40,000 14.2 / 15.4, 48,000 15.6 / 15.3, 56,000 17 / 15.3).
+//   - More rows of 12,288 slots and more: the row pairs under way do not fit the L2s, and the second read is one from memory
+//     (bf16, V = 112,000, 96 to 2047 rows 0.82 to 0.95 of the time, 256 rows 46.1 / 46.4; V = 151,936, 2048 rows 438 / 374; fp32, 64,000,
+//     512 rows 0.81, 2048 rows 360 / 290; at 12,000 slots bf16, 256 rows 40.5 / 42.5).
+//   - Shorter ones: over many rows, where a member's LDS is well filled (parts of 1600 slots, or half a row; bf16,
+//     2048 rows, V = 20,000 73 / 68, 32,000 98 / 88, 56,000 157 / 147, 64,000 183 / 165, but parts of 1250 and 1500 V = 40,000 110 / 125, 48,000
+//     129 / 137, 80,000 219 / 242; 2047 rows are not worth it; fp32, 1500 rows, V = 16,000 0.95, 28,000 0.96, 32,000 0.92, but
+//     20,000 75 / 84, 24,000 89 / 93; 1024 rows, 11,200 35.7 / 37.0).
 int kd_team(int32_t rows, int32_t V, bool bf16) {
     const int64_t slots = V / (bf16 ? 8 : 4);
     int team = 1;
     while (team <= kKdMaxTeam && (slots + team - 1) / team > kKdMaxChunks * kKdChunk) team *= 2;
     if (team == 1) return 1;
     if (team > kKdMaxTeam) return 0;
-    const bool few = rows <= 64 && V >= 32000;
-    if (!few && slots < 12000 && rows < (bf16 ? 2048 : 1024)) return 0;
+    const bool few = rows <= 64 && V >= 48000;
+    if (!few && slots < 12288 && (rows < (bf16 ? 2048 : 1500) || (team > 2 && slots < 1600 * team))) return 0;
     while (team < kKdMaxTeam && (int64_t)rows * team * 2 <= kKdFill && slots / (2 * team) >= kThreads) team *= 2;
     return team;
 }

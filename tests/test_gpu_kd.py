@@ -147,15 +147,17 @@ def test_bad_arguments_are_rejected_before_any_launch():
 
 
 # ---- row pairs kept by teams of work-groups (a part: at most 38 pieces of 64 16-byte slots; streaming wave w takes the pieces
-# w, w + 8, ...; few rows are shared by more work-groups than one part each would need)
+# w, w + 8, ...; few rows are shared by more work-groups than one part each would need, never into parts below 512 slots, so
+# every member has pieces)
 @pytest.mark.parametrize("dtype,V,rows", [
     ("bf16", 8 * 2432, 300),      # the longest row of one work-group, more rows than work-groups
     ("bf16", 8 * 2433, 2048),     # one slot more: two members, the second part ragged
     ("bf16", 8 * 511, 700),       # eight pieces, the last one a slot short
     ("bf16", 8 * 513, 5),         # ... and one of a single slot
-    ("f32", 4 * 2440, 1030),      # two members
-    ("f32", 50256, 6),            # few rows: four-way and wider parts of 64 to 512 slots
-    ("bf16", 151936, 1),          # a single row: 32 members, the last one's part short
+    ("f32", 4 * 2440, 1030),      # (two members' worth, but too few rows: streamed)
+    ("f32", 4 * 2440, 1500),      # two members
+    ("f32", 50256, 6),            # few rows: 16 members of 792 slots, the last one's part 684
+    ("bf16", 151936, 1),          # a single row: 32 members of 600 slots, the last one's part 392: its last wave has no piece
     ("f32", 151936, 33),          # several rows per team, not the same number for all
 ])
 def test_row_pairs_kept_by_teams(oracle, dtype, V, rows):

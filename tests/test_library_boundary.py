@@ -58,6 +58,21 @@ def test_a_distillation_workspace_is_enough_for_fewer_rows(lib):
             assert all(s % 256 == 0 and s >= 8 for s in sizes) and sizes == sorted(sizes), (V, dt)
 
 
+def test_distillation_rows_are_shared_only_where_that_is_no_slower(lib):
+    # the size tells: 8 bytes a row where it is streamed, 72 bytes a row and member where a team keeps it (a size is also enough
+    # for fewer rows, which rows of 48,000 logits and more are shared for)
+    size = lib.respec_kd_rows_workspace_bytes
+    bf16, f32 = binding.RESPEC_BF16, binding.RESPEC_F32
+    for rows, V, dt in [(64, 32000, bf16), (32, 40000, bf16), (64, 40000, f32), (2047, 32000, bf16), (1024, 11200, f32), (2048, 40000, bf16),
+                        (2048, 20000, f32)]:                               # (were slower by 4 to 20 %, 2047 rows aside)
+        assert size(rows, V, dt) == (8 * rows + 255) // 256 * 256, (rows, V, dt)
+    for rows, V, dt in [(256, 96000, bf16), (2048, 48000, bf16), (2048, 80000, bf16)]:
+        assert size(rows, V, dt) < 288 * rows, (rows, V, dt)
+    for rows, V, dt, team in [(8, 151936, bf16, 32), (64, 48000, f32, 8), (2048, 32000, bf16, 2), (2048, 64000, bf16, 4), (2048, 32000, f32, 4),
+                              (256, 151936, bf16, 8), (1500, 11200, f32, 2)]:
+        assert 72 * rows * team <= size(rows, V, dt) <= 72 * rows * team + 512, (rows, V, dt)
+
+
 def test_attention_argument_errors_need_no_gpu(lib):
     null = ctypes.c_void_p(None)
     bogus = ctypes.c_void_p(0x1000)
