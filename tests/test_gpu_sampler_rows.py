@@ -353,7 +353,8 @@ def test_crossings_in_every_region(oracle, split, T):
         batch.u_final[b] = (b + 0.5) / 32 if b < 30 else (0.0, 1.0 - 2.0 ** -24)[b - 30]
     ref = oracle_sample(oracle, batch)
     with helpers.sampler_split(split):
-        compare_sampler(gpu_sample(batch), ref)
+        tally = compare_sampler(gpu_sample(batch), ref)
+    assert tally["flagged"] <= 6, tally   # (the uniforms 0 and 1 - 2^-24, and a quarter of a boundary draw per row or so)
 
 
 # Masked vocabularies: the finite logits of a row lie in one stretch (its start, its end, across the middle, one token), of a
