@@ -103,6 +103,7 @@ struct AttnParams {
     float scale_abs;       // its magnitude, at least 1e-37, and ...
     uint32_t q_sign;       // ... the sign bits that make up for it, two bf16 (bf16 kernel)
     int32_t inline_setup;  // the main kernel builds the split itself (no set-up kernel in front of it)
+    uint32_t g_inverse;    // ceil(65536 / G)
 };
 
 struct SeqInfo {
@@ -1189,6 +1190,422 @@ __global__ __launch_bounds__((4 + kProducers) * 64, 1) void attn_bf16_small_kern
     attn_bf16<D, 1, OutT, 4, 4>(p);
 }
 
+
+// ------------------------------------------------------------------------------------------
+// bf16 kernel for batches of a few tiles per compute unit (the end of a rollout, short prompts)
+// ------------------------------------------------------------------------------------------
+// Bound by the chain of latencies, not by bandwidth: launch, index arrays, first tile, write-out.  The
+// main kernel's chain is long there (a split searched by binary steps behind three barriers, a tile that
+// passes through a producer's registers and a ring, four consumers that each see every tile of a
+// range).  Here a work-group takes one part of one sequence's tiles for one KV head, its four waves
+// every fourth tile of it with all columns, K from memory straight into the registers that the
+// product reads, V through LDS for the transposing reads; the waves' results meet in LDS.  A wave's next
+// tile is requested as the registers of the one at hand become free (requested two ahead from two
+// sets of registers the code is twice as long, which a kernel that runs through it once pays for in
+// instruction fetches: 15.4 against 18.2 us below).  The registers are held at 256: beyond, the compiler
+// moves the accumulators between two register files for every tile.  What a call takes (main and
+// combine kernel; the main kernel's forms / this one, us): 3B shape, 512 to 4096 tokens, k = 0 and 4, B = 8
+// 17.5 / 11.3 and 20.4 / 14.1; k = 3, B = 1, 24, 64 17.4 / 11.1, 25.3 / 18.2, 40.8 / 35.0; 7B shape, k = 3, B = 8
+// and 32 22.6 / 16.0 and 38.8 / 32.3; heads of 64, two KV heads, k = 2, B = 8 16.3 / 10.5.  In cycles, B = 8, k = 4:
+// split 2.6 thousand, query rows 3.3, first tile 4 (memory, 2.4 of arithmetic), second 2.4, merge and
+// write-out 4.4.
+constexpr int kFewSeqs = 64;    // sequences: a lane each
+constexpr int kFewWaves = 4;    // waves per work-group
+
+template <int D, int NT>
+struct FewForm {
+    using C = Bf16Cfg<D>;
+    static constexpr int kCols = NT * kColTile;
+    // a wave's LDS: a V tile while it works, its accumulators once it has finished
+    static constexpr int kStageBytes = kCols * C::kMergeStride * 4;
+    static constexpr int kWaveBytes = kStageBytes > C::kVTileBytes ? kStageBytes : C::kVTileBytes;
+    static constexpr int kStatOffset = kFewWaves * kWaveBytes;  // [kFewWaves][kCols] (max, sum)
+    static constexpr int kQueryOffset = kStatOffset + kFewWaves * kCols * 8;
+    static constexpr int kBytes = kQueryOffset + kCols * C::kRowBytes;
+    // where a row's 16-byte piece c is staged: two pieces that a thread reads together lie half a row
+    // apart, so that the threads of a row read neighbouring pieces (in row order: two-way bank conflicts)
+    static constexpr int chunk(int c) { return c / 2 + c % 2 * (D / 8); }
+    static_assert(kBytes <= 160 * 1024, "fits the LDS of a compute unit");
+};
+
+// Inclusive sums over the lanes of a wave, without LDS.
+__device__ inline int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
+
+// Query row of a column (below 256): col / G without a division.
+__device__ inline int column_row(const AttnParams &p, int col) { return (int)(((uint32_t)col * p.g_inverse) >> 16); }
+
+template <int CTRL>
+__device__ inline float dpp_mov(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
+template <int D, int NT>
+__global__ __launch_bounds__(kFewWaves * 64, D == 128 && NT == 4 ? 1 : 2) void attn_bf16_few_kernel(AttnParams p) {
+    using C = Bf16Cfg<D>;
+    using F = FewForm<D, NT>;
+    extern __shared__ __align__(16) char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c16 = lane & 15, g4 = lane >> 4;
+    // The split: every sequence is cut into parts, as equal as its tiles allow, so that all (part, KV head)
+    // pairs find a work-group: ceil(f t) parts of a sequence of t tiles are less than f total + seqs in all.
+    // Of four values of f the largest is taken whose parts fit; the first always does.  (At most a part
+    // per four tiles, a tile for each wave: smaller parts only add partials; one sequence of 4096 tokens, 3B
+    // shape, k = 4 14.4 -> 12.2 us.)  Every wave works it out for itself, a lane per sequence: one round
+    // trip to memory and no barrier.
+    const int r = blockIdx.x, kvh = blockIdx.y, u = r * p.Hkv + kvh;
+    SeqInfo si{};
+    int t0 = 0, n = 0;
+    int4 cut = {0, 0, 0, 0}, no_cut = {0, 0, 0, 0};
+    int cut_at = -1;           // entry of the cut table that is this work-group's to write
+    bool empty_lane = false;   // work-group 0: this lane's sequence has no tiles
+    if (p.inline_setup) {      // uniform over the launch
+        SeqInfo mine{};
+        if (lane < p.B) mine = seq_info(p, lane);
+        const int tiles = mine.tiles, rows = gridDim.x;
+        const int seqs = __popcll(__ballot(tiles > 0));
+        const float t = (float)tiles, per_tile = 1.f / (float)max(__builtin_amdgcn_readlane(wave_scan(tiles), 63), 1);
+        int parts = 0, upto = 0;  // of this lane's sequence; up to and with it
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float f = fminf((float)(4 * (rows - seqs) + i * seqs) * 0.2499999f * per_tile, 0.25f);
+            const int x = tiles > 0 ? min(max((int)ceilf(t * f), 1), tiles) : 0;
+            const int sum = wave_scan(x);
+            if (i == 0 || __builtin_amdgcn_readlane(sum, 63) <= rows) {
+                parts = x;
+                upto = sum;
+            }
+        }
+        const int b = __popcll(__ballot(upto <= r));
+        if (b < kFewSeqs) {  // (64: no part is left for this work-group)
+            auto of_b = [&](int x) { return __builtin_amdgcn_readlane(x, b); };
+            si.q0 = of_b(mine.q0);
+            si.R = of_b(mine.R);
+            si.L = of_b(mine.L);
+            si.tiles = of_b(mine.tiles);
+            si.kv0 = (int64_t)(uint32_t)of_b((int)mine.kv0) | ((int64_t)of_b((int)(mine.kv0 >> 32)) << 32);
+            const int n_parts = of_b(parts), first = of_b(upto) - n_parts, part = r - first;
+            const int least = (int)((uint32_t)si.tiles / (uint32_t)n_parts), more = si.tiles - least * n_parts;
+            t0 = part * least + min(part, more);
+            n = least + (part < more ? 1 : 0);
+            cut = int4{first, first + n_parts - 1, si.q0, si.R};
+            cut_at = part == 0 ? b * p.Hkv + kvh : -1;
+        }
+        empty_lane = u == 0 && lane < p.B && tiles == 0;
+        no_cut = int4{0, 0, mine.q0, mine.R};
+    } else {
+        const ConstPtr<int32_t> src = as_constant(reinterpret_cast<const int32_t *>(p.wave_start + u));
+        t0 = src[2];
+        n = src[3];
+        si.q0 = src[4];
+        si.R = src[5];
+        si.L = src[6];
+        si.tiles = src[7];
+        si.kv0 = (int64_t)(uint32_t)src[8] | ((int64_t)src[9] << 32);
+    }
+    const int count = n > wave ? (n - wave + kFewWaves - 1) / kFewWaves : 0;  // this wave's tiles: t0 + wave, + kFewWaves, ...
+    char *own = smem + wave * F::kWaveBytes;
+    float *stage = reinterpret_cast<float *>(own);  // [kCols][kMergeStride]
+    floatx2 *stat = reinterpret_cast<floatx2 *>(smem + F::kStatOffset);
+
+    // what the combine kernel and the later layers of a forward read (behind the first requests)
+    auto leave_plan = [&]() __attribute__((always_inline)) {
+        if (p.inline_setup && wave == kFewWaves - 1) {
+            if (lane == 0) {
+                p.wave_start[u] = WaveStart{kvh, 0, t0, n, si.q0, si.R, si.L, si.tiles, si.kv0, 0};
+                if (cut_at >= 0) *reinterpret_cast<int4 *>(p.cuts + 4 * (int64_t)cut_at) = cut;
+                if (u == 0) {
+                    p.error_flag[0] = 0;
+                    p.error_flag[1] = 1;  // every part that the cut table names owns tiles
+                }
+            }
+            if (empty_lane)
+                for (int h = 0; h < p.Hkv; ++h) *reinterpret_cast<int4 *>(p.cuts + 4 * ((int64_t)lane * p.Hkv + h)) = no_cut;
+        }
+    };
+    if (n > 0) {  // block-uniform
+        const int32_t row_bytes = p.Hkv * D * 2;
+        // query rows: loaded by the waves together, for each of them through LDS
+        constexpr int kPieces = F::kCols * (D / 8), kQLoads = (kPieces + kFewWaves * 64 - 1) / (kFewWaves * 64);
+        char *q_lds = smem + F::kQueryOffset;
+        u32x4 qr[kQLoads];
+#pragma unroll
+        for (int i = 0; i < kQLoads; ++i) {  // (a column without a row reads row 0; nothing reads its result)
+            const int piece = min(i * kFewWaves * 64 + (int)threadIdx.x, kPieces - 1);
+            const int col = piece / (D / 8), row = column_row(p, col), gh = col - row * p.G;
+            qr[i] = *reinterpret_cast<const u32x4 *>(static_cast<const char *>(p.q) +
+                                                     ((int64_t)(si.q0 + (row < si.R ? row : 0)) * p.Hq + kvh * p.G + gh) * (D * 2) +
+                                                     (piece % (D / 8)) * 16);
+        }
+        // K goes from memory to the registers that the product reads (lane: key c16 of a half tile, 16 bytes
+        // of every 64), V through LDS for the transposing reads
+        u32x4 kr[2][C::kKSteps], vr[C::kLoads];
+        TileOffsets off;
+        auto locate = [&](const int j) __attribute__((always_inline)) {
+            const int t = t0 + min(wave + j * kFewWaves, n - 1);
+            if (p.page_table) {
+                off = paged_tile_offsets(p, si, t, kvh, D * 2, row_bytes);
+            } else {
+                off.lo = (si.kv0 * p.Hkv + kvh) * (int64_t)(D * 2) + (int64_t)(t * kTileKeys) * row_bytes;
+                off.hi = off.lo;
+            }
+        };
+        // (rows past the sequence's end read its last one: a tile's 16-row halves lie at off.lo and off.hi)
+        auto request_k = [&](const int j) __attribute__((always_inline)) {
+            const int rows_valid = si.L - 1 - (t0 + min(wave + j * kFewWaves, n - 1)) * kTileKeys;
+#pragma unroll
+            for (int js = 0; js < 2; ++js) {
+                const char *base = static_cast<const char *>(p.k) + (js == 1 && rows_valid >= 16 ? off.hi : off.lo);
+                const uint32_t o = __umul24((uint32_t)min(js * 16 + c16, rows_valid), (uint32_t)row_bytes) + (uint32_t)g4 * 16u;
+#pragma unroll
+                for (int x = 0; x < C::kKSteps; ++x)
+                    kr[js][x] = stream_load(reinterpret_cast<const u32x4 *>(base + (o + (uint32_t)x * 64u)));
+            }
+        };
+        auto request_v = [&](const int j) __attribute__((always_inline)) {
+            const int rows_valid = si.L - 1 - (t0 + min(wave + j * kFewWaves, n - 1)) * kTileKeys;
+#pragma unroll
+            for (int x = 0; x < C::kLoads; ++x) {
+                const char *base = static_cast<const char *>(p.v) + (x >= C::kLoads / 2 && rows_valid >= 16 ? off.hi : off.lo);
+                const uint32_t row = (uint32_t)min(lane / C::kLanesPerRow + x * C::kRowsPerLoad, rows_valid);
+                vr[x] = stream_load(reinterpret_cast<const u32x4 *>(base + (__umul24(row, (uint32_t)row_bytes) + (uint32_t)(lane % C::kLanesPerRow) * 16u)));
+            }
+        };
+        // which of the sequence's new tokens a column's row sees (a tree's mask, or those up to its own)
+        const int first_new = si.L - si.R;
+        uint64_t col_mask[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const int row = min(column_row(p, nt * kColTile + c16), si.R - 1);
+            col_mask[nt] = p.tree_mask ? p.tree_mask[si.q0 + row] & (~0ull >> (64 - si.R)) : (2ull << row) - 1;
+        }
+        // (a wave without tiles requests the last one as well: the wait for the query rows then leaves
+        // the same requests in flight on every path)
+        locate(0);
+        request_k(0);
+        request_v(0);
+        leave_plan();
+#pragma unroll
+        for (int i = 0; i < kQLoads; ++i) {
+            const int piece = min(i * kFewWaves * 64 + (int)threadIdx.x, kPieces - 1);
+            // (a negative scale: the rows are negated, which is exact)
+            *reinterpret_cast<u32x4 *>(q_lds + piece / (D / 8) * C::kRowBytes + (piece % (D / 8)) * 16) = qr[i] ^ p.q_sign;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");  // (LDS only: the tiles stay in flight)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+
+        float m_run[NT], l_run[NT];
+        floatx4 acc_o[NT][C::kDTiles];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            m_run[nt] = kNoMax;
+            l_run[nt] = 0.f;
+#pragma unroll
+            for (int t = 0; t < C::kDTiles; ++t) acc_o[nt][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+
+#pragma unroll 1
+        for (int j = 0; j < count; ++j) {
+            const int key0 = (t0 + wave + j * kFewWaves) * kTileKeys;
+            // (the query rows of a step are read one step ahead: all of them at once do not fit the registers)
+            bf16x8 qf[2][NT];
+            auto read_q = [&](const int x) __attribute__((always_inline)) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    qf[x & 1][nt] = *reinterpret_cast<const bf16x8 *>(q_lds + (nt * kColTile + c16) * C::kRowBytes + (x * 32 + g4 * 8) * 2);
+            };
+            floatx4 s_acc[NT][2];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) s_acc[nt][0] = s_acc[nt][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+            read_q(0);
+#pragma unroll
+            for (int x = 0; x < C::kKSteps; ++x) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (x + 1 < C::kKSteps) read_q(x + 1);
+#pragma unroll
+                for (int js = 0; js < 2; ++js)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt)
+                        s_acc[nt][js] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[js][x]), qf[x & 1][nt],
+                                                                                s_acc[nt][js], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // (the next tile's requests go out as its registers become free)
+            if (j + 1 < count) {
+                locate(j + 1);
+                request_k(j + 1);
+            }
+            asm volatile("" ::: "memory");
+            store_tile<D, C::kVRowBytes>(vr, own, lane);
+            asm volatile("" ::: "memory");
+            if (j + 1 < count) request_v(j + 1);
+
+            // online softmax as in the main kernel: the reference moves only when a score exceeds it by
+            // more than kRescaleSlack
+            if (key0 + kTileKeys > first_new + 1) {  // wave-uniform: some row does not see some key
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int js = 0; js < 2; ++js) {
+                        const int at = key0 + js * 16 + g4 * 4 - first_new;  // first of four keys, among the new tokens
+                        const uint64_t after = at > 63 ? 0 : col_mask[nt] >> (at & 63), before = ~(~col_mask[nt] << (-at & 63));
+                        const uint32_t seen = (uint32_t)(at >= 0 ? after : at > -4 ? before : ~0ull);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s_acc[nt][js][i] = (seen >> i) & 1u ? s_acc[nt][js][i] : -INFINITY;
+                    }
+            }
+            float lane_max[NT];
+            bool rescale = false;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const floatx4 x = s_acc[nt][0], y = s_acc[nt][1];
+                lane_max[nt] = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])));
+                rescale |= fmaf(lane_max[nt], p.scale_abs, -m_run[nt]) > kRescaleSlack;
+            }
+            if (__any(rescale)) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    const float mloc = max_across_rows(lane_max[nt]) * p.scale_abs;
+                    const float mnew = mloc > m_run[nt] + kRescaleSlack ? mloc : m_run[nt];
+                    const float alpha = hw_exp2(m_run[nt] - mnew);
+                    m_run[nt] = mnew;
+                    if (j > 0) {  // wave-uniform
+                        l_run[nt] *= alpha;
+#pragma unroll
+                        for (int t = 0; t < C::kDTiles; ++t) acc_o[nt][t] *= alpha;
+                    }
+                }
+            }
+            bf16x8 pfrag[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                float psum = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; e += 2) {
+                    const float a = hw_exp2(fmaf(s_acc[nt][e / 4][e % 4], p.scale_abs, -m_run[nt]));
+                    const float c = hw_exp2(fmaf(s_acc[nt][e / 4][e % 4 + 1], p.scale_abs, -m_run[nt]));
+                    psum += a;
+                    psum += c;
+                    const bf16x2 two = __builtin_convertvector(floatx2{a, c}, bf16x2);
+                    pfrag[nt][e] = two[0];
+                    pfrag[nt][e + 1] = two[1];
+                }
+                l_run[nt] += psum;
+            }
+
+            typedef s16x4 __attribute__((address_space(3))) *LdsV;
+            const char *v_lane = own + (4 * g4 + c16 / 4) * C::kVRowBytes + (c16 % 4) * 8;
+            s16x4 vf[C::kDTiles][2];
+#pragma unroll
+            for (int t = 0; t < C::kDTiles; ++t)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    vf[t][h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsV)(v_lane + h * 16 * C::kVRowBytes + t * 32));
+#pragma unroll
+            for (int t = 0; t < C::kDTiles; ++t) {
+                const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vf[t][0], vf[t][1], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc_o[nt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, pfrag[nt], acc_o[nt][t], 0, 0, 0);
+            }
+            asm volatile("" ::: "memory");  // (the reads have been issued: a wave's LDS operations run in order)
+        }
+
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {  // (of a wave without tiles: zeros)
+            const float lt = sum_across_rows(l_run[nt]);
+            float *row = stage + (nt * kColTile + c16) * C::kMergeStride;
+#pragma unroll
+            for (int t = 0; t < C::kDTiles; ++t) *reinterpret_cast<floatx4 *>(row + F::chunk(4 * t + g4) * 4) = acc_o[nt][t];
+            if (g4 == 0) stat[wave * F::kCols + nt * kColTile + c16] = floatx2{m_run[nt], lt};
+        }
+    } else {
+        leave_plan();
+    }
+    __syncthreads();
+
+    // the waves' results are merged in wave order; eight values of a column per thread
+    constexpr int kTpc = D / 8;
+    constexpr int kColsPerPass = kFewWaves * 64 / kTpc;
+    const bool whole = n == si.tiles;
+    const int64_t slot = 2 * (int64_t)u + (t0 > 0 ? 0 : 1);
+    const int M = n > 0 ? p.G * si.R : 0;
+    constexpr int kPasses = (F::kCols + kColsPerPass - 1) / kColsPerPass;
+    const int d8 = ((int)threadIdx.x % kTpc) * 8;
+    // (all reads ahead of all arithmetic: left alone the compiler keeps two of them in flight)
+    floatx2 ml[kPasses][kFewWaves];
+    floatx4 part[kPasses][kFewWaves][2];
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        const int col = min(i * kColsPerPass + (int)threadIdx.x / kTpc, F::kCols - 1);
+#pragma unroll
+        for (int w = 0; w < kFewWaves; ++w) {
+            const float *src = reinterpret_cast<const float *>(smem + w * F::kWaveBytes) + col * C::kMergeStride + d8 / 2;
+            ml[i][w] = stat[w * F::kCols + col];
+            part[i][w][0] = *reinterpret_cast<const floatx4 *>(src);
+            part[i][w][1] = *reinterpret_cast<const floatx4 *>(src + D / 2);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    floatx4 o[kPasses][2];
+    float mt[kPasses], lt[kPasses], amax[kPasses];
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        mt[i] = kNoMax;
+#pragma unroll
+        for (int w = 0; w < kFewWaves; ++w) mt[i] = fmaxf(mt[i], ml[i][w][0]);
+        lt[i] = 0.f;
+        o[i][0] = o[i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kFewWaves; ++w) {
+            const float wgt = hw_exp2(ml[i][w][0] - mt[i]);
+            lt[i] += ml[i][w][1] * wgt;
+            o[i][0] = o[i][0] + part[i][w][0] * wgt;
+            o[i][1] = o[i][1] + part[i][w][1] * wgt;
+        }
+        // (16-bit fixed point relative to the row's largest magnitude, as the main kernel writes it)
+        float m = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(o[i][e / 4][e % 4]));
+        m = fmaxf(m, dpp_mov<0xb1>(m));                     // quad_perm:[1,0,3,2]
+        m = fmaxf(m, dpp_mov<0x4e>(m));                     // quad_perm:[2,3,0,1]
+        m = fmaxf(m, dpp_mov<0x141>(m));                    // row_half_mirror
+        if (kTpc == 16) m = fmaxf(m, dpp_mov<0x140>(m));    // row_mirror
+        amax[i] = m;
+    }
+#pragma unroll
+    for (int i = 0; i < kPasses; ++i) {
+        const int col = i * kColsPerPass + (int)threadIdx.x / kTpc;
+        if (col >= M) break;
+        const floatx4 a = o[i][0], c = o[i][1];
+        if (whole) {
+            const float inv = lt[i] > 0.f ? 1.f / lt[i] : 0.f;
+            const int row = column_row(p, col), gh = col - row * p.G;
+            const int64_t orow = (int64_t)(si.q0 + row) * p.Hq + kvh * p.G + gh;
+            auto pack = [&](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{x * inv, y * inv}, bf16x2)); };
+            stream_store(reinterpret_cast<u32x4 *>(static_cast<uint16_t *>(p.out) + orow * D + d8),
+                         (u32x4{pack(a[0], a[1]), pack(a[2], a[3]), pack(c[0], c[1]), pack(c[2], c[3])}));
+            if (p.lse && d8 == 0) p.lse[orow] = lt[i] > 0.f ? (mt[i] + log2f(lt[i])) * 0.6931471805599453f : -INFINITY;
+        } else {
+            const float qs = (amax[i] > 0.f && amax[i] < INFINITY) ? 32767.f / amax[i] : 0.f;
+            auto pack = [&](float x, float y) { return ((uint32_t)(int)__builtin_rintf(x * qs) & 0xffffu) | ((uint32_t)(int)__builtin_rintf(y * qs) << 16); };
+            const int64_t row = slot * p.Mpad + col;
+            *reinterpret_cast<u32x4 *>(p.ws_o + row * D + d8) = u32x4{pack(a[0], a[1]), pack(a[2], a[3]), pack(c[0], c[1]), pack(c[2], c[3])};
+            if (d8 == 0) *reinterpret_cast<floatx4 *>(p.ws_ml + row * 4) = floatx4{mt[i], lt[i], amax[i], 0.f};
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // fp32 kernel: one work-group per (sequence, query head, query row), no split
 // ------------------------------------------------------------------------------------------
@@ -1578,9 +1995,9 @@ int compute_units() {
     return cached[dev];
 }
 
-// One launch of a form of the main kernel (Form: its LDS, NC: its consumers).
-template <auto kernel, typename Form, int NC>
-hipError_t launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream) {
+// One launch of a form of the main kernel (Form: its LDS).
+template <auto kernel, typename Form>
+hipError_t launch_bf16(const AttnParams &p, dim3 grid, int waves, hipStream_t stream) {
     static bool configured[64] = {false};  // per kernel and device; benign race: the attribute is idempotent
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = -1;
@@ -1590,7 +2007,7 @@ hipError_t launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream) {
         if (e != hipSuccess) return e;
         if (dev >= 0) configured[dev] = true;
     }
-    hipLaunchKernelGGL(kernel, grid, dim3((NC + kProducers) * 64), Form::kBytes, stream, p);
+    hipLaunchKernelGGL(kernel, grid, dim3(waves * 64), Form::kBytes, stream, p);
     return hipGetLastError();
 }
 
@@ -1598,14 +2015,15 @@ hipError_t launch_bf16(const AttnParams &p, dim3 grid, hipStream_t stream) {
 // average, times how much longer than the average the longest can be (at most twice that is
 // counted: the bound is the caller's and may be the model's).  Sharing them between waves wins from
 // 16 parts on (7.5 -> 4.3 us) and loses at 8 (5.5 -> 6.8 us); eight waves win over four from 64 on
-// (5.9 -> 5.2 us).  forced: 1, 4 or 8 (RESPEC_ATTN_COMBINE), 0 = by this rule.
+// (5.9 -> 5.2 us).  most: parts that a sequence can have (the form for few tiles gives four tiles to a
+// part); forced: 1, 4 or 8 (RESPEC_ATTN_COMBINE), 0 = by this rule.
 template <int D>
-hipError_t launch_combine(const AttnParams &p, int M, int64_t kv_tokens, long forced, hipStream_t stream) {
+hipError_t launch_combine(const AttnParams &p, int M, int64_t kv_tokens, double most, long forced, hipStream_t stream) {
     const int cols_per_wave = 64 / (D / 8);
     const int64_t pairs = (int64_t)p.B * p.Hkv;
     const int groups = (M + cols_per_wave - 1) / cols_per_wave;
     const double longest = std::fmin(2.0, std::fmax(1.0, (double)p.max_kv_len * p.B / (double)kv_tokens));
-    const double parts = (double)p.W / (double)pairs * longest;
+    const double parts = std::fmin((double)p.W / (double)pairs * longest, most);
     const long pw = forced == 1 || forced == 4 || forced == 8 ? forced : parts >= 64.0 ? 8 : parts >= 12.0 ? 4 : 1;
     if (pw == 8)
         hipLaunchKernelGGL((attn_combine_kernel<D, uint16_t, 8>), dim3((unsigned)pairs, (unsigned)groups), dim3(512), 0, stream, p);
@@ -1619,13 +2037,51 @@ hipError_t launch_combine(const AttnParams &p, int M, int64_t kv_tokens, long fo
 // nt: column tiles of a column block; cw: consumers that share a range; nc: consumers of a work-group
 template <int D>
 hipError_t launch_bf16_nt(int nt, int cw, int nc, const AttnParams &p, dim3 grid, hipStream_t stream) {
-#define RESPEC_FORM(NT, CW) launch_bf16<&attn_bf16_kernel<D, NT, uint16_t, CW>, Bf16Form<D, NT, consumers_of(CW)>, consumers_of(CW)>(p, grid, stream)
-    if (cw == 4 && nc == 4) return launch_bf16<&attn_bf16_small_kernel<D, uint16_t>, Bf16Form<D, 1, 4>, 4>(p, grid, stream);
+#define RESPEC_FORM(NT, CW) launch_bf16<&attn_bf16_kernel<D, NT, uint16_t, CW>, Bf16Form<D, NT, consumers_of(CW)>>(p, grid, consumers_of(CW) + kProducers, stream)
+    if (cw == 4 && nc == 4) return launch_bf16<&attn_bf16_small_kernel<D, uint16_t>, Bf16Form<D, 1, 4>>(p, grid, 4 + kProducers, stream);
     if (cw == 4) return nt <= 4 ? RESPEC_FORM(1, 4) : RESPEC_FORM(2, 4);
     if (cw == 2) return nt <= 2 ? RESPEC_FORM(1, 2) : RESPEC_FORM(2, 2);
     if constexpr (D == 128)
         if (nt == 3) return RESPEC_FORM(3, 1);
     return RESPEC_FORM(1, 1);
+}
+
+template <int D>
+hipError_t launch_few(int nt, const AttnParams &p, hipStream_t stream) {
+    const dim3 grid((unsigned)(p.W / p.Hkv), (unsigned)p.Hkv);
+#define RESPEC_FEW(NT) launch_bf16<&attn_bf16_few_kernel<D, NT>, FewForm<D, NT>>(p, grid, kFewWaves, stream)
+    return nt == 1 ? RESPEC_FEW(1) : nt == 2 ? RESPEC_FEW(2) : nt == 3 ? RESPEC_FEW(3) : RESPEC_FEW(4);
+}
+
+// Work-groups per compute unit that a batch gets in the form for few tiles (attn_bf16_few_kernel), 0 where
+// the main kernel's forms are the better ones.  What counts is how many tiles its largest part has, on
+// work-groups in number one or two per compute unit: the longest sequence's, or what the split leaves
+// (which gets coarse where there are nearly as many pairs as work-groups).  Lines, from a sweep over
+// 1 to 64 sequences of 40 to 250, 512 to 4096 and 2000 to 8192 tokens at the 3B, 7B and 14B shapes and with
+// heads of 64, one to four column tiles (us per call: main kernel's forms / one / two per unit, at the
+// tiles of the largest part with one): one column tile: 7B shape 11 18.3, 15.1, 14.8; 24 22.9, 23.1, 21.4;
+// 41 31.6, 34.2, 30.8; 74 43.6, 75.0, 44.8; two: 3B 19 27.0, 20.1, 22.1; 51 40.8, 36.3, 35.0; 126 77.4, 76.5, 69.8;
+// 7B 46 38.8, 35.0, 32.3; 128 64.6, 83.4, 65.8; three and four: 7B 46 42.0, 36.8, 39.3; 82 59.9, 59.2, 60.5; 128
+// 69.4, 85.9, 69.5; heads of 64, two tiles: 15 18.1, 13.7, 12.8; 126 42.0, 44.0, 37.7.  With eight KV heads a
+// part reads an eighth of every cache row, and the lines lie lower: 14B, one tile 15 19.5, 18.7, 18.0; 24 22.0,
+// 22.5, 23.6; two 48 43.3, 40.0, 41.2; 96 60.2, 61.7, 63.7; three 48 46.0, 41.6, 46.1; 59 47.8, 49.7, 46.2.
+int few_tiles_groups(int D, int nt, int32_t B, int32_t Hkv, int64_t kv_tokens, int32_t max_kv_len) {
+    const int units = compute_units();
+    if (B > kFewSeqs || (int64_t)B * Hkv > units) return 0;
+    const double tiles = (double)kv_tokens / kTileKeys + B;  // of one KV head, about
+    const double longest = ((double)max_kv_len + kTileKeys - 1) / kTileKeys;
+    auto largest_part = [&](int groups) {
+        const double seats = (double)(units * groups / Hkv) - 0.6 * B;
+        return std::fmin(longest, tiles / std::fmax(seats, 1e-3));
+    };
+    const bool many_heads = Hkv >= 8;
+    if (D == 64 || nt <= 2) {  // two fit a compute unit
+        const double two_from = D == 64 ? (nt <= 2 ? 12 : 26) : nt == 1 ? 13 : 34;
+        const double most = nt == 1 ? (many_heads ? 8 : D == 64 ? 48 : 20) : many_heads ? 28 : 48;
+        if (largest_part(1) < two_from) return 1;
+        return largest_part(2) <= most ? 2 : 0;
+    }
+    return largest_part(1) <= (many_heads ? 56 : 84) ? 1 : 0;
 }
 
 }  // namespace
@@ -1755,6 +2211,7 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     p.Hq = Hq;
     p.Hkv = Hkv;
     p.G = Hq / Hkv;
+    p.g_inverse = (65536u + (uint32_t)p.G - 1) / (uint32_t)p.G;
     p.Mpad = pl.Mpad;
     p.scale2 = (float)((double)sm_scale * 1.4426950408889634074);
     // (a scale of zero becomes 1e-37: every exponent rounds to the one it has at zero, and a hidden
@@ -1798,10 +2255,8 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     // consumers of one tile each share a range, four per work-group: a quarter of the ranges and of the
     // partials to fold (two consumers / four: 24.8 / 23.4 at B = 6, 21.8 / 18.2 at B = 2, 7B; 19.5 / 18.1 at
     // B = 8, 3B with heads of 64; from two tiles on 28.1 / 28.9 at B = 12, 7B; 29.7 / 32.0 at B = 32, 3B).
-    // Where 16 (sequence, head) pairs or fewer share the ranges, folding the partials weighs more and the
-    // line is at four tiles (two consumers / four at 2 and 3 tiles, k = 3, 3B shape: one sequence of 39,000
-    // and 57,000 tokens 35.0 / 27.7 and 37.6 / 30.1, four of 9,800 and 14,300 23.7 / 21.9 and 26.4 / 24.2,
-    // eight of 4,900 and 7,200 22.4 / 21.5 and 24.7 / 23.7; heads of 64, eight, 17.2 / 17.4 and 18.0 / 18.7).
+    // (Most batches that small take the form for few tiles, few_tiles_groups: what comes here has more than
+    // 64 sequences, or more pairs of a sequence and a KV head than compute units.)
     // Three and four tiles: four consumers per range, eight per work-group (one, two and four consumers
     // per range: k = 4, B = 256 and 768 at the 3B shape 135, 133, 124 and 336, 331, 318; k = 5, B = 256 at the
     // 7B shape 239, 237, 233; k = 7, B = 64 at the 14B shape 125, 121, 117).  But that form's two ranges
@@ -1830,12 +2285,11 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
     const int nt = quad ? 8 : (cols + kColTile - 1) / kColTile;  // column tiles of a block
     const bool many_heads = Hkv >= 8 && tiles_per_consumer >= (D == 64 ? 32 : 64);
     const bool one = nt == 1 || (nt == 3 && D == 128 && wide != 1 && (wide == 0 || many_heads));
-    const bool few_pairs = (int64_t)B * Hkv * 16 <= compute_units();
     int cw;
     if (quad || (quad_env == 2 && nt >= 2 && M <= kMaxColsPerBlock)) cw = 4;
     else if (one) cw = 1;
     else if (wide >= 0 || quad_env == 0 || M > kMaxColsPerBlock) cw = 2;
-    else if (nt == 2) cw = tiles_per_consumer < (few_pairs ? 4 : 2) ? 4 : 2;
+    else if (nt == 2) cw = tiles_per_consumer < 2 ? 4 : 2;
     else cw = many_heads ? 2 : 4;
     const long nc_env = kn.get(&Knobs::attn_consumers, 0);  // 4 / 8: the narrow four-way form's consumers
     const int nc = cw == 1 ? 4 : cw == 4 && nt <= 4 && (nc_env ? nc_env == 4 : tiles_per_consumer < 2) ? 4 : 8;
@@ -1865,19 +2319,29 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
         const int64_t most = ((int64_t)B * longest * Hkv + per - 1) / per;
         if (W > most) W = (long)((most + streams - 1) / streams * streams);
     }
+    // (a knob that shapes the main kernel keeps to it)
+    const long few_env = kn.get(&Knobs::attn_few, -1);  // 0: never, 1 / 2: that many work-groups per compute unit wherever the form takes the batch
+    int few = 0;
+    if (M <= kMaxColsPerBlock && B <= kFewSeqs && (int64_t)B * Hkv <= compute_units()) {
+        if (few_env >= 0) few = (int)std::min(few_env, 2l);
+        else if (kn.get(&Knobs::attn_wgs, 0) <= 0 && quad_env == 1 && wide < 0 && nc_env == 0 && kn.get(&Knobs::attn_head_major, 0) == 0 &&
+                 kn.get(&Knobs::attn_inline, 1) != 0)
+            few = few_tiles_groups(D, nt, B, Hkv, kv_tokens, max_kv_len);
+    }
+    if (few) W = (long)compute_units() * few / Hkv * Hkv;
     if (W < 1) W = 1;
     if (W > max_waves) W = max_waves;
     p.W = (int32_t)W;
     int hi = Hkv % 4 == 0 ? 4 : (Hkv % 2 == 0 ? 2 : 1);
     if (hi > streams) hi = streams;
     if (W % hi != 0 || kn.get(&Knobs::attn_head_major, 0) != 0) hi = 1;
-    p.HI = hi;
+    p.HI = few ? Hkv : hi;  // (the few-tiles form: work-group part * Hkv + head)
 
     // the set-up depends on the index arrays and the sizes only: the layers of one forward share
     // it (reuse_plan: the workspace still holds what the set-up of an earlier call left there)
     // (small batches: the main kernel's work-groups build it in their prologue and leave it in
     // the workspace; large ones take a set-up kernel in front)
-    p.inline_setup = !reuse_plan && B <= kInlineSeqs && kn.get(&Knobs::attn_inline, 1) != 0 ? 1 : 0;
+    p.inline_setup = !reuse_plan && B <= kInlineSeqs && (few || kn.get(&Knobs::attn_inline, 1) != 0) ? 1 : 0;
     if (!reuse_plan && !p.inline_setup) {
         hipLaunchKernelGGL(attn_prep_kernel, dim3(1), dim3(1024), 0, stream, p);
         err = hipGetLastError();
@@ -1889,7 +2353,10 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
         g_mark_before_main = nullptr;
     }
     const dim3 grid((unsigned)((W + streams - 1) / streams), (unsigned)col_blocks);
-    err = D == 128 ? launch_bf16_nt<128>(nt, cw, nc, p, grid, stream) : launch_bf16_nt<64>(nt, cw, nc, p, grid, stream);
+    if (few)
+        err = D == 128 ? launch_few<128>(nt, p, stream) : launch_few<64>(nt, p, stream);
+    else
+        err = D == 128 ? launch_bf16_nt<128>(nt, cw, nc, p, grid, stream) : launch_bf16_nt<64>(nt, cw, nc, p, grid, stream);
     if (err != hipSuccess)
         return fail(RESPEC_ERR_HIP, "verify_attention: main launch failed: %s", hipGetErrorString(err));
     if (g_mark_after_main) {
@@ -1897,8 +2364,9 @@ respec_status_t verify_attention_any(const void *q, const void *k_cache, const v
         g_mark_after_main = nullptr;
     }
     {
-        err = D == 128 ? launch_combine<128>(p, M, kv_tokens, kn.get(&Knobs::attn_combine, 0), stream)
-                       : launch_combine<64>(p, M, kv_tokens, kn.get(&Knobs::attn_combine, 0), stream);
+        const double most = few ? (double)max_kv_len / (4 * kTileKeys) + 1 : (double)kMaxWaves;
+        err = D == 128 ? launch_combine<128>(p, M, kv_tokens, most, kn.get(&Knobs::attn_combine, 0), stream)
+                       : launch_combine<64>(p, M, kv_tokens, most, kn.get(&Knobs::attn_combine, 0), stream);
         if (err != hipSuccess)
             return fail(RESPEC_ERR_HIP, "verify_attention: combine launch failed: %s", hipGetErrorString(err));
     }

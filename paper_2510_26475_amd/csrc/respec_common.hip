@@ -42,6 +42,7 @@ void read_knobs_locked() {
     g_knobs.attn_quad = env_long("RESPEC_ATTN_QUAD");
     g_knobs.attn_inline = env_long("RESPEC_ATTN_INLINE");
     g_knobs.attn_consumers = env_long("RESPEC_ATTN_CONSUMERS");
+    g_knobs.attn_few = env_long("RESPEC_ATTN_FEW");
     g_knobs.attn_combine = env_long("RESPEC_ATTN_COMBINE");
     g_knobs.sampler_split = env_long("RESPEC_SAMPLER_SPLIT");
     g_knobs.sampler_two_term = env_long("RESPEC_SAMPLER_TWO_TERM");

@@ -34,6 +34,7 @@ struct Knobs {
     long attn_quad;         // RESPEC_ATTN_QUAD: 0/1/2 four consumers per range never / by rule / also narrow blocks
     long attn_inline;       // RESPEC_ATTN_INLINE: 0 = the set-up kernel also for small batches
     long attn_consumers;    // RESPEC_ATTN_CONSUMERS: 4/8 consumer waves per work-group of the four-way form up to 64 columns
+    long attn_few;          // RESPEC_ATTN_FEW: 0/1/2 never / one / two work-groups per compute unit in the form for few tiles, wherever it takes the batch
     long attn_combine;      // RESPEC_ATTN_COMBINE: waves that share a column's parts in the combine kernel (1, 4, 8)
     long sampler_split;     // RESPEC_SAMPLER_SPLIT: work-groups per sequence (1, 2, 4, 8)
     long sampler_two_term;  // RESPEC_SAMPLER_TWO_TERM: never the one-fma exponent
