@@ -170,12 +170,14 @@ def _dev_ptr(t: Optional[torch.Tensor], name: str):
         raise ValueError(f"{name} must live on the GPU (got {t.device})")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
+# (A small step is bound by this module: its calls enqueue in about the time that its kernels take.  A
+# stream object made for its handle takes 2.7 us of the 9 to 12 us that a call needs here, the handle
+# alone 0.3: the fp32 step of 4 sequences 19.4 -> 14.9 us.)
 def _stream_ptr(stream: Optional[torch.cuda.Stream]):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
 
 
 def respec_reload_knobs():
@@ -344,7 +346,7 @@ def respec_rejection_sample(target_logits, draft_logits, draft_tokens, q_indptr,
             return None
         if not t.is_cuda:
             raise ValueError(f"{name} must live on the GPU")
-        return ctypes.c_void_p(t.data_ptr())
+        return t.data_ptr()
 
     _check(lib.respec_rejection_sample(
         row_ptr(target_logits, "target_logits"), row_ptr(draft_logits, "draft_logits"),
@@ -393,7 +395,7 @@ def respec_rejection_sample_per_seq(target_logits, draft_logits, draft_tokens, q
             return None
         if not t.is_cuda:
             raise ValueError(f"{name} must live on the GPU")
-        return ctypes.c_void_p(t.data_ptr())
+        return t.data_ptr()
 
     _check(lib.respec_rejection_sample_per_seq(
         row_ptr(target_logits, "target_logits"), row_ptr(draft_logits, "draft_logits"),
@@ -435,7 +437,7 @@ def respec_tree_rejection_sample(target_logits, draft_logits, node_tokens, paren
         if not t.is_cuda:
             raise ValueError(f"{name} must live on the GPU")
     _check(lib.respec_tree_rejection_sample(
-        ctypes.c_void_p(target_logits.data_ptr()), ctypes.c_void_p(draft_logits.data_ptr()),
+        target_logits.data_ptr(), draft_logits.data_ptr(),
         _dev_ptr(node_tokens, "node_tokens"), _dev_ptr(parent, "parent"), _dev_ptr(q_indptr, "q_indptr"),
         _dev_ptr(u_accept, "u_accept"), _dev_ptr(u_final, "u_final"), _dev_ptr(out_tokens, "out_tokens"),
         _dev_ptr(out_path, "out_path"), _dev_ptr(out_num_accepted, "out_num_accepted"),
@@ -535,8 +537,8 @@ def respec_kd_rows(target_logits, draft_logits, row_weight, grad, row_loss, tota
             raise ValueError(f"{name} must live on the GPU")
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib.respec_kd_rows(
-        ctypes.c_void_p(target_logits.data_ptr()), ctypes.c_void_p(draft_logits.data_ptr()),
-        _dev_ptr(row_weight, "row_weight"), ctypes.c_void_p(grad.data_ptr()), _dev_ptr(row_loss, "row_loss"),
+        target_logits.data_ptr(), draft_logits.data_ptr(),
+        _dev_ptr(row_weight, "row_weight"), grad.data_ptr(), _dev_ptr(row_loss, "row_loss"),
         _dev_ptr(total_loss, "total_loss"), rows, V, target_logits.stride(0), draft_logits.stride(0),
         grad.stride(0), _dtype_code(target_logits), _dev_ptr(workspace, "workspace"), ws_bytes,
         _stream_ptr(stream)))
