@@ -361,8 +361,13 @@ respec_status_t respec_rejection_sample(const void *target_logits, const void *d
  *
  *   temperature   [B] f32, device; each finite and >= 0
  *   draft_logits, u_accept   may be NULL when every sequence with drafted tokens is greedy
- *   other arguments as in respec_rejection_sample; there is no workspace (a sequence is
- *   handled by one work-group).
+ *   other arguments as in respec_rejection_sample; there is no workspace.  While the batch leaves
+ *   compute units idle, two or four work-groups share a sequence all the same, through
+ *   mailboxes of the library's own (a static device array): they meet before the walk begins,
+ *   and a sequence whose work-groups do not find each other within 20 us (compute units held by
+ *   another stream's kernel) is walked by one.  Calls may overlap on any streams and be
+ *   captured.  As with a workspace, the row pair right behind a rejected position may be read
+ *   (never used).
  * Device-side data errors that the host cannot see (a negative or non-finite temperature, a
  * sampled sequence with drafted tokens but draft_logits or u_accept NULL) give
  * out_num_accepted[b] = -1 and out_tokens[b, :] = -1 for that sequence.
@@ -408,7 +413,9 @@ respec_status_t respec_rejection_sample_per_seq(const void *target_logits, const
  *                 (bit1 is also set when a residual came out empty and the target was used)
  *   max_q_per_seq host-side bound of the rows of a sequence, <= 64 (RESPEC_ERR_UNSUPPORTED)
  *   max_depth     host-side bound of the depth of any tree (root = depth 0)
- * A chain-shaped tree gives the tokens of respec_rejection_sample bit for bit.
+ * A chain-shaped tree gives the tokens of respec_rejection_sample bit for bit (draws flagged
+ * as boundary draws apart, where the two share a sequence differently).  Sequences are shared
+ * between work-groups as in respec_rejection_sample_per_seq.
  */
 respec_status_t respec_tree_rejection_sample(const void *target_logits, const void *draft_logits,
                                              const int32_t *node_tokens, const int32_t *parent,

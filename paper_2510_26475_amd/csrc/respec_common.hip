@@ -49,6 +49,8 @@ void read_knobs_locked() {
     g_knobs.sampler_guarded = env_long("RESPEC_SAMPLER_GUARDED");
     g_knobs.sampler_no_table = env_long("RESPEC_SAMPLER_NO_TABLE");
     g_knobs.sampler_two_items = env_long("RESPEC_SAMPLER_TWO_ITEMS");
+    g_knobs.sampler_claim = env_long("RESPEC_SAMPLER_CLAIM");
+    g_knobs.sampler_claim_ticks = env_long("RESPEC_SAMPLER_CLAIM_TICKS");
     g_knobs.kd_wgs = env_long("RESPEC_KD_WGS");
     g_knobs.kd_team = env_long("RESPEC_KD_TEAM");
     g_knobs.kd_spin = env_long("RESPEC_KD_SPIN");

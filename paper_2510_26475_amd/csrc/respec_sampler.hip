@@ -26,8 +26,9 @@
 // systematic error enters).  "ref" is a per-thread reference near the row maximum, not
 // necessarily the maximum: fp32 keeps full relative precision for any offset, and the
 // references are reconciled in fp64 when threads (and parts) are combined.
-#include "respec_sampler_rows.hpp"
+#include "respec_sampler_share.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace respec {
@@ -59,145 +60,10 @@ struct SamplerParams : RowMath {
     char *boxes;       // [B] mailboxes of kBoxBytes (split > 1)
     const float *temps;  // [B] one temperature per sequence (0: greedy), or NULL: the RowMath constants hold
     int tab_slots;       // > 0: the launch carries dynamic LDS for one float per slot of a row
+    uint32_t claim;      // > 0: the parts of a sequence meet in the library's own mailboxes, under this key, ...
+    int claim_ticks;     // ... and wait for each other that long
 };
 
-
-// ------------------------------------------------------------------------------------------
-// mailbox: the few numbers the parts of one sequence exchange after a streaming pass
-// ------------------------------------------------------------------------------------------
-// Layout of one box (kBoxBytes): word 0 the epoch (calls that have used the box), then
-// [part][stage parity][16] tagged words of payload: the eight doubles a part publishes per
-// stage, each as two 64-bit words that carry 32 bits of the value below a 32-bit mark,
-// mark = epoch*1024 + stage + 1.  A word is written and read with one 8-byte device-scope
-// access, so a reader that finds the mark it waits for has the value that belongs to it: no
-// separate flag and no fence; a reader fetches a partner's sixteen words together and is done
-// after one memory round trip once the partner has published (a flag behind the payload costs
-// three: the writer's wait for its stores, the reader's poll, the reader's dependent read).
-// A part that has read every partner's stage s may publish stage s+1 into the other parity
-// buffer, and nobody can be two stages ahead of the slowest reader, so a word is never
-// overwritten while somebody still waits for it.  Part 0 bumps the epoch when it leaves (every
-// partner has read it by then: they publish their first stage after reading it, and part 0 has
-// read that stage), so nothing needs resetting and the box only has to be zero before its
-// first use (a mark is never 0).  All accesses are device-scope atomics: the parts run on
-// compute units whose L2 caches are not coherent with each other.
-struct Mailbox {
-    uint32_t *words;
-    unsigned long long *payload;
-    uint32_t base;          // valid from the first exchange on
-    int part, split, stage;
-    uint32_t epoch;         // thread 0: the box's epoch, requested at the start of the kernel
-    uint32_t *sh_epoch;     // LDS word it is handed to the block in
-};
-
-// One exchange.  Every thread of the block calls it with the same `mine`; afterwards
-// sh.xchg[j] holds what part j published.  Ends with a barrier.  A wait that runs out of its
-// (very large) spin budget marks the block as failed and goes on, so that every block ends.
-__device__ inline void exchange(Mailbox &mb, const double (&mine)[8], SharedState &sh) {
-    if (mb.stage == 0) {  // block-uniform; (by now the epoch has arrived: the first pass did not wait for it)
-        if (threadIdx.x == 0) {
-            *mb.sh_epoch = mb.epoch;
-            // a box that an earlier call left poisoned (one of its waits ran out) cannot be trusted
-            // until the caller has zeroed it again: every part reports failure without waiting
-            if (mb.epoch == kBoxPoison) sh.failed = 1;
-        }
-        __syncthreads();
-        mb.base = *mb.sh_epoch * 1024u;
-    }
-    const int parity = mb.stage & 1;
-    const uint32_t mark = mb.base + (uint32_t)mb.stage + 1u;
-    const unsigned long long tag = (unsigned long long)mark << 32;
-    if (threadIdx.x == 64) {  // (a thread of the second wave publishes, the first wave collects)
-        unsigned long long *dst = mb.payload + (mb.part * 2 + parity) * 16;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const unsigned long long bits = __builtin_bit_cast(unsigned long long, mine[i]);
-            __hip_atomic_store(dst + 2 * i, tag | (bits & 0xffffffffull), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(dst + 2 * i + 1, tag | (bits >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    if ((int)threadIdx.x < mb.split) {
-        const int j = threadIdx.x;
-        if (j == mb.part) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sh.xchg[j][i] = mine[i];
-        } else {
-            const unsigned long long *src = mb.payload + (j * 2 + parity) * 16;
-            unsigned long long w[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) w[i] = 0;
-            if (!sh.failed) {
-                int spin = 0;
-                for (;;) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        w[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    bool all = true;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) all = all && (uint32_t)(w[i] >> 32) == mark;
-                    if (all) break;
-                    if (++spin > kSpinLimit) {
-                        sh.failed = 1;
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) w[i] = 0;
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(2);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                sh.xchg[j][i] = __builtin_bit_cast(double, (w[2 * i] & 0xffffffffull) | (w[2 * i + 1] << 32));
-        }
-    }
-    ++mb.stage;
-    __syncthreads();
-}
-
-// (M, S) of a row (and, if TWO, of the drafter row) over the whole vocabulary.  This block
-// streams its own part (`rowp`, `rowq` point at the part's first slot, `nslots` and `Vrow`
-// are the part's); with several parts the partial results are exchanged and combined in part
-// order, so every part holds the same bits afterwards.  A part whose fast pass overflowed or came out empty repeats
-// it by itself, the others wait for it in the exchange.
-template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL, int TH, class Meanwhile = Nothing>
-__device__ inline void row_stats_any(const void *rowp, const void *rowq, int nslots, int Vrow, SharedState &sh,
-                                     int parity, Mailbox &mb, const SamplerParams &p, float &Mp,
-                                     double &Sp, float &Mq, double &Sq, Meanwhile &&meanwhile = Nothing{}) {
-    if constexpr (!FULL) meanwhile();
-    if constexpr (!SHARED) {
-        if constexpr (FULL) {
-            if (row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile))
-                return;        // block-uniform
-            __syncthreads();   // every thread has read the combine buffers of this parity
-        }
-        row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
-        return;
-    }
-    bool ok = false;  // block-uniform
-    if (nslots <= 0) {  // a part without slots (tiny vocabulary): nothing to read, no mass
-        if constexpr (FULL) meanwhile();
-        __syncthreads();  // (in place of the pass's own: every wave has read what the last exchange brought)
-        Mp = Mq = kRefInit;
-        Sp = Sq = 0.0;
-        ok = true;
-    } else if constexpr (FULL) {
-        ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile);
-        if (!ok) __syncthreads();  // every thread has read the combine buffers of this parity
-    }
-    if (!ok) row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
-    const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, 0.0, 0.0, 0.0, 0.0};
-    exchange(mb, mine, sh);
-    // In every wave, so that no barrier is needed (the next exchange has one ahead of it): lane 8 r + j: row r (p, q)
-    // of part j; one exp2 per lane.
-    const int r = (threadIdx.x / kMaxSplit) & 1, j = threadIdx.x & (kMaxSplit - 1);
-    const bool have = j < mb.split;
-    const float m_j = have ? (float)sh.xchg[j][2 * r] : -INFINITY;
-    const float M = group_max<kMaxSplit>(m_j);
-    const double S = group_sum<kMaxSplit>(have ? sh.xchg[j][2 * r + 1] * exp2_f64(((double)m_j - (double)M) * p.c_d) : 0.0);
-    Mp = lane_value(M, 0);
-    Sp = lane_value(S, 0);
-    Mq = lane_value(M, kMaxSplit);
-    Sq = lane_value(S, kMaxSplit);
-}
 
 // The normalisers of one row pair: references and sums of the p row and the q row.
 struct DrawNorm {
@@ -938,9 +804,10 @@ __device__ inline void device_row_math(RowMath &m, float temperature) {
 
 // The first argmax of a row: its largest logit, the lowest token id among equal ones (an
 // all -inf row gives token 0).  Every thread returns the same value.  Ends with a barrier.
-template <bool BF16, bool FULL, bool PARTIAL>
-__device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedState &sh) {
-    constexpr int EPV = Elem<BF16>::EPV;
+// `value`: that largest logit.
+template <bool BF16, bool FULL, bool PARTIAL, int TH>
+__device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedState &sh, float &value) {
+    constexpr int EPV = Elem<BF16>::EPV, kThreads = TH, kWaves = TH / 64;
     const int nslots = PARTIAL ? whole_slots<BF16>(nslots_all, V) : nslots_all;
     constexpr int kBatch = kThreads * kUnroll;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
@@ -1025,6 +892,7 @@ __device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedS
         }
     }
     __syncthreads();  // everyone has read the wave results before the next row overwrites them
+    value = best;
     return best_i == 0x7fffffff ? 0 : best_i;
 }
 
@@ -1032,33 +900,48 @@ __device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedS
 // accepted iff it is the first argmax of its target row; the first one that is not is replaced
 // by that argmax; if all are accepted the bonus token is the argmax of row k.  Reads target
 // rows 0..n only, no drafter logits and no uniforms.
-template <bool BF16, bool FULL, bool PARTIAL>
-__device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, int drow0, int k, SharedState &sh) {
+// A shared sequence's parts look through a part of the row each and exchange what they found.
+template <bool BF16, bool FULL, bool PARTIAL, bool SHARED, int TH>
+__device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, int drow0, int k, int lo, int nslots, int Vrow,
+                                       SharedState &sh, Mailbox &mb) {
     constexpr int EPV = Elem<BF16>::EPV;
-    const int nslots = (p.V + EPV - 1) / EPV;
     const size_t esz = BF16 ? 2 : 4;
     int32_t *out = p.out_tokens + (size_t)b * (p.max_k + 1);
     int n = 0, a;
     for (;;) {
-        const char *rowp = static_cast<const char *>(p.target) + (size_t)(row0 + n) * p.ld_t * esz;
-        a = row_argmax<BF16, FULL, PARTIAL>(rowp, nslots, p.V, sh);
+        const char *rowp = static_cast<const char *>(p.target) + (size_t)(row0 + n) * p.ld_t * esz + (size_t)lo * 16;
+        float value;
+        a = lo * EPV + row_argmax<BF16, FULL, PARTIAL, TH>(rowp, nslots, Vrow, sh, value);
+        if constexpr (SHARED) {
+            const double mine[8] = {(double)value, (double)a, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            exchange(mb, mine, sh);
+            double best = sh.xchg[0][0];
+            a = (int)sh.xchg[0][1];
+            for (int j = 1; j < mb.split; ++j)  // in vocabulary order: strict > keeps the first
+                if (sh.xchg[j][0] > best) {
+                    best = sh.xchg[j][0];
+                    a = (int)sh.xchg[j][1];
+                }
+        }
         if (n >= k) break;
         const int x = p.draft_tokens[drow0 + n];
         if (x != a) break;
-        if (threadIdx.x == 0) out[n] = x;
+        if (threadIdx.x == 0 && mb.part == 0) out[n] = x;
         ++n;
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && mb.part == 0) {
         out[n] = a;
         for (int j = n + 1; j <= p.max_k; ++j) out[j] = -1;
-        p.out_num_accepted[b] = n;
+        p.out_num_accepted[b] = SHARED && sh.failed != 0 ? -1 : n;
         if (p.out_flags) p.out_flags[b] = 0;
     }
 }
 
 // SHORT: the form for rows of at most kShortSlots slots (one work-group per sequence).
-template <bool BF16, bool ONE_TERM, bool FULL, int SHARE, bool SHORT, bool PARTIAL>
+// CLAIM: the parts of a shared sequence meet in the library's own mailboxes (one temperature per sequence).
+template <bool BF16, bool ONE_TERM, bool FULL, int SHARE, bool SHORT, bool PARTIAL, bool CLAIM = false>
 __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
+    static_assert(!CLAIM || (SHARE != kOwn && !ONE_TERM), "shared, and two-term constants");
     constexpr bool SHARED = SHARE != kOwn;
     constexpr int kThreads = share_threads(SHARE), kWaves = kThreads / 64, TH = kThreads;
     __shared__ SharedState sh;
@@ -1070,8 +953,15 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     constexpr bool kFastScan = ONE_TERM;
     extern __shared__ __align__(16) char sampler_smem[];
     float *tab = kFastScan && p.tab_slots > 0 ? reinterpret_cast<float *>(sampler_smem) : nullptr;
-    const int split = SHARED ? p.split : 1;
+    int split = SHARED ? p.split : 1;
     const int b = blockIdx.x / split, part = blockIdx.x % split;
+    uint32_t claim_epoch = 0;
+    if constexpr (CLAIM) {
+        if (!claim_meet(claim_box(p.claim, b), p.claim, part, split, p.claim_ticks, &sh_epoch, sh, claim_epoch)) {  // block-uniform
+            if (part != 0) return;
+            split = 1;
+        }
+    }
     // bounds come from device data: clamp them by the host-side totals so that no value of
     // q_indptr can push a row outside the logits buffers
     const int row0 = max(0, min(p.q_indptr[b], p.total_q - 1));
@@ -1089,36 +979,44 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     const char *tbase = static_cast<const char *>(p.target);
     const char *dbase = static_cast<const char *>(p.draft);
     int32_t *out = p.out_tokens + (size_t)b * (p.max_k + 1);
-    if constexpr (!SHARED && !ONE_TERM) {
+    const double u_fin = (double)p.u_final[b];
+    Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch};
+    if (threadIdx.x == 0) sh.failed = 0;
+    if constexpr (CLAIM) {
+        mb = claim_mailbox(claim_box(p.claim, b), part, split, claim_epoch, &sh_epoch);
+    } else if constexpr (SHARED) {
+        mb.words = reinterpret_cast<uint32_t *>(p.boxes + (size_t)b * kBoxBytes);
+        mb.payload = reinterpret_cast<unsigned long long *>(p.boxes + (size_t)b * kBoxBytes + kBoxHeaderBytes);
+        if (threadIdx.x == 0) mb.epoch = load_dev(mb.words);
+    }
+    auto leave = [&]() __attribute__((always_inline)) {  // one thread of the block, behind its last exchange
+        if constexpr (CLAIM) {
+            // (a box whose wait ran out stays taken, and its sequence is walked alone from then on)
+            if (mb.split > 1 && sh.failed == 0) claim_leave(claim_box(p.claim, b), mb.split, mb.epoch);
+        }
+    };
+    if constexpr ((!SHARED || CLAIM) && !ONE_TERM) {
         if (p.temps != nullptr) {  // block-uniform
             const float T = p.temps[b];
             const bool bad = !(T >= 0.f) || T == INFINITY ||
                              (T > 0.f && k > 0 && (p.draft == nullptr || p.u_accept == nullptr));
             if (bad) {  // a caller error: make it impossible to miss
-                if (threadIdx.x == 0) {
+                if (threadIdx.x == 0 && part == 0) {
                     for (int j = 0; j <= p.max_k; ++j) out[j] = -1;
                     p.out_num_accepted[b] = -1;
                     if (p.out_flags) p.out_flags[b] = 0;
                 }
+                if (threadIdx.x == 0) leave();
                 return;
             }
             if (T == 0.f) {
-                greedy_sequence<BF16, FULL, PARTIAL>(p, b, row0, drow0, k, sh);
+                greedy_sequence<BF16, FULL, PARTIAL, SHARED, TH>(p, b, row0, drow0, k, lo, nslots, Vrow, sh, mb);
+                if (threadIdx.x == 0) leave();
                 return;
             }
             device_row_math(p, T);
         }
     }
-    const double u_fin = (double)p.u_final[b];
-
-    Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch};
-    if (threadIdx.x == 0) sh.failed = 0;
-    if constexpr (SHARED) {
-        mb.words = reinterpret_cast<uint32_t *>(p.boxes + (size_t)b * kBoxBytes);
-        mb.payload = reinterpret_cast<unsigned long long *>(p.boxes + (size_t)b * kBoxBytes + kBoxHeaderBytes);
-        if (threadIdx.x == 0) mb.epoch = load_dev(mb.words);
-    }
-
     int n = 0, flag_accept = 0, flag_cdf = 0, final_token = -1;
     bool rejected = false, mine = false;
     // shared sequences walk their chain two items per stage (see row_stats_two_items); `ahead`
@@ -1333,7 +1231,9 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         } else if (failed) {
             p.out_num_accepted[b] = -1;  // a wait for a partner ran out: make it impossible to miss
         }
-        if constexpr (SHARED) {
+        if constexpr (CLAIM) {
+            leave();
+        } else if constexpr (SHARED) {
             // Part 0 advances the epoch; a part whose wait ran out poisons the box instead (a
             // partner that turns up later must not find an epoch it could publish under, and the
             // next call must not trust what this one left).  Both are atomic maxima, so the
@@ -1366,6 +1266,17 @@ __global__ __launch_bounds__(kThreads) void partial_rows_sample_kernel(SamplerPa
 template <bool BF16>
 __global__ __launch_bounds__(share_threads(kTwoAtATime)) void partial_rows_two_items_kernel(SamplerParams p) {
     rejection_sample<BF16, false, true, kTwoAtATime, false, true>(p);
+}
+
+// One temperature per sequence, shared between work-groups that meet in the library's mailboxes.
+template <bool BF16, bool PARTIAL>
+__global__ __launch_bounds__(kThreads) void claimed_sample_kernel(SamplerParams p) {
+    rejection_sample<BF16, false, true, kOneAtATime, false, PARTIAL, true>(p);
+}
+
+template <bool BF16, bool PARTIAL>
+__global__ __launch_bounds__(share_threads(kTwoAtATime)) void claimed_two_items_kernel(SamplerParams p) {
+    rejection_sample<BF16, false, true, kTwoAtATime, false, PARTIAL, true>(p);
 }
 
 template <bool BF16, bool ONE_TERM>
@@ -1428,8 +1339,11 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
     // part keeps a useful share of the row; one (and no mailbox) without a workspace
     int split = 1, cus = 256;
     bool two_items = false;
-    if (workspace) {
-        if (workspace_bytes < (size_t)B * kBoxBytes || !aligned_to(workspace, 16))
+    // (per-sequence temperatures have no workspace argument: their parts meet in the library's own mailboxes)
+    const bool claim = temps && V >= (logits_dt == RESPEC_BF16 ? 8 : 4) && kn.get(&Knobs::sampler_guarded, 0) == 0 &&
+                       kn.get(&Knobs::sampler_claim, 1) != 0;
+    if (workspace || claim) {
+        if (workspace && (workspace_bytes < (size_t)B * kBoxBytes || !aligned_to(workspace, 16)))
             return fail(RESPEC_ERR_WORKSPACE, "rejection_sample: workspace of %zu bytes (16-byte aligned) needed, got %zu",
                         (size_t)B * kBoxBytes, workspace_bytes);
         int dev = 0;
@@ -1459,6 +1373,14 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         if (V % epv0 != 0)
             while (split > 1 && (long)(split - 1) * (((slots_row + split - 1) / split + 63) / 64 * 64) >= V / epv0) split /= 2;
         if (2 * ((long)max_k + 1) + 4 >= 1024) split = 1;
+        if (claim) {
+            split = std::min(split, kClaimSplit);
+            while (split > 1 && (long)B * split > kClaimGroups) split /= 2;
+        }
+    }
+    if (claim && split > 1) {
+        p.claim = next_claim_key();
+        p.claim_ticks = (int)kn.get(&Knobs::sampler_claim_ticks, kClaimTicks);
     }
     if ((int64_t)B * split > 0x7fffffffLL)
         return fail(RESPEC_ERR_UNSUPPORTED, "rejection_sample: too many work-groups");
@@ -1501,6 +1423,11 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         else if (two_items) RESPEC_LAUNCH_SAMPLER_SHARED((two_items_sample_kernel<BF, ONE>), kTwoAtATime); \
         else RESPEC_LAUNCH_SAMPLER_SHARED((rejection_sample_kernel<BF, ONE, true, true>), kOneAtATime);     \
     } while (0)
+#define RESPEC_LAUNCH_CLAIMED(BF, PARTIAL)                                                                          \
+    do {                                                                                                           \
+        if (two_items) RESPEC_LAUNCH_SAMPLER_SHARED((claimed_two_items_kernel<BF, PARTIAL>), kTwoAtATime);         \
+        else RESPEC_LAUNCH_SAMPLER_SHARED((claimed_sample_kernel<BF, PARTIAL>), kOneAtATime);                      \
+    } while (0)
 #define RESPEC_LAUNCH_GUARDED(BF)                                                                                   \
     do {                                                                                                           \
         if (split == 1) RESPEC_LAUNCH_SAMPLER_ONE((rejection_sample_kernel<BF, false, false, false>));              \
@@ -1529,7 +1456,10 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
     // some sequence goes on: 24.2 / 23.2), with a single draft (V = 2048 9.5 / 10.6) and at 1024 slots
     // (V = 4096, B = 2048 128 / 135, drafts rarely accepted 87 / 133).
     const bool short_rows = full && split == 1 && max_k > 1 && ((int64_t)V + epv - 1) / epv <= kShortSlots;
-    if (short_rows && bf) {
+    if (p.claim) {
+        if (bf) { if (whole_rows) RESPEC_LAUNCH_CLAIMED(true, false); else RESPEC_LAUNCH_CLAIMED(true, true); }
+        else { if (whole_rows) RESPEC_LAUNCH_CLAIMED(false, false); else RESPEC_LAUNCH_CLAIMED(false, true); }
+    } else if (short_rows && bf) {
         if (one) RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<true, true>));
         else RESPEC_LAUNCH_SAMPLER_ONE((short_rows_sample_kernel<true, false>));
     } else if (short_rows) {
@@ -1545,6 +1475,7 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         if (one) RESPEC_LAUNCH_FORM(false, true); else RESPEC_LAUNCH_FORM(false, false);
     }
 #undef RESPEC_LAUNCH_FORM
+#undef RESPEC_LAUNCH_CLAIMED
 #undef RESPEC_LAUNCH_GUARDED
 #undef RESPEC_LAUNCH_PARTIAL
 #undef RESPEC_LAUNCH_SAMPLER_SHARED

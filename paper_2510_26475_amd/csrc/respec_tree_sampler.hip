@@ -11,17 +11,49 @@
 // node; when no child is left the one final token is drawn from the running distribution.
 // A chain is the tree with one child per node and gives exactly the chain sampler's tokens.
 //
-// One work-group of 512 threads walks one sequence.  p_r(x) is a pointwise function of
+// One work-group of 512 threads walks one sequence, or, while the batch leaves compute units idle, two or four do,
+// a part of the vocabulary each: after every pass they exchange their partial results and take the same decisions
+// from the same numbers (respec_sampler_share.hpp).  p_r(x) is a pointwise function of
 // p(x), q(x) and the r scalars Z_1..Z_r, so nothing is materialised: every rejection costs
 // one streaming pass over the node's row pair that sums max(0, p_r - q) (region totals in
 // fp64, which also serve the final draw when the rejected child was the last), and an
 // acceptance test needs only the candidate's own two logits.
-#include "respec_sampler_rows.hpp"
+#include "respec_sampler_share.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace respec {
 namespace {
+
+// The two logits of a candidate as they are in memory, fetched through the scalar cache: the same for every thread and in
+// scalar registers, requested behind a pass's first batch, so that the test behind the pass waits for nothing and the
+// pass keeps its vector registers (a test's chain of loads, token, logits and uniform, took 1.5 us of
+// every pass).  A 16-bit logit comes with the rest of its aligned word.
+struct Candidate {
+    uint32_t p, q;
+};
+
+template <bool BF16>
+__device__ inline uint32_t scalar_logit_word(const char *row, int x) {
+    const uint64_t at = (reinterpret_cast<uintptr_t>(row) + (uintptr_t)x * (BF16 ? 2 : 4)) & ~(uintptr_t)3;
+    const uint64_t uniform = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)at) |
+                             (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32;
+    return *(const uint32_t __attribute__((address_space(4))) *)uniform;
+}
+
+template <bool BF16>
+__device__ inline Candidate fetch_candidate(const char *rowp, const char *rowq, int x) {
+    Candidate c{scalar_logit_word<BF16>(rowp, x), scalar_logit_word<BF16>(rowq, x)};
+    asm volatile("" : "+s"(c.p), "+s"(c.q));  // (here, not where they are used)
+    return c;
+}
+
+template <bool BF16>
+__device__ inline float logit_of_word(uint32_t word, const char *row, int x) {
+    if constexpr (BF16) word = (reinterpret_cast<uintptr_t>(row) + (uintptr_t)x * 2) & 2 ? word & 0xffff0000u : word << 16;
+    return __uint_as_float(word);
+}
 
 constexpr int kMaxTreeRows = 64;   // rows (nodes) of one sequence: the attention's mask width
 constexpr int kRegDepth = 3;       // rejection depths whose normalisers are held in registers
@@ -40,6 +72,9 @@ struct TreeParams : RowMath {
     int32_t *out_flags;
     int32_t B, total_q, max_depth, V;
     int64_t ld_t, ld_d;
+    int split;        // work-groups per sequence
+    uint32_t claim;   // their call's key in the library's mailboxes, and ...
+    int claim_ticks;  // ... how long they wait to meet
 };
 
 // The running distribution after `depth` rejections at one node, without its normaliser:
@@ -165,12 +200,14 @@ __device__ inline float tree_slot_weights_f32(const u32x4 &vp, const u32x4 &vq, 
 
 // Region totals of the running distribution: each wave owns a contiguous eighth of the row
 // and streams it with coalesced loads; lanes keep their own fp64 sums, one reduction per wave
-// gives the region total (left in sh.wave_total).  Returns Z = the ordered sum of the region
-// totals, the same bits in every thread.  At depth 0 only the target row is read.
-template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND>
+// gives the region total (left in sh.wave_total; of a shared sequence those of all parts, in vocabulary order, in
+// sh.xchg).  Returns Z = the ordered sum of the region totals, the same bits in every thread.  At depth 0
+// only the target row is read.
+// `meanwhile` is called once the first batch has been requested.
+template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND, bool SHARED, class Meanwhile = Nothing>
 __device__ inline double tree_region_totals(const void *rowp, const void *rowq, int nslots, int V, float Mp,
                                             double Sp, float Mq, double Sq, const Depth &d, double raw_1, SharedState &sh,
-                                            const RowMath &p) {
+                                            Mailbox &mb, const RowMath &p, Meanwhile &&meanwhile = Nothing{}) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     constexpr bool two = KIND > 0;
@@ -214,6 +251,7 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
         };
         constexpr int kStep = 64 * kUnroll;
         load_batch(beg, vp, vq);
+        meanwhile();
         // (the loads of the steady state are unconditional: behind a condition the wait for the
         // batch in front of a load becomes a wait for everything in flight)
         int s0 = beg;
@@ -231,6 +269,7 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
             sum_batch(s0, vp, vq, std::false_type{});
         }
     }
+    if (beg >= end) meanwhile();
     if constexpr (PARTIAL) {
         if (beg <= whole && whole < end_all && lane == 0) {  // the row's partial slot
             const u32x4 a = load_partial_slot<BF16>(rowp, whole, V), b = two ? load_partial_slot<BF16>(rowq, whole, V) : a;
@@ -245,21 +284,31 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
     if (lane == 0) sh.wave_total[wave] = region_total;
     __syncthreads();
     double Z = 0.0;
-    for (int w = 0; w < kWaves; ++w) Z += sh.wave_total[w];
-    return Z;
+    if constexpr (SHARED) {
+        static_assert(kWaves == 8, "a part publishes eight numbers");
+        double mine[8];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) mine[w] = sh.wave_total[w];
+        exchange(mb, mine, sh);
+        for (int w = 0; w < mb.split * kWaves; ++w) Z += sh.xchg[w / kWaves][w % kWaves];
+    } else {
+        for (int w = 0; w < kWaves; ++w) Z += sh.wave_total[w];
+    }
+    return lane_value(Z, 0);  // (every lane's, in scalar registers)
 }
 
-// The final draw, given the region totals in sh.wave_total (Z > 0): first token, in ascending
+// The final draw, given the region totals that tree_region_totals left (Z > 0): first token, in ascending
 // id, whose running sum of weights exceeds u*Z.  Every thread finds the region that holds the
 // crossing from the ordered prefix over the region totals; the block re-reads that region,
 // each thread a short contiguous run of slots: thread totals -> one block scan -> the first
 // thread whose running sum passes u*Z walks its run element by element.  The re-read adds
 // the same numbers in another order than the region pass, so at the last bit a crossing can
 // fall off the end of the region; that draw takes the last token with mass and is flagged.
-template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND>
+// SHARED: -1 with mine = false when the region lies in another part of the row.
+template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND, bool SHARED>
 __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, int V, float Mp, double Sp,
                                 float Mq, double Sq, const Depth &d, double raw_1, double u, SharedState &sh,
-                                const RowMath &p, int &near_edge) {
+                                const Mailbox &mb, const RowMath &p, int &near_edge, bool &mine) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     constexpr bool two = KIND > 0;
@@ -273,13 +322,15 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
         sh.first_thread = kThreads;
         sh.last_positive = -1;
     }
+    const int regions = SHARED ? mb.split * kWaves : kWaves;
+    auto total_of = [&](int w) { return SHARED ? sh.xchg[w / kWaves][w % kWaves] : sh.wave_total[w]; };
     double Z = 0.0;
-    for (int w = 0; w < kWaves; ++w) Z += sh.wave_total[w];
+    for (int w = 0; w < regions; ++w) Z += total_of(w);
     const double t = u * Z;
     int rstar = -1, rlast = 0;
     double base = 0.0, prefix = 0.0;
-    for (int w = 0; w < kWaves; ++w) {
-        const double tot = sh.wave_total[w];
+    for (int w = 0; w < regions; ++w) {
+        const double tot = total_of(w);
         const double next = prefix + tot;  // same additions, same order as Z above
         if (rstar < 0 && next > t) {
             rstar = w;
@@ -290,6 +341,12 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     }
     const bool forced = rstar < 0;  // u*Z rounded up to Z: take the last token with mass
     if (forced) rstar = rlast;
+    mine = true;
+    if constexpr (SHARED) {
+        mine = rstar / kWaves == mb.part;  // block-uniform
+        if (!mine) return -1;
+        rstar %= kWaves;
+    }
     __syncthreads();
 
     const int whole = PARTIAL ? whole_slots<BF16>(nslots, V) : nslots;
@@ -439,28 +496,50 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     return tok;
 }
 
-template <bool BF16, bool ONE_TERM, bool FULL, bool PARTIAL>
+template <bool BF16, bool ONE_TERM, bool FULL, bool PARTIAL, bool SHARED>
 __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
+    static_assert(FULL || !SHARED, "the guarded form is not shared");
     __shared__ SharedState sh;
+    __shared__ uint32_t sh_epoch;
     __shared__ int sh_parent[kMaxTreeRows];
     __shared__ double sh_inv_z[kMaxTreeRows];
+    __shared__ int sh_token[kMaxTreeRows];
+    __shared__ float sh_u[kMaxTreeRows];
     constexpr int EPV = Elem<BF16>::EPV;
-    const int b = blockIdx.x;
+    int split = SHARED ? p.split : 1;
+    const int b = blockIdx.x / split, part = blockIdx.x % split;
+    Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch};
+    if constexpr (SHARED) {
+        uint32_t epoch;
+        if (!claim_meet(claim_box(p.claim, b), p.claim, part, split, p.claim_ticks, &sh_epoch, sh, epoch)) {  // block-uniform
+            if (part != 0) return;
+            split = 1;
+        }
+        mb = claim_mailbox(claim_box(p.claim, b), part, split, epoch, &sh_epoch);
+    }
     // bounds come from device data: clamp them by the host-side totals so that no value of
     // q_indptr or parent can push a row outside the logits buffers
     const int row0 = max(0, min(p.q_indptr[b], p.total_q - 1));
     const int R = max(1, min(p.q_indptr[b + 1] - row0, min(kMaxTreeRows, p.total_q - row0)));
-    const int nslots = (p.V + EPV - 1) / EPV;
+    const int nslots_row = (p.V + EPV - 1) / EPV;
+    // this block's part of the vocabulary: a whole number of 64-slot groups
+    const int part_span = SHARED ? ((nslots_row + split - 1) / split + 63) / 64 * 64 : nslots_row;
+    const int lo = min(part * part_span, nslots_row);
+    const int nslots = min(lo + part_span, nslots_row) - lo, V = p.V - lo * EPV;
     const size_t esz = BF16 ? 2 : 4;
     const char *tbase = static_cast<const char *>(p.target);
     const char *dbase = static_cast<const char *>(p.draft);
     // (the output rows are addressed where they are written and the final uniform is loaded where
     // it is used: values that live across the streaming passes cost registers there)
     auto out_row = [&]() { return p.out_tokens + (size_t)b * (p.max_depth + 1); };
+    auto at = [&](const char *row) { return row + (size_t)lo * 16; };  // this part of a row
     auto path_row = [&]() { return p.out_path + (size_t)b * max(p.max_depth, 1); };
     if (threadIdx.x < kMaxTreeRows) {
         sh_parent[threadIdx.x] = (int)threadIdx.x < R ? p.parent[row0 + threadIdx.x] : -2;
         sh_inv_z[threadIdx.x] = 1.0;
+        const int at = row0 + min((int)threadIdx.x, R - 1);
+        sh_token[threadIdx.x] = max(0, min(p.node_tokens[at], p.V - 1));  // memory safety only; ids outside [0,V) are a caller error
+        sh_u[threadIdx.x] = p.u_accept[at];
     }
     __syncthreads();
 
@@ -482,23 +561,20 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
         int c = cur + 1;
         while (c < R && sh_parent[c] != cur) ++c;
         if (c >= R || n >= p.max_depth) break;  // a leaf (or the output row is full): draw from the target
-        if constexpr (FULL) {
-            if (!row_stats_fast<BF16, true, ONE_TERM, PARTIAL>(rowp, rowq, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq)) {
-                __syncthreads();
-                row_stats<BF16, true>(rowp, rowq, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
-            }
-        } else {
-            row_stats<BF16, true>(rowp, rowq, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
-        }
+        Candidate cand{};
+        int x = 0;
+        auto fetch = [&]() __attribute__((always_inline)) {  // child c's token and its logits
+            x = __builtin_amdgcn_readfirstlane(sh_token[c]);
+            cand = fetch_candidate<BF16>(rowp, rowq, x);
+        };
+        row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, kThreads>(at(rowp), at(rowq), nslots, V, sh, parity, mb, p, Mp, Sp, Mq, Sq, fetch);
         parity ^= 1;
         have_norm = true;
         bool moved = false;
         double Zd = 1.0;  // normaliser of the running distribution (Z_depth)
         while (c < R) {
-            int x = p.node_tokens[row0 + c];
-            x = max(0, min(x, p.V - 1));  // memory safety only; ids outside [0,V) are a caller error
-            const float zpx = logit_at<BF16>(rowp, x), zqx = logit_at<BF16>(rowq, x);
-            const double u = (double)p.u_accept[row0 + c];
+            const float zpx = logit_of_word<BF16>(cand.p, rowp, x), zqx = logit_of_word<BF16>(cand.q, rowq, x);
+            const double u = (double)sh_u[c];
             // Eq. 1 in fp64 against the running distribution: rho = p_depth(x)/q(x)
             double rho;
             if (depth == 0) {
@@ -509,7 +585,7 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
             } else {
                 const double px = exp(((double)zpx - (double)Mp) * p.inv_T) / Sp;
                 const double qx = exp(((double)zqx - (double)Mq) * p.inv_T) / Sq;
-                const Depth d{depth, sh_inv_z[1], sh_inv_z[2], sh_inv_z};
+                const Depth d{depth, lane_value(sh_inv_z[1], 0), lane_value(sh_inv_z[2], 0), sh_inv_z};
                 const double a = running_weight(px, qx, d) / Zd;
                 if (qx == 0.0)
                     rho = a > 0.0 ? (double)INFINITY : 0.0;
@@ -519,7 +595,7 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
             const double thr = rho < 1.0 ? rho : 1.0;
             if (fabs(u - thr) <= kBoundaryEps) flag_accept = 1;
             if (u < thr) {  // accepted: the child becomes the node
-                if (threadIdx.x == 0) {
+                if (threadIdx.x == 0 && part == 0) {
                     out_row()[n] = x;
                     path_row()[n] = c;
                 }
@@ -530,17 +606,22 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
             }
             // rejected: the running distribution becomes max(0, p_depth - q)/Z (Eq. 2)
             depth += 1;
+            ++c;
+            while (c < R && sh_parent[c] != cur) ++c;
+            auto fetch_next = [&]() __attribute__((always_inline)) {
+                if (c < R) fetch();
+            };
             {
-                const Depth d{depth, sh_inv_z[1], sh_inv_z[2], sh_inv_z};
+                const Depth d{depth, lane_value(sh_inv_z[1], 0), lane_value(sh_inv_z[2], 0), sh_inv_z};
                 if (depth == 1) {
-                    raw_1 = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 1>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                    raw_1 = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 1, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
                     Zd = raw_1;
                     if constexpr (ONE_TERM) Zd += raw_1 * (double)make_fast_norm(Mp, Sp, Mq, Sq, p).ep;
                 } else if (depth == 2) {
-                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 2>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 2, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
                     if constexpr (ONE_TERM) Zd /= raw_1;
                 } else {
-                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, p);
+                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
                 }
             }
             if (Zd > 0.0) {
@@ -553,12 +634,10 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
                 flag_cdf = 1;
             }
             __syncthreads();
-            ++c;
-            while (c < R && sh_parent[c] != cur) ++c;
         }
         if (!moved) break;  // every child was rejected: one draw from the running distribution
     }
-    const Depth d{depth, sh_inv_z[1], sh_inv_z[2], sh_inv_z};
+    const Depth d{depth, lane_value(sh_inv_z[1], 0), lane_value(sh_inv_z[2], 0), sh_inv_z};
     double Z = 1.0;
     if (!have_totals) {  // a leaf, or an exact tie: the target row itself
         // At a leaf one pass serves instead of two: the draw compares running sums with u times
@@ -572,54 +651,65 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
         }
         for (;;) {
             if (!trial && !have_norm) {
-                bool ok = false;
-                if constexpr (FULL) {
-                    ok = row_stats_fast<BF16, false, ONE_TERM, PARTIAL>(rowp, rowp, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
-                    if (!ok) __syncthreads();
-                }
-                if (!ok) row_stats<BF16, false>(rowp, rowp, nslots, p.V, sh, parity, p, Mp, Sp, Mq, Sq);
+                row_stats_any<BF16, false, ONE_TERM, FULL, SHARED, PARTIAL, kThreads>(at(rowp), at(rowp), nslots, V, sh, parity, mb, p, Mp, Sp, Mq, Sq);
                 have_norm = true;
             }
-            Z = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 0>(rowp, rowp, nslots, p.V, Mp, Sp, Mp, Sp, d, raw_1, sh, p);
+            Z = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 0, SHARED>(at(rowp), at(rowp), nslots, V, Mp, Sp, Mp, Sp, d, raw_1, sh, mb, p);
             if (!trial || (Z > 0.0 && Z < 1.0e300)) break;
             trial = false;
         }
     }
+    bool mine = part == 0;
     if (Z > 0.0) {
         const double u = (double)p.u_final[b];
         int edge = 0;
         if (depth == 0)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 0>(rowp, rowp, nslots, p.V, Mp, Sp, Mp, Sp, d, raw_1, u, sh, p, edge);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 0, SHARED>(at(rowp), at(rowp), nslots, V, Mp, Sp, Mp, Sp, d, raw_1, u, sh, mb, p, edge, mine);
         else if (depth == 1)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 1>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 1, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
         else if (depth == 2)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 2>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 2, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
         else
-            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth>(rowp, rowq, nslots, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, p, edge);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
+        final_token += lo * EPV;  // (what is drawn is an index in this part)
         flag_cdf |= edge;
     } else {  // row without any finite logit: report the last token
         final_token = p.V - 1;
         flag_cdf = 1;
     }
     if (threadIdx.x == 0) {
-        int32_t *out = out_row(), *path = path_row();
-        out[n] = final_token;
-        for (int j = n + 1; j <= p.max_depth; ++j) out[j] = -1;
-        for (int j = n; j < p.max_depth; ++j) path[j] = -1;
-        p.out_num_accepted[b] = n;
-        if (p.out_flags) p.out_flags[b] = (flag_accept ? 1 : 0) | (flag_cdf ? 2 : 0);
+        const bool failed = SHARED && sh.failed != 0;  // a wait for a part that was there ran out
+        if (mine) {
+            int32_t *out = out_row(), *path = path_row();
+            out[n] = final_token;
+            for (int j = n + 1; j <= p.max_depth; ++j) out[j] = -1;
+            for (int j = n; j < p.max_depth; ++j) path[j] = -1;
+            p.out_num_accepted[b] = failed ? -1 : n;
+            if (p.out_flags) p.out_flags[b] = (flag_accept ? 1 : 0) | (flag_cdf ? 2 : 0);
+        } else if (failed) {
+            p.out_num_accepted[b] = -1;
+        }
+        if constexpr (SHARED) {
+            if (split > 1 && !failed) claim_leave(claim_box(p.claim, b), split, mb.epoch);
+        }
     }
 }
 
 template <bool BF16, bool ONE_TERM, bool FULL>
 __global__ __launch_bounds__(kThreads) void tree_rejection_sample_kernel(TreeParams p) {
-    tree_rejection_sample<BF16, ONE_TERM, FULL, false>(p);
+    tree_rejection_sample<BF16, ONE_TERM, FULL, false, false>(p);
 }
 
-// Rows that are not whole aligned slots (fp64 weights).
 template <bool BF16>
+__global__ __launch_bounds__(kThreads) void shared_tree_kernel(TreeParams p) {
+    tree_rejection_sample<BF16, true, true, false, true>(p);
+}
+
+// Rows that are not whole aligned slots (fp64 weights); shared sequences with a two-term constant take it for
+// any rows.
+template <bool BF16, bool SHARED>
 __global__ __launch_bounds__(kThreads) void tree_partial_rows_kernel(TreeParams p) {
-    tree_rejection_sample<BF16, false, true, true>(p);
+    tree_rejection_sample<BF16, false, true, true, SHARED>(p);
 }
 
 }  // namespace
@@ -681,18 +771,41 @@ extern "C" respec_status_t respec_tree_rejection_sample(
                             aligned_to(draft_logits, 16) && (ld_d * esz) % 16 == 0;
     p.one_term = p.one_term && whole_rows;
     const bool bf = logits_dt == RESPEC_BF16, one = p.one_term != 0;
-#define RESPEC_LAUNCH_TREE(KERNEL) hipLaunchKernelGGL(KERNEL, dim3((unsigned)B), dim3(kThreads), 0, stream, p)
+    // Work-groups per sequence: while compute units are idle and a part keeps 4096 slots (fp32, half as many elements, 8192); below, what a pass gets shorter by
+    // is less than meeting after it costs (one / two / four work-groups, us per call, 3 x 2 candidates at T = 0.6: bf16,
+    // V = 151,936, B = 128 86.8 / 77.3 / -, B = 64 86.2 / - / 60.0, B = 1 55.7 / - / 40.2; V = 77,777, B = 100 74.2 / 65.5 / -; V = 32,768, B = 64
+    // 36.0 / 41.9 / -; fp32, V = 151,936, B = 64 90.3 / - / 71.1, V = 50,257 46.6 / 48.5 / 47.2).
+    p.split = 1;
+    const Knobs kn = knobs();
+    if (full && kn.get(&Knobs::sampler_claim, 1) != 0) {
+        int dev = 0, cus = 256;
+        if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        cus = std::min(cus, kClaimGroups);
+        const long slots_row = ((long)V + epv - 1) / epv;
+        while (p.split < kClaimSplit && (long)B * p.split * 2 <= cus && slots_row / (p.split * 2) >= (bf ? 4096 : 8192)) p.split *= 2;
+    }
+    if (p.split > 1) {
+        p.claim = next_claim_key();
+        p.claim_ticks = (int)kn.get(&Knobs::sampler_claim_ticks, kClaimTicks);
+    }
+#define RESPEC_LAUNCH_TREE(KERNEL) hipLaunchKernelGGL(KERNEL, dim3((unsigned)(B * p.split)), dim3(kThreads), 0, stream, p)
+    const bool shared = p.split > 1;
     if (!full) {
         if (bf) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<true, false, false>));
         else RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<false, false, false>));
+    } else if (shared && one) {
+        if (bf) RESPEC_LAUNCH_TREE((shared_tree_kernel<true>));
+        else RESPEC_LAUNCH_TREE((shared_tree_kernel<false>));
+    } else if (shared) {
+        if (bf) RESPEC_LAUNCH_TREE((tree_partial_rows_kernel<true, true>));
+        else RESPEC_LAUNCH_TREE((tree_partial_rows_kernel<false, true>));
     } else if (!whole_rows) {
-        if (bf) RESPEC_LAUNCH_TREE((tree_partial_rows_kernel<true>));
-        else RESPEC_LAUNCH_TREE((tree_partial_rows_kernel<false>));
-    } else if (bf) {
-        if (one) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<true, true, true>));
-        else RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<true, false, true>));
+        if (bf) RESPEC_LAUNCH_TREE((tree_partial_rows_kernel<true, false>));
+        else RESPEC_LAUNCH_TREE((tree_partial_rows_kernel<false, false>));
     } else {
-        if (one) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<false, true, true>));
+        if (bf && one) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<true, true, true>));
+        else if (bf) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<true, false, true>));
+        else if (one) RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<false, true, true>));
         else RESPEC_LAUNCH_TREE((tree_rejection_sample_kernel<false, false, true>));
     }
 #undef RESPEC_LAUNCH_TREE

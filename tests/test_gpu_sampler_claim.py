@@ -1,0 +1,111 @@
+"""Sequences shared between work-groups without a workspace (one temperature per sequence, trees of drafts):
+the parts meet in the library's own mailboxes, or part 0 walks alone.  Exact against the CPU oracle on
+unflagged sequences either way, in order, beside other calls and under replay."""
+import pytest
+import torch
+
+from helpers import compare_sampler, compare_tree_sampler, env_setting, gpu_tree_sample, oracle_tree_sample
+from paper_2510_26475_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+TEMPS = (0.6, 0.0, 1.0, 0.4)
+
+
+def _wl(B, k, V, dtype, T=0.6):
+    return synth.Workload("claim", B=B, k=k, Hq=8, Hkv=1, D=64, V=V, dtype=dtype, len_dist="uniform", len_lo=64, len_hi=64, temperature=T)
+
+
+def _chain(B, k, V, dtype, seed):
+    batch = synth.make_batch(_wl(B, k, V, dtype), device="cuda", kv_lens=[64] * B, k_per_seq=[(k, k, 1, 0)[b % 4] for b in range(B)], seed=seed,
+                             with_attention=False)
+    return batch, [TEMPS[(b * 7 + b // 4) % 4] for b in range(B)]
+
+
+class _Call:
+    """A call with one temperature per sequence and buffers of its own."""
+
+    def __init__(self, batch, temps):
+        B, dev = len(batch.k_per_seq), "cuda"
+        self.batch, self.temps = batch, torch.tensor(temps, dtype=torch.float32, device=dev)
+        self.toks = torch.full((B, batch.max_k + 1), -7, dtype=torch.int32, device=dev)
+        self.n, self.flags = (torch.full((B,), -7, dtype=torch.int32, device=dev) for _ in range(2))
+
+    def __call__(self):
+        b = self.batch
+        binding.respec_rejection_sample_per_seq(b.target_logits, b.draft_logits, b.draft_tokens, b.q_indptr, b.u_accept, b.u_final,
+                                                self.temps, self.toks, self.n, self.flags, b.max_k)
+
+    def result(self):
+        torch.cuda.synchronize()
+        return self.toks.cpu().numpy(), self.n.cpu().numpy(), self.flags.cpu().numpy()
+
+    def reference(self, oracle):
+        b = self.batch
+        dt = oracle.F32 if b.wl.dtype == "f32" else oracle.BF16
+        return oracle.rejection_sample_per_seq(
+            synth.to_host_array(b.target_logits), synth.to_host_array(b.draft_logits), b.draft_tokens.cpu().numpy(),
+            b.q_indptr.cpu().numpy(), b.u_accept.cpu().numpy(), b.u_final.cpu().numpy(), b.max_k, self.temps.cpu().numpy(), dt,
+            n_threads=0)
+
+
+def _tree(B, V, dtype, seed, T):
+    shapes = [synth.caterpillar_parents(3, 2), synth.caterpillar_parents(2, 4), [-1], [-1, 0, 1, 2]]
+    return synth.make_tree_batch(_wl(B, 6, V, dtype, T), [shapes[b % 4] for b in range(B)], device="cuda", kv_lens=[64] * B, seed=seed,
+                                 with_attention=False)
+
+
+# parts of two and four, one and two items per stage, whole and ragged rows; ticks 0: whoever does not find the others
+# at once gives up, so sequences are walked alone, shared, or found given up
+@pytest.mark.parametrize("ticks", [None, 0])
+@pytest.mark.parametrize("B,V,dtype", [(1, 151936, "bf16"), (9, 151936, "bf16"), (64, 33000, "bf16"), (65, 40000, "bf16"), (128, 65536, "bf16"),
+                                       (20, 77777, "bf16"), (33, 50257, "f32"), (70, 50257, "f32"), (5, 151936, "f32")])
+def test_temperatures(oracle, B, V, dtype, ticks):
+    batch, temps = _chain(B, 4, V, dtype, seed=B)
+    call = _Call(batch, temps)
+    ref = call.reference(oracle)
+    with env_setting("RESPEC_SAMPLER_CLAIM_TICKS", ticks):
+        for _ in range(3):
+            call()
+            compare_sampler(call.result(), ref)
+
+
+@pytest.mark.parametrize("ticks", [None, 0])
+@pytest.mark.parametrize("B,V,dtype,T", [(1, 151936, "bf16", 0.6), (9, 151936, "bf16", 1.0), (64, 131072, "bf16", 0.6), (70, 65536, "bf16", 1.0),
+                                         (20, 77777, "bf16", 0.6), (12, 50257, "f32", 0.6), (5, 151936, "f32", 1.0)])
+def test_trees(oracle, B, V, dtype, T, ticks):
+    tb = _tree(B, V, dtype, B, T)
+    ref = oracle_tree_sample(oracle, tb)
+    with env_setting("RESPEC_SAMPLER_CLAIM_TICKS", ticks):
+        for _ in range(3):
+            compare_tree_sampler(gpu_tree_sample(tb), ref)
+
+
+# calls of several streams at a time (their work-groups compete for the compute units), and replays of a graph
+def test_streams_and_replays(oracle):
+    calls = []
+    for i, B in enumerate((100, 60, 128)):
+        batch, temps = _chain(B, 3, 65536, "bf16", seed=20 + i)
+        calls.append(_Call(batch, temps))
+        calls[-1]()
+    torch.cuda.synchronize()
+    refs = [c.reference(oracle) for c in calls]
+    streams = [torch.cuda.Stream() for _ in calls]
+    for _ in range(40):
+        for c, s in zip(calls, streams):
+            with torch.cuda.stream(s):
+                c()
+    for c, ref in zip(calls, refs):
+        compare_sampler(c.result(), ref)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for c in calls:
+            c()
+    for _ in range(3):
+        for c in calls:
+            c.toks.zero_()
+            c.n.fill_(-7)
+        graph.replay()
+        calls[0]()  # eager work between the replays
+        for c, ref in zip(calls, refs):
+            compare_sampler(c.result(), ref)
