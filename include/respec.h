@@ -20,7 +20,8 @@
  * General rules
  *   - Every data pointer is a DEVICE pointer (HIP global memory) unless it says "host".
  *     The caller owns all buffers; the library allocates and frees nothing on the device
- *     and keeps no state between calls (the profiling hook below aside).
+ *     and keeps no state between calls (the profiling hook below and the samplers' own
+ *     mailboxes aside, which no call has to know of).
  *   - Calls are asynchronous on `hip_stream` (a hipStream_t passed as void*, NULL = the
  *     default stream) and never synchronise.  Inputs must stay valid and unchanged until
  *     the stream has passed the call.
