@@ -1361,7 +1361,17 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
         // B = 64, k = 1 15.2 / 16.4 in parts of 1000, k = 0 10.2 / 12.7).
         const int epv0 = logits_dt == RESPEC_BF16 ? 8 : 4;
         const long slots_row = ((long)V + epv0 - 1) / epv0;
-        const long least = two_items && max_k >= 3 && slots_row >= (logits_dt == RESPEC_BF16 ? 3328 : 4096) ? 768 : 2048;  // slots of a part
+        long least = two_items && max_k >= 3 && slots_row >= (logits_dt == RESPEC_BF16 ? 3328 : 4096) ? 768 : 2048;  // slots of a part
+        // Parts that have to meet first want longer rows (mixed temperatures, by one work-group / shared, us per call: bf16, one item, B = 100,
+        // V = 36,000 and 44,000 32.4 / 36.4, 35.0 / 37.3, V = 50,000, B = 128 40.9 / 39.8; two items, V = 30,000 and more 34.1 / 28.7; fp32, whose
+        // slots hold half as many elements: two items, B = 64, k = 3, V = 32,000 in two and four 26.3 / 30.5, 26.0 / 27.2, V = 40,000 in two 28.7 / 33.3,
+        // V = 50,000 in four 33.3 / 32.4; one item, B = 128, V = 50,000 35.3 / 39.5, V = 70,000 43.4 / 43.9).
+        if (claim) {
+            const bool bf16 = logits_dt == RESPEC_BF16, wide_chain = two_items && max_k >= 3;
+            if (!bf16) least = !two_items ? 9600 : slots_row >= 4 * 3072 ? 3072 : slots_row;
+            else if (!wide_chain) least = two_items ? 4096 : 3072;
+            else if (slots_row < 3700) least = slots_row;
+        }
         while (split < kMaxSplit && (long)B * split * 2 <= cus && slots_row / (split * 2) >= least) split *= 2;
         const long forced = kn.get(&Knobs::sampler_split, 0);
         if (forced == 1 || forced == 2 || forced == 4 || forced == 8) split = (int)forced;

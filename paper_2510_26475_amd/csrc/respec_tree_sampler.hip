@@ -771,18 +771,20 @@ extern "C" respec_status_t respec_tree_rejection_sample(
                             aligned_to(draft_logits, 16) && (ld_d * esz) % 16 == 0;
     p.one_term = p.one_term && whole_rows;
     const bool bf = logits_dt == RESPEC_BF16, one = p.one_term != 0;
-    // Work-groups per sequence: while compute units are idle and a part keeps 4096 slots (fp32, half as many elements, 8192); below, what a pass gets shorter by
-    // is less than meeting after it costs (one / two / four work-groups, us per call, 3 x 2 candidates at T = 0.6: bf16,
-    // V = 151,936, B = 128 86.8 / 77.3 / -, B = 64 86.2 / - / 60.0, B = 1 55.7 / - / 40.2; V = 77,777, B = 100 74.2 / 65.5 / -; V = 32,768, B = 64
-    // 36.0 / 41.9 / -; fp32, V = 151,936, B = 64 90.3 / - / 71.1, V = 50,257 46.6 / 48.5 / 47.2).
+    // Work-groups per sequence: while compute units are idle and a part keeps 4800 slots (fp32, half as many elements: 9216; two per
+    // sequence on the whole device, which memory bounds: 6144, fp32 16,384); below, what a pass gets shorter by is less than meeting and
+    // exchanging cost.  One work-group / shared, us per call, T = 0.6: 3 x 2 candidates, bf16, V = 151,936, B = 128 86.8 / 78.3, B = 64
+    // 86.2 / 60.0, B = 1 55.7 / 40.2, V = 77,777, B = 100 74.2 / 65.5; V = 32,768, B = 64 36.0 / 41.9; fp32, V = 151,936, B = 64 90.3 / 71.1;
+    // 2 x 2 candidates, bf16, V = 66,000, B = 64 and 128 42.8 / 44.1, 44.0 / 46.5, V = 80,000 and 110,000, B = 128 47.5 / 48.3, 57.6 / 57.8; fp32, B = 64, V = 66,000 and 74,000 40.8 / 41.8, 44.3 / 43.7,
+    // B = 128, V = 66,000, 77,777, 110,000, 131,072 48.0 / 54.4, 58.8 / 59.8, 72.5 / 73.6, 85.4 / 83.2.
     p.split = 1;
     const Knobs kn = knobs();
     if (full && kn.get(&Knobs::sampler_claim, 1) != 0) {
         int dev = 0, cus = 256;
         if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         cus = std::min(cus, kClaimGroups);
-        const long slots_row = ((long)V + epv - 1) / epv;
-        while (p.split < kClaimSplit && (long)B * p.split * 2 <= cus && slots_row / (p.split * 2) >= (bf ? 4096 : 8192)) p.split *= 2;
+        const long slots_row = ((long)V + epv - 1) / epv, least = (long)B * 4 > cus ? (bf ? 6144 : 16384) : (bf ? 4800 : 9216);
+        while (p.split < kClaimSplit && (long)B * p.split * 2 <= cus && slots_row / (p.split * 2) >= least) p.split *= 2;
     }
     if (p.split > 1) {
         p.claim = next_claim_key();
