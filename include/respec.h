@@ -365,9 +365,9 @@ respec_status_t respec_rejection_sample(const void *target_logits, const void *d
  *   other arguments as in respec_rejection_sample; there is no workspace.  While the batch leaves
  *   compute units idle, two or four work-groups share a sequence all the same, through
  *   mailboxes of the library's own (a static device array): they meet before the walk begins,
- *   and a sequence whose work-groups do not find each other within 20 us (compute units held by
- *   another stream's kernel) is walked by one.  Calls may overlap on any streams and be
- *   captured.  As with a workspace, the row pair right behind a rejected position may be read
+ *   and where they do not find each other within 20 us (compute units held by another stream's
+ *   kernel) one does the work of all, in the same order: the result has the same bits, later.
+ *   Calls may overlap on any streams and be captured.  As with a workspace, the row pair right behind a rejected position may be read
  *   (never used).
  * Device-side data errors that the host cannot see (a negative or non-finite temperature, a
  * sampled sequence with drafted tokens but draft_logits or u_accept NULL) give

@@ -42,7 +42,7 @@ struct Knobs {
     long sampler_no_table;  // RESPEC_SAMPLER_NO_TABLE: the final draw without its table of slot totals
     long sampler_two_items; // RESPEC_SAMPLER_TWO_ITEMS: 0/1 shared sequences walk one or two chain items per stage
     long sampler_claim;     // RESPEC_SAMPLER_CLAIM: 0 = calls without a workspace never share a sequence
-    long sampler_claim_ticks; // RESPEC_SAMPLER_CLAIM_TICKS: 10 ns ticks that the parts of such a sequence wait to meet
+    long sampler_claim_ticks; // RESPEC_SAMPLER_CLAIM_TICKS: 10 ns ticks that the parts of such a sequence wait to meet (negative: they never do)
     long kd_wgs;            // RESPEC_KD_WGS: work-groups of the distillation kernel
     long kd_team;           // RESPEC_KD_TEAM: 0 = one work-group per row pair, which it streams twice
     long kd_spin;           // RESPEC_KD_SPIN: 10 ns ticks that a member's part of a row is waited for

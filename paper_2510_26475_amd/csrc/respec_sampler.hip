@@ -88,10 +88,11 @@ struct DrawNorm {
 // The two items are one stream of batches: B's first batch is requested ahead of A's last, and the
 // four sums are reduced together behind one barrier (one pass after the other left the memory pipeline
 // empty for 3 us of every stage).
+// The rows' share of one part (pointers at its first slot): leaves its own normalisers in A and Bn.
 template <bool BF16, bool ONE_TERM, bool PARTIAL, int TH, class Meanwhile>
-__device__ inline void row_stats_two_items(const void *pa, const void *qa, const void *pb, const void *qb,
-                                           bool b_pair, int nslots_all, int Vrow, SharedState &sh, Mailbox &mb,
-                                           const SamplerParams &p, DrawNorm &A, DrawNorm &Bn, Meanwhile &&meanwhile) {
+__device__ __forceinline__ void part_stats_two_items(const char *pa, const char *qa, const char *pb, const char *qb,
+                                                     bool b_pair, int nslots_all, int Vrow, SharedState &sh,
+                                                     const SamplerParams &p, DrawNorm &A, DrawNorm &Bn, Meanwhile &&meanwhile) {
     constexpr int EPV = Elem<BF16>::EPV, kThreads = TH, kWaves = TH / 64, kBatch = kThreads * kUnroll;
     A.Mp = A.Mq = Bn.Mp = Bn.Mq = kRefInit;
     A.Sp = A.Sq = Bn.Sp = Bn.Sq = 0.0;
@@ -246,13 +247,26 @@ __device__ inline void row_stats_two_items(const void *pa, const void *qa, const
         meanwhile();
         __syncthreads();  // (as in row_stats_any)
     }
-    // two binary32 references travel as the halves of one 8-byte word (moved, never computed with)
-    auto pack = [](float lo, float hi) {
-        return __builtin_bit_cast(double, (unsigned long long)__float_as_uint(lo) |
-                                              ((unsigned long long)__float_as_uint(hi) << 32));
-    };
-    const double mine[8] = {pack(A.Mp, A.Mq), A.Sp, A.Sq, pack(Bn.Mp, Bn.Mq), Bn.Sp, Bn.Sq, 0.0, 0.0};
-    exchange(mb, mine, sh);
+}
+
+// (the rows from their starts)
+template <bool BF16, bool ONE_TERM, bool PARTIAL, int TH, bool MEETS, class Meanwhile>
+__device__ inline void row_stats_two_items(const char *pa, const char *qa, const char *pb, const char *qb, bool b_pair,
+                                           const PartView &own, SharedState &sh, Mailbox &mb, const SamplerParams &p,
+                                           DrawNorm &A, DrawNorm &Bn, Meanwhile &&meanwhile) {
+    for_parts<BF16, MEETS>(mb, own, p.V, sh, [&](int, const PartView &v, double(&mine)[8]) __attribute__((always_inline)) {
+        const size_t at = (size_t)v.lo * 16;
+        part_stats_two_items<BF16, ONE_TERM, PARTIAL, TH>(pa + at, qa + at, pb + at, qb + at, b_pair, v.nslots, v.Vrow, sh, p, A, Bn,
+                                                          meanwhile);
+        // two binary32 references travel as the halves of one 8-byte word (moved, never computed with)
+        auto pack = [](float lo, float hi) {
+            return __builtin_bit_cast(double, (unsigned long long)__float_as_uint(lo) |
+                                                  ((unsigned long long)__float_as_uint(hi) << 32));
+        };
+        mine[0] = pack(A.Mp, A.Mq), mine[1] = A.Sp, mine[2] = A.Sq;
+        mine[3] = pack(Bn.Mp, Bn.Mq), mine[4] = Bn.Sp, mine[5] = Bn.Sq;
+        mine[6] = mine[7] = 0.0;
+    });
     // in every wave (see row_stats_any): lane 8 (2 item + row) + j: part j; one exp2 per lane
     const int g = (threadIdx.x / kMaxSplit) & 3, j = threadIdx.x & (kMaxSplit - 1);
     const int item = g >> 1, r = g & 1;
@@ -754,34 +768,65 @@ __device__ inline int draw_finish(double tot, int my_reg0, const RowPart &part,
     return tok;
 }
 
+// What the weights of one part are formed against (a drawing block's own part).  scale: what brings them to the scale that
+// the parts of a sequence share (NaN: no usable reference; every block then finds Z_out NaN).
+struct PartRef {
+    float M;
+    double scale;
+};
+
 // The draw of a block that sees one part of the row: its own share of a sequence that several
 // work-groups walk together (SHARED: the region totals are exchanged, and the block that holds
-// the crossing finishes), or the whole row.  scale: what brings the weights of this block, formed
-// against its own reference, to the scale that the blocks of a sequence share (NaN: no usable
-// reference; every block then finds Z_out NaN).
-template <bool BF16, bool RESID, bool FULL, bool SHARED, bool FAST, bool PARTIAL, int TH>
-__device__ inline int inverse_cdf_pass(const void *rowp, const void *rowq, int nslots, int Vrow, int tok_off,
-                                       float Mp, double Sp, float Mq, double Sq, double u, SharedState &sh,
-                                       Mailbox &mb, const SamplerParams &p, int &near_edge, double &Z_out,
-                                       bool &mine, float *tab = nullptr, double scale = 1.0) {
-    constexpr int kWaves = TH / 64;
-    const RowPart part{rowp, rowq, nslots, Vrow, tok_off, tab};
-    const DrawNorm nm{Mp, Mq, Sp, Sq};
-    draw_region_totals<BF16, RESID, FULL, FAST, PARTIAL, TH>(part, nm, sh, p);
-    __syncthreads();
-    // the region totals of all parts, in vocabulary order
+// the crossing finishes), or the whole row.  `ref_of(view)`: the reference of a part, for draws whose parts
+// have references of their own (OwnRefs; the normaliser is then taken as 1); others go by `nm`.
+template <bool BF16, bool RESID, bool FULL, bool SHARED, bool FAST, bool PARTIAL, int TH, bool MEETS, bool OwnRefs, class RefOf>
+__device__ inline int inverse_cdf_pass(const char *rowp, const char *rowq, const PartView &own, const DrawNorm &nm, double u,
+                                       SharedState &sh, Mailbox &mb, const SamplerParams &p, int &near_edge, double &Z_out,
+                                       bool &mine, float *tab, RefOf &&ref_of) {
+    constexpr int EPV = Elem<BF16>::EPV, kWaves = TH / 64;
     const int lane = threadIdx.x & 63;
-    const int n_reg = SHARED ? mb.split * kWaves : kWaves;
-    if constexpr (SHARED) {
-        double pub[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    auto row_part = [&](const PartView &v) __attribute__((always_inline)) {
+        return RowPart{rowp + (size_t)v.lo * 16, rowq + (size_t)v.lo * 16, v.nslots, v.Vrow, v.lo * EPV, tab};
+    };
+    auto norm_at = [&](float M) __attribute__((always_inline)) { return OwnRefs ? DrawNorm{M, M, 1.0, 1.0} : nm; };
+    if constexpr (!SHARED) {
+        const RowPart part = row_part(own);
+        draw_region_totals<BF16, RESID, FULL, FAST, PARTIAL, TH>(part, nm, sh, p);
+        __syncthreads();
+        const double tot = lane < kWaves ? sh.wave_total[lane] : 0.0;
+        return draw_finish<BF16, RESID, FULL, FAST, false, PARTIAL, TH>(tot, 0, part, nm, u, sh, p, near_edge, Z_out, mine, 1.0);
+    } else {
+        PartRef ref{0.f, 1.0};
+        for_parts<BF16, MEETS>(mb, own, p.V, sh, [&](int j, const PartView &v, double(&pub)[8]) __attribute__((always_inline)) {
+            if constexpr (OwnRefs) {
+                ref = ref_of(v);
+                if constexpr (MEETS)
+                    if (threadIdx.x == 0) {
+                        sh.part_ref[j] = ref.M;
+                        sh.part_scale[j] = ref.scale;
+                    }
+            }
+            draw_region_totals<BF16, RESID, FULL, FAST, PARTIAL, TH>(row_part(v), norm_at(ref.M), sh, p);
+            __syncthreads();
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) pub[w] = sh.wave_total[w] * scale;
-        exchange(mb, pub, sh);
+            for (int w = 0; w < 8; ++w) pub[w] = w < kWaves ? sh.wave_total[w] * ref.scale : 0.0;
+        });
+        // the region totals of all parts, in vocabulary order
+        const double tot = lane < mb.split * kWaves ? sh.xchg[lane / kWaves][lane % kWaves] : 0.0;
+        if constexpr (!MEETS) {
+            return draw_finish<BF16, RESID, FULL, FAST, true, PARTIAL, TH>(tot, mb.part * kWaves, row_part(own), norm_at(ref.M), u, sh, p,
+                                                                           near_edge, Z_out, mine, ref.scale);
+        } else {
+            PartView v = own;
+            for (int j = mb.part;;) {  // (conditions are block-uniform; a part without the crossing only looks for it)
+                if constexpr (OwnRefs) ref = PartRef{sh.part_ref[j], sh.part_scale[j]};
+                const int tok = draw_finish<BF16, RESID, FULL, FAST, true, PARTIAL, TH>(tot, j * kWaves, row_part(v), norm_at(ref.M), u, sh,
+                                                                                        p, near_edge, Z_out, mine, ref.scale);
+                if (__builtin_expect(!mb.alone, 1) || mine || !(Z_out > 0.0) || ++j == mb.split) return tok;
+                v = part_view<BF16>(p.V, j, mb.split);
+            }
+        }
     }
-    double tot = 0.0;
-    if (lane < n_reg) tot = SHARED ? sh.xchg[lane / kWaves][lane % kWaves] : sh.wave_total[lane];
-    return draw_finish<BF16, RESID, FULL, FAST, SHARED, PARTIAL, TH>(tot, SHARED ? mb.part * kWaves : 0, part, nm, u, sh,
-                                                        p, near_edge, Z_out, mine, scale);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -902,19 +947,23 @@ __device__ inline int row_argmax(const void *row, int nslots_all, int V, SharedS
 // rows 0..n only, no drafter logits and no uniforms.
 // A shared sequence's parts look through a part of the row each and exchange what they found.
 template <bool BF16, bool FULL, bool PARTIAL, bool SHARED, int TH>
-__device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, int drow0, int k, int lo, int nslots, int Vrow,
+__device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, int drow0, int k, const PartView &own,
                                        SharedState &sh, Mailbox &mb) {
     constexpr int EPV = Elem<BF16>::EPV;
     const size_t esz = BF16 ? 2 : 4;
     int32_t *out = p.out_tokens + (size_t)b * (p.max_k + 1);
     int n = 0, a;
     for (;;) {
-        const char *rowp = static_cast<const char *>(p.target) + (size_t)(row0 + n) * p.ld_t * esz + (size_t)lo * 16;
+        const char *rowp = static_cast<const char *>(p.target) + (size_t)(row0 + n) * p.ld_t * esz;
         float value;
-        a = lo * EPV + row_argmax<BF16, FULL, PARTIAL, TH>(rowp, nslots, Vrow, sh, value);
-        if constexpr (SHARED) {
-            const double mine[8] = {(double)value, (double)a, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-            exchange(mb, mine, sh);
+        if constexpr (!SHARED) {
+            a = row_argmax<BF16, FULL, PARTIAL, TH>(rowp, own.nslots, p.V, sh, value);
+        } else {
+            for_parts<BF16, true>(mb, own, p.V, sh, [&](int, const PartView &v, double(&mine)[8]) __attribute__((always_inline)) {
+                a = v.lo * EPV + row_argmax<BF16, FULL, PARTIAL, TH>(rowp + (size_t)v.lo * 16, v.nslots, v.Vrow, sh, value);
+                mine[0] = (double)value, mine[1] = (double)a;
+                mine[2] = mine[3] = mine[4] = mine[5] = mine[6] = mine[7] = 0.0;
+            });
             double best = sh.xchg[0][0];
             a = (int)sh.xchg[0][1];
             for (int j = 1; j < mb.split; ++j)  // in vocabulary order: strict > keeps the first
@@ -946,21 +995,19 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     constexpr int kThreads = share_threads(SHARE), kWaves = kThreads / 64, TH = kThreads;
     __shared__ SharedState sh;
     __shared__ uint32_t sh_epoch;
-    constexpr int EPV = Elem<BF16>::EPV;
     // the fp32 form of the final draw's weights: calls whose exponent constant rounds well (the
     // parts of a shared sequence form identical constants from the identical normalisers they
     // hold after the exchange); the table holds the totals of the slots of this block's part
     constexpr bool kFastScan = ONE_TERM;
     extern __shared__ __align__(16) char sampler_smem[];
     float *tab = kFastScan && p.tab_slots > 0 ? reinterpret_cast<float *>(sampler_smem) : nullptr;
-    int split = SHARED ? p.split : 1;
+    const int split = SHARED ? p.split : 1;
     const int b = blockIdx.x / split, part = blockIdx.x % split;
     uint32_t claim_epoch = 0;
+    bool alone = false;  // block-uniform
     if constexpr (CLAIM) {
-        if (!claim_meet(claim_box(p.claim, b), p.claim, part, split, p.claim_ticks, &sh_epoch, sh, claim_epoch)) {  // block-uniform
-            if (part != 0) return;
-            split = 1;
-        }
+        alone = !claim_meet(claim_box(p.claim, b), p.claim, part, split, p.claim_ticks, &sh_epoch, sh, claim_epoch);
+        if (alone && part != 0) return;
     }
     // bounds come from device data: clamp them by the host-side totals so that no value of
     // q_indptr can push a row outside the logits buffers
@@ -969,21 +1016,16 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     k = max(0, min(k, min(p.max_k, p.total_q - 1 - row0)));
     const int drow0 = row0 - b;
     if (drow0 < 0 || drow0 + k > p.total_q - p.B) k = 0;
-    const int nslots_row = (p.V + EPV - 1) / EPV;
-    // this block's part of the vocabulary: a whole number of 64-slot groups
-    const int part_span = SHARED ? ((nslots_row + split - 1) / split + 63) / 64 * 64 : nslots_row;
-    const int lo = min(part * part_span, nslots_row);
-    const int nslots = min(lo + part_span, nslots_row) - lo;
-    const int Vrow = p.V - lo * EPV, tok_off = lo * EPV;
+    const PartView own = part_view<BF16>(p.V, part, split);  // this block's part of the vocabulary
     const size_t esz = BF16 ? 2 : 4;
     const char *tbase = static_cast<const char *>(p.target);
     const char *dbase = static_cast<const char *>(p.draft);
     int32_t *out = p.out_tokens + (size_t)b * (p.max_k + 1);
     const double u_fin = (double)p.u_final[b];
-    Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch};
+    Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch, false};
     if (threadIdx.x == 0) sh.failed = 0;
     if constexpr (CLAIM) {
-        mb = claim_mailbox(claim_box(p.claim, b), part, split, claim_epoch, &sh_epoch);
+        mb = claim_mailbox(claim_box(p.claim, b), part, split, claim_epoch, &sh_epoch, alone);
     } else if constexpr (SHARED) {
         mb.words = reinterpret_cast<uint32_t *>(p.boxes + (size_t)b * kBoxBytes);
         mb.payload = reinterpret_cast<unsigned long long *>(p.boxes + (size_t)b * kBoxBytes + kBoxHeaderBytes);
@@ -992,7 +1034,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     auto leave = [&]() __attribute__((always_inline)) {  // one thread of the block, behind its last exchange
         if constexpr (CLAIM) {
             // (a box whose wait ran out stays taken, and its sequence is walked alone from then on)
-            if (mb.split > 1 && sh.failed == 0) claim_leave(claim_box(p.claim, b), mb.split, mb.epoch);
+            if (!mb.alone && sh.failed == 0) claim_leave(claim_box(p.claim, b), mb.split, mb.epoch);
         }
     };
     if constexpr ((!SHARED || CLAIM) && !ONE_TERM) {
@@ -1010,7 +1052,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                 return;
             }
             if (T == 0.f) {
-                greedy_sequence<BF16, FULL, PARTIAL, SHARED, TH>(p, b, row0, drow0, k, lo, nslots, Vrow, sh, mb);
+                greedy_sequence<BF16, FULL, PARTIAL, SHARED, TH>(p, b, row0, drow0, k, own, sh, mb);
                 if (threadIdx.x == 0) leave();
                 return;
             }
@@ -1069,7 +1111,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                     const double u = (double)p.u_accept[drow0 + i + wave];
                     float M[2];
                     double S[2];
-                    wave_row_pair_stats<BF16>(rp, rq, nslots, Vrow, p, M, S);
+                    wave_row_pair_stats<BF16>(rp, rq, own.nslots, own.Vrow, p, M, S);
                     const double rho = ratio(zpx, zqx, M[0], S[0], M[1], S[1]);
                     if ((threadIdx.x & 63) == 0) {
                         sh.pos_m[0][wave] = M[0];
@@ -1103,9 +1145,8 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                 const char *rowpb = tbase + (size_t)(row0 + i + 1) * p.ld_t * esz;
                 const char *rowqb = b_pair ? dbase + (size_t)(drow0 + i + 1) * p.ld_d * esz : rowpb;
                 DrawNorm a;
-                row_stats_two_items<BF16, ONE_TERM, PARTIAL, TH>(
-                    rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, rowpb + (size_t)lo * 16, rowqb + (size_t)lo * 16, b_pair,
-                    nslots, Vrow, sh, mb, p, a, ahead, [&]() __attribute__((always_inline)) {
+                row_stats_two_items<BF16, ONE_TERM, PARTIAL, TH, CLAIM>(
+                    rowp, rowq, rowpb, rowqb, b_pair, own, sh, mb, p, a, ahead, [&]() __attribute__((always_inline)) {
                         d = draft_at(i);
                         if (b_pair) d_ahead = draft_at(i + 1);
                     });
@@ -1113,8 +1154,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
                 Mp = a.Mp, Sp = a.Sp, Mq = a.Mq, Sq = a.Sq;
             }
         } else if constexpr (!SHORT) {
-            row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, TH>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow, sh,
-                                                      i & 1, mb, p, Mp, Sp, Mq, Sq, [&]() __attribute__((always_inline)) { d = draft_at(i); });
+            row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, TH, CLAIM>(rowp, rowq, own, p.V, sh, i & 1, mb, p, Mp, Sp, Mq, Sq, [&]() __attribute__((always_inline)) { d = draft_at(i); });
         }
         last_Mp = Mp;
         double rho;
@@ -1130,8 +1170,8 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         // first rejection: one draw from the residual distribution (Eq. 2)
         double Z;
         int edge = 0;
-        final_token = inverse_cdf_pass<BF16, true, FULL, SHARED, kFastScan, PARTIAL, TH>(rowp + (size_t)lo * 16, rowq + (size_t)lo * 16, nslots, Vrow,
-                                                         tok_off, Mp, Sp, Mq, Sq, u_fin, sh, mb, p, edge, Z, mine, tab);
+        final_token = inverse_cdf_pass<BF16, true, FULL, SHARED, kFastScan, PARTIAL, TH, CLAIM, false>(
+            rowp, rowq, own, DrawNorm{Mp, Mq, Sp, Sq}, u_fin, sh, mb, p, edge, Z, mine, tab, Nothing{});
         flag_cdf = edge;
         rejected = true;
         scan_row = rowp;
@@ -1157,30 +1197,36 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
         // leaves the draw to the two passes below; every block sees the same total and decides alike.
         if (!rejected && (!SHARED || (k > 0 && ahead_of != k))) {
             scan_row = tbase + (size_t)(row0 + k) * p.ld_t * esz;
-            const char *part_row = scan_row + (size_t)lo * 16;
-            const int whole = PARTIAL ? whole_slots<BF16>(nslots, Vrow) : nslots;
-            float M0 = block_max_of_row_start<BF16, !PARTIAL, kRefSlots<ONE_TERM>, TH>(part_row, whole, sh);
-            if constexpr (SHARED) {  // block-uniform
-                for (int at = kRefSlots<ONE_TERM> * TH; M0 == -INFINITY && at < whole; at += kUnroll * TH)
-                    M0 = block_max_of_row_start<BF16, !PARTIAL, kUnroll, TH>(part_row + (size_t)at * 16, whole - at, sh);
-            }
-            const bool usable = M0 > -INFINITY && M0 < INFINITY;  // block-uniform
-            double scale = 1.0;
-            if constexpr (SHARED) {
-                if (usable) {
-                    // what the weights are formed with: exp2(z c_f + K) or exp2((z - M0) c)
-                    if constexpr (kFastScan) scale = exp2_f64(-(double)make_fast_norm(M0, 1.0, M0, 1.0, p).Kp - (double)last_Mp * (double)p.c_f);
-                    else scale = exp2_f64(((double)M0 - (double)last_Mp) * p.c_d);
-                } else {  // no mass, unless the partial slot has some
-                    scale = M0 == -INFINITY && whole == nslots ? 1.0 : (double)NAN;
-                    M0 = 0.f;
+            auto start_max = [&](const PartView &v) __attribute__((always_inline)) {
+                const char *part_row = scan_row + (size_t)v.lo * 16;
+                const int whole = PARTIAL ? whole_slots<BF16>(v.nslots, v.Vrow) : v.nslots;
+                float M0 = block_max_of_row_start<BF16, !PARTIAL, kRefSlots<ONE_TERM>, TH>(part_row, whole, sh);
+                if constexpr (SHARED) {  // block-uniform
+                    for (int at = kRefSlots<ONE_TERM> * TH; M0 == -INFINITY && at < whole; at += kUnroll * TH)
+                        M0 = block_max_of_row_start<BF16, !PARTIAL, kUnroll, TH>(part_row + (size_t)at * 16, whole - at, sh);
                 }
-            }
-            if (SHARED || usable) {
+                return M0;
+            };
+            auto ref_of = [&](const PartView &v) __attribute__((always_inline)) {  // (shared sequences)
+                PartRef ref{start_max(v), 1.0};
+                if (ref.M > -INFINITY && ref.M < INFINITY) {  // block-uniform
+                    // what the weights are formed with: exp2(z c_f + K) or exp2((z - M0) c)
+                    if constexpr (kFastScan) ref.scale = exp2_f64(-(double)make_fast_norm(ref.M, 1.0, ref.M, 1.0, p).Kp - (double)last_Mp * (double)p.c_f);
+                    else ref.scale = exp2_f64(((double)ref.M - (double)last_Mp) * p.c_d);
+                } else {  // no mass, unless the partial slot has some
+                    const int whole = PARTIAL ? whole_slots<BF16>(v.nslots, v.Vrow) : v.nslots;
+                    ref.scale = ref.M == -INFINITY && whole == v.nslots ? 1.0 : (double)NAN;
+                    ref.M = 0.f;
+                }
+                return ref;
+            };
+            float M0 = 0.f;
+            if constexpr (!SHARED) M0 = start_max(own);
+            if (SHARED || (M0 > -INFINITY && M0 < INFINITY)) {  // block-uniform
                 double Z;
                 int edge = 0;
-                const int tok = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL, TH>(part_row, part_row, nslots, Vrow, tok_off,
-                                                                               M0, 1.0, M0, 1.0, u_fin, sh, mb, p, edge, Z, mine, tab, scale);
+                const int tok = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL, TH, CLAIM, SHARED>(
+                    scan_row, scan_row, own, DrawNorm{M0, M0, 1.0, 1.0}, u_fin, sh, mb, p, edge, Z, mine, tab, ref_of);
                 if (Z > 1.0e-280 && Z < 1.0e280) {
                     final_token = tok;
                     flag_cdf = edge;
@@ -1201,8 +1247,8 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
             scan_M = ahead.Mp;
             scan_S = ahead.Sp;
         } else {
-            row_stats_any<BF16, false, ONE_TERM, FULL, SHARED, PARTIAL, TH>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
-                                                       Vrow, sh, k & 1, mb, p, scan_M, scan_S, Mq, Sq);
+            row_stats_any<BF16, false, ONE_TERM, FULL, SHARED, PARTIAL, TH, CLAIM>(scan_row, scan_row, own, p.V, sh, k & 1, mb, p, scan_M,
+                                                                                   scan_S, Mq, Sq);
         }
         scan_target = true;
     } else if (final_token == -2) {
@@ -1211,9 +1257,8 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     if (scan_target) {
         double Z;
         int edge = 0;
-        final_token = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL, TH>(scan_row + (size_t)lo * 16, scan_row + (size_t)lo * 16, nslots,
-                                                          Vrow, tok_off, scan_M, scan_S, scan_M, scan_S, u_fin, sh,
-                                                          mb, p, edge, Z, mine, tab);
+        final_token = inverse_cdf_pass<BF16, false, FULL, SHARED, kFastScan, PARTIAL, TH, CLAIM, false>(
+            scan_row, scan_row, own, DrawNorm{scan_M, scan_M, scan_S, scan_S}, u_fin, sh, mb, p, edge, Z, mine, tab, Nothing{});
         flag_cdf = rejected ? 1 : edge;
         if (!(Z > 0.0)) {  // row without any finite logit: part 0 reports the last token
             mine = part == 0;

@@ -316,6 +316,8 @@ struct SharedState {
     double scan_total[kWaves];
     double xchg[kMaxSplit][8];             // what the parts published in the current stage
     int failed;                            // a bounded wait for a partner ran out
+    float part_ref[kMaxSplit];             // references and scales of the parts of a draw
+    double part_scale[kMaxSplit];
     float arg_val[kWaves];                 // per-wave (largest logit, its first token) of an argmax pass
     int arg_idx[kWaves];
     float pos_m[2][kWaves];                // short rows: [p/q][position] references and sums, ...

@@ -35,7 +35,22 @@ struct Mailbox {
     int part, split, stage;
     uint32_t epoch;         // thread 0: the box's epoch, requested at the start of the kernel
     uint32_t *sh_epoch;     // LDS word it is handed to the block in
+    bool alone;             // the parts did not meet (MEETS forms only): this one does the work of all
 };
+
+// A part of the vocabulary: its first slot, its slots and the elements from there to the end of the row.  Parts are a
+// whole number of 64-slot groups (the last one aside).
+struct PartView {
+    int lo, nslots, Vrow;
+};
+
+template <bool BF16>
+__device__ inline PartView part_view(int V, int part, int split) {
+    constexpr int EPV = Elem<BF16>::EPV;
+    const int slots = (V + EPV - 1) / EPV, span = split > 1 ? ((slots + split - 1) / split + 63) / 64 * 64 : slots;
+    const int lo = min(part * span, slots);
+    return PartView{lo, min(lo + span, slots) - lo, V - lo * EPV};
+}
 
 // One exchange.  Every thread of the block calls it with the same `mine`; afterwards
 // sh.xchg[j] holds what part j published.  Ends with a barrier.  A wait that runs out of its
@@ -101,39 +116,73 @@ __device__ inline void exchange(Mailbox &mb, const double (&mine)[8], SharedStat
     __syncthreads();
 }
 
+// One stage of a shared sequence: `work(j, view, mine)` does part j's share and leaves the eight numbers it publishes;
+// afterwards sh.xchg holds those of all parts.  Has a barrier behind the work; the work has one of its own
+// ahead of which every wave has read what the last stage left in sh.xchg.
+// MEETS, and the parts did not: one work-group does their work in turn, on the same parts with the same
+// threads, so that a sequence's numbers have the same bits however it was walked.
+template <bool BF16, bool MEETS, class Work>
+__device__ __forceinline__ void for_parts(Mailbox &mb, const PartView &own, int V, SharedState &sh, Work &&work) {
+    if constexpr (!MEETS) {
+        double mine[8];
+        work(mb.part, own, mine);
+        exchange(mb, mine, sh);
+    } else {
+        PartView view = own;
+#pragma unroll 1
+        for (int j = mb.part;;) {  // every condition is block-uniform
+            double mine[8];
+            work(j, view, mine);
+            if (__builtin_expect(!mb.alone, 1)) {
+                exchange(mb, mine, sh);
+                break;
+            }
+            if (threadIdx.x == 0) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sh.xchg[j][i] = mine[i];
+            }
+            __syncthreads();
+            if (++j == mb.split) break;
+            view = part_view<BF16>(V, j, mb.split);
+        }
+    }
+}
+
 // (M, S) of a row (and, if TWO, of the drafter row) over the whole vocabulary.  This block
-// streams its own part (`rowp`, `rowq` point at the part's first slot, `nslots` and `Vrow`
-// are the part's); with several parts the partial results are exchanged and combined in part
-// order, so every part holds the same bits afterwards.  A part whose fast pass overflowed or came out empty repeats
-// it by itself, the others wait for it in the exchange.
-template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL, int TH, class Meanwhile = Nothing>
-__device__ inline void row_stats_any(const void *rowp, const void *rowq, int nslots, int Vrow, SharedState &sh,
+// streams its own part (`own`; the whole row when the sequence is not shared); with several parts the partial
+// results are exchanged and combined in part order, so every part holds the same bits afterwards.  A
+// part whose fast pass overflowed or came out empty repeats it by itself, the others wait for it in the exchange.
+template <bool BF16, bool TWO, bool ONE_TERM, bool FULL, bool SHARED, bool PARTIAL, int TH, bool MEETS = false, class Meanwhile = Nothing>
+__device__ inline void row_stats_any(const char *rowp, const char *rowq, const PartView &own, int V, SharedState &sh,
                                      int parity, Mailbox &mb, const RowMath &p, float &Mp,
                                      double &Sp, float &Mq, double &Sq, Meanwhile &&meanwhile = Nothing{}) {
     if constexpr (!FULL) meanwhile();
     if constexpr (!SHARED) {
         if constexpr (FULL) {
-            if (row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile))
+            if (row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, own.nslots, V, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile))
                 return;        // block-uniform
             __syncthreads();   // every thread has read the combine buffers of this parity
         }
-        row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
+        row_stats<BF16, TWO, TH>(rowp, rowq, own.nslots, V, sh, parity, p, Mp, Sp, Mq, Sq);
         return;
     }
-    bool ok = false;  // block-uniform
-    if (nslots <= 0) {  // a part without slots (tiny vocabulary): nothing to read, no mass
-        if constexpr (FULL) meanwhile();
-        __syncthreads();  // (in place of the pass's own: every wave has read what the last exchange brought)
-        Mp = Mq = kRefInit;
-        Sp = Sq = 0.0;
-        ok = true;
-    } else if constexpr (FULL) {
-        ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile);
-        if (!ok) __syncthreads();  // every thread has read the combine buffers of this parity
-    }
-    if (!ok) row_stats<BF16, TWO, TH>(rowp, rowq, nslots, Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
-    const double mine[8] = {(double)Mp, Sp, (double)Mq, Sq, 0.0, 0.0, 0.0, 0.0};
-    exchange(mb, mine, sh);
+    for_parts<BF16, MEETS>(mb, own, V, sh, [&](int, const PartView &v, double(&mine)[8]) __attribute__((always_inline)) {
+        const char *vp = rowp + (size_t)v.lo * 16, *vq = rowq + (size_t)v.lo * 16;
+        bool ok = false;  // block-uniform
+        if (v.nslots <= 0) {  // a part without slots (tiny vocabulary): nothing to read, no mass
+            if constexpr (FULL) meanwhile();
+            __syncthreads();  // (in place of the pass's own: every wave has read what the last exchange brought)
+            Mp = Mq = kRefInit;
+            Sp = Sq = 0.0;
+            ok = true;
+        } else if constexpr (FULL) {
+            ok = row_stats_fast<BF16, TWO, ONE_TERM, PARTIAL, TH>(vp, vq, v.nslots, v.Vrow, sh, parity, p, Mp, Sp, Mq, Sq, meanwhile);
+            if (!ok) __syncthreads();  // every thread has read the combine buffers of this parity
+        }
+        if (!ok) row_stats<BF16, TWO, TH>(vp, vq, v.nslots, v.Vrow, sh, parity, p, Mp, Sp, Mq, Sq);
+        mine[0] = (double)Mp, mine[1] = Sp, mine[2] = (double)Mq, mine[3] = Sq;
+        mine[4] = mine[5] = mine[6] = mine[7] = 0.0;
+    });
     // In every wave, so that no barrier is needed (the next exchange has one ahead of it): lane 8 r + j: row r (p, q)
     // of part j; one exp2 per lane.
     const int r = (threadIdx.x / kMaxSplit) & 1, j = threadIdx.x & (kMaxSplit - 1);
@@ -152,11 +201,11 @@ __device__ inline void row_stats_any(const void *rowp, const void *rowq, int nsl
 // ------------------------------------------------------------------------------------------
 // A call's parts meet before the walk begins: each enters its bit in the state word of its sequence's box, and
 // only if all of them turn up in time is the sequence shared (then all of them run, so that every later wait ends).
-// Otherwise whoever gives up leaves the box free again, part 0 walks the sequence alone and the others
+// Otherwise whoever gives up leaves the box free again, part 0 does the work of all parts (for_parts) and the others
 // end.  All of it is one compare-and-swap per step on one word, so the parts agree: a box's word goes from "all
 // arrived" to "free" only when every part has left.  A box that belongs to another call in flight (they take
 // turns over kClaimRegions sets of boxes, by a number of the call that its replays keep) counts as not
-// found, and so does one whose call never ended: such sequences are walked alone, at the price of the unshared form.
+// found, and so does one whose call never ended: such sequences are walked alone.
 //
 // State word: epoch (22 bits: uses of the box, what the marks in its payload are made from), key of the call that
 // holds it (30 bits, 0: free), parts that have arrived (4), parts that have left (4).
@@ -169,16 +218,14 @@ static __device__ __align__(256) unsigned char claim_boxes[kClaimRegions * kClai
 constexpr unsigned long long kClaimEpoch = (1ull << 22) - 1, kClaimKey = ((1ull << 30) - 1) << 22;
 constexpr int kClaimArrived = 52, kClaimLeft = 56;
 
-// What a sequence walked alone publishes goes here; nobody reads it.
-static __device__ unsigned long long claim_nowhere[2 * 16];
-
 __device__ inline unsigned long long *claim_box(uint32_t key, int b) {
     return reinterpret_cast<unsigned long long *>(claim_boxes + ((size_t)(key % kClaimRegions) * kClaimBoxes + b) * kClaimBoxBytes);
 }
 
 // One thread of each part calls this; true: all parts are here, `epoch` is the box's.  ticks: 10 ns each, how long
-// the others are waited for.
+// the others are waited for (negative: the box is left alone, and so is every sequence).
 __device__ inline bool claim_arrive(unsigned long long *state, uint32_t key, int part, int split, int ticks, uint32_t &epoch) {
+    if (ticks < 0) return false;
     const unsigned long long mine = (unsigned long long)key << 22, bit = 1ull << (kClaimArrived + part);
     const unsigned long long all = ((1ull << split) - 1) << kClaimArrived;
     auto swap = [&](unsigned long long &seen, unsigned long long want) {  // on failure `seen` is what the word holds
@@ -231,9 +278,8 @@ __device__ inline void claim_leave(unsigned long long *state, int split, uint32_
         __hip_atomic_store(state, ((unsigned long long)epoch + 1) & kClaimEpoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ inline Mailbox claim_mailbox(unsigned long long *state, int part, int split, uint32_t epoch, uint32_t *sh_epoch) {
-    unsigned long long *payload = split > 1 ? state + kBoxHeaderBytes / sizeof(*state) : claim_nowhere;
-    return Mailbox{reinterpret_cast<uint32_t *>(state), payload, 0u, part, split, 0, epoch, sh_epoch};
+__device__ inline Mailbox claim_mailbox(unsigned long long *state, int part, int split, uint32_t epoch, uint32_t *sh_epoch, bool alone) {
+    return Mailbox{reinterpret_cast<uint32_t *>(state), state + kBoxHeaderBytes / sizeof(*state), 0u, part, split, 0, epoch, sh_epoch, alone};
 }
 
 // The key of a call.

@@ -198,16 +198,16 @@ __device__ inline float tree_slot_weights_f32(const u32x4 &vp, const u32x4 &vq, 
         return (w[0] + w[1]) + (w[2] + w[3]);
 }
 
-// Region totals of the running distribution: each wave owns a contiguous eighth of the row
+// Region totals of the running distribution: each wave owns a contiguous eighth of the row (or of a part of it)
 // and streams it with coalesced loads; lanes keep their own fp64 sums, one reduction per wave
 // gives the region total (left in sh.wave_total; of a shared sequence those of all parts, in vocabulary order, in
-// sh.xchg).  Returns Z = the ordered sum of the region totals, the same bits in every thread.  At depth 0
+// sh.xchg).  tree_region_totals returns Z = the ordered sum of the region totals, the same bits in every thread.  At depth 0
 // only the target row is read.
 // `meanwhile` is called once the first batch has been requested.
-template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND, bool SHARED, class Meanwhile = Nothing>
-__device__ inline double tree_region_totals(const void *rowp, const void *rowq, int nslots, int V, float Mp,
-                                            double Sp, float Mq, double Sq, const Depth &d, double raw_1, SharedState &sh,
-                                            Mailbox &mb, const RowMath &p, Meanwhile &&meanwhile = Nothing{}) {
+template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND, class Meanwhile>
+__device__ __forceinline__ void part_region_totals(const void *rowp, const void *rowq, int nslots, int V, float Mp,
+                                                   double Sp, float Mq, double Sq, const Depth &d, double raw_1, SharedState &sh,
+                                                   const RowMath &p, Meanwhile &&meanwhile) {
     constexpr int EPV = Elem<BF16>::EPV;
     const int lane = opaque_thread_index() & 63, wave = threadIdx.x >> 6;
     constexpr bool two = KIND > 0;
@@ -283,15 +283,25 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
     if (PARTIAL && region_total > kFastMost) region_total = (double)INFINITY;
     if (lane == 0) sh.wave_total[wave] = region_total;
     __syncthreads();
+}
+
+// (the rows from their starts; `own`: this block's part)
+template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND, bool SHARED, class Meanwhile = Nothing>
+__device__ inline double tree_region_totals(const char *rowp, const char *rowq, const PartView &own, int V, float Mp,
+                                            double Sp, float Mq, double Sq, const Depth &d, double raw_1, SharedState &sh,
+                                            Mailbox &mb, const RowMath &p, Meanwhile &&meanwhile = Nothing{}) {
     double Z = 0.0;
     if constexpr (SHARED) {
         static_assert(kWaves == 8, "a part publishes eight numbers");
-        double mine[8];
+        for_parts<BF16, true>(mb, own, V, sh, [&](int, const PartView &v, double(&mine)[8]) __attribute__((always_inline)) {
+            part_region_totals<BF16, FULL, FAST, PARTIAL, KIND>(rowp + (size_t)v.lo * 16, rowq + (size_t)v.lo * 16, v.nslots, v.Vrow, Mp, Sp,
+                                                                Mq, Sq, d, raw_1, sh, p, meanwhile);
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) mine[w] = sh.wave_total[w];
-        exchange(mb, mine, sh);
+            for (int w = 0; w < kWaves; ++w) mine[w] = sh.wave_total[w];
+        });
         for (int w = 0; w < mb.split * kWaves; ++w) Z += sh.xchg[w / kWaves][w % kWaves];
     } else {
+        part_region_totals<BF16, FULL, FAST, PARTIAL, KIND>(rowp, rowq, own.nslots, V, Mp, Sp, Mq, Sq, d, raw_1, sh, p, meanwhile);
         for (int w = 0; w < kWaves; ++w) Z += sh.wave_total[w];
     }
     return lane_value(Z, 0);  // (every lane's, in scalar registers)
@@ -306,7 +316,7 @@ __device__ inline double tree_region_totals(const void *rowp, const void *rowq, 
 // fall off the end of the region; that draw takes the last token with mass and is flagged.
 // SHARED: -1 with mine = false when the region lies in another part of the row.
 template <bool BF16, bool FULL, bool FAST, bool PARTIAL, int KIND, bool SHARED>
-__device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, int V, float Mp, double Sp,
+__device__ inline int tree_draw(const char *row_p, const char *row_q, const PartView &own, int V_row, float Mp, double Sp,
                                 float Mq, double Sq, const Depth &d, double raw_1, double u, SharedState &sh,
                                 const Mailbox &mb, const RowMath &p, int &near_edge, bool &mine) {
     constexpr int EPV = Elem<BF16>::EPV;
@@ -315,7 +325,6 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     const double Cp = 1.0 / Sp, Cq = two ? 1.0 / Sq : 0.0;
     const FastNorm fn = make_fast_norm(Mp, Sp, Mq, two ? Sq : Sp, p);
     const FastDepth fd = make_fast_depth(d, raw_1, fn);
-    const int span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
     if (threadIdx.x == 0) {
         sh.token = -1;
         sh.near_edge = 0;
@@ -342,11 +351,15 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
     const bool forced = rstar < 0;  // u*Z rounded up to Z: take the last token with mass
     if (forced) rstar = rlast;
     mine = true;
+    PartView v = own;
     if constexpr (SHARED) {
-        mine = rstar / kWaves == mb.part;  // block-uniform
+        mine = mb.alone || rstar / kWaves == mb.part;  // block-uniform
         if (!mine) return -1;
+        if (mb.alone) v = part_view<BF16>(V_row, __builtin_amdgcn_readfirstlane(rstar / kWaves), mb.split);
         rstar %= kWaves;
     }
+    const char *rowp = row_p + (size_t)v.lo * 16, *rowq = row_q + (size_t)v.lo * 16;
+    const int nslots = v.nslots, V = v.Vrow, span = ((nslots + kWaves - 1) / kWaves + 63) / 64 * 64;
     __syncthreads();
 
     const int whole = PARTIAL ? whole_slots<BF16>(nslots, V) : nslots;
@@ -493,7 +506,7 @@ __device__ inline int tree_draw(const void *rowp, const void *rowq, int nslots, 
         near_edge = 1;
     }
     __syncthreads();
-    return tok;
+    return v.lo * EPV + tok;
 }
 
 template <bool BF16, bool ONE_TERM, bool FULL, bool PARTIAL, bool SHARED>
@@ -506,33 +519,26 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
     __shared__ int sh_token[kMaxTreeRows];
     __shared__ float sh_u[kMaxTreeRows];
     constexpr int EPV = Elem<BF16>::EPV;
-    int split = SHARED ? p.split : 1;
+    const int split = SHARED ? p.split : 1;
     const int b = blockIdx.x / split, part = blockIdx.x % split;
-    Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch};
+    Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch, false};
     if constexpr (SHARED) {
         uint32_t epoch;
-        if (!claim_meet(claim_box(p.claim, b), p.claim, part, split, p.claim_ticks, &sh_epoch, sh, epoch)) {  // block-uniform
-            if (part != 0) return;
-            split = 1;
-        }
-        mb = claim_mailbox(claim_box(p.claim, b), part, split, epoch, &sh_epoch);
+        const bool alone = !claim_meet(claim_box(p.claim, b), p.claim, part, split, p.claim_ticks, &sh_epoch, sh, epoch);  // block-uniform
+        if (alone && part != 0) return;
+        mb = claim_mailbox(claim_box(p.claim, b), part, split, epoch, &sh_epoch, alone);
     }
     // bounds come from device data: clamp them by the host-side totals so that no value of
     // q_indptr or parent can push a row outside the logits buffers
     const int row0 = max(0, min(p.q_indptr[b], p.total_q - 1));
     const int R = max(1, min(p.q_indptr[b + 1] - row0, min(kMaxTreeRows, p.total_q - row0)));
-    const int nslots_row = (p.V + EPV - 1) / EPV;
-    // this block's part of the vocabulary: a whole number of 64-slot groups
-    const int part_span = SHARED ? ((nslots_row + split - 1) / split + 63) / 64 * 64 : nslots_row;
-    const int lo = min(part * part_span, nslots_row);
-    const int nslots = min(lo + part_span, nslots_row) - lo, V = p.V - lo * EPV;
+    const PartView own = part_view<BF16>(p.V, part, split);  // this block's part of the vocabulary
     const size_t esz = BF16 ? 2 : 4;
     const char *tbase = static_cast<const char *>(p.target);
     const char *dbase = static_cast<const char *>(p.draft);
     // (the output rows are addressed where they are written and the final uniform is loaded where
     // it is used: values that live across the streaming passes cost registers there)
     auto out_row = [&]() { return p.out_tokens + (size_t)b * (p.max_depth + 1); };
-    auto at = [&](const char *row) { return row + (size_t)lo * 16; };  // this part of a row
     auto path_row = [&]() { return p.out_path + (size_t)b * max(p.max_depth, 1); };
     if (threadIdx.x < kMaxTreeRows) {
         sh_parent[threadIdx.x] = (int)threadIdx.x < R ? p.parent[row0 + threadIdx.x] : -2;
@@ -567,7 +573,7 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
             x = __builtin_amdgcn_readfirstlane(sh_token[c]);
             cand = fetch_candidate<BF16>(rowp, rowq, x);
         };
-        row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, kThreads>(at(rowp), at(rowq), nslots, V, sh, parity, mb, p, Mp, Sp, Mq, Sq, fetch);
+        row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, kThreads, SHARED>(rowp, rowq, own, p.V, sh, parity, mb, p, Mp, Sp, Mq, Sq, fetch);
         parity ^= 1;
         have_norm = true;
         bool moved = false;
@@ -614,14 +620,14 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
             {
                 const Depth d{depth, lane_value(sh_inv_z[1], 0), lane_value(sh_inv_z[2], 0), sh_inv_z};
                 if (depth == 1) {
-                    raw_1 = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 1, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
+                    raw_1 = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 1, SHARED>(rowp, rowq, own, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
                     Zd = raw_1;
                     if constexpr (ONE_TERM) Zd += raw_1 * (double)make_fast_norm(Mp, Sp, Mq, Sq, p).ep;
                 } else if (depth == 2) {
-                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 2, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
+                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 2, SHARED>(rowp, rowq, own, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
                     if constexpr (ONE_TERM) Zd /= raw_1;
                 } else {
-                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
+                    Zd = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth, SHARED>(rowp, rowq, own, p.V, Mp, Sp, Mq, Sq, d, raw_1, sh, mb, p, fetch_next);
                 }
             }
             if (Zd > 0.0) {
@@ -651,10 +657,10 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
         }
         for (;;) {
             if (!trial && !have_norm) {
-                row_stats_any<BF16, false, ONE_TERM, FULL, SHARED, PARTIAL, kThreads>(at(rowp), at(rowp), nslots, V, sh, parity, mb, p, Mp, Sp, Mq, Sq);
+                row_stats_any<BF16, false, ONE_TERM, FULL, SHARED, PARTIAL, kThreads, SHARED>(rowp, rowp, own, p.V, sh, parity, mb, p, Mp, Sp, Mq, Sq);
                 have_norm = true;
             }
-            Z = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 0, SHARED>(at(rowp), at(rowp), nslots, V, Mp, Sp, Mp, Sp, d, raw_1, sh, mb, p);
+            Z = tree_region_totals<BF16, FULL, ONE_TERM, PARTIAL, 0, SHARED>(rowp, rowp, own, p.V, Mp, Sp, Mp, Sp, d, raw_1, sh, mb, p);
             if (!trial || (Z > 0.0 && Z < 1.0e300)) break;
             trial = false;
         }
@@ -664,14 +670,13 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
         const double u = (double)p.u_final[b];
         int edge = 0;
         if (depth == 0)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 0, SHARED>(at(rowp), at(rowp), nslots, V, Mp, Sp, Mp, Sp, d, raw_1, u, sh, mb, p, edge, mine);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 0, SHARED>(rowp, rowp, own, p.V, Mp, Sp, Mp, Sp, d, raw_1, u, sh, mb, p, edge, mine);
         else if (depth == 1)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 1, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 1, SHARED>(rowp, rowq, own, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
         else if (depth == 2)
-            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 2, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, 2, SHARED>(rowp, rowq, own, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
         else
-            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth, SHARED>(at(rowp), at(rowq), nslots, V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
-        final_token += lo * EPV;  // (what is drawn is an index in this part)
+            final_token = tree_draw<BF16, FULL, ONE_TERM, PARTIAL, kAnyDepth, SHARED>(rowp, rowq, own, p.V, Mp, Sp, Mq, Sq, d, raw_1, u, sh, mb, p, edge, mine);
         flag_cdf |= edge;
     } else {  // row without any finite logit: report the last token
         final_token = p.V - 1;
@@ -690,7 +695,7 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
             p.out_num_accepted[b] = -1;
         }
         if constexpr (SHARED) {
-            if (split > 1 && !failed) claim_leave(claim_box(p.claim, b), split, mb.epoch);
+            if (!mb.alone && !failed) claim_leave(claim_box(p.claim, b), split, mb.epoch);
         }
     }
 }

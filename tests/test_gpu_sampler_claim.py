@@ -1,6 +1,7 @@
 """Sequences shared between work-groups without a workspace (one temperature per sequence, trees of drafts):
 the parts meet in the library's own mailboxes, or part 0 walks alone.  Exact against the CPU oracle on
 unflagged sequences either way, in order, beside other calls and under replay."""
+import numpy as np
 import pytest
 import torch
 
@@ -56,8 +57,8 @@ def _tree(B, V, dtype, seed, T):
 
 
 # parts of two and four, one and two items per stage, whole and ragged rows; ticks 0: whoever does not find the others
-# at once gives up, so sequences are walked alone, shared, or found given up
-@pytest.mark.parametrize("ticks", [None, 0])
+# at once gives up, so sequences are walked alone, shared, or found given up; ticks -1: all are walked alone
+@pytest.mark.parametrize("ticks", [None, 0, -1])
 @pytest.mark.parametrize("B,V,dtype", [(1, 151936, "bf16"), (9, 151936, "bf16"), (64, 33000, "bf16"), (65, 52000, "bf16"), (128, 65536, "bf16"),
                                        (20, 77777, "bf16"), (33, 50257, "f32"), (70, 80001, "f32"), (5, 151936, "f32")])
 def test_temperatures(oracle, B, V, dtype, ticks):
@@ -70,7 +71,7 @@ def test_temperatures(oracle, B, V, dtype, ticks):
             compare_sampler(call.result(), ref)
 
 
-@pytest.mark.parametrize("ticks", [None, 0])
+@pytest.mark.parametrize("ticks", [None, 0, -1])
 @pytest.mark.parametrize("B,V,dtype,T", [(1, 151936, "bf16", 0.6), (9, 151936, "bf16", 1.0), (64, 131072, "bf16", 0.6), (70, 100003, "bf16", 1.0),
                                          (20, 77777, "bf16", 0.6), (12, 80001, "f32", 0.6), (5, 151936, "f32", 1.0)])
 def test_trees(oracle, B, V, dtype, T, ticks):
@@ -79,6 +80,61 @@ def test_trees(oracle, B, V, dtype, T, ticks):
     with env_setting("RESPEC_SAMPLER_CLAIM_TICKS", ticks):
         for _ in range(3):
             compare_tree_sampler(gpu_tree_sample(tb), ref)
+
+
+def _edge_uniforms(weights, count):
+    """Binary32 uniforms on top of edges of a distribution's cells, where the last bits of the sums decide the token."""
+    cdf = weights.double().cumsum(0)
+    cdf = cdf / cdf[-1]
+    cdf = cdf[(cdf > 0.25) & (cdf < 0.999999)]
+    near = (cdf.float().double() - cdf).abs().argsort()[:count]
+    return cdf[near].float()
+
+
+def _on_edges(target, draft, k, T):
+    """Draft tokens that are rejected (uniform 0.999) and final uniforms on edges of what is then drawn from: the residual,
+    or the target row where there is no draft."""
+    p, q = torch.softmax(target.double() / T, -1), torch.softmax(draft.double() / T, -1)
+    x = (q - p).argmax(-1)
+    ratio = (p / q).gather(1, x[:, None])
+    assert bool((ratio < 0.99).all())
+    w = torch.where(torch.tensor(k, device=p.device)[:, None] > 0, (p - q).clamp_min(0), p)
+    return x.int(), torch.cat([_edge_uniforms(w[b], 8)[b % 8, None] for b in range(len(k))])
+
+
+# The bits of a sequence's sums, and so its tokens on the edges of cells, do not depend on whether its parts met.
+@pytest.mark.parametrize("kind", ["temperatures", "tree"])
+@pytest.mark.parametrize("B,V,dtype,T", [(64, 151936, "bf16", 1.0), (128, 151936, "bf16", 0.6), (48, 80001, "f32", 0.6), (50, 100003, "bf16", 1.3)])
+def test_meeting_does_not_change_a_result(kind, B, V, dtype, T):
+    k = [b % 2 for b in range(B)]
+    if kind == "tree":
+        batch = synth.make_tree_batch(_wl(B, 1, V, dtype, T), [[-1] + [0] * n for n in k], device="cuda", kv_lens=[64] * B, seed=7, with_attention=False)
+        rows = batch.q_indptr[:-1].long()
+        x, batch.u_final[:] = _on_edges(batch.target_logits[rows], batch.draft_logits[rows], k, T)
+        child = rows[1::2] + 1
+        batch.node_tokens[child] = x[1::2]
+        batch.u_accept[child] = 0.999
+        call = lambda: gpu_tree_sample(batch)  # noqa: E731
+    else:
+        batch = synth.make_batch(_wl(B, 1, V, dtype, T), device="cuda", kv_lens=[64] * B, k_per_seq=k, seed=7, with_attention=False)
+        rows = batch.q_indptr[:-1].long()
+        draft = batch.draft_logits.repeat_interleave(2, 0)  # (of sequences without a draft nothing is used)
+        x, batch.u_final[:] = _on_edges(batch.target_logits[rows], draft, k, T)
+        batch.draft_tokens[:] = x[1::2]
+        batch.u_accept[:] = 0.999
+        one = _Call(batch, [T] * B)
+
+        def call():
+            one()
+            return one.result()
+    first = None
+    for ticks in (None, -1, 0, 0, 0, None):
+        with env_setting("RESPEC_SAMPLER_CLAIM_TICKS", ticks):
+            got = [a.copy() for a in call()]
+        first = first or got
+        for a, b in zip(first, got):
+            np.testing.assert_array_equal(a, b)
+    assert (first[-2] == 0).all() and (first[-1] & 2).sum() > B // 2  # drafts rejected, draws on edges
 
 
 # calls of several streams at a time (their work-groups compete for the compute units), and replays of a graph
