@@ -960,7 +960,13 @@ __device__ inline void greedy_sequence(const SamplerParams &p, int b, int row0, 
             a = row_argmax<BF16, FULL, PARTIAL, TH>(rowp, own.nslots, p.V, sh, value);
         } else {
             for_parts<BF16, true>(mb, own, p.V, sh, [&](int, const PartView &v, double(&mine)[8]) __attribute__((always_inline)) {
-                a = v.lo * EPV + row_argmax<BF16, FULL, PARTIAL, TH>(rowp + (size_t)v.lo * 16, v.nslots, v.Vrow, sh, value);
+                if (v.nslots > 0) {  // block-uniform
+                    a = v.lo * EPV + row_argmax<BF16, FULL, PARTIAL, TH>(rowp + (size_t)v.lo * 16, v.nslots, v.Vrow, sh, value);
+                } else {  // a part without slots (a split forced on a short row): nothing to read
+                    __syncthreads();  // (as in row_stats_any)
+                    value = -INFINITY;
+                    a = 0;
+                }
                 mine[0] = (double)value, mine[1] = (double)a;
                 mine[2] = mine[3] = mine[4] = mine[5] = mine[6] = mine[7] = 0.0;
             });

@@ -82,6 +82,22 @@ def test_trees(oracle, B, V, dtype, T, ticks):
             compare_tree_sampler(gpu_tree_sample(tb), ref)
 
 
+# a forced split that leaves the last parts of a short row without a slot, greedy sequences among the others; the last row ends
+# with its buffer
+@pytest.mark.parametrize("ticks", [None, -1])
+@pytest.mark.parametrize("V,dtype", [(1024, "bf16"), (512, "f32"), (520, "bf16"), (64, "bf16"), (32, "f32")])
+def test_parts_without_slots(oracle, V, dtype, ticks):
+    batch, temps = _chain(12, 3, V, dtype, seed=V)
+    first = batch.target_logits[0].float().argmax().int()
+    batch.draft_tokens[0] = first  # a greedy sequence that goes on past its first draft
+    call = _Call(batch, [0.0] * 4 + temps[4:])
+    with env_setting("RESPEC_SAMPLER_CLAIM_TICKS", ticks), env_setting("RESPEC_SAMPLER_SPLIT", 4):
+        call()
+        ref = call.reference(oracle)
+        compare_sampler(call.result(), ref)
+        assert ref[1][0] >= 1
+
+
 def _edge_uniforms(weights, count):
     """Binary32 uniforms on top of edges of a distribution's cells, where the last bits of the sums decide the token."""
     cdf = weights.double().cumsum(0)
