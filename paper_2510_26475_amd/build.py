@@ -32,7 +32,7 @@ FLAGS = [
 def _inputs():
     files = [os.path.join(CSRC, s) for s in SOURCES]
     files += [os.path.join(CSRC, "respec_common.hpp"), os.path.join(CSRC, "respec_sampler_rows.hpp"),
-              os.path.join(CSRC, "respec_sampler_share.hpp"),
+              os.path.join(CSRC, "respec_sampler_share.hpp"), os.path.join(CSRC, "respec_tree_candidate.hpp"),
               os.path.join(CSRC, "respec_kd_absent.hpp"), os.path.join(INCLUDE, "respec.h")]
     return files
 

@@ -1027,7 +1027,6 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     const char *tbase = static_cast<const char *>(p.target);
     const char *dbase = static_cast<const char *>(p.draft);
     int32_t *out = p.out_tokens + (size_t)b * (p.max_k + 1);
-    const double u_fin = (double)p.u_final[b];
     Mailbox mb{nullptr, nullptr, 0u, part, split, 0, 0u, &sh_epoch, false};
     if (threadIdx.x == 0) sh.failed = 0;
     if constexpr (CLAIM) {
@@ -1065,6 +1064,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
             device_row_math(p, T);
         }
     }
+    const double u_fin = (double)p.u_final[b];
     int n = 0, flag_accept = 0, flag_cdf = 0, final_token = -1;
     bool rejected = false, mine = false;
     // shared sequences walk their chain two items per stage (see row_stats_two_items); `ahead`

@@ -19,6 +19,7 @@
 // fp64, which also serve the final draw when the rejected child was the last), and an
 // acceptance test needs only the candidate's own two logits.
 #include "respec_sampler_share.hpp"
+#include "respec_tree_candidate.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -26,33 +27,35 @@
 namespace respec {
 namespace {
 
-// The two logits of a candidate as they are in memory, fetched through the scalar cache: the same for every thread and in
-// scalar registers, requested behind a pass's first batch, so that the test behind the pass waits for nothing and the
-// pass keeps its vector registers (a test's chain of loads, token, logits and uniform, took 1.5 us of
-// every pass).  A 16-bit logit comes with the rest of its aligned word.
+// The two logits of a candidate as they are in memory, requested behind a pass's first batch, so that the test behind
+// the pass waits for nothing (its chain of loads, token, logits and uniform, took 1.5 us of every pass).  WORD: through
+// the scalar cache, the same for every thread and in scalar registers, so that the pass keeps its vector registers; a
+// 16-bit logit then comes with the rest of its aligned word.
 struct Candidate {
     uint32_t p, q;
 };
 
-template <bool BF16>
-__device__ inline uint32_t scalar_logit_word(const char *row, int x) {
-    const uint64_t at = (reinterpret_cast<uintptr_t>(row) + (uintptr_t)x * (BF16 ? 2 : 4)) & ~(uintptr_t)3;
+__device__ inline uint32_t scalar_word(uint64_t at) {
     const uint64_t uniform = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)at) |
                              (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32;
     return *(const uint32_t __attribute__((address_space(4))) *)uniform;
 }
 
-template <bool BF16>
+template <bool BF16, bool WORD>
 __device__ inline Candidate fetch_candidate(const char *rowp, const char *rowq, int x) {
-    Candidate c{scalar_logit_word<BF16>(rowp, x), scalar_logit_word<BF16>(rowq, x)};
-    asm volatile("" : "+s"(c.p), "+s"(c.q));  // (here, not where they are used)
-    return c;
+    if constexpr (WORD) {
+        Candidate c{scalar_word(candidate_word_at(reinterpret_cast<uintptr_t>(rowp), x, BF16)),
+                    scalar_word(candidate_word_at(reinterpret_cast<uintptr_t>(rowq), x, BF16))};
+        asm volatile("" : "+s"(c.p), "+s"(c.q));  // (here, not where they are used)
+        return c;
+    } else {
+        return Candidate{__float_as_uint(logit_at<BF16>(rowp, x)), __float_as_uint(logit_at<BF16>(rowq, x))};
+    }
 }
 
-template <bool BF16>
-__device__ inline float logit_of_word(uint32_t word, const char *row, int x) {
-    if constexpr (BF16) word = (reinterpret_cast<uintptr_t>(row) + (uintptr_t)x * 2) & 2 ? word & 0xffff0000u : word << 16;
-    return __uint_as_float(word);
+template <bool BF16, bool WORD>
+__device__ inline float candidate_logit(uint32_t word, const char *row, int x) {
+    return __uint_as_float(WORD ? candidate_bits(word, reinterpret_cast<uintptr_t>(row), x, BF16) : word);
 }
 
 constexpr int kMaxTreeRows = 64;   // rows (nodes) of one sequence: the attention's mask width
@@ -512,6 +515,7 @@ __device__ inline int tree_draw(const char *row_p, const char *row_q, const Part
 template <bool BF16, bool ONE_TERM, bool FULL, bool PARTIAL, bool SHARED>
 __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
     static_assert(FULL || !SHARED, "the guarded form is not shared");
+    constexpr bool kWord = candidate_by_word(BF16, FULL && !PARTIAL);
     __shared__ SharedState sh;
     __shared__ uint32_t sh_epoch;
     __shared__ int sh_parent[kMaxTreeRows];
@@ -543,9 +547,10 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
     if (threadIdx.x < kMaxTreeRows) {
         sh_parent[threadIdx.x] = (int)threadIdx.x < R ? p.parent[row0 + threadIdx.x] : -2;
         sh_inv_z[threadIdx.x] = 1.0;
-        const int at = row0 + min((int)threadIdx.x, R - 1);
-        sh_token[threadIdx.x] = max(0, min(p.node_tokens[at], p.V - 1));  // memory safety only; ids outside [0,V) are a caller error
-        sh_u[threadIdx.x] = p.u_accept[at];
+        if (threadIdx.x > 0 && (int)threadIdx.x < R) {  // (the root has neither a token nor a test)
+            sh_token[threadIdx.x] = max(0, min(p.node_tokens[row0 + threadIdx.x], p.V - 1));  // memory safety only; ids outside [0,V) are a caller error
+            sh_u[threadIdx.x] = p.u_accept[row0 + threadIdx.x];
+        }
     }
     __syncthreads();
 
@@ -571,7 +576,7 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
         int x = 0;
         auto fetch = [&]() __attribute__((always_inline)) {  // child c's token and its logits
             x = __builtin_amdgcn_readfirstlane(sh_token[c]);
-            cand = fetch_candidate<BF16>(rowp, rowq, x);
+            cand = fetch_candidate<BF16, kWord>(rowp, rowq, x);
         };
         row_stats_any<BF16, true, ONE_TERM, FULL, SHARED, PARTIAL, kThreads, SHARED>(rowp, rowq, own, p.V, sh, parity, mb, p, Mp, Sp, Mq, Sq, fetch);
         parity ^= 1;
@@ -579,7 +584,7 @@ __device__ __forceinline__ void tree_rejection_sample(const TreeParams &p) {
         bool moved = false;
         double Zd = 1.0;  // normaliser of the running distribution (Z_depth)
         while (c < R) {
-            const float zpx = logit_of_word<BF16>(cand.p, rowp, x), zqx = logit_of_word<BF16>(cand.q, rowq, x);
+            const float zpx = candidate_logit<BF16, kWord>(cand.p, rowp, x), zqx = candidate_logit<BF16, kWord>(cand.q, rowq, x);
             const double u = (double)sh_u[c];
             // Eq. 1 in fp64 against the running distribution: rho = p_depth(x)/q(x)
             double rho;

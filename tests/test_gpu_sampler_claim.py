@@ -98,6 +98,30 @@ def test_parts_without_slots(oracle, V, dtype, ticks):
         assert ref[1][0] >= 1
 
 
+# what the interface says is never read may hold anything: a root's token and uniform, a greedy sequence's uniforms and drafter rows
+@pytest.mark.parametrize("V", [151936, 2048, 2047])
+def test_entries_that_are_not_used(oracle, V):
+    tb = _tree(32, V, "bf16", 3, 0.6)
+    want = gpu_tree_sample(tb)
+    root = tb.q_indptr[:-1].long()
+    tb.u_accept[root] = float("nan")
+    tb.node_tokens[root] = 0x7fffffff
+    for a, b in zip(want, gpu_tree_sample(tb)):
+        np.testing.assert_array_equal(a, b)
+    batch, temps = _chain(32, 3, V, "bf16", seed=4)
+    call = _Call(batch, temps)
+    call()
+    want = [a.copy() for a in call.result()]
+    for b, (k, q0) in enumerate(zip(batch.k_per_seq, batch.q_indptr.tolist())):
+        if temps[b] == 0.0:
+            batch.u_final[b] = float("nan")
+            batch.u_accept[q0 - b:q0 - b + k] = float("nan")
+            batch.draft_logits[q0 - b:q0 - b + k] = float("nan")
+    call()
+    for a, b in zip(want, call.result()):
+        np.testing.assert_array_equal(a, b)
+
+
 def _edge_uniforms(weights, count):
     """Binary32 uniforms on top of edges of a distribution's cells, where the last bits of the sums decide the token."""
     cdf = weights.double().cumsum(0)
