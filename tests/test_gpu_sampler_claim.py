@@ -193,15 +193,16 @@ def test_streams_and_replays(oracle):
                 c()
     for c, ref in zip(calls, refs):
         compare_sampler(c.result(), ref)
+    between = _Call(calls[0].batch, calls[0].temps.tolist())  # (buffers of its own: what a replay wrote is looked at)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         for c in calls:
             c()
     for _ in range(3):
-        for c in calls:
+        for c in calls + [between]:
             c.toks.zero_()
             c.n.fill_(-7)
         graph.replay()
-        calls[0]()  # eager work between the replays
-        for c, ref in zip(calls, refs):
+        between()  # eager work between the replays
+        for c, ref in zip(calls + [between], refs + refs[:1]):
             compare_sampler(c.result(), ref)

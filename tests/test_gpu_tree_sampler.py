@@ -8,7 +8,7 @@ import pytest
 import torch
 from scipy import stats
 
-from helpers import compare_tree_sampler, gpu_sample, gpu_tree_sample, oracle_tree_sample
+from helpers import compare_sampler, compare_tree_sampler, env_setting, gpu_sample, gpu_tree_sample, oracle_tree_sample
 from paper_2510_26475_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
@@ -78,7 +78,9 @@ def test_many_rejected_siblings_in_a_row(oracle):
     assert (ref[2] == 0).sum() >= 8                # plenty of sequences rejected every child
 
 
-def test_chain_shaped_tree_gives_the_chain_samplers_tokens_bit_for_bit():
+# (bit for bit in one work-group per sequence; where the tree's sequences are shared, boundary draws apart)
+@pytest.mark.parametrize("claim", [0, None])
+def test_chain_shaped_tree_gives_the_chain_samplers_tokens_bit_for_bit(claim):
     wl = _wl("tree_chain", 151936, "bf16")
     ks = [3, 0, 4, 1, 2, 4, 3, 3] * 4
     tb = _batch(wl, [list(range(-1, k)) for k in ks], seed=12)
@@ -92,11 +94,16 @@ def test_chain_shaped_tree_gives_the_chain_samplers_tokens_bit_for_bit():
         kv_indptr=torch.empty(0), target_logits=tb.target_logits, draft_logits=tb.draft_logits[d_idx].contiguous(),
         draft_tokens=tb.node_tokens[c_idx].contiguous(), u_accept=tb.u_accept[c_idx].contiguous(),
         u_final=tb.u_final, k_per_seq=ks, kv_lens=[k + 1 for k in ks])
-    t_tok, t_path, t_n, t_flags = gpu_tree_sample(tb)
+    with env_setting("RESPEC_SAMPLER_CLAIM", claim):
+        t_tok, t_path, t_n, t_flags = gpu_tree_sample(tb)
     c_tok, c_n, c_flags = gpu_sample(chain, workspace=None)
-    np.testing.assert_array_equal(t_tok, c_tok)
-    np.testing.assert_array_equal(t_n, c_n)
-    np.testing.assert_array_equal(t_flags, c_flags)
+    if claim is None:
+        compare_sampler((t_tok, t_n, t_flags), (c_tok, c_n, c_flags))
+        assert (t_flags == c_flags).mean() > 0.9
+    else:
+        np.testing.assert_array_equal(t_tok, c_tok)
+        np.testing.assert_array_equal(t_n, c_n)
+        np.testing.assert_array_equal(t_flags, c_flags)
     for b, n in enumerate(t_n):
         assert t_path[b, :n].tolist() == list(range(1, n + 1))
 
