@@ -17,3 +17,11 @@ def oracle():
     import oracle as _oracle
     _oracle.build()
     return _oracle
+
+
+@pytest.fixture(params=[None, 0], ids=["form by size", "main kernel"])
+def attn_few(request):
+    """Small bf16 batches in the attention form that their size gives them, and in the main kernel's."""
+    from helpers import env_setting
+    with env_setting("RESPEC_ATTN_FEW", request.param):
+        yield request.param

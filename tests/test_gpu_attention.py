@@ -87,6 +87,7 @@ def test_bf16_d64(oracle, wgs):
     _run(oracle, wl, [33, 130, 700, 9, 257], [3, 4, 0, 8, 2], seed=11, wgs=wgs)
 
 
+@pytest.mark.usefixtures("attn_few")
 @pytest.mark.parametrize("k", [0, 1, 2, 4, 8])
 def test_bf16_draft_lengths_14b_heads(oracle, k):
     # G = 5: 5, 10, 15, 25, 45 MFMA columns -> 1..3 column tiles
@@ -141,6 +142,7 @@ def test_both_forms_of_a_wide_column_block_agree_with_the_oracle(oracle, D, wide
         _run(oracle, wl, [700, 9, 1300, 12, 4096, 257], [8, 8, 8, 7, 8, 8], seed=60 + D + wide, wgs=13)
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_ragged_draft_lengths_in_one_batch(oracle):
     wl = _wl("bf16_ragged", 40, 8, 128, "bf16")
     ks = [0, 8, 3, 1, 7, 0, 5, 2]
@@ -149,6 +151,7 @@ def test_ragged_draft_lengths_in_one_batch(oracle):
     _run(oracle, wl, lens, ks, seed=42, wgs=29)
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_causal_boundary_with_spiked_keys(oracle):
     """A key with a huge score sits just past each row's horizon: it must capture exactly the
     rows that may see it (2e-2 would not notice an off-by-one on N(0,1) data)."""
@@ -176,6 +179,7 @@ def test_causal_boundary_with_spiked_keys(oracle):
     assert (np.abs(ref - 1.5) < 1e-3).mean() > 0.02
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_cache_holding_only_the_new_tokens(oracle):
     wl = _wl("bf16_min", 28, 4, 128, "bf16")
     err, batch, out = _run(oracle, wl, [4, 1, 5], [3, 0, 4], seed=6)
@@ -185,6 +189,7 @@ def test_cache_holding_only_the_new_tokens(oracle):
     assert np.array_equal(got, np.broadcast_to(v0[:, None, :], got.shape))
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_runs_are_bitwise_reproducible(oracle):
     wl = _wl("bf16_det", 28, 4, 128, "bf16")
     batch = synth.make_batch(wl, device="cuda", kv_lens=[3000, 700, 129], k_per_seq=[3, 3, 3],
@@ -195,6 +200,7 @@ def test_runs_are_bitwise_reproducible(oracle):
     assert torch.equal(a.view(torch.int16), b.view(torch.int16)) and torch.equal(la, lb)
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_rows_beyond_the_batch_are_never_read(oracle):
     wl = _wl("bf16_poison", 16, 2, 128, "bf16")
     lens, ks = [200, 77], [4, 2]
@@ -212,6 +218,7 @@ def test_rows_beyond_the_batch_are_never_read(oracle):
     _check(out, lse, ref, ref_lse, "bf16")
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_custom_scale_and_no_lse(oracle):
     wl = _wl("bf16_scale", 8, 2, 128, "bf16")
     batch = synth.make_batch(wl, device="cuda", kv_lens=[500, 64], k_per_seq=[2, 4], seed=9,
@@ -222,6 +229,7 @@ def test_custom_scale_and_no_lse(oracle):
     _check(out, None, ref, None, "bf16")
 
 
+@pytest.mark.usefixtures("attn_few")
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_a_scale_of_zero_weighs_every_visible_key_alike(oracle, dtype):
     # every score is zero then, hidden keys still count for nothing
@@ -256,6 +264,7 @@ def test_qwen7b_headline_workload_whole_batch(oracle):
     print(f"headline attention: max abs err {worst:.3e} over {batch.total_q} rows")
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_next_layer_reuses_the_set_up_and_is_bit_equal_to_a_full_call(oracle):
     """The layers of one forward share the index arrays: respec_verify_attention_next_layer skips
     the set-up kernel and must give the bits of a full call on the same arguments."""

@@ -61,8 +61,9 @@ def test_forms_agree_with_the_oracle(oracle, shape, wgs, form):
         _check(oracle, batch)
 
 
-# The form by size where few sequences share all ranges: on both sides of each of its lines (two tiles
-# per consumer of the device, and four for 16 pairs of a sequence and a KV head or fewer)
+# Few sequences that share all ranges: the main kernel on both sides of its line (two tiles per consumer of the device) and
+# well beyond it, and the form for few tiles, which takes the same batches by size
+@pytest.mark.usefixtures("attn_few")
 @pytest.mark.parametrize("pairs,tiles", [(1, 1), (1, 2), (1, 3), (4, 2), (4, 3), (4, 4), (16, 3), (18, 2)])
 def test_few_long_sequences(oracle, pairs, tiles):
     B, Hkv = {1: (1, 1), 4: (2, 2), 16: (8, 2), 18: (9, 2)}[pairs]
@@ -126,6 +127,7 @@ def test_paged_and_trees_are_bit_equal_to_contiguous(form, page_size):
 
 # A caller without a bound on the lengths passes the largest int32: the same split, the same bits (the
 # combine kernel's form follows the bound and is held)
+@pytest.mark.usefixtures("attn_few")
 def test_no_bound_on_the_lengths(oracle):
     batch = synth.make_batch(_wl(28, 4, 128), device="cuda", kv_lens=[4096, 3000, 4095, 31, 2048, 4000, 4096, 3500],
                              k_per_seq=[0] * 8, seed=4, with_logits=False)

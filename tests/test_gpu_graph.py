@@ -11,6 +11,7 @@ from paper_2510_26475_amd import binding, synth
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_verify_step_replays_from_a_graph():
     wl = synth.Workload("graph", B=24, k=3, Hq=28, Hkv=4, D=128, V=151936, dtype="bf16",
                         len_dist="uniform", len_lo=100, len_hi=3000, seed=21)

@@ -142,6 +142,7 @@ def test_chain_commit_only_cuts_the_length():
     assert pk.kv_len.cpu().tolist() == [30 - 4 + 2, 9 - 3 + 3, 5, 17 - 2]
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_verify_commit_then_plain_decode(oracle):
     """A speculative step followed by a non-speculative one on the same cache: tree verify,
     sampling, commit, then one decode row (k = 0) per sequence over the committed cache; the
@@ -197,6 +198,7 @@ def test_verify_commit_then_plain_decode(oracle):
     _check(out, lse, ref, ref_lse, "bf16")
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_next_layer_on_a_paged_cache_is_bit_equal_to_a_full_call(oracle):
     """Another layer's K/V pools behind the same page table: the set-up in the workspace is reused."""
     wl = _wl("paged_layers", 28, 4, 128, "bf16")
@@ -234,6 +236,7 @@ def test_next_layer_on_a_paged_cache_is_bit_equal_to_a_full_call(oracle):
 # The form of the attention kernel follows the cached tokens; a page table with room to grow must not
 # count as a larger batch.  Equal lengths: the longest length bounds both entry points alike, and the
 # results are the same bits.  Ragged ones may take another form: the oracle's bounds.
+@pytest.mark.usefixtures("attn_few")
 @pytest.mark.parametrize("lens", [[2304] * 8, [2304, 40, 700, 1500, 9, 333, 64, 2000]])
 def test_pages_in_reserve(oracle, lens):
     wl = synth.Workload("reserve", B=0, k=0, Hq=16, Hkv=2, D=128, V=8, dtype="bf16", len_dist="uniform", len_lo=1, len_hi=1)

@@ -70,6 +70,7 @@ def test_bf16_trees(oracle, heads, wgs):
     _check(out, lse, ref, ref_lse, "bf16")
 
 
+@pytest.mark.usefixtures("attn_few")
 def test_chain_mask_equals_the_chain_entry_point_bit_for_bit():
     wl = _wl("tree_chain", 28, 4, 128, "bf16")
     ks = [3, 0, 4, 1, 2, 4]
