@@ -49,13 +49,15 @@ __device__ inline Candidate fetch_candidate(const char *rowp, const char *rowq, 
         asm volatile("" : "+s"(c.p), "+s"(c.q));  // (here, not where they are used)
         return c;
     } else {
-        return Candidate{__float_as_uint(logit_at<BF16>(rowp, x)), __float_as_uint(logit_at<BF16>(rowq, x))};
+        // (as they come: whatever is done to them here would wait for them here)
+        return Candidate{reinterpret_cast<const uint16_t *>(rowp)[x], reinterpret_cast<const uint16_t *>(rowq)[x]};
     }
 }
 
 template <bool BF16, bool WORD>
 __device__ inline float candidate_logit(uint32_t word, const char *row, int x) {
-    return __uint_as_float(WORD ? candidate_bits(word, reinterpret_cast<uintptr_t>(row), x, BF16) : word);
+    static_assert(WORD || BF16, "fp32 logits are words");
+    return __uint_as_float(WORD ? candidate_bits(word, reinterpret_cast<uintptr_t>(row), x, BF16) : word << 16);
 }
 
 constexpr int kMaxTreeRows = 64;   // rows (nodes) of one sequence: the attention's mask width
