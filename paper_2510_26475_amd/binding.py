@@ -175,9 +175,17 @@ def _dev_ptr(t: Optional[torch.Tensor], name: str):
 
 # (A small step is bound by this module: its calls enqueue in about the time that its kernels take.  A
 # stream object made for its handle takes 2.7 us of the 9 to 12 us that a call needs here, the handle
-# alone 0.3: the fp32 step of 4 sequences 19.4 -> 14.9 us.)
+# alone 0.3: the fp32 step of 4 sequences 19.4 -> 14.9 us.  The function is not part of torch's public
+# interface: without it a stream object is made.)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream: Optional[torch.cuda.Stream]):
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(torch.cuda.current_device())
 
 
 def respec_reload_knobs():

@@ -162,3 +162,15 @@ def test_tree_entry_points_argument_errors_need_no_gpu(lib):
     assert run(max_rows=65, total_q=100) == 2
     assert run(max_depth=-1) == 1
     assert run(dt=7) == 1
+
+
+def test_the_current_stream_is_found_without_torchs_private_function(monkeypatch):
+    import torch
+    from types import SimpleNamespace
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=41))
+    monkeypatch.setattr(binding, "_current_raw_stream", lambda device: 100 + device)
+    assert binding._stream_ptr(None) == 103
+    assert binding._stream_ptr(SimpleNamespace(cuda_stream=7)) == 7
+    monkeypatch.setattr(binding, "_current_raw_stream", None)
+    assert binding._stream_ptr(None) == 41
