@@ -261,8 +261,8 @@ respec_status_t respec_commit_accepted_paged(void *k_pages, void *v_pages, const
  * `after_main` (if non-NULL) right after it, before the combine kernel; then both are
  * forgotten.  Both are hipEvent_t passed as void*.  Pass NULL, NULL to disarm a hook that was
  * set and not used.  Do not arm it in front of a call that is being captured into a HIP graph.
- * Apart from the knobs below this is the only state the library keeps between calls; it is
- * thread-local.
+ * Apart from the knobs below and the samplers' own mailboxes (respec_rejection_sample_per_seq)
+ * this is the only state the library keeps between calls; it is thread-local.
  */
 void respec_profile_mark_main(void *before_main, void *after_main);
 
@@ -367,8 +367,12 @@ respec_status_t respec_rejection_sample(const void *target_logits, const void *d
  *   mailboxes of the library's own (a static device array): they meet before the walk begins,
  *   and where they do not find each other within 20 us (compute units held by another stream's
  *   kernel) one does the work of all, in the same order: the result has the same bits, later.
- *   Calls may overlap on any streams and be captured.  As with a workspace, the row pair right behind a rejected position may be read
- *   (never used).
+ *   Calls may overlap on any streams and be captured (replays of one captured call follow one
+ *   another, as they write the same outputs).  Once the work-groups have met they wait for one
+ *   another as with a workspace, for seconds at most: a wait that runs out (a device fault)
+ *   gives out_num_accepted[b] = -1, and the mailbox it happened in, one of 4096, is not used
+ *   again by this process (sequences that come to it are walked by one work-group).  As with a
+ *   workspace, the row pair right behind a rejected position may be read (never used).
  * Device-side data errors that the host cannot see (a negative or non-finite temperature, a
  * sampled sequence with drafted tokens but draft_logits or u_accept NULL) give
  * out_num_accepted[b] = -1 and out_tokens[b, :] = -1 for that sequence.
@@ -416,7 +420,8 @@ respec_status_t respec_rejection_sample_per_seq(const void *target_logits, const
  *   max_depth     host-side bound of the depth of any tree (root = depth 0)
  * A chain-shaped tree gives the tokens of respec_rejection_sample bit for bit (draws flagged
  * as boundary draws apart, where the two share a sequence differently).  Sequences are shared
- * between work-groups as in respec_rejection_sample_per_seq.
+ * between work-groups as in respec_rejection_sample_per_seq, and repeated calls on the same
+ * inputs give the same bits as there.
  */
 respec_status_t respec_tree_rejection_sample(const void *target_logits, const void *draft_logits,
                                              const int32_t *node_tokens, const int32_t *parent,

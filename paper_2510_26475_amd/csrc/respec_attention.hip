@@ -2065,6 +2065,8 @@ hipError_t launch_few(int nt, const AttnParams &p, hipStream_t stream) {
 // 69.4, 85.9, 69.5; heads of 64, two tiles: 15 18.1, 13.7, 12.8; 126 42.0, 44.0, 37.7.  With eight KV heads a
 // part reads an eighth of every cache row, and the lines lie lower: 14B, one tile 15 19.5, 18.7, 18.0; 24 22.0,
 // 22.5, 23.6; two 48 43.3, 40.0, 41.2; 96 60.2, 61.7, 63.7; three 48 46.0, 41.6, 46.1; 59 47.8, 49.7, 46.2.
+// The upper line of two per unit (48 tiles) is the 7B shape's; with two KV heads two per unit still win at 126 (the
+// 3B and the heads of 64 above), which the line leaves to the main kernel.
 int few_tiles_groups(int D, int nt, int32_t B, int32_t Hkv, int64_t kv_tokens, int32_t max_kv_len) {
     const int units = compute_units();
     if (B > kFewSeqs || (int64_t)B * Hkv > units) return 0;

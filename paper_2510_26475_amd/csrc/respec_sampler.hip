@@ -17,8 +17,9 @@
 // sequences are shared only while that fills otherwise idle compute units (batches of at
 // most half as many sequences as the device has compute units).  The mailbox is
 // self-synchronising across calls (an epoch counter per sequence), so it only has to be
-// zero before its first use.  Without a workspace a sequence gets one work-group and no
-// mailbox is touched.
+// zero before its first use.  Without a workspace a sequence of a call with one temperature gets
+// one work-group and no mailbox is touched; calls with a temperature per sequence, which have no
+// workspace, share their sequences through mailboxes of the library's own (respec_sampler_share.hpp).
 //
 // Numerics.  Token decisions are discontinuous in the sums, so everything that decides a
 // token is carried in fp64; only exp2 of a single element runs in fp32 (hardware exp2,
@@ -56,8 +57,8 @@ struct SamplerParams : RowMath {
     int32_t *out_flags;
     int32_t B, total_q, max_k, V;
     int64_t ld_t, ld_d;
-    int split;         // work-groups per sequence (1 when there is no workspace)
-    char *boxes;       // [B] mailboxes of kBoxBytes (split > 1)
+    int split;         // work-groups per sequence
+    char *boxes;       // [B] mailboxes of kBoxBytes in the workspace (split > 1 and claim == 0)
     const float *temps;  // [B] one temperature per sequence (0: greedy), or NULL: the RowMath constants hold
     int tab_slots;       // > 0: the launch carries dynamic LDS for one float per slot of a row
     uint32_t claim;      // > 0: the parts of a sequence meet in the library's own mailboxes, under this key, ...
@@ -1038,7 +1039,7 @@ __device__ __forceinline__ void rejection_sample(SamplerParams &p) {
     }
     auto leave = [&]() __attribute__((always_inline)) {  // one thread of the block, behind its last exchange
         if constexpr (CLAIM) {
-            // (a box whose wait ran out stays taken, and its sequence is walked alone from then on)
+            // (a box whose wait ran out stays taken: sequences that come to it are walked alone from then on)
             if (!mb.alone && sh.failed == 0) claim_leave(claim_box(p.claim, b), mb.split, mb.epoch);
         }
     };
@@ -1336,7 +1337,7 @@ __global__ __launch_bounds__(kThreads) void short_rows_sample_kernel(SamplerPara
 }
 
 // Both entry points: `temps` NULL = one temperature for the batch (`temperature`), else one per
-// sequence on the device (no workspace then: a sequence has one work-group).
+// sequence on the device (no workspace then: sequences are shared through the library's own mailboxes).
 respec_status_t sample_common(const void *target_logits, const void *draft_logits, const int32_t *draft_tokens,
                               const int32_t *q_indptr, const float *u_accept, const float *u_final,
                               int32_t *out_tokens, int32_t *out_num_accepted, int32_t *out_flags, int32_t B,
@@ -1387,7 +1388,7 @@ respec_status_t sample_common(const void *target_logits, const void *draft_logit
     if (temps) p.one_term = 0;  // the per-sequence constants are formed on the device, two-term
 
     // work-groups per sequence: as many as there are otherwise idle compute units, as long as a
-    // part keeps a useful share of the row; one (and no mailbox) without a workspace
+    // part keeps a useful share of the row; one (and no mailbox) with one temperature and no workspace
     int split = 1, cus = 256;
     bool two_items = false;
     // (per-sequence temperatures have no workspace argument: their parts meet in the library's own mailboxes)
